@@ -45,7 +45,7 @@ __global__ void __launch_bounds__(kCenterThreads) k_ff_center(BvhDev bv, const i
         const SurfRec rj = bv.rec[bv.inv[j]];
         const Segment g = make_segment(ri, rj, t_eps);
         float T = 1.0f;
-        trace_segment(bv, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, (uint32_t)row, (uint32_t)j, g.t_lo, g.t_hi,
+        trace_segment<kWalkHead>(bv, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, (uint32_t)row, (uint32_t)j, g.t_lo, g.t_hi,
                       stack_mem + threadIdx.x, kCenterThreads, err, [&](const SurfRec &r) {
                           T = __fmul_rn(T, transmit(r.c.w, kernel_gamma(hit_r2_exact(r, g.ox, g.oy, g.oz, g.dx,
                                                                                      g.dy, g.dz))));
@@ -182,7 +182,7 @@ __global__ void __launch_bounds__(kCenterThreads) k_center_bwd(BvhDev bv, const 
             const float W = G * fval[kk];
             float T = 1.0f;
             float gpi[3] = {0.0f, 0.0f, 0.0f}, gpj[3] = {0.0f, 0.0f, 0.0f};
-            trace_segment(bv, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, i, j, g.t_lo, g.t_hi, stack_mem + threadIdx.x,
+            trace_segment<kWalkHead>(bv, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, i, j, g.t_lo, g.t_hi, stack_mem + threadIdx.x,
                           kCenterThreads, err, [&](const SurfRec &r) {
                               // exact kernel value for T, FP32 geometry for the derivatives
                               const float gam = kernel_gamma(hit_r2_exact(r, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz));
@@ -494,7 +494,7 @@ __global__ void __launch_bounds__(128) k_direct_bwd(BvhDev bv, const float *__re
             const float r3 = dd * len, r5 = r3 * dd;
             // the transmittance first (the occluders' weight W needs it)
             float T = 1.0f;
-            trace_segment(bv, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz, (uint32_t)i, (uint32_t)i, t_lo, 1.0f,
+            trace_segment<kWalkHead>(bv, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz, (uint32_t)i, (uint32_t)i, t_lo, 1.0f,
                           stack_mem + threadIdx.x, blockDim.x, err, [&](const SurfRec &r) {
                               T = __fmul_rn(T, transmit(r.c.w, kernel_gamma(hit_r2_exact(r, rr.a.x, rr.a.y, rr.a.z,
                                                                                          dx, dy, dz))));
@@ -516,7 +516,7 @@ __global__ void __launch_bounds__(128) k_direct_bwd(BvhDev bv, const float *__re
             gl[2] = gvz;
             sink.add3(9, (uint32_t)i, Q * dx / r3, Q * dy / r3, Q * dz / r3);
             const float W = S * oc * base;
-            trace_segment(bv, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz, (uint32_t)i, (uint32_t)i, t_lo, 1.0f,
+            trace_segment<kWalkHead>(bv, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz, (uint32_t)i, (uint32_t)i, t_lo, 1.0f,
                           stack_mem + threadIdx.x, blockDim.x, err, [&](const SurfRec &r) {
                               const float gam = kernel_gamma(hit_r2_exact(r, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz));
                               const uint32_t k = __float_as_uint(r.d.w);
@@ -621,7 +621,7 @@ gsrad_status launch_ff_center(const BvhDev &bv, const Csr &P, const float *lambd
     if (P.n == 0) return GSRAD_OK;
     const int64_t nb = (P.n + 1) / 2;
     hipLaunchKernelGGL(k_ff_center, dim3((unsigned)nb), dim3(kCenterThreads),
-                       (size_t)kStackDeep * kCenterThreads * sizeof(uint32_t), st, bv, P.row_ptr, P.col, P.n, lambda,
+                       walk_bytes(kWalkHead), st, bv, P.row_ptr, P.col, P.n, lambda,
                        val, nb, P.order, err);
     return check_hip(hipGetLastError(), "centre-to-centre form factor launch");
 }
@@ -674,7 +674,7 @@ gsrad_status launch_center_backward(const BvhDev &bv, const Csr &F, const float 
     unsigned long long *a = static_cast<unsigned long long *>(acc);
     uint32_t *maxbits = reinterpret_cast<uint32_t *>(a + (size_t)8 * kCenterFields * F.n);
     int *fx = reinterpret_cast<int *>(maxbits + kCenterFields);
-    const size_t smem = (size_t)kStackDeep * kCenterThreads * sizeof(uint32_t);
+    const size_t smem = walk_bytes(kWalkHead);
     auto run = [&](int pass, int stride) {
         const int64_t rows = (F.n + stride - 1) / stride;
         const int64_t nb = (rows + 1) / 2;
@@ -743,7 +743,7 @@ gsrad_status launch_direct_backward(const BvhDev &bv, const float *albedo, const
     uint32_t *maxbits = reinterpret_cast<uint32_t *>(la + (size_t)8 * 4 * Lt);
     int *fx = reinterpret_cast<int *>(maxbits + 32);
     const dim3 grid((unsigned)((bv.n + 127) / 128));
-    const size_t smem = ff_stack_bytes(128);
+    const size_t smem = walk_bytes(kWalkHead);
     hipLaunchKernelGGL(k_direct_bwd<0>, grid, dim3(128), smem, st, bv, albedo, lpos, lI, Lt, K, gE, maxbits, fx, a, la,
                        g_alb, err);
     hipLaunchKernelGGL(k_light_exp, dim3(1), dim3(64), 0, st, maxbits, bv.n * (int64_t)Lt + bv.n, bv.n, fx);

@@ -210,7 +210,7 @@ __global__ void __launch_bounds__(kCenterThreads) k_mc_ne(BvhDev bv, int G, cons
         const SurfRec rj = bv.rec[bv.inv[jsel]];
         const Segment g = make_segment(ra, rj, bv.bounds[6]);
         float T = 1.0f;
-        trace_segment(bv, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, (uint32_t)a, (uint32_t)jsel, g.t_lo, g.t_hi,
+        trace_segment<kStackDeep>(bv, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, (uint32_t)a, (uint32_t)jsel, g.t_lo, g.t_hi,
                       stack_mem + threadIdx.x, kCenterThreads, err, [&](const SurfRec &r) {
                           T = __fmul_rn(T, transmit(r.c.w, kernel_gamma(hit_r2_exact(r, g.ox, g.oy, g.oz, g.dx,
                                                                                      g.dy, g.dz))));
@@ -358,7 +358,7 @@ gsrad_status mc_step(const BvhDev &bv, const McBuffers &mb, int G, float rmin2, 
     hipLaunchKernelGGL(k_mc_lum, dim3((unsigned)((G + 3) / 4)), dim3(256), 0, st, G, mb.goff, mb.members, B, Lt, K,
                        mb.L);
     hipLaunchKernelGGL(k_mc_ne, dim3((unsigned)((n + kCenterThreads - 1) / kCenterThreads)), dim3(kCenterThreads),
-                       (size_t)kStackDeep * kCenterThreads * sizeof(uint32_t), st, bv, G, mb.goff, mb.members, mb.cent,
+                       walk_bytes(kStackDeep), st, bv, G, mb.goff, mb.members, mb.cent,
                        mb.gnrm, mb.L, rmin2, recv, n, lambda, rho, E, B, Lt, K, seed, step, delta, err);
     return check_hip(hipGetLastError(), "next event launch");
 }

@@ -747,6 +747,7 @@ __global__ void __launch_bounds__(256) k_ell_to_csr(const int32_t *__restrict__ 
 // ---------------------------------------------------------------------------
 // direct light
 // ---------------------------------------------------------------------------
+template <int HEAD>
 __global__ void __launch_bounds__(128) k_direct(BvhDev bv, const float *__restrict__ albedo,
                                                 const float *__restrict__ lpos, const float *__restrict__ lI, int Lt,
                                                 int K, float *__restrict__ E, int *err) {
@@ -766,7 +767,7 @@ __global__ void __launch_bounds__(128) k_direct(BvhDev bv, const float *__restri
     float base = 0.0f;
     if (ndot > 0.0f && dd > 0.0f) {
         const float t_lo = __fdiv_rn(bv.bounds[6], len);
-        const float T = trace_shadow(bv, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz, (uint32_t)i, t_lo,
+        const float T = trace_shadow<HEAD>(bv, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz, (uint32_t)i, t_lo,
                                      stack_mem + threadIdx.x, blockDim.x, err);
         base = bv.op[i] * 1.1283791670955126f * lI[l] * (ndot / len) / dd * T;
     }
@@ -778,7 +779,7 @@ __global__ void __launch_bounds__(128) k_direct(BvhDev bv, const float *__restri
 
 // Direct light with the BRDF: E_i,l = (R_i / pi) (.) Y(w^(i)) I_l max(0, n_i . w) / r^2 T_il
 // with w the unit direction to the light expressed in i's tangent frame.
-template <int K>
+template <int K, int HEAD>
 __global__ void __launch_bounds__(128) k_direct_sh(BvhDev bv, const float *__restrict__ R,
                                                    const float *__restrict__ lpos, const float *__restrict__ lI, int Lt,
                                                    float *__restrict__ E, int *err) {
@@ -799,7 +800,7 @@ __global__ void __launch_bounds__(128) k_direct_sh(BvhDev bv, const float *__res
     float Y[K];
     if (ndot > 0.0f && dd > 0.0f) {
         const float t_lo = __fdiv_rn(bv.bounds[6], len);
-        const float T = trace_shadow(bv, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz, (uint32_t)i, t_lo,
+        const float T = trace_shadow<HEAD>(bv, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz, (uint32_t)i, t_lo,
                                      stack_mem + threadIdx.x, blockDim.x, err);
         base = lI[l] * (ndot / len) / dd * T * 0.318309886183791f;
         const float il = 1.0f / len;
@@ -1223,8 +1224,9 @@ gsrad_status launch_ell_to_csr(const int32_t *ell_col, const float *ell_val, int
 gsrad_status launch_direct(const BvhDev &bv, const float *albedo, const float *lpos, const float *lI, int Lt, int K,
                            float *E, int *err, hipStream_t st) {
     const int64_t total = bv.n * Lt;
-    hipLaunchKernelGGL(k_direct, dim3((unsigned)((total + 127) / 128)), dim3(128), ff_stack_bytes(128), st, bv, albedo,
-                       lpos, lI, Lt, K, E, err);
+    const bool fills = total > kWalkFill;
+    hipLaunchKernelGGL(fills ? k_direct<kWalkHead> : k_direct<kStackDeep>, dim3((unsigned)((total + 127) / 128)),
+                       dim3(128), walk_bytes(fills ? kWalkHead : kStackDeep), st, bv, albedo, lpos, lI, Lt, K, E, err);
     return check_hip(hipGetLastError(), "direct light launch");
 }
 
@@ -1249,12 +1251,16 @@ gsrad_status launch_direct_sh(const BvhDev &bv, const float *R, const float *lpo
                               float *E, int *err, hipStream_t st) {
     const int64_t total = bv.n * Lt;
     const dim3 grid((unsigned)((total + 127) / 128));
-    const size_t smem = ff_stack_bytes(128);
+    const bool fills = total > kWalkFill;
+    const size_t smem = walk_bytes(fills ? kWalkHead : kStackDeep);
+    auto run = [&](auto small, auto large) {
+        hipLaunchKernelGGL(fills ? large : small, grid, dim3(128), smem, st, bv, R, lpos, lI, Lt, E, err);
+    };
     switch (K) {
-        case 1: hipLaunchKernelGGL(k_direct_sh<1>, grid, dim3(128), smem, st, bv, R, lpos, lI, Lt, E, err); break;
-        case 4: hipLaunchKernelGGL(k_direct_sh<4>, grid, dim3(128), smem, st, bv, R, lpos, lI, Lt, E, err); break;
-        case 9: hipLaunchKernelGGL(k_direct_sh<9>, grid, dim3(128), smem, st, bv, R, lpos, lI, Lt, E, err); break;
-        case 16: hipLaunchKernelGGL(k_direct_sh<16>, grid, dim3(128), smem, st, bv, R, lpos, lI, Lt, E, err); break;
+        case 1: run(k_direct_sh<1, kStackDeep>, k_direct_sh<1, kWalkHead>); break;
+        case 4: run(k_direct_sh<4, kStackDeep>, k_direct_sh<4, kWalkHead>); break;
+        case 9: run(k_direct_sh<9, kStackDeep>, k_direct_sh<9, kWalkHead>); break;
+        case 16: run(k_direct_sh<16, kStackDeep>, k_direct_sh<16, kWalkHead>); break;
         default: set_error("direct light: K must be 1, 4, 9 or 16"); return GSRAD_EINVAL;
     }
     return check_hip(hipGetLastError(), "SH direct light launch");

@@ -22,6 +22,33 @@ constexpr int kStackDeep = 64;
 constexpr int kKB = 20;   // k-buffer entries per traversal round (measured best of 8-32)
 constexpr uint32_t kEmpty = 0xffffffffu;
 
+// Stack of the shadow and segment walks, 64 entries a lane: the first HEAD in
+// LDS (column `lds`, entries `stride` apart), the deeper ones, which few
+// walks reach (an LBVH of 100k surfels is some 20 levels high), in the lane's
+// private memory.  The walks wait for dependent node and leaf loads, so where
+// a launch fills the chip, waves in flight count: all 64 entries in LDS hold
+// a CU to ten waves (10 M segments of a 20k-surfel bowl: F 29.6 ms, with a
+// head of 20 24.2 ms; their gradients 183 and 156 ms).  A launch that does
+// not reach ten waves a CU walks faster without the choice of memory (512
+// surfels, one light: 49 against 60 us) and takes HEAD = 64.
+constexpr int kWalkHead = 20;
+constexpr int64_t kWalkFill = (int64_t)256 * 10 * 64;   // lanes of ten waves on each of 256 CUs
+
+template <int HEAD>
+struct WalkStack {
+    uint32_t *lds;
+    int stride;
+    uint32_t tail[HEAD < kStackDeep ? kStackDeep - HEAD : 1];
+    __device__ __forceinline__ WalkStack(uint32_t *column, int stride_) : lds(column), stride(stride_) {}
+    __device__ __forceinline__ void put(int k, uint32_t v) {
+        if (HEAD >= kStackDeep || k < HEAD) lds[k * stride] = v;
+        else tail[k - HEAD] = v;
+    }
+    __device__ __forceinline__ uint32_t get(int k) const {
+        return HEAD >= kStackDeep || k < HEAD ? lds[k * stride] : tail[k - HEAD];
+    }
+};
+
 // Workgroups are dispatched round-robin over the 8 XCDs; give each XCD a
 // contiguous range of receivers so its L2 sees one region of the scene.
 __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t g) {
@@ -170,8 +197,9 @@ __device__ __forceinline__ float trace_sorted(const BvhDev &bv, float ox, float 
 
 // Transmittance of the segment t in (t_lo, 1) of o + t d: product of
 // (1 - alpha) over every surfel crossed (order-free).
+template <int HEAD>
 __device__ __forceinline__ float trace_shadow(const BvhDev &bv, float ox, float oy, float oz, float dx, float dy,
-                                              float dz, uint32_t self, float t_lo, uint32_t *stack, int stride,
+                                              float dz, uint32_t self, float t_lo, uint32_t *column, int stride,
                                               int *err) {
     const float ix = safe_inv(dx), iy = safe_inv(dy), iz = safe_inv(dz);
     const float t0 = t_lo * 0.99999f, t1 = 1.00001f;
@@ -192,6 +220,7 @@ __device__ __forceinline__ float trace_shadow(const BvhDev &bv, float ox, float 
         leaf(0);
         return T;
     }
+    WalkStack<HEAD> stack(column, stride);
     int sp = 0, node = 0;
     bool ovf = false;
     for (;;) {
@@ -212,13 +241,13 @@ __device__ __forceinline__ float trace_shadow(const BvhDev &bv, float ox, float 
         // push past the stack's end ends the walk with an error.
         const bool both = h0 && h1;
         ovf = both && sp >= kStackDeep;
-        if (both) stack[min(sp, kStackDeep - 1) * stride] = (uint32_t)c1;
+        if (both) stack.put(min(sp, kStackDeep - 1), (uint32_t)c1);
         sp += both ? 1 : 0;
         node = h0 ? c0 : c1;
         if (!h0 && !h1) {
             if (sp == 0) break;
             --sp;
-            node = (int)stack[sp * stride];
+            node = (int)stack.get(sp);
         }
         if (ovf) break;
     }
@@ -295,10 +324,10 @@ __device__ __forceinline__ float row_hash_lookup(const uint32_t *hk, const float
 // Every surfel other than skip_a and skip_b whose support the segment
 // o + t d, t in (t_lo, t_hi), crosses (D_hit, both faces occlude);
 // on_hit(record) per crossing, in traversal order.
-template <typename OnHit>
+template <int HEAD, typename OnHit>
 __device__ __forceinline__ void trace_segment(const BvhDev &bv, float ox, float oy, float oz, float dx, float dy,
                                               float dz, uint32_t skip_a, uint32_t skip_b, float t_lo, float t_hi,
-                                              uint32_t *stack, int stride, int *err, OnHit &&on_hit) {
+                                              uint32_t *column, int stride, int *err, OnHit &&on_hit) {
     const float ix = safe_inv(dx), iy = safe_inv(dy), iz = safe_inv(dz);
     const float t0 = t_lo * 0.99999f, t1 = t_hi * 1.00001f;
     auto leaf = [&](int s) {
@@ -315,6 +344,7 @@ __device__ __forceinline__ void trace_segment(const BvhDev &bv, float ox, float 
         leaf(0);
         return;
     }
+    WalkStack<HEAD> stack(column, stride);
     int sp = 0, node = 0;
     bool ovf = false;
     for (;;) {
@@ -335,13 +365,13 @@ __device__ __forceinline__ void trace_segment(const BvhDev &bv, float ox, float 
         // push past the stack's end ends the walk with an error.
         const bool both = h0 && h1;
         ovf = both && sp >= kStackDeep;
-        if (both) stack[min(sp, kStackDeep - 1) * stride] = (uint32_t)c1;
+        if (both) stack.put(min(sp, kStackDeep - 1), (uint32_t)c1);
         sp += both ? 1 : 0;
         node = h0 ? c0 : c1;
         if (!h0 && !h1) {
             if (sp == 0) break;
             --sp;
-            node = (int)stack[sp * stride];
+            node = (int)stack.get(sp);
         }
         if (ovf) break;
     }
@@ -349,6 +379,8 @@ __device__ __forceinline__ void trace_segment(const BvhDev &bv, float ox, float 
 }
 
 constexpr int kCenterThreads = 128;   // two rows (waves) per workgroup
+// LDS of a workgroup's walks
+constexpr size_t walk_bytes(int head) { return (size_t)head * kCenterThreads * sizeof(uint32_t); }
 constexpr int kCenterFields = 16;     // p(3), t_u(3), t_v(3), n(3), s_u, s_v, o, lambda
 constexpr float kInvPi = 0.318309886183790672f;
 
