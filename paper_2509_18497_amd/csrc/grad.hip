@@ -11,6 +11,7 @@
 //                   and shadow-segment occluders.
 // All sums are 64-bit fixed point with per-field scales (bit-identical
 // between runs), one copy per XCD.
+#include <algorithm>
 #include <functional>
 
 #include "gsrad_internal.h"
@@ -46,7 +47,7 @@ __global__ void __launch_bounds__(kCenterThreads) k_ff_center(BvhDev bv, const i
         const Segment g = make_segment(ri, rj, t_eps);
         float T = 1.0f;
         trace_segment<kWalkHead>(bv, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, (uint32_t)row, (uint32_t)j, g.t_lo, g.t_hi,
-                      stack_mem + threadIdx.x, kCenterThreads, err, [&](const SurfRec &r) {
+                      stack_mem + threadIdx.x, kCenterThreads, err, [&](const SurfRec &r, int) {
                           T = __fmul_rn(T, transmit(r.c.w, kernel_gamma(hit_r2_exact(r, g.ox, g.oy, g.oz, g.dx,
                                                                                      g.dy, g.dz))));
                       });
@@ -58,17 +59,48 @@ __global__ void __launch_bounds__(kCenterThreads) k_ff_center(BvhDev bv, const i
     }
 }
 
-// Gradients of sum_e G_e F_e (same decomposition as the oracle's): pass 0
-// finds max |contribution| per field, pass 1 adds the contributions in
-// 64-bit fixed point with a per-field power-of-two scale (integer adds
+// Accumulated fields of the gradient kernels, per surfel in 64-bit fixed
+// point.  0-11 hold world-space sums (centre, t_u, t_v, n) of the terms that
+// have no plane of their own: a receiver's or a segment's ends.  12 is the
+// opacity, 13 a pair's sum of G T Phi (the chain through lambda_j A_j).
+// 14-22 are the sums of what a crossing adds to the surfel it crosses: with h
+// the crossing relative to its centre, du = dL/du / s_u, dw = dL/dw / s_v and
+// beta = (du t_u + dw t_v) . d / (d . n),
+//   p += beta n - du t_u - dw t_v,  t_u += du h,  t_v += dw h,  n -= beta h,
+//   s_u -= du u,  s_v -= dw w.
+// t_u, t_v, n are the surfel's own and h lies in its plane (h . n = 0), so h's
+// two coordinates outside the largest axis of n give the third: ten sums per
+// crossing (these nine and the opacity) instead of the fifteen gradients they
+// determine, which k_fields_finish forms from them.
+enum {
+    kFp = 0, kFtu = 3, kFtv = 6, kFn = 9, kFo = 12, kFpair = 13,
+    kFdu = 14, kFdw = 15, kFbeta = 16, kFduh = 17, kFdwh = 19, kFbetah = 21, kFields = 23
+};
+
+// Axis of n that k_fields_finish recovers (its largest; the first on ties)
+__device__ __forceinline__ int plane_axis(float nx, float ny, float nz) {
+    const float ax = fabsf(nx), ay = fabsf(ny), az = fabsf(nz);
+    return ax >= ay && ax >= az ? 0 : (ay >= az ? 1 : 2);
+}
+
+// Pass 0 finds max |contribution| per field, pass 1 adds the contributions
+// in 64-bit fixed point with a per-field power-of-two scale (integer adds
 // commute: bit-identical between runs) into one copy per XCD.
 template <int PASS>
-struct CenterSink {
-    float m[kCenterFields];   // pass 0: largest |contribution| per field
+struct FieldSink {
+    float m[kFields];         // pass 0: largest |contribution| per field
     float qm;                 // pass 1: largest |scaled contribution| (INFINITY once one is not finite)
     unsigned long long *acc;
     const int *fx;
     int64_t n;
+    __device__ __forceinline__ void init(unsigned long long *copies, const int *exps, int64_t surfels) {
+#pragma unroll
+        for (int f = 0; f < kFields; ++f) m[f] = 0.0f;
+        qm = 0.0f;
+        acc = copies + (int64_t)xcc_id() * kFields * surfels;
+        fx = exps;
+        n = surfels;
+    }
     __device__ __forceinline__ void track(float q) {
         const float a = fabsf(q);
         qm = a <= 3.0e38f ? fmaxf(qm, a) : INFINITY;
@@ -90,13 +122,27 @@ struct CenterSink {
         add(f + 1, surfel, y);
         add(f + 2, surfel, z);
     }
-    // wave maxima to maxbits[0..15] (pass 0) or maxbits[32] (pass 1); every
-    // lane of the wave calls this
-    template <int P>
+    // a crossing of surfel k (record r) at h
+    __device__ __forceinline__ void cross(uint32_t k, const SurfRec &r, float du, float dw, float beta, float hx,
+                                          float hy, float hz) {
+        const int ax = plane_axis(r.b.x, r.b.y, r.b.z);
+        const float ha = ax == 0 ? hy : hx, hb = ax == 2 ? hy : hz;
+        add(kFdu, k, du);
+        add(kFdw, k, dw);
+        add(kFbeta, k, beta);
+        add(kFduh, k, du * ha);
+        add(kFduh + 1, k, du * hb);
+        add(kFdwh, k, dw * ha);
+        add(kFdwh + 1, k, dw * hb);
+        add(kFbetah, k, beta * ha);
+        add(kFbetah + 1, k, beta * hb);
+    }
+    // wave maxima to maxbits[f] (pass 0) or maxbits[2 kFields] (pass 1);
+    // every lane of the wave calls this
     __device__ __forceinline__ void report(uint32_t *maxbits) {
-        if (P == 0) {
+        if (PASS == 0) {
 #pragma unroll
-            for (int f = 0; f < kCenterFields; ++f) {
+            for (int f = 0; f < kFields; ++f) {
                 float v = m[f];
                 for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
                 if (__lane_id() == 0 && v > 0.0f) atomicMax(maxbits + f, __float_as_uint(v));
@@ -104,7 +150,7 @@ struct CenterSink {
         } else {
             float v = qm;
             for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-            if (__lane_id() == 0 && v > 0.0f) atomicMax(maxbits + 2 * kCenterFields, __float_as_uint(v));
+            if (__lane_id() == 0 && v > 0.0f) atomicMax(maxbits + 2 * kFields, __float_as_uint(v));
         }
     }
 };
@@ -157,15 +203,10 @@ __global__ void __launch_bounds__(kCenterThreads) k_center_bwd(BvhDev bv, const 
                                                                int stride, int *err) {
     extern __shared__ uint32_t stack_mem[];
     const int64_t idx = (xcd_block(blockIdx.x, nblocks) * (kCenterThreads / 64) + threadIdx.x / 64) * stride;
-    CenterSink<PASS> sink;
-#pragma unroll
-    for (int f = 0; f < kCenterFields; ++f) sink.m[f] = 0.0f;
-    sink.qm = 0.0f;
-    sink.acc = acc + (int64_t)xcc_id() * kCenterFields * n;
-    sink.fx = fx;
-    sink.n = n;
+    FieldSink<PASS> sink;
+    sink.init(acc, fx, n);
     const float t_eps = bv.bounds[6];
-    SharedSurfelAcc<6> accI;   // the row's receiver: p (fields 0-2) and n (9-11)
+    SharedSurfelAcc<6> accI;   // the row's receiver: p and n
     accI.zero();
     uint32_t i = 0;
     if (idx < n) {
@@ -183,7 +224,7 @@ __global__ void __launch_bounds__(kCenterThreads) k_center_bwd(BvhDev bv, const 
             float T = 1.0f;
             float gpi[3] = {0.0f, 0.0f, 0.0f}, gpj[3] = {0.0f, 0.0f, 0.0f};
             trace_segment<kWalkHead>(bv, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, i, j, g.t_lo, g.t_hi, stack_mem + threadIdx.x,
-                          kCenterThreads, err, [&](const SurfRec &r) {
+                          kCenterThreads, err, [&](const SurfRec &r, int) {
                               // exact kernel value for T, FP32 geometry for the derivatives
                               const float gam = kernel_gamma(hit_r2_exact(r, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz));
                               T = __fmul_rn(T, transmit(r.c.w, gam));
@@ -201,14 +242,9 @@ __global__ void __launch_bounds__(kCenterThreads) k_center_bwd(BvhDev bv, const 
                               const float beta = (ghx * g.dx + ghy * g.dy + ghz * g.dz) / den;
                               const float gqx = beta * r.b.x - ghx, gqy = beta * r.b.y - ghy,
                                           gqz = beta * r.b.z - ghz;
-                              sink.add3(0, k, gqx, gqy, gqz);
-                              sink.add3(3, k, fu * hx, fu * hy, fu * hz);
-                              sink.add3(6, k, fw * hx, fw * hy, fw * hz);
-                              sink.add3(9, k, -beta * hx, -beta * hy, -beta * hz);
-                              sink.add(12, k, -fu * u);
-                              sink.add(13, k, -fw * w);
+                              sink.cross(k, r, fu, fw, beta, hx, hy, hz);
                               const float ok = bv.raw_op[k];
-                              if (ok > 0.0f && ok < kOpacityMax) sink.add(14, k, -W * gam / (1.0f - ok));
+                              if (ok > 0.0f && ok < kOpacityMax) sink.add(kFo, k, -W * gam / (1.0f - ok));
                               gpi[0] -= (1.0f - tk) * gqx;
                               gpi[1] -= (1.0f - tk) * gqy;
                               gpi[2] -= (1.0f - tk) * gqz;
@@ -230,36 +266,31 @@ __global__ void __launch_bounds__(kCenterThreads) k_center_bwd(BvhDev bv, const 
             const float dpx = c1 * ri.b.x + c2 * rj.b.x - c3 * g.dx;
             const float dpy = c1 * ri.b.y + c2 * rj.b.y - c3 * g.dy;
             const float dpz = c1 * ri.b.z + c2 * rj.b.z - c3 * g.dz;
-            sink.add3(0, j, dpx + gpj[0], dpy + gpj[1], dpz + gpj[2]);
-            accI.add<PASS>(sink, 0, 0, gpi[0] - dpx);
-            accI.add<PASS>(sink, 1, 1, gpi[1] - dpy);
-            accI.add<PASS>(sink, 2, 2, gpi[2] - dpz);
-            accI.add<PASS>(sink, 3, 9, c1 * g.dx);
-            accI.add<PASS>(sink, 4, 10, c1 * g.dy);
-            accI.add<PASS>(sink, 5, 11, c1 * g.dz);
-            sink.add3(9, j, c2 * g.dx, c2 * g.dy, c2 * g.dz);
-            const float phi = aa * ab / r4;
-            sink.add(15, j, G * A * T * phi * kInvPi);
-            const float gA = G * lambda[j] * T * phi * kInvPi;
-            sink.add(12, j, gA * A * rj.a.w);
-            sink.add(13, j, gA * A * rj.b.w);
-            sink.add(14, j, gA * bv.dado[j]);
+            sink.add3(kFp, j, dpx + gpj[0], dpy + gpj[1], dpz + gpj[2]);
+            accI.add<PASS>(sink, 0, kFp, gpi[0] - dpx);
+            accI.add<PASS>(sink, 1, kFp + 1, gpi[1] - dpy);
+            accI.add<PASS>(sink, 2, kFp + 2, gpi[2] - dpz);
+            accI.add<PASS>(sink, 3, kFn, c1 * g.dx);
+            accI.add<PASS>(sink, 4, kFn + 1, c1 * g.dy);
+            accI.add<PASS>(sink, 5, kFn + 2, c1 * g.dz);
+            sink.add3(kFn, j, c2 * g.dx, c2 * g.dy, c2 * g.dz);
+            sink.add(kFpair, j, G * T * (aa * ab / r4) * kInvPi);
         }
     }
     // one row per wave: every lane's receiver is the row's
     if (idx < n) {
-        const int fI[6] = {0, 1, 2, 9, 10, 11};
+        const int fI[6] = {kFp, kFp + 1, kFp + 2, kFn, kFn + 1, kFn + 2};
         accI.flush<PASS>(sink.acc, n, i, fI);
     }
-    sink.template report<PASS>(maxbits);
+    sink.report(maxbits);
 }
 
 // per-field exponent: (max contribution) * count * 2^margin < 2^62 (count
 // bounds the contributions a surfel's field can receive; margin: headroom
 // over a maximum estimated on sampled rows)
-__global__ void k_center_exp_count(const uint32_t *maxbits, int64_t count, int margin, int *fx) {
+__global__ void k_fields_exp(const uint32_t *maxbits, int64_t count, int margin, int *fx) {
     const int f = threadIdx.x;
-    if (f >= kCenterFields) return;
+    if (f >= kFields) return;
     const float m = __uint_as_float(maxbits[f]);
     int e = 0;
     if (!(m <= 3.0e38f)) {
@@ -272,20 +303,64 @@ __global__ void k_center_exp_count(const uint32_t *maxbits, int64_t count, int m
     fx[f] = e;
 }
 
-
-__global__ void __launch_bounds__(256) k_center_finish(const unsigned long long *__restrict__ acc, const int *fx,
-                                                       int64_t n, CenterOutputs out) {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= n * kCenterFields) return;
-    const int f = (int)(t / n);
-    const int64_t i = t - (int64_t)f * n;
-    float *o = out.p[f];
-    if (!o) return;
-    unsigned long long s = 0;
+// The gradients of the 15 surfel fields (and lambda) from the summed copies
+// of the fields, one thread per surfel, FP64 up to the one rounding.
+__global__ void __launch_bounds__(256) k_fields_finish(BvhDev bv, const unsigned long long *__restrict__ acc,
+                                                       const int *fx, const float *__restrict__ lambda,
+                                                       CenterOutputs out) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= bv.n) return;
+    double v[kFields];
 #pragma unroll
-    for (int x = 0; x < 8; ++x) s += acc[((int64_t)x * kCenterFields + f) * n + i];
-    const int e = fx[f];
-    o[i] = e == kFxNonFinite ? __builtin_nanf("") : __builtin_ldexpf(__ll2float_rn((long long)s), -e);
+    for (int f = 0; f < kFields; ++f) {
+        unsigned long long s = 0;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) s += acc[((int64_t)x * kFields + f) * bv.n + i];
+        const int e = fx[f];
+        v[f] = e == kFxNonFinite ? (double)__builtin_nanf("") : ldexp((double)(long long)s, -e);
+    }
+    const SurfRec r = bv.rec[bv.inv[i]];
+    const double tu[3] = {r.c.x, r.c.y, r.c.z}, tv[3] = {r.d.x, r.d.y, r.d.z}, nr[3] = {r.b.x, r.b.y, r.b.z};
+    // the crossings' sums of du h, dw h, beta h with their third coordinate
+    double duh[3], dwh[3], bh[3];
+    auto expand = [&](int f, double (&h)[3]) {
+        const int ax = plane_axis(r.b.x, r.b.y, r.b.z);
+        const double a = v[f], b = v[f + 1];
+        const double na = ax == 0 ? nr[1] : nr[0], nb = ax == 2 ? nr[1] : nr[2];
+        const double nd = ax == 0 ? nr[0] : (ax == 1 ? nr[1] : nr[2]);
+        const double c = a == 0.0 && b == 0.0 ? 0.0 : -(na * a + nb * b) / nd;
+        h[0] = ax == 0 ? c : a;
+        h[1] = ax == 1 ? c : (ax == 0 ? a : b);
+        h[2] = ax == 2 ? c : b;
+    };
+    expand(kFduh, duh);
+    expand(kFdwh, dwh);
+    expand(kFbetah, bh);
+    auto times = [](double s, double x) { return s == 0.0 ? 0.0 : s * x; };   // no crossing: 0 whatever the frame
+    double su = 0.0, sv = 0.0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        if (out.p[c])
+            out.p[c][i] = (float)(v[kFp + c] + times(v[kFbeta], nr[c]) - times(v[kFdu], tu[c]) - times(v[kFdw], tv[c]));
+        if (out.p[3 + c]) out.p[3 + c][i] = (float)(v[kFtu + c] + duh[c]);
+        if (out.p[6 + c]) out.p[6 + c][i] = (float)(v[kFtv + c] + dwh[c]);
+        if (out.p[9 + c]) out.p[9 + c][i] = (float)(v[kFn + c] - bh[c]);
+        su -= times(duh[c], tu[c]);
+        sv -= times(dwh[c], tv[c]);
+    }
+    // through lambda_j A_j: dA/ds_u = A / s_u, dA/do as stored
+    double lam = 0.0, o = v[kFo];
+    if (lambda && v[kFpair] != 0.0) {
+        const double A = (double)(float)bv.area[i], gA = v[kFpair] * lambda[i];
+        lam = v[kFpair] * A;
+        su += gA * A;
+        sv += gA * A;
+        o += gA * bv.dado[i];
+    }
+    if (out.p[12]) out.p[12][i] = (float)times(su, (double)r.a.w);
+    if (out.p[13]) out.p[13][i] = (float)times(sv, (double)r.b.w);
+    if (out.p[14]) out.p[14][i] = (float)o;
+    if (out.p[15]) out.p[15][i] = (float)lam;
 }
 
 // ---------------------------------------------------------------------------
@@ -298,7 +373,7 @@ __global__ void __launch_bounds__(256) k_center_finish(const unsigned long long 
 // u = h . t_u / s_u, w = h . t_v / s_v, h = t d - q, q = p_k - p_i,
 // t = (q . n_k)/(d . n_k).  The hit point is the FP64 intersection.  Sums in
 // 64-bit fixed point with per-field scales from a first pass (bit-identical
-// between runs), one copy per XCD; fields px..o as in CenterOutputs.
+// between runs), one copy per XCD.
 template <int PASS>
 __global__ void __launch_bounds__(256) k_geometry_rec(BvhDev bv, int R, uint64_t seed, const uint2 *__restrict__ recs,
                                                       const uint32_t *__restrict__ rcnt, int rcap, int64_t nblocks,
@@ -326,13 +401,8 @@ __global__ void __launch_bounds__(256) k_geometry_rec(BvhDev bv, int R, uint64_t
         hv[h] = gF[e0 + k] * invR;
     }
     __syncthreads();
-    CenterSink<PASS> sink;
-#pragma unroll
-    for (int f = 0; f < kCenterFields; ++f) sink.m[f] = 0.0f;
-    sink.qm = 0.0f;
-    sink.acc = acc + (int64_t)xcc_id() * kCenterFields * bv.n;
-    sink.fx = fx;
-    sink.n = bv.n;
+    FieldSink<PASS> sink;
+    sink.init(acc, fx, bv.n);
     SharedSurfelAcc<12> accI;   // the receiver: p, t_u, t_v, n (fields 0-11)
     accI.zero();
     for (int r = tid; r < R; r += blockDim.x) {
@@ -375,7 +445,7 @@ __global__ void __launch_bounds__(256) k_geometry_rec(BvhDev bv, int R, uint64_t
             T = __fmul_rn(T, f);
             if (dLda == 0.0f) continue;
             const float ok = bv.raw_op[k];
-            if (ok > 0.0f && ok < kOpacityMax) sink.add(14, k, dLda * g * f / (1.0f - ok));
+            if (ok > 0.0f && ok < kOpacityMax) sink.add(kFo, k, dLda * g * f / (1.0f - ok));
             // the FP64 hit point of the FP32 ray on k's plane
             const SurfRec rk = bv.rec[bv.inv[k]];
             const double nx = rk.b.x, ny = rk.b.y, nz = rk.b.z;
@@ -390,12 +460,7 @@ __global__ void __launch_bounds__(256) k_geometry_rec(BvhDev bv, int R, uint64_t
             const float ghx = du * rk.c.x + dw * rk.d.x, ghy = du * rk.c.y + dw * rk.d.y, ghz = du * rk.c.z + dw * rk.d.z;
             const float beta = (ghx * dx + ghy * dy + ghz * dz) / (float)den;
             const float gqx = beta * rk.b.x - ghx, gqy = beta * rk.b.y - ghy, gqz = beta * rk.b.z - ghz;
-            sink.add3(0, k, gqx, gqy, gqz);
-            sink.add3(3, k, du * hx, du * hy, du * hz);
-            sink.add3(6, k, dw * hx, dw * hy, dw * hz);
-            sink.add3(9, k, -beta * hx, -beta * hy, -beta * hz);
-            sink.add(12, k, -du * u);
-            sink.add(13, k, -dw * w);
+            sink.cross(k, rk, du, dw, beta, hx, hy, hz);
             const float tf = (float)tk;
             gpi[0] -= gqx;
             gpi[1] -= gqy;
@@ -416,7 +481,7 @@ __global__ void __launch_bounds__(256) k_geometry_rec(BvhDev bv, int R, uint64_t
         const int fI[12] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11};
         accI.flush<PASS>(sink.acc, bv.n, i, fI);
     }
-    sink.template report<PASS>(maxbits);
+    sink.report(maxbits);
 }
 
 
@@ -424,64 +489,61 @@ __global__ void __launch_bounds__(256) k_geometry_rec(BvhDev bv, int R, uint64_t
 // direct-light gradients: light positions and intensities, albedo, surfel
 // fields of the receivers and of the occluders on the shadow segments
 // ---------------------------------------------------------------------------
-// One thread per receiver, lights in turn.  With v = x_l - p_i, r = |v|,
-// ndot = n_i . v > 0, E_c = o a_c kappa I ndot T / r^3 (kappa = 2/sqrt(pi)),
+// One thread per receiver and chunk of lights (lanes: neighbouring receivers
+// in Morton order).  With v = x_l - p_i, r = |v|, ndot = n_i . v > 0,
+// E_c = o a_c kappa I ndot T / r^3 (kappa = 2/sqrt(pi)),
 // S = sum_c dL/dE_c a_c, Q = S o kappa I T:
 //   dL/dI += S o kappa ndot T / r^3, dL/da_c += dL/dE_c o kappa I ndot T / r^3,
 //   dL/do_i += S kappa I ndot T / r^3, g_v = Q (n/r^3 - 3 ndot v/r^5):
 //   x_l += g_v, p_i -= g_v, n_i += Q v / r^3,
 // and the shadow segment's occluders as for a centre-to-centre segment with
-// W = S o kappa I ndot T / r^3.  Fields 0..14 surfel (px..o), 15..18 the
-// light (x, y, z, I) in their own accumulators; fixed point as above.
-constexpr int kLightFields = 19;
+// W = S o kappa I ndot T / r^3.  The surfel fields are FieldSink's, the
+// light's (x, y, z, I) have accumulators of their own; fixed point as above.
+//
+// Bound by the latency of the walks, so by the lanes that walk: one lane per
+// receiver that walked the lights in turn left most of the chip idle (16k
+// surfels, 100 lights: 458 ms); chunks of lights give 2^19 lanes.  A walk
+// finds T and keeps the positions of the first kLightHits surfels crossed;
+// their terms, which need T, are formed from that list.  Only a segment with
+// more crossings is walked again.  The lights' chunks of dL/da are added in
+// order by k_light_albedo.
+constexpr int kLightFields = kFields + 4;
+constexpr int kLightHits = 24;   // in LDS: a private array becomes registers (183 VGPRs)
+constexpr int64_t kLightLanes = (int64_t)1 << 19;
+
+// lights per lane
+inline int light_chunk(int64_t n, int Lt) {
+    const int64_t chunks = std::min<int64_t>(Lt, std::max<int64_t>(1, kLightLanes / n));
+    return (int)((Lt + chunks - 1) / chunks);
+}
 
 template <int PASS>
-struct LightSink {
-    float m[kLightFields];
-    unsigned long long *acc;     // surfel fields [16][n] of this XCD
-    unsigned long long *lacc;    // light fields [4][Lt] of this XCD
-    const int *fx;
-    int64_t n;
-    int Lt;
-    __device__ __forceinline__ void add(int f, uint32_t surfel, float v) {
-        if (PASS == 0) m[f] = fmaxf(m[f], fabsf(v));
-        else fx_add(acc + (int64_t)f * n + surfel, v, __builtin_ldexpf(1.0f, fx[f]));
-    }
-    __device__ __forceinline__ void add3(int f, uint32_t surfel, float x, float y, float z) {
-        add(f, surfel, x);
-        add(f + 1, surfel, y);
-        add(f + 2, surfel, z);
-    }
-};
-
-template <int PASS>
-__global__ void __launch_bounds__(128) k_direct_bwd(BvhDev bv, const float *__restrict__ albedo,
-                                                    const float *__restrict__ lpos, const float *__restrict__ lI,
-                                                    int Lt, int K, const float *__restrict__ gE, uint32_t *maxbits,
-                                                    const int *fx, unsigned long long *acc, unsigned long long *lacc,
-                                                    float *__restrict__ g_alb, int *err) {
+__global__ void __launch_bounds__(kCenterThreads) k_direct_bwd(BvhDev bv, const float *__restrict__ albedo,
+                                                               const float *__restrict__ lpos,
+                                                               const float *__restrict__ lI, int Lt, int chunk, int K,
+                                                               const float *__restrict__ gE, uint32_t *maxbits,
+                                                               const int *fx, unsigned long long *acc,
+                                                               unsigned long long *lacc, float *__restrict__ g_alb,
+                                                               int *err) {
     extern __shared__ uint32_t stack_mem[];
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    LightSink<PASS> sink;
-#pragma unroll
-    for (int f = 0; f < kLightFields; ++f) sink.m[f] = 0.0f;
-    const int xcc = xcc_id();
-    sink.acc = acc + (int64_t)xcc * kCenterFields * bv.n;
-    sink.lacc = lacc + (int64_t)xcc * 4 * Lt;
-    sink.fx = fx;
-    sink.n = bv.n;
-    sink.Lt = Lt;
-    const bool live = i < bv.n;
-    const SurfRec rr = live ? bv.rec[bv.inv[i]] : bv.rec[0];
+    uint32_t *hit = stack_mem + kWalkHead * kCenterThreads + threadIdx.x;   // the lane's list of crossings
+    const int64_t slot = (int64_t)blockIdx.x * kCenterThreads + threadIdx.x;
+    FieldSink<PASS> sink;
+    sink.init(acc, fx, bv.n);
+    unsigned long long *lsum = lacc + (int64_t)xcc_id() * 4 * Lt;   // this XCD's light fields [4][Lt]
+    float lm[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    const bool live = slot < bv.n;
+    const SurfRec rr = bv.rec[live ? slot : 0];
+    const uint32_t i = __float_as_uint(rr.d.w);
     const float oc = live ? bv.op[i] : 0.0f;
     const float oraw = live ? bv.raw_op[i] : 0.0f;
     const bool inside = oraw > 0.0f && oraw < kOpacityMax;
     float ga[3] = {0.0f, 0.0f, 0.0f};
-    const float a0 = live ? albedo[3 * i] : 0.0f, a1 = live ? albedo[3 * i + 1] : 0.0f,
-                a2 = live ? albedo[3 * i + 2] : 0.0f;
-    for (int l = 0; l < Lt; ++l) {
+    const float a0 = albedo[3 * (int64_t)i], a1 = albedo[3 * (int64_t)i + 1], a2 = albedo[3 * (int64_t)i + 2];
+    const int l0 = (int)blockIdx.y * chunk, l1 = min(Lt, l0 + chunk);
+    for (int l = l0; l < l1; ++l) {
         float gl[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        const float *ge = gE + ((i * Lt + l) * K) * 3;
+        const float *ge = gE + (((int64_t)i * Lt + l) * K) * 3;
         const float S = live ? ge[0] * a0 + ge[1] * a1 + ge[2] * a2 : 0.0f;
         const float dx = __fsub_rn(lpos[3 * l + 0], rr.a.x);
         const float dy = __fsub_rn(lpos[3 * l + 1], rr.a.y);
@@ -494,18 +556,21 @@ __global__ void __launch_bounds__(128) k_direct_bwd(BvhDev bv, const float *__re
             const float r3 = dd * len, r5 = r3 * dd;
             // the transmittance first (the occluders' weight W needs it)
             float T = 1.0f;
-            trace_segment<kWalkHead>(bv, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz, (uint32_t)i, (uint32_t)i, t_lo, 1.0f,
-                          stack_mem + threadIdx.x, blockDim.x, err, [&](const SurfRec &r) {
-                              T = __fmul_rn(T, transmit(r.c.w, kernel_gamma(hit_r2_exact(r, rr.a.x, rr.a.y, rr.a.z,
-                                                                                         dx, dy, dz))));
-                          });
+            int hits = 0;
+            trace_segment<kWalkHead>(bv, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz, i, i, t_lo, 1.0f, stack_mem + threadIdx.x,
+                                     kCenterThreads, err, [&](const SurfRec &r, int s) {
+                                         T = __fmul_rn(T, transmit(r.c.w, kernel_gamma(hit_r2_exact(
+                                                                              r, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz))));
+                                         if (hits < kLightHits) hit[hits * kCenterThreads] = (uint32_t)s;
+                                         ++hits;
+                                     });
             const float kI = 1.1283791670955126f * lI[l];
             const float base = kI * ndot * T / r3;
             gl[3] = S * oc * 1.1283791670955126f * ndot * T / r3;
             ga[0] += ge[0] * oc * base;
             ga[1] += ge[1] * oc * base;
             ga[2] += ge[2] * oc * base;
-            if (inside) sink.add(14, (uint32_t)i, S * base);
+            if (inside) sink.add(kFo, i, S * base);
             const float Q = S * oc * kI * T;
             const float gvx = Q * (rr.b.x / r3 - 3.0f * ndot * dx / r5);
             const float gvy = Q * (rr.b.y / r3 - 3.0f * ndot * dy / r5);
@@ -514,70 +579,81 @@ __global__ void __launch_bounds__(128) k_direct_bwd(BvhDev bv, const float *__re
             gl[0] = gvx;
             gl[1] = gvy;
             gl[2] = gvz;
-            sink.add3(9, (uint32_t)i, Q * dx / r3, Q * dy / r3, Q * dz / r3);
+            sink.add3(kFn, i, Q * dx / r3, Q * dy / r3, Q * dz / r3);
             const float W = S * oc * base;
-            trace_segment<kWalkHead>(bv, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz, (uint32_t)i, (uint32_t)i, t_lo, 1.0f,
-                          stack_mem + threadIdx.x, blockDim.x, err, [&](const SurfRec &r) {
-                              const float gam = kernel_gamma(hit_r2_exact(r, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz));
-                              const uint32_t k = __float_as_uint(r.d.w);
-                              const float qx = r.a.x - rr.a.x, qy = r.a.y - rr.a.y, qz = r.a.z - rr.a.z;
-                              const float den = dx * r.b.x + dy * r.b.y + dz * r.b.z;
-                              const float tk = (qx * r.b.x + qy * r.b.y + qz * r.b.z) / den;
-                              const float hx = tk * dx - qx, hy = tk * dy - qy, hz = tk * dz - qz;
-                              const float u = (hx * r.c.x + hy * r.c.y + hz * r.c.z) * r.a.w;
-                              const float w = (hx * r.d.x + hy * r.d.y + hz * r.d.z) * r.b.w;
-                              const float f = W * 3.4f * r.c.w * gam;
-                              const float fu = f * u * r.a.w, fw = f * w * r.b.w;
-                              const float ghx = fu * r.c.x + fw * r.d.x, ghy = fu * r.c.y + fw * r.d.y,
-                                          ghz = fu * r.c.z + fw * r.d.z;
-                              const float beta = (ghx * dx + ghy * dy + ghz * dz) / den;
-                              const float gqx = beta * r.b.x - ghx, gqy = beta * r.b.y - ghy,
-                                          gqz = beta * r.b.z - ghz;
-                              sink.add3(0, k, gqx, gqy, gqz);
-                              sink.add3(3, k, fu * hx, fu * hy, fu * hz);
-                              sink.add3(6, k, fw * hx, fw * hy, fw * hz);
-                              sink.add3(9, k, -beta * hx, -beta * hy, -beta * hz);
-                              sink.add(12, k, -fu * u);
-                              sink.add(13, k, -fw * w);
-                              const float ok = bv.raw_op[k];
-                              if (ok > 0.0f && ok < kOpacityMax) sink.add(14, k, -W * gam / (1.0f - ok));
-                              gpi[0] -= (1.0f - tk) * gqx;
-                              gpi[1] -= (1.0f - tk) * gqy;
-                              gpi[2] -= (1.0f - tk) * gqz;
-                              gl[0] -= tk * gqx;
-                              gl[1] -= tk * gqy;
-                              gl[2] -= tk * gqz;
-                          });
-            sink.add3(0, (uint32_t)i, gpi[0], gpi[1], gpi[2]);
+            auto crossed = [&](const SurfRec &r, int) {
+                const float gam = kernel_gamma(hit_r2_exact(r, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz));
+                const uint32_t k = __float_as_uint(r.d.w);
+                const float qx = r.a.x - rr.a.x, qy = r.a.y - rr.a.y, qz = r.a.z - rr.a.z;
+                const float den = dx * r.b.x + dy * r.b.y + dz * r.b.z;
+                const float tk = (qx * r.b.x + qy * r.b.y + qz * r.b.z) / den;
+                const float hx = tk * dx - qx, hy = tk * dy - qy, hz = tk * dz - qz;
+                const float u = (hx * r.c.x + hy * r.c.y + hz * r.c.z) * r.a.w;
+                const float w = (hx * r.d.x + hy * r.d.y + hz * r.d.z) * r.b.w;
+                const float f = W * 3.4f * r.c.w * gam;
+                const float fu = f * u * r.a.w, fw = f * w * r.b.w;
+                const float ghx = fu * r.c.x + fw * r.d.x, ghy = fu * r.c.y + fw * r.d.y,
+                            ghz = fu * r.c.z + fw * r.d.z;
+                const float beta = (ghx * dx + ghy * dy + ghz * dz) / den;
+                const float gqx = beta * r.b.x - ghx, gqy = beta * r.b.y - ghy, gqz = beta * r.b.z - ghz;
+                sink.cross(k, r, fu, fw, beta, hx, hy, hz);
+                const float ok = bv.raw_op[k];
+                if (ok > 0.0f && ok < kOpacityMax) sink.add(kFo, k, -W * gam / (1.0f - ok));
+                gpi[0] -= (1.0f - tk) * gqx;
+                gpi[1] -= (1.0f - tk) * gqy;
+                gpi[2] -= (1.0f - tk) * gqz;
+                gl[0] -= tk * gqx;
+                gl[1] -= tk * gqy;
+                gl[2] -= tk * gqz;
+            };
+            if (hits <= kLightHits) {
+                for (int h = 0; h < hits; ++h) crossed(bv.rec[hit[h * kCenterThreads]], 0);
+            } else {
+                trace_segment<kWalkHead>(bv, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz, i, i, t_lo, 1.0f,
+                                         stack_mem + threadIdx.x, kCenterThreads, err, crossed);
+            }
+            sink.add3(kFp, i, gpi[0], gpi[1], gpi[2]);
         }
         // the light's fields: one wave sum, then one fixed-point add per wave
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             if (PASS == 0) {
-                sink.m[15 + q] = fmaxf(sink.m[15 + q], fabsf(gl[q]));
+                lm[q] = fmaxf(lm[q], fabsf(gl[q]));
             } else {
-                const long long fxv = __float2ll_rn(gl[q] * __builtin_ldexpf(1.0f, fx[15 + q]));
+                const long long fxv = __float2ll_rn(gl[q] * __builtin_ldexpf(1.0f, fx[kFields + q]));
                 unsigned long long tot = (unsigned long long)fxv;
                 for (int off = 32; off > 0; off >>= 1) tot += (unsigned long long)__shfl_xor((long long)tot, off, 64);
                 if (__lane_id() == 0 && tot != 0)
-                    __hip_atomic_fetch_add(sink.lacc + (int64_t)q * Lt + l, tot, __ATOMIC_RELAXED,
+                    __hip_atomic_fetch_add(lsum + (int64_t)q * Lt + l, tot, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_WORKGROUP);
             }
         }
     }
     if (PASS == 1 && live && g_alb) {
-        g_alb[3 * i + 0] = ga[0];
-        g_alb[3 * i + 1] = ga[1];
-        g_alb[3 * i + 2] = ga[2];
+        float *o = g_alb + ((int64_t)blockIdx.y * bv.n + i) * 3;
+        o[0] = ga[0];
+        o[1] = ga[1];
+        o[2] = ga[2];
     }
     if (PASS == 0) {
+        sink.report(maxbits);
 #pragma unroll
-        for (int f = 0; f < kLightFields; ++f) {
-            float v = sink.m[f];
+        for (int q = 0; q < 4; ++q) {
+            float v = lm[q];
             for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-            if (__lane_id() == 0 && v > 0.0f) atomicMax(maxbits + f, __float_as_uint(v));
+            if (__lane_id() == 0 && v > 0.0f) atomicMax(maxbits + kFields + q, __float_as_uint(v));
         }
     }
+}
+
+// dL/dalbedo: the chunks' sums in the lights' order
+__global__ void __launch_bounds__(256) k_light_albedo(const float *__restrict__ part, int64_t vals, int chunks,
+                                                      float *__restrict__ g_alb) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= vals) return;
+    float s = part[t];
+    for (int y = 1; y < chunks; ++y) s += part[(int64_t)y * vals + t];
+    g_alb[t] = s;
 }
 
 __global__ void k_light_exp(const uint32_t *maxbits, int64_t count_surfel, int64_t count_light, int *fx) {
@@ -589,7 +665,7 @@ __global__ void k_light_exp(const uint32_t *maxbits, int64_t count_surfel, int64
         e = kFxNonFinite;
     } else if (m > 0.0f) {
         int ex;
-        (void)frexpf(m * (float)(f < 15 ? count_surfel : count_light), &ex);
+        (void)frexpf(m * (float)(f < kFields ? count_surfel : count_light), &ex);
         e = min(120, max(-120, 62 - ex));
     }
     fx[f] = e;
@@ -602,7 +678,7 @@ __global__ void k_light_finish(const unsigned long long *__restrict__ lacc, cons
     const int q = t / Lt, l = t % Lt;
     unsigned long long s = 0;
     for (int x = 0; x < 8; ++x) s += lacc[((int64_t)x * 4 + q) * Lt + l];
-    const int e = fx[15 + q];
+    const int e = fx[kFields + q];
     const float v = e == kFxNonFinite ? __builtin_nanf("") : __builtin_ldexpf(__ll2float_rn((long long)s), -e);
     if (q < 3) {
         if (g_lpos) g_lpos[3 * l + q] = v;
@@ -634,21 +710,21 @@ gsrad_status launch_ff_center(const BvhDev &bv, const Csr &P, const float *lambd
 constexpr int kScaleStride = 64;
 constexpr int kScaleMargin = 12;
 
-size_t center_acc_bytes(int64_t n) { return (size_t)8 * kCenterFields * n * 8 + 512; }
+size_t center_acc_bytes(int64_t n) { return (size_t)8 * kFields * n * 8 + 512; }
 
-// accumulator layout: [8 XCD copies][16 fields][n] u64, then maxbits[16],
-// fx[16], the largest scaled contribution of the accumulating pass (as
-// float bits) at maxbits[32]
+// accumulator layout: [8 XCD copies][kFields][n] u64, then maxbits[kFields],
+// fx[kFields], the largest scaled contribution of the accumulating pass (as
+// float bits) at maxbits[2 kFields]
 static gsrad_status center_scaled_passes(int64_t n, int64_t count, void *acc, hipStream_t st,
                                          const std::function<void(int pass, int stride)> &run) {
     unsigned long long *a = static_cast<unsigned long long *>(acc);
-    uint32_t *maxbits = reinterpret_cast<uint32_t *>(a + (size_t)8 * kCenterFields * n);
-    int *fx = reinterpret_cast<int *>(maxbits + kCenterFields);
+    uint32_t *maxbits = reinterpret_cast<uint32_t *>(a + (size_t)8 * kFields * n);
+    int *fx = reinterpret_cast<int *>(maxbits + kFields);
     run(0, kScaleStride);
-    hipLaunchKernelGGL(k_center_exp_count, dim3(1), dim3(64), 0, st, maxbits, count, kScaleMargin, fx);
+    hipLaunchKernelGGL(k_fields_exp, dim3(1), dim3(64), 0, st, maxbits, count, kScaleMargin, fx);
     run(1, 1);
     uint32_t qbits = 0;
-    gsrad_status e = check_hip(hipMemcpyAsync(&qbits, maxbits + 2 * kCenterFields, 4, hipMemcpyDeviceToHost, st),
+    gsrad_status e = check_hip(hipMemcpyAsync(&qbits, maxbits + 2 * kFields, 4, hipMemcpyDeviceToHost, st),
                                "scale check copy");
     if (e != GSRAD_OK) return e;
     if ((e = check_hip(hipStreamSynchronize(st), "scale check sync")) != GSRAD_OK) return e;
@@ -657,12 +733,12 @@ static gsrad_status center_scaled_passes(int64_t n, int64_t count, void *acc, hi
     if (!(qmax * (double)count < 4.6e18)) {
         // the sampled rows missed the largest contributions: exact maxima from
         // every row, then the sums again
-        const size_t bytes = (size_t)8 * kCenterFields * n * 8;
-        if ((e = check_hip(hipMemsetAsync(a, 0, bytes + 3 * kCenterFields * 4, st), "accumulators zero")) !=
+        const size_t bytes = (size_t)8 * kFields * n * 8;
+        if ((e = check_hip(hipMemsetAsync(a, 0, bytes + 3 * kFields * 4, st), "accumulators zero")) !=
             GSRAD_OK)
             return e;
         run(0, 1);
-        hipLaunchKernelGGL(k_center_exp_count, dim3(1), dim3(64), 0, st, maxbits, count, 0, fx);
+        hipLaunchKernelGGL(k_fields_exp, dim3(1), dim3(64), 0, st, maxbits, count, 0, fx);
         run(1, 1);
     }
     return check_hip(hipGetLastError(), "scaled passes");
@@ -672,8 +748,8 @@ gsrad_status launch_center_backward(const BvhDev &bv, const Csr &F, const float 
                                     const CenterOutputs &out, int *err, hipStream_t st) {
     if (F.n == 0) return GSRAD_OK;
     unsigned long long *a = static_cast<unsigned long long *>(acc);
-    uint32_t *maxbits = reinterpret_cast<uint32_t *>(a + (size_t)8 * kCenterFields * F.n);
-    int *fx = reinterpret_cast<int *>(maxbits + kCenterFields);
+    uint32_t *maxbits = reinterpret_cast<uint32_t *>(a + (size_t)8 * kFields * F.n);
+    int *fx = reinterpret_cast<int *>(maxbits + kFields);
     const size_t smem = walk_bytes(kWalkHead);
     auto run = [&](int pass, int stride) {
         const int64_t rows = (F.n + stride - 1) / stride;
@@ -687,8 +763,7 @@ gsrad_status launch_center_backward(const BvhDev &bv, const Csr &F, const float 
     };
     gsrad_status e = center_scaled_passes(F.n, 2 * F.nnz + 2, acc, st, run);
     if (e != GSRAD_OK) return e;
-    const int64_t tot = F.n * kCenterFields;
-    hipLaunchKernelGGL(k_center_finish, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, a, fx, F.n, out);
+    hipLaunchKernelGGL(k_fields_finish, dim3((unsigned)((F.n + 255) / 256)), dim3(256), 0, st, bv, a, fx, lambda, out);
     return check_hip(hipGetLastError(), "centre-to-centre backward launch");
 }
 
@@ -711,8 +786,8 @@ gsrad_status launch_geometry_rec(const BvhDev &bv, int R, uint64_t seed, const u
         attr_set = true;
     }
     unsigned long long *a = static_cast<unsigned long long *>(acc);
-    uint32_t *maxbits = reinterpret_cast<uint32_t *>(a + (size_t)8 * kCenterFields * bv.n);
-    int *fx = reinterpret_cast<int *>(maxbits + kCenterFields);
+    uint32_t *maxbits = reinterpret_cast<uint32_t *>(a + (size_t)8 * kFields * bv.n);
+    int *fx = reinterpret_cast<int *>(maxbits + kFields);
     auto run = [&](int pass, int stride) {
         const int64_t nb = (bv.n + stride - 1) / stride;
         if (pass == 0)
@@ -726,33 +801,46 @@ gsrad_status launch_geometry_rec(const BvhDev &bv, int R, uint64_t seed, const u
     if (e != GSRAD_OK) return e;
     CenterOutputs o15 = out;
     o15.p[15] = nullptr;
-    const int64_t tot = bv.n * kCenterFields;
-    hipLaunchKernelGGL(k_center_finish, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, a, fx, bv.n, o15);
+    hipLaunchKernelGGL(k_fields_finish, dim3((unsigned)((bv.n + 255) / 256)), dim3(256), 0, st, bv, a, fx, nullptr,
+                       o15);
     return check_hip(hipGetLastError(), "geometry backward launch");
 }
 
-size_t light_acc_bytes(int64_t n, int Lt) {
-    return (size_t)8 * kCenterFields * n * 8 + (size_t)8 * 4 * Lt * 8 + 256;
+// [8 XCD copies][kFields][n] u64, the lights' [8][4][Lt] u64, maxbits[32],
+// fx[32], then the chunks' dL/dalbedo [chunks][n][3] (one chunk writes the
+// caller's array)
+size_t light_acc_bytes(int64_t n, int Lt) { return (size_t)8 * kFields * n * 8 + (size_t)8 * 4 * Lt * 8 + 256; }
+
+size_t light_part_bytes(int64_t n, int Lt) {
+    const int chunk = light_chunk(n, Lt), chunks = (Lt + chunk - 1) / chunk;
+    return chunks > 1 ? (size_t)chunks * n * 3 * 4 : 0;
 }
 
 gsrad_status launch_direct_backward(const BvhDev &bv, const float *albedo, const float *lpos, const float *lI, int Lt,
                                     int K, const float *gE, void *acc, float *g_lpos, float *g_lI, float *g_alb,
                                     const CenterOutputs &out, int *err, hipStream_t st) {
+    static_assert(kLightFields <= 32, "maxbits and fx hold 32 entries each");
     unsigned long long *a = static_cast<unsigned long long *>(acc);
-    unsigned long long *la = a + (size_t)8 * kCenterFields * bv.n;
+    unsigned long long *la = a + (size_t)8 * kFields * bv.n;
     uint32_t *maxbits = reinterpret_cast<uint32_t *>(la + (size_t)8 * 4 * Lt);
     int *fx = reinterpret_cast<int *>(maxbits + 32);
-    const dim3 grid((unsigned)((bv.n + 127) / 128));
-    const size_t smem = walk_bytes(kWalkHead);
-    hipLaunchKernelGGL(k_direct_bwd<0>, grid, dim3(128), smem, st, bv, albedo, lpos, lI, Lt, K, gE, maxbits, fx, a, la,
-                       g_alb, err);
+    float *part = reinterpret_cast<float *>(fx + 32);
+    const int chunk = light_chunk(bv.n, Lt), chunks = (Lt + chunk - 1) / chunk;
+    const dim3 grid((unsigned)((bv.n + kCenterThreads - 1) / kCenterThreads), (unsigned)chunks);
+    const size_t smem = walk_bytes(kWalkHead + kLightHits);
+    float *ga = chunks > 1 && g_alb ? part : g_alb;
+    hipLaunchKernelGGL(k_direct_bwd<0>, grid, dim3(kCenterThreads), smem, st, bv, albedo, lpos, lI, Lt, chunk, K, gE,
+                       maxbits, fx, a, la, ga, err);
     hipLaunchKernelGGL(k_light_exp, dim3(1), dim3(64), 0, st, maxbits, bv.n * (int64_t)Lt + bv.n, bv.n, fx);
-    hipLaunchKernelGGL(k_direct_bwd<1>, grid, dim3(128), smem, st, bv, albedo, lpos, lI, Lt, K, gE, maxbits, fx, a, la,
-                       g_alb, err);
+    hipLaunchKernelGGL(k_direct_bwd<1>, grid, dim3(kCenterThreads), smem, st, bv, albedo, lpos, lI, Lt, chunk, K, gE,
+                       maxbits, fx, a, la, ga, err);
+    if (ga != g_alb)
+        hipLaunchKernelGGL(k_light_albedo, dim3((unsigned)((3 * bv.n + 255) / 256)), dim3(256), 0, st, part, 3 * bv.n,
+                           chunks, g_alb);
     CenterOutputs o15 = out;
     o15.p[15] = nullptr;
-    const int64_t tot = bv.n * kCenterFields;
-    hipLaunchKernelGGL(k_center_finish, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, a, fx, bv.n, o15);
+    hipLaunchKernelGGL(k_fields_finish, dim3((unsigned)((bv.n + 255) / 256)), dim3(256), 0, st, bv, a, fx, nullptr,
+                       o15);
     hipLaunchKernelGGL(k_light_finish, dim3((unsigned)((4 * Lt + 63) / 64)), dim3(64), 0, st, la, fx, Lt, g_lpos, g_lI);
     return check_hip(hipGetLastError(), "direct light backward launch");
 }

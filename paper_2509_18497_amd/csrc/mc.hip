@@ -211,7 +211,7 @@ __global__ void __launch_bounds__(kCenterThreads) k_mc_ne(BvhDev bv, int G, cons
         const Segment g = make_segment(ra, rj, bv.bounds[6]);
         float T = 1.0f;
         trace_segment<kStackDeep>(bv, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, (uint32_t)a, (uint32_t)jsel, g.t_lo, g.t_hi,
-                      stack_mem + threadIdx.x, kCenterThreads, err, [&](const SurfRec &r) {
+                      stack_mem + threadIdx.x, kCenterThreads, err, [&](const SurfRec &r, int) {
                           T = __fmul_rn(T, transmit(r.c.w, kernel_gamma(hit_r2_exact(r, g.ox, g.oy, g.oz, g.dx,
                                                                                      g.dy, g.dz))));
                       });

@@ -323,7 +323,7 @@ __device__ __forceinline__ float row_hash_lookup(const uint32_t *hk, const float
 
 // Every surfel other than skip_a and skip_b whose support the segment
 // o + t d, t in (t_lo, t_hi), crosses (D_hit, both faces occlude);
-// on_hit(record) per crossing, in traversal order.
+// on_hit(record, sorted position) per crossing, in traversal order.
 template <int HEAD, typename OnHit>
 __device__ __forceinline__ void trace_segment(const BvhDev &bv, float ox, float oy, float oz, float dx, float dy,
                                               float dz, uint32_t skip_a, uint32_t skip_b, float t_lo, float t_hi,
@@ -338,7 +338,7 @@ __device__ __forceinline__ void trace_segment(const BvhDev &bv, float ox, float 
         float t, r2;
         bool front;
         if (!hit_test(r, ox, oy, oz, dx, dy, dz, t_lo, t_hi, true, t, r2, front)) return;
-        on_hit(r);
+        on_hit(r, s);
     };
     if (bv.n == 1) {
         leaf(0);
@@ -381,7 +381,6 @@ __device__ __forceinline__ void trace_segment(const BvhDev &bv, float ox, float 
 constexpr int kCenterThreads = 128;   // two rows (waves) per workgroup
 // LDS of a workgroup's walks
 constexpr size_t walk_bytes(int head) { return (size_t)head * kCenterThreads * sizeof(uint32_t); }
-constexpr int kCenterFields = 16;     // p(3), t_u(3), t_v(3), n(3), s_u, s_v, o, lambda
 constexpr float kInvPi = 0.318309886183790672f;
 
 struct Segment {
