@@ -1399,7 +1399,7 @@ gsrad_status gsrad_direct_light_backward(const gsrad_bvh *bvh, const float *albe
     hipStream_t st = S(stream);
     gsrad_bvh *h = const_cast<gsrad_bvh *>(bvh);
     const size_t bytes = light_acc_bytes(bvh->n, n_lights);
-    GS_TRY(h->lacc.ensure(bytes + light_part_bytes(bvh->n, n_lights), "direct light gradient accumulators"));
+    GS_TRY(h->lacc.ensure(bytes + light_seg_bytes(bvh->n, n_lights), "direct light gradient accumulators"));
     GS_TRY(check_hip(hipMemsetAsync(h->lacc.p, 0, bytes, st), "accumulators zero"));
     GS_TRY(h->height.ensure(64, "flags"));
     const gsrad_surfel_grads z{};

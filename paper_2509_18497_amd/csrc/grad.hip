@@ -83,6 +83,23 @@ __device__ __forceinline__ int plane_axis(float nx, float ny, float nz) {
     return ax >= ay && ax >= az ? 0 : (ay >= az ? 1 : 2);
 }
 
+// a crossing at h of a surfel with record r: what it adds to fields
+// kFdu ... kFdu + 8
+__device__ __forceinline__ void cross_terms(const SurfRec &r, float du, float dw, float beta, float hx,
+                                            float hy, float hz, float *x) {
+    const int ax = plane_axis(r.b.x, r.b.y, r.b.z);
+    const float ha = ax == 0 ? hy : hx, hb = ax == 2 ? hy : hz;
+    x[0] = du;
+    x[1] = dw;
+    x[2] = beta;
+    x[3] = du * ha;
+    x[4] = du * hb;
+    x[5] = dw * ha;
+    x[6] = dw * hb;
+    x[7] = beta * ha;
+    x[8] = beta * hb;
+}
+
 // Pass 0 finds max |contribution| per field, pass 1 adds the contributions
 // in 64-bit fixed point with a per-field power-of-two scale (integer adds
 // commute: bit-identical between runs) into one copy per XCD.
@@ -105,16 +122,21 @@ struct FieldSink {
         const float a = fabsf(q);
         qm = a <= 3.0e38f ? fmaxf(qm, a) : INFINITY;
     }
+    __device__ __forceinline__ long long scaled(int f, float v) {
+        const float q = v * __builtin_ldexpf(1.0f, fx[f]);
+        track(q);
+        return __float2ll_rn(q);
+    }
+    __device__ __forceinline__ void add_scaled(int f, uint32_t surfel, long long q) {
+        __hip_atomic_fetch_add(acc + (int64_t)f * n + surfel, (unsigned long long)q, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
     __device__ __forceinline__ void add(int f, uint32_t surfel, float v) {
         if (PASS == 0) {
             m[f] = fmaxf(m[f], fabsf(v));
         } else {
-            const float q = v * __builtin_ldexpf(1.0f, fx[f]);
-            track(q);
-            const long long qq = __float2ll_rn(q);
-            if (qq != 0)
-                __hip_atomic_fetch_add(acc + (int64_t)f * n + surfel, (unsigned long long)qq, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+            const long long q = scaled(f, v);
+            if (q != 0) add_scaled(f, surfel, q);
         }
     }
     __device__ __forceinline__ void add3(int f, uint32_t surfel, float x, float y, float z) {
@@ -122,20 +144,12 @@ struct FieldSink {
         add(f + 1, surfel, y);
         add(f + 2, surfel, z);
     }
-    // a crossing of surfel k (record r) at h
     __device__ __forceinline__ void cross(uint32_t k, const SurfRec &r, float du, float dw, float beta, float hx,
                                           float hy, float hz) {
-        const int ax = plane_axis(r.b.x, r.b.y, r.b.z);
-        const float ha = ax == 0 ? hy : hx, hb = ax == 2 ? hy : hz;
-        add(kFdu, k, du);
-        add(kFdw, k, dw);
-        add(kFbeta, k, beta);
-        add(kFduh, k, du * ha);
-        add(kFduh + 1, k, du * hb);
-        add(kFdwh, k, dw * ha);
-        add(kFdwh + 1, k, dw * hb);
-        add(kFbetah, k, beta * ha);
-        add(kFbetah + 1, k, beta * hb);
+        float x[9];
+        cross_terms(r, du, dw, beta, hx, hy, hz, x);
+#pragma unroll
+        for (int q = 0; q < 9; ++q) add(kFdu + q, k, x[q]);
     }
     // wave maxima to maxbits[f] (pass 0) or maxbits[2 kFields] (pass 1);
     // every lane of the wave calls this
@@ -489,8 +503,7 @@ __global__ void __launch_bounds__(256) k_geometry_rec(BvhDev bv, int R, uint64_t
 // direct-light gradients: light positions and intensities, albedo, surfel
 // fields of the receivers and of the occluders on the shadow segments
 // ---------------------------------------------------------------------------
-// One thread per receiver and chunk of lights (lanes: neighbouring receivers
-// in Morton order).  With v = x_l - p_i, r = |v|, ndot = n_i . v > 0,
+// With v = x_l - p_i, r = |v|, ndot = n_i . v > 0,
 // E_c = o a_c kappa I ndot T / r^3 (kappa = 2/sqrt(pi)),
 // S = sum_c dL/dE_c a_c, Q = S o kappa I T:
 //   dL/dI += S o kappa ndot T / r^3, dL/da_c += dL/dE_c o kappa I ndot T / r^3,
@@ -500,160 +513,367 @@ __global__ void __launch_bounds__(256) k_geometry_rec(BvhDev bv, int R, uint64_t
 // W = S o kappa I ndot T / r^3.  The surfel fields are FieldSink's, the
 // light's (x, y, z, I) have accumulators of their own; fixed point as above.
 //
-// Bound by the latency of the walks, so by the lanes that walk: one lane per
-// receiver that walked the lights in turn left most of the chip idle (16k
-// surfels, 100 lights: 458 ms); chunks of lights give 2^19 lanes.  A walk
-// finds T and keeps the positions of the first kLightHits surfels crossed;
-// their terms, which need T, are formed from that list.  Only a segment with
-// more crossings is walked again.  The lights' chunks of dL/da are added in
-// order by k_light_albedo.
+// Bound by the walks' latency and by the sums' atomics.  One lane per
+// receiver that walked its lights in turn, twice in each of two passes, left
+// most of the chip idle: 458 ms for 16k surfels x 100 lights.  Here
+// k_light_walk walks every (receiver, light) segment once, in its own lane,
+// and keeps T and the positions of the surfels crossed (kSegHits places per
+// lane and for the lanes with more a block of kSegMore from a pool); the two
+// passes (largest contributions, then the sums) read those lists.  A segment
+// crosses between none and some 130 surfels, so a workgroup's crossings are
+// dealt out evenly to its lanes rather than each lane its own segment's.  Its
+// segments start at neighbouring receivers in Morton order, end at one light
+// and cross the same surfels (256 of them some 500, 27 a segment), so the sums
+// are formed in a table in LDS first (CrossTable).  The lists hold one slice
+// of the lights at a time (kSegLanes); more slices are walked once per pass.
 constexpr int kLightFields = kFields + 4;
-constexpr int kLightHits = 24;   // in LDS: a private array becomes registers (183 VGPRs)
-constexpr int64_t kLightLanes = (int64_t)1 << 19;
+constexpr uint32_t kSegAgain = 0xffffffffu;   // count of a lane whose list is not complete
+constexpr int kSegHits = 64, kSegMore = 96, kSegShare = 8;   // a block for every eighth lane
+constexpr int64_t kSegLanes = (int64_t)1 << 21;
 
-// lights per lane
-inline int light_chunk(int64_t n, int Lt) {
-    const int64_t chunks = std::min<int64_t>(Lt, std::max<int64_t>(1, kLightLanes / n));
-    return (int)((Lt + chunks - 1) / chunks);
+// Lists of one slice: lane (light - first light) * pad + receiver slot
+struct SegLists {
+    float *T;          // [lanes] transmittance
+    uint32_t *count;   // [lanes] surfels crossed
+    uint32_t *hit;     // [lanes][kSegHits] their sorted positions
+    uint32_t *block;   // [lanes] block of a lane with more than kSegHits
+    uint32_t *more;    // [lanes / kSegShare][kSegMore]
+    uint32_t *used;    // blocks given out (zeroed before each slice's walk)
+    int64_t pad, lanes;
+    static constexpr int64_t words_per_lane = 3 + kSegHits + kSegMore / kSegShare;
+};
+
+// Crossings' sums of a workgroup in LDS: open addressing on the surfel, ten
+// 64-bit fixed-point sums each (fields kFdu ... kFdu + 8 and kFo); a surfel
+// that finds no place within kProbes adds to the global sums.
+template <int SLOTS>
+struct CrossTable {
+    static constexpr int kProbes = 8, kSums = 10;
+    uint32_t key[SLOTS];
+    unsigned long long sum[kSums][SLOTS];
+    static __device__ __forceinline__ int field(int q) { return q < 9 ? kFdu + q : kFo; }
+    __device__ __forceinline__ void clear(int tid, int threads) {
+        for (int z = tid; z < SLOTS; z += threads) {
+            key[z] = kEmpty;
+#pragma unroll
+            for (int q = 0; q < kSums; ++q) sum[q][z] = 0;
+        }
+    }
+    template <typename Sink>
+    __device__ __forceinline__ void add(Sink &sink, uint32_t k, const float (&x)[kSums]) {
+        const uint32_t h = (k * 0x9e3779b1u) >> 16;
+        int at = -1;
+        for (int p = 0; p < kProbes && at < 0; ++p) {
+            const int z = (int)((h + (uint32_t)p) & (uint32_t)(SLOTS - 1));
+            uint32_t old = key[z];
+            if (old == kEmpty) old = atomicCAS(&key[z], kEmpty, k);
+            if (old == kEmpty || old == k) at = z;
+        }
+#pragma unroll
+        for (int q = 0; q < kSums; ++q) {
+            const long long v = sink.scaled(field(q), x[q]);
+            if (v == 0) continue;
+            if (at >= 0) atomicAdd(&sum[q][at], (unsigned long long)v);
+            else sink.add_scaled(field(q), k, v);
+        }
+    }
+    template <typename Sink>
+    __device__ __forceinline__ void flush(Sink &sink, int tid, int threads) {
+        for (int z = tid; z < SLOTS; z += threads) {
+            const uint32_t k = key[z];
+            if (k == kEmpty) continue;
+#pragma unroll
+            for (int q = 0; q < kSums; ++q)
+                if (sum[q][z] != 0) sink.add_scaled(field(q), k, (long long)sum[q][z]);
+        }
+    }
+};
+
+// The light's side of one (receiver, light): nothing to do where !on.
+struct LightTerm {
+    float dx, dy, dz, dd, ndot, len, S;
+    bool on;
+    __device__ __forceinline__ LightTerm(const SurfRec &rr, bool live, const float *lpos, int l, const float *ge,
+                                         const float *a) {
+        dx = __fsub_rn(lpos[3 * l + 0], rr.a.x);
+        dy = __fsub_rn(lpos[3 * l + 1], rr.a.y);
+        dz = __fsub_rn(lpos[3 * l + 2], rr.a.z);
+        dd = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, __fmul_rn(dx, dx)));
+        ndot = rr.b.x * dx + rr.b.y * dy + rr.b.z * dz;
+        len = sqrt_rn(dd);
+        S = live ? ge[0] * a[0] + ge[1] * a[1] + ge[2] * a[2] : 0.0f;
+        on = live && ndot > 0.0f && dd > 0.0f && S != 0.0f;
+    }
+};
+
+__global__ void k_seg_reset(uint32_t *used) { *used = 0; }
+
+template <int HEAD>
+__global__ void __launch_bounds__(kCenterThreads) k_light_walk(BvhDev bv, const float *__restrict__ albedo,
+                                                               const float *__restrict__ lpos, int l0, int Lt, int K,
+                                                               const float *__restrict__ gE, SegLists seg, int *err) {
+    extern __shared__ uint32_t stack_mem[];
+    const int64_t slot = (int64_t)blockIdx.x * kCenterThreads + threadIdx.x;
+    if (slot >= bv.n) return;
+    const int l = l0 + (int)blockIdx.y;
+    const int64_t at = (int64_t)blockIdx.y * seg.pad + slot;
+    const SurfRec rr = bv.rec[slot];
+    const uint32_t i = __float_as_uint(rr.d.w);
+    const LightTerm t(rr, true, lpos, l, gE + (((int64_t)i * Lt + l) * K) * 3, albedo + 3 * (int64_t)i);
+    float T = 1.0f;
+    uint32_t hits = 0, block = 0;
+    const uint32_t blocks = (uint32_t)(seg.lanes / kSegShare);
+    if (t.on)
+        trace_segment<HEAD>(bv, rr.a.x, rr.a.y, rr.a.z, t.dx, t.dy, t.dz, i, i, __fdiv_rn(bv.bounds[6], t.len), 1.0f,
+                            stack_mem + threadIdx.x, kCenterThreads, err, [&](const SurfRec &r, int s) {
+                                T = __fmul_rn(T, transmit(r.c.w, kernel_gamma(hit_r2_exact(r, rr.a.x, rr.a.y, rr.a.z,
+                                                                                           t.dx, t.dy, t.dz))));
+                                if (hits < (uint32_t)kSegHits) {
+                                    seg.hit[at * kSegHits + hits] = (uint32_t)s;
+                                } else {
+                                    if (hits == (uint32_t)kSegHits) block = atomicAdd(seg.used, 1u);
+                                    const uint32_t h = hits - kSegHits;
+                                    if (h < (uint32_t)kSegMore && block < blocks)
+                                        seg.more[(int64_t)block * kSegMore + h] = (uint32_t)s;
+                                }
+                                ++hits;
+                            });
+    seg.T[at] = T;
+    if (hits > (uint32_t)kSegHits) {
+        if (block >= blocks || hits > (uint32_t)(kSegHits + kSegMore)) hits = kSegAgain;
+        else seg.block[at] = block;
+    }
+    seg.count[at] = hits;
 }
 
+constexpr int kTermThreads = 256;
+constexpr int kLightSlots = 512;   // 43 KB
+
+// One crossing of a shadow segment o + t d with weight W: the surfel's ten
+// sums x, the light's share gl and the receiver's share gp of its centre's
+// gradient.
+__device__ __forceinline__ void light_crossing(const BvhDev &bv, const SurfRec &r, float ox, float oy, float oz,
+                                               float dx, float dy, float dz, float W, float (&x)[10], float (&gl)[4],
+                                               float (&gp)[3]) {
+    const float ok = bv.raw_op[__float_as_uint(r.d.w)];
+    const float gam = kernel_gamma(hit_r2_exact(r, ox, oy, oz, dx, dy, dz));
+    const float qx = r.a.x - ox, qy = r.a.y - oy, qz = r.a.z - oz;
+    const float den = dx * r.b.x + dy * r.b.y + dz * r.b.z;
+    const float tk = (qx * r.b.x + qy * r.b.y + qz * r.b.z) / den;
+    const float hx = tk * dx - qx, hy = tk * dy - qy, hz = tk * dz - qz;
+    const float u = (hx * r.c.x + hy * r.c.y + hz * r.c.z) * r.a.w;
+    const float w = (hx * r.d.x + hy * r.d.y + hz * r.d.z) * r.b.w;
+    const float f = W * 3.4f * r.c.w * gam;
+    const float fu = f * u * r.a.w, fw = f * w * r.b.w;
+    const float ghx = fu * r.c.x + fw * r.d.x, ghy = fu * r.c.y + fw * r.d.y, ghz = fu * r.c.z + fw * r.d.z;
+    const float beta = (ghx * dx + ghy * dy + ghz * dz) / den;
+    const float gqx = beta * r.b.x - ghx, gqy = beta * r.b.y - ghy, gqz = beta * r.b.z - ghz;
+    cross_terms(r, fu, fw, beta, hx, hy, hz, x);
+    x[9] = ok > 0.0f && ok < kOpacityMax ? -W * gam / (1.0f - ok) : 0.0f;
+    gl[0] -= tk * gqx;
+    gl[1] -= tk * gqy;
+    gl[2] -= tk * gqz;
+    gp[0] = -(1.0f - tk) * gqx;
+    gp[1] = -(1.0f - tk) * gqy;
+    gp[2] = -(1.0f - tk) * gqz;
+}
+
+// The light's fields: largest |value| of the wave's lanes (pass 0), or one
+// wave sum and one fixed-point add per field
 template <int PASS>
-__global__ void __launch_bounds__(kCenterThreads) k_direct_bwd(BvhDev bv, const float *__restrict__ albedo,
-                                                               const float *__restrict__ lpos,
-                                                               const float *__restrict__ lI, int Lt, int chunk, int K,
-                                                               const float *__restrict__ gE, uint32_t *maxbits,
-                                                               const int *fx, unsigned long long *acc,
-                                                               unsigned long long *lacc, float *__restrict__ g_alb,
-                                                               int *err) {
-    extern __shared__ uint32_t stack_mem[];
-    uint32_t *hit = stack_mem + kWalkHead * kCenterThreads + threadIdx.x;   // the lane's list of crossings
-    const int64_t slot = (int64_t)blockIdx.x * kCenterThreads + threadIdx.x;
+__device__ __forceinline__ void add_light(const float (&gl)[4], uint32_t *maxbits, const int *fx,
+                                          unsigned long long *lacc, int Lt, int l) {
+    unsigned long long *lsum = lacc + (int64_t)xcc_id() * 4 * Lt;   // this XCD's light fields [4][Lt]
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (PASS == 0) {
+            float v = fabsf(gl[q]);
+            for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
+            if (__lane_id() == 0 && v > 0.0f) atomicMax(maxbits + kFields + q, __float_as_uint(v));
+        } else {
+            unsigned long long tot =
+                (unsigned long long)__float2ll_rn(gl[q] * __builtin_ldexpf(1.0f, fx[kFields + q]));
+            for (int off = 32; off > 0; off >>= 1) tot += (unsigned long long)__shfl_xor((long long)tot, off, 64);
+            if (__lane_id() == 0 && tot != 0)
+                __hip_atomic_fetch_add(lsum + (int64_t)q * Lt + l, tot, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    }
+}
+
+// What a workgroup's segments share with the lanes that take their crossings
+struct SegShared {
+    float o[3][kTermThreads], d[3][kTermThreads], W[kTermThreads];
+    uint32_t first[kTermThreads + 1];        // crossings of the segments before
+    unsigned long long own[3][kTermThreads];   // the crossings' share of the receiver's centre, fixed point
+};
+
+template <int PASS>
+__global__ void __launch_bounds__(kTermThreads) k_light_terms(BvhDev bv, const float *__restrict__ albedo,
+                                                              const float *__restrict__ lpos,
+                                                              const float *__restrict__ lI, int l0, int Lt, int K,
+                                                              const float *__restrict__ gE, SegLists seg,
+                                                              uint32_t *maxbits, const int *fx,
+                                                              unsigned long long *acc, unsigned long long *lacc) {
+    __shared__ CrossTable<PASS == 1 ? kLightSlots : 1> table;
+    __shared__ SegShared sh;
+    const int tid = threadIdx.x;
+    const int64_t slot = (int64_t)blockIdx.x * kTermThreads + tid;
+    const int l = l0 + (int)blockIdx.y;
+    const int64_t at0 = (int64_t)blockIdx.y * seg.pad + (int64_t)blockIdx.x * kTermThreads;
     FieldSink<PASS> sink;
     sink.init(acc, fx, bv.n);
-    unsigned long long *lsum = lacc + (int64_t)xcc_id() * 4 * Lt;   // this XCD's light fields [4][Lt]
-    float lm[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     const bool live = slot < bv.n;
     const SurfRec rr = bv.rec[live ? slot : 0];
     const uint32_t i = __float_as_uint(rr.d.w);
-    const float oc = live ? bv.op[i] : 0.0f;
-    const float oraw = live ? bv.raw_op[i] : 0.0f;
-    const bool inside = oraw > 0.0f && oraw < kOpacityMax;
-    float ga[3] = {0.0f, 0.0f, 0.0f};
-    const float a0 = albedo[3 * (int64_t)i], a1 = albedo[3 * (int64_t)i + 1], a2 = albedo[3 * (int64_t)i + 2];
-    const int l0 = (int)blockIdx.y * chunk, l1 = min(Lt, l0 + chunk);
-    for (int l = l0; l < l1; ++l) {
-        float gl[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        const float *ge = gE + (((int64_t)i * Lt + l) * K) * 3;
-        const float S = live ? ge[0] * a0 + ge[1] * a1 + ge[2] * a2 : 0.0f;
-        const float dx = __fsub_rn(lpos[3 * l + 0], rr.a.x);
-        const float dy = __fsub_rn(lpos[3 * l + 1], rr.a.y);
-        const float dz = __fsub_rn(lpos[3 * l + 2], rr.a.z);
-        const float dd = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, __fmul_rn(dx, dx)));
-        const float ndot = rr.b.x * dx + rr.b.y * dy + rr.b.z * dz;
-        if (live && ndot > 0.0f && dd > 0.0f && S != 0.0f) {
-            const float len = sqrt_rn(dd);
-            const float t_lo = __fdiv_rn(bv.bounds[6], len);
-            const float r3 = dd * len, r5 = r3 * dd;
-            // the transmittance first (the occluders' weight W needs it)
-            float T = 1.0f;
-            int hits = 0;
-            trace_segment<kWalkHead>(bv, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz, i, i, t_lo, 1.0f, stack_mem + threadIdx.x,
-                                     kCenterThreads, err, [&](const SurfRec &r, int s) {
-                                         T = __fmul_rn(T, transmit(r.c.w, kernel_gamma(hit_r2_exact(
-                                                                              r, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz))));
-                                         if (hits < kLightHits) hit[hits * kCenterThreads] = (uint32_t)s;
-                                         ++hits;
-                                     });
-            const float kI = 1.1283791670955126f * lI[l];
-            const float base = kI * ndot * T / r3;
-            gl[3] = S * oc * 1.1283791670955126f * ndot * T / r3;
-            ga[0] += ge[0] * oc * base;
-            ga[1] += ge[1] * oc * base;
-            ga[2] += ge[2] * oc * base;
-            if (inside) sink.add(kFo, i, S * base);
-            const float Q = S * oc * kI * T;
-            const float gvx = Q * (rr.b.x / r3 - 3.0f * ndot * dx / r5);
-            const float gvy = Q * (rr.b.y / r3 - 3.0f * ndot * dy / r5);
-            const float gvz = Q * (rr.b.z / r3 - 3.0f * ndot * dz / r5);
-            float gpi[3] = {-gvx, -gvy, -gvz};
-            gl[0] = gvx;
-            gl[1] = gvy;
-            gl[2] = gvz;
-            sink.add3(kFn, i, Q * dx / r3, Q * dy / r3, Q * dz / r3);
-            const float W = S * oc * base;
-            auto crossed = [&](const SurfRec &r, int) {
-                const float gam = kernel_gamma(hit_r2_exact(r, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz));
-                const uint32_t k = __float_as_uint(r.d.w);
-                const float qx = r.a.x - rr.a.x, qy = r.a.y - rr.a.y, qz = r.a.z - rr.a.z;
-                const float den = dx * r.b.x + dy * r.b.y + dz * r.b.z;
-                const float tk = (qx * r.b.x + qy * r.b.y + qz * r.b.z) / den;
-                const float hx = tk * dx - qx, hy = tk * dy - qy, hz = tk * dz - qz;
-                const float u = (hx * r.c.x + hy * r.c.y + hz * r.c.z) * r.a.w;
-                const float w = (hx * r.d.x + hy * r.d.y + hz * r.d.z) * r.b.w;
-                const float f = W * 3.4f * r.c.w * gam;
-                const float fu = f * u * r.a.w, fw = f * w * r.b.w;
-                const float ghx = fu * r.c.x + fw * r.d.x, ghy = fu * r.c.y + fw * r.d.y,
-                            ghz = fu * r.c.z + fw * r.d.z;
-                const float beta = (ghx * dx + ghy * dy + ghz * dz) / den;
-                const float gqx = beta * r.b.x - ghx, gqy = beta * r.b.y - ghy, gqz = beta * r.b.z - ghz;
-                sink.cross(k, r, fu, fw, beta, hx, hy, hz);
-                const float ok = bv.raw_op[k];
-                if (ok > 0.0f && ok < kOpacityMax) sink.add(kFo, k, -W * gam / (1.0f - ok));
-                gpi[0] -= (1.0f - tk) * gqx;
-                gpi[1] -= (1.0f - tk) * gqy;
-                gpi[2] -= (1.0f - tk) * gqz;
-                gl[0] -= tk * gqx;
-                gl[1] -= tk * gqy;
-                gl[2] -= tk * gqz;
-            };
-            if (hits <= kLightHits) {
-                for (int h = 0; h < hits; ++h) crossed(bv.rec[hit[h * kCenterThreads]], 0);
-            } else {
-                trace_segment<kWalkHead>(bv, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz, i, i, t_lo, 1.0f,
-                                         stack_mem + threadIdx.x, kCenterThreads, err, crossed);
-            }
-            sink.add3(kFp, i, gpi[0], gpi[1], gpi[2]);
-        }
-        // the light's fields: one wave sum, then one fixed-point add per wave
+    const LightTerm t(rr, live, lpos, l, gE + (((int64_t)i * Lt + l) * K) * 3, albedo + 3 * (int64_t)i);
+    if (PASS == 1) table.clear(tid, kTermThreads);
+    float gl[4] = {0.0f, 0.0f, 0.0f, 0.0f};   // the light's terms of this lane
+    uint32_t count = 0;
+    sh.W[tid] = 0.0f;
+    if (t.on) {
+        const float T = seg.T[at0 + tid], oc = bv.op[i], oraw = bv.raw_op[i];
+        count = seg.count[at0 + tid];
+        if (count == kSegAgain) count = 0;   // k_light_again's
+        const float r3 = t.dd * t.len, r5 = r3 * t.dd;
+        const float kI = 1.1283791670955126f * lI[l];
+        const float base = kI * t.ndot * T / r3;
+        gl[3] = t.S * oc * 1.1283791670955126f * t.ndot * T / r3;
+        if (oraw > 0.0f && oraw < kOpacityMax) sink.add(kFo, i, t.S * base);
+        const float Q = t.S * oc * kI * T;
+        gl[0] = Q * (rr.b.x / r3 - 3.0f * t.ndot * t.dx / r5);
+        gl[1] = Q * (rr.b.y / r3 - 3.0f * t.ndot * t.dy / r5);
+        gl[2] = Q * (rr.b.z / r3 - 3.0f * t.ndot * t.dz / r5);
+        sink.add3(kFp, i, -gl[0], -gl[1], -gl[2]);
+        sink.add3(kFn, i, Q * t.dx / r3, Q * t.dy / r3, Q * t.dz / r3);
+        sh.W[tid] = t.S * oc * base;
+    }
+    sh.o[0][tid] = rr.a.x;
+    sh.o[1][tid] = rr.a.y;
+    sh.o[2][tid] = rr.a.z;
+    sh.d[0][tid] = t.dx;
+    sh.d[1][tid] = t.dy;
+    sh.d[2][tid] = t.dz;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (PASS == 0) {
-                lm[q] = fmaxf(lm[q], fabsf(gl[q]));
-            } else {
-                const long long fxv = __float2ll_rn(gl[q] * __builtin_ldexpf(1.0f, fx[kFields + q]));
-                unsigned long long tot = (unsigned long long)fxv;
-                for (int off = 32; off > 0; off >>= 1) tot += (unsigned long long)__shfl_xor((long long)tot, off, 64);
-                if (__lane_id() == 0 && tot != 0)
-                    __hip_atomic_fetch_add(lsum + (int64_t)q * Lt + l, tot, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+    for (int c = 0; c < 3; ++c) sh.own[c][tid] = 0;
+    // exclusive sums of the counts
+    uint32_t sum = count;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t o = __shfl_up(sum, off, 64);
+        if ((int)__lane_id() >= off) sum += o;
+    }
+    __shared__ uint32_t wave_total[kTermThreads / 64];
+    if (__lane_id() == 63) wave_total[tid / 64] = sum;
+    __syncthreads();
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < kTermThreads / 64; ++w) {
+        if (w < tid / 64) before += wave_total[w];
+        total += wave_total[w];
+    }
+    sh.first[tid] = before + sum - count;
+    if (tid == 0) sh.first[kTermThreads] = total;
+    __syncthreads();
+    for (uint32_t e = tid; e < total; e += kTermThreads) {
+        int g = 0;
+#pragma unroll
+        for (int step = kTermThreads / 2; step > 0; step >>= 1)
+            if (sh.first[g + step] <= e) g += step;
+        const uint32_t h = e - sh.first[g];
+        const uint32_t s = h < (uint32_t)kSegHits
+                               ? seg.hit[(at0 + g) * kSegHits + h]
+                               : seg.more[(int64_t)seg.block[at0 + g] * kSegMore + (h - kSegHits)];
+        const SurfRec r = bv.rec[s];
+        float x[10], gp[3];
+        light_crossing(bv, r, sh.o[0][g], sh.o[1][g], sh.o[2][g], sh.d[0][g], sh.d[1][g], sh.d[2][g], sh.W[g], x, gl,
+                       gp);
+        if (PASS == 0) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) sink.add(kFp + c, 0, gp[c]);
+#pragma unroll
+            for (int q = 0; q < 10; ++q) sink.add(table.field(q), 0, x[q]);
+        } else {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const long long v = sink.scaled(kFp + c, gp[c]);
+                if (v != 0) atomicAdd(&sh.own[c][g], (unsigned long long)v);
             }
+            table.add(sink, __float_as_uint(r.d.w), x);
         }
     }
-    if (PASS == 1 && live && g_alb) {
-        float *o = g_alb + ((int64_t)blockIdx.y * bv.n + i) * 3;
-        o[0] = ga[0];
-        o[1] = ga[1];
-        o[2] = ga[2];
-    }
+    add_light<PASS>(gl, maxbits, fx, lacc, Lt, l);
     if (PASS == 0) {
         sink.report(maxbits);
+    } else {
+        __syncthreads();
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            float v = lm[q];
-            for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-            if (__lane_id() == 0 && v > 0.0f) atomicMax(maxbits + kFields + q, __float_as_uint(v));
-        }
+        for (int c = 0; c < 3; ++c)
+            if (live && sh.own[c][tid] != 0) sink.add_scaled(kFp + c, i, (long long)sh.own[c][tid]);
+        table.flush(sink, tid, kTermThreads);
     }
 }
 
-// dL/dalbedo: the chunks' sums in the lights' order
-__global__ void __launch_bounds__(256) k_light_albedo(const float *__restrict__ part, int64_t vals, int chunks,
-                                                      float *__restrict__ g_alb) {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= vals) return;
-    float s = part[t];
-    for (int y = 1; y < chunks; ++y) s += part[(int64_t)y * vals + t];
-    g_alb[t] = s;
+// The crossings of the segments whose lists are not complete (kSegAgain),
+// walked again, a lane each
+template <int PASS>
+__global__ void __launch_bounds__(kCenterThreads) k_light_again(BvhDev bv, const float *__restrict__ albedo,
+                                                                const float *__restrict__ lpos,
+                                                                const float *__restrict__ lI, int l0, int Lt, int K,
+                                                                const float *__restrict__ gE, SegLists seg,
+                                                                uint32_t *maxbits, const int *fx,
+                                                                unsigned long long *acc, unsigned long long *lacc,
+                                                                int *err) {
+    extern __shared__ uint32_t stack_mem[];
+    const int64_t slot = (int64_t)blockIdx.x * kCenterThreads + threadIdx.x;
+    const int l = l0 + (int)blockIdx.y;
+    const int64_t at = (int64_t)blockIdx.y * seg.pad + slot;
+    const bool mine = slot < bv.n && seg.count[at] == kSegAgain;
+    if (!__any(mine)) return;
+    FieldSink<PASS> sink;
+    sink.init(acc, fx, bv.n);
+    float gl[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (mine) {
+        const SurfRec rr = bv.rec[slot];
+        const uint32_t i = __float_as_uint(rr.d.w);
+        const LightTerm t(rr, true, lpos, l, gE + (((int64_t)i * Lt + l) * K) * 3, albedo + 3 * (int64_t)i);
+        const float W = t.S * bv.op[i] * (1.1283791670955126f * lI[l] * t.ndot * seg.T[at] / (t.dd * t.len));
+        trace_segment<kWalkHead>(bv, rr.a.x, rr.a.y, rr.a.z, t.dx, t.dy, t.dz, i, i, __fdiv_rn(bv.bounds[6], t.len),
+                                 1.0f, stack_mem + threadIdx.x, kCenterThreads, err, [&](const SurfRec &r, int) {
+                                     float x[10], gp[3];
+                                     light_crossing(bv, r, rr.a.x, rr.a.y, rr.a.z, t.dx, t.dy, t.dz, W, x, gl, gp);
+                                     sink.add3(kFp, i, gp[0], gp[1], gp[2]);
+#pragma unroll
+                                     for (int q = 0; q < 10; ++q)
+                                         sink.add(CrossTable<1>::field(q), __float_as_uint(r.d.w), x[q]);
+                                 });
+    }
+    add_light<PASS>(gl, maxbits, fx, lacc, Lt, l);
+    if (PASS == 0) sink.report(maxbits);
+}
+
+// dL/dalbedo of a slice's lights, in their order (added to the earlier
+// slices' where l0 > 0)
+__global__ void __launch_bounds__(256) k_light_albedo(BvhDev bv, const float *__restrict__ albedo,
+                                                      const float *__restrict__ lpos, const float *__restrict__ lI,
+                                                      int l0, int l1, int Lt, int K, const float *__restrict__ gE,
+                                                      SegLists seg, float *__restrict__ g_alb) {
+    const int64_t slot = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (slot >= bv.n) return;
+    const SurfRec rr = bv.rec[slot];
+    const int64_t i = (int64_t)__float_as_uint(rr.d.w);
+    const float oc = bv.op[i];
+    float ga[3] = {0.0f, 0.0f, 0.0f};
+    if (l0 > 0)
+        for (int c = 0; c < 3; ++c) ga[c] = g_alb[3 * i + c];
+    for (int l = l0; l < l1; ++l) {
+        const float *ge = gE + ((i * Lt + l) * K) * 3;
+        const LightTerm t(rr, true, lpos, l, ge, albedo + 3 * i);
+        if (!t.on) continue;
+        const float base = 1.1283791670955126f * lI[l] * t.ndot * seg.T[(int64_t)(l - l0) * seg.pad + slot] /
+                           (t.dd * t.len);
+        for (int c = 0; c < 3; ++c) ga[c] += ge[c] * oc * base;
+    }
+    for (int c = 0; c < 3; ++c) g_alb[3 * i + c] = ga[c];
 }
 
 __global__ void k_light_exp(const uint32_t *maxbits, int64_t count_surfel, int64_t count_light, int *fx) {
@@ -807,36 +1027,63 @@ gsrad_status launch_geometry_rec(const BvhDev &bv, int R, uint64_t seed, const u
 }
 
 // [8 XCD copies][kFields][n] u64, the lights' [8][4][Lt] u64, maxbits[32],
-// fx[32], then the chunks' dL/dalbedo [chunks][n][3] (one chunk writes the
-// caller's array)
+// fx[32]
 size_t light_acc_bytes(int64_t n, int Lt) { return (size_t)8 * kFields * n * 8 + (size_t)8 * 4 * Lt * 8 + 256; }
 
-size_t light_part_bytes(int64_t n, int Lt) {
-    const int chunk = light_chunk(n, Lt), chunks = (Lt + chunk - 1) / chunk;
-    return chunks > 1 ? (size_t)chunks * n * 3 * 4 : 0;
+// receivers padded to the workgroups of k_light_terms, lights of a slice
+static int64_t light_pad(int64_t n) { return (n + kTermThreads - 1) / kTermThreads * kTermThreads; }
+static int light_slice(int64_t n, int Lt) {
+    return (int)std::min<int64_t>({(int64_t)Lt, 32768, std::max<int64_t>(1, kSegLanes / light_pad(n))});
 }
+size_t light_seg_bytes(int64_t n, int Lt) { return (size_t)light_slice(n, Lt) * light_pad(n) * SegLists::words_per_lane * 4; }
 
 gsrad_status launch_direct_backward(const BvhDev &bv, const float *albedo, const float *lpos, const float *lI, int Lt,
                                     int K, const float *gE, void *acc, float *g_lpos, float *g_lI, float *g_alb,
                                     const CenterOutputs &out, int *err, hipStream_t st) {
-    static_assert(kLightFields <= 32, "maxbits and fx hold 32 entries each");
+    static_assert(kLightFields < 32, "maxbits and fx hold 32 entries each, the last of maxbits counts blocks");
     unsigned long long *a = static_cast<unsigned long long *>(acc);
     unsigned long long *la = a + (size_t)8 * kFields * bv.n;
     uint32_t *maxbits = reinterpret_cast<uint32_t *>(la + (size_t)8 * 4 * Lt);
     int *fx = reinterpret_cast<int *>(maxbits + 32);
-    float *part = reinterpret_cast<float *>(fx + 32);
-    const int chunk = light_chunk(bv.n, Lt), chunks = (Lt + chunk - 1) / chunk;
-    const dim3 grid((unsigned)((bv.n + kCenterThreads - 1) / kCenterThreads), (unsigned)chunks);
-    const size_t smem = walk_bytes(kWalkHead + kLightHits);
-    float *ga = chunks > 1 && g_alb ? part : g_alb;
-    hipLaunchKernelGGL(k_direct_bwd<0>, grid, dim3(kCenterThreads), smem, st, bv, albedo, lpos, lI, Lt, chunk, K, gE,
-                       maxbits, fx, a, la, ga, err);
-    hipLaunchKernelGGL(k_light_exp, dim3(1), dim3(64), 0, st, maxbits, bv.n * (int64_t)Lt + bv.n, bv.n, fx);
-    hipLaunchKernelGGL(k_direct_bwd<1>, grid, dim3(kCenterThreads), smem, st, bv, albedo, lpos, lI, Lt, chunk, K, gE,
-                       maxbits, fx, a, la, ga, err);
-    if (ga != g_alb)
-        hipLaunchKernelGGL(k_light_albedo, dim3((unsigned)((3 * bv.n + 255) / 256)), dim3(256), 0, st, part, 3 * bv.n,
-                           chunks, g_alb);
+    const int slice = light_slice(bv.n, Lt);
+    SegLists seg;
+    seg.pad = light_pad(bv.n);
+    seg.lanes = seg.pad * slice;
+    seg.T = reinterpret_cast<float *>(fx + 32);
+    seg.count = reinterpret_cast<uint32_t *>(seg.T + seg.lanes);
+    seg.block = seg.count + seg.lanes;
+    seg.hit = seg.block + seg.lanes;
+    seg.more = seg.hit + (int64_t)kSegHits * seg.lanes;
+    seg.used = maxbits + 31;
+    const unsigned gw = (unsigned)((bv.n + kCenterThreads - 1) / kCenterThreads), gt = (unsigned)(seg.pad / kTermThreads);
+    auto walk = [&](int l0) {
+        const int m = std::min(slice, Lt - l0);
+        const bool fills = bv.n * m > kWalkFill;
+        hipLaunchKernelGGL(k_seg_reset, dim3(1), dim3(1), 0, st, seg.used);
+        hipLaunchKernelGGL(fills ? k_light_walk<kWalkHead> : k_light_walk<kStackDeep>, dim3(gw, (unsigned)m),
+                           dim3(kCenterThreads), walk_bytes(fills ? kWalkHead : kStackDeep), st, bv, albedo, lpos, l0,
+                           Lt, K, gE, seg, err);
+        return m;
+    };
+    for (int l0 = 0; l0 < Lt; l0 += slice) {
+        const int m = walk(l0);
+        if (g_alb)
+            hipLaunchKernelGGL(k_light_albedo, dim3((unsigned)((bv.n + 255) / 256)), dim3(256), 0, st, bv, albedo, lpos,
+                               lI, l0, l0 + m, Lt, K, gE, seg, g_alb);
+        hipLaunchKernelGGL(k_light_terms<0>, dim3(gt, (unsigned)m), dim3(kTermThreads), 0, st, bv, albedo, lpos, lI, l0,
+                           Lt, K, gE, seg, maxbits, fx, a, la);
+        hipLaunchKernelGGL(k_light_again<0>, dim3(gw, (unsigned)m), dim3(kCenterThreads), walk_bytes(kWalkHead), st,
+                           bv, albedo, lpos, lI, l0, Lt, K, gE, seg, maxbits, fx, a, la, err);
+    }
+    hipLaunchKernelGGL(k_light_exp, dim3(1), dim3(64), 0, st, maxbits,
+                       2 * (bv.n * (int64_t)Lt + bv.n), 2 * seg.pad, fx);
+    for (int l0 = 0; l0 < Lt; l0 += slice) {
+        const int m = slice < Lt ? walk(l0) : Lt;
+        hipLaunchKernelGGL(k_light_terms<1>, dim3(gt, (unsigned)m), dim3(kTermThreads), 0, st, bv, albedo, lpos, lI, l0,
+                           Lt, K, gE, seg, maxbits, fx, a, la);
+        hipLaunchKernelGGL(k_light_again<1>, dim3(gw, (unsigned)m), dim3(kCenterThreads), walk_bytes(kWalkHead), st,
+                           bv, albedo, lpos, lI, l0, Lt, K, gE, seg, maxbits, fx, a, la, err);
+    }
     CenterOutputs o15 = out;
     o15.p[15] = nullptr;
     hipLaunchKernelGGL(k_fields_finish, dim3((unsigned)((bv.n + 255) / 256)), dim3(256), 0, st, bv, a, fx, nullptr,

@@ -29,10 +29,12 @@ constexpr uint32_t kEmpty = 0xffffffffu;
 // a launch fills the chip, waves in flight count: all 64 entries in LDS hold
 // a CU to ten waves (10 M segments of a 20k-surfel bowl: F 29.6 ms, with a
 // head of 20 24.2 ms; their gradients 183 and 156 ms).  A launch that does
-// not reach ten waves a CU walks faster without the choice of memory (512
-// surfels, one light: 49 against 60 us) and takes HEAD = 64.
+// not reach ten waves a CU (kWalkFill lanes) walks faster without the choice
+// of memory and takes HEAD = 64 (16 Monte-Carlo rounds of 50k receivers, three
+// waves a CU: 27.7 ms, with a head of 20 29.6 ms; the direct light of 512
+// surfels 49 and 60 us).
 constexpr int kWalkHead = 20;
-constexpr int64_t kWalkFill = (int64_t)256 * 10 * 64;   // lanes of ten waves on each of 256 CUs
+constexpr int64_t kWalkFill = (int64_t)256 * 10 * 64;
 
 template <int HEAD>
 struct WalkStack {
@@ -193,66 +195,6 @@ __device__ __forceinline__ float trace_sorted(const BvhDev &bv, float ox, float 
         if (found < KB) return T;
         last = key_bits(key[KB - 1]);
     }
-}
-
-// Transmittance of the segment t in (t_lo, 1) of o + t d: product of
-// (1 - alpha) over every surfel crossed (order-free).
-template <int HEAD>
-__device__ __forceinline__ float trace_shadow(const BvhDev &bv, float ox, float oy, float oz, float dx, float dy,
-                                              float dz, uint32_t self, float t_lo, uint32_t *column, int stride,
-                                              int *err) {
-    const float ix = safe_inv(dx), iy = safe_inv(dy), iz = safe_inv(dz);
-    const float t0 = t_lo * 0.99999f, t1 = 1.00001f;
-    float T = 1.0f;
-    auto leaf = [&](int s) {
-        const SurfRec r = bv.rec[s];
-        asm volatile("" : : "v"(r.a.x), "v"(r.b.x), "v"(r.c.x), "v"(r.d.w));   // whole record in one latency
-        const uint32_t j = __float_as_uint(r.d.w);
-        if (j == self) return;
-        float t, r2;
-        bool front;
-        if (!hit_test(r, ox, oy, oz, dx, dy, dz, t_lo, 1.0f, true, t, r2, front)) return;
-        // kernel value from the exact intersection (the FP32 hit point loses
-        // the offset from the centre when the centre is many radii away)
-        T = __fmul_rn(T, transmit(r.c.w, kernel_gamma(hit_r2_exact(r, ox, oy, oz, dx, dy, dz))));
-    };
-    if (bv.n == 1) {
-        leaf(0);
-        return T;
-    }
-    WalkStack<HEAD> stack(column, stride);
-    int sp = 0, node = 0;
-    bool ovf = false;
-    for (;;) {
-        const Node nd = bv.nodes[node];
-        float tn0, tn1;
-        bool h0 = slab(nd.b0.x, nd.b0.y, nd.b0.z, nd.b0.w, nd.b1.x, nd.b1.y, ox, oy, oz, ix, iy, iz, t0, t1, tn0);
-        bool h1 = slab(nd.b1.z, nd.b1.w, nd.b2.x, nd.b2.y, nd.b2.z, nd.b2.w, ox, oy, oz, ix, iy, iz, t0, t1, tn1);
-        const int c0 = nd.ch.x, c1 = nd.ch.y;
-        if (h0 && c0 < 0) {
-            leaf(~c0);
-            h0 = false;
-        }
-        if (h1 && c1 < 0) {
-            leaf(~c1);
-            h1 = false;
-        }
-        // descend (first child first), push the other; none left: pop.  A
-        // push past the stack's end ends the walk with an error.
-        const bool both = h0 && h1;
-        ovf = both && sp >= kStackDeep;
-        if (both) stack.put(min(sp, kStackDeep - 1), (uint32_t)c1);
-        sp += both ? 1 : 0;
-        node = h0 ? c0 : c1;
-        if (!h0 && !h1) {
-            if (sp == 0) break;
-            --sp;
-            node = (int)stack.get(sp);
-        }
-        if (ovf) break;
-    }
-    if (ovf) atomicOr(err, kErrStack);
-    return T;
 }
 
 // Slot of surfel j in an open-addressing table of 2^log2h entries.  A full
