@@ -16,6 +16,7 @@
 
 #include "bvh_build.h"
 #include "gsrad_internal.h"
+#include "rows.h"
 #include "trace_api.h"
 #include "dense_api.h"
 #include "batch_api.h"
@@ -252,6 +253,9 @@ struct gsrad_batch {
     DevBuf row_off, val_off, scene_C, row_scene, order, counter, temp;
     std::vector<int64_t> scene_rows;   // row offsets (host copy)
     std::vector<int32_t> scene_cols;   // C_s (host copy)
+    std::vector<int64_t> scene_vals;   // value offsets (host copy)
+    DevBuf scenes;                     // RowScene table and first workgroups
+    RowTable table;
     // forward iterates B^(0..nb-1) and adjoint iterates lambda^(1..nb)
     int nb = -1;
     DevBuf Bt, Lt, lam0;
@@ -270,7 +274,7 @@ struct gsrad_batch {
     // captured adjoint loop and its arguments
     hipGraph_t agraph = nullptr;
     hipGraphExec_t aexec = nullptr;
-    const void *a_rho = nullptr, *a_gE = nullptr, *a_L = nullptr, *a_lam0 = nullptr, *a_ft[3] = {}, *a_h = nullptr;
+    const void *a_rho = nullptr, *a_gB = nullptr, *a_gE = nullptr, *a_L = nullptr, *a_lam0 = nullptr, *a_ft[3] = {}, *a_h = nullptr;
     int a_nb = -1, a_lpr = 0, a_prec = GSRAD_FP32;
     // lanes per row forced by gsrad_batch_set_lanes (0: tuned)
     int force_fwd = 0, force_adj = 0;
@@ -284,6 +288,9 @@ struct gsrad_batch {
         d.row_scene = row_scene.as<int32_t>();
         d.order = order.as<int64_t>();
         return d;
+    }
+    RowScene scene(int s) const {
+        return {scene_rows[s], scene_rows[s + 1] - scene_rows[s], scene_vals[s], scene_cols[s]};
     }
     void drop_graph() {
         if (exec) (void)hipGraphExecDestroy(exec);
@@ -301,7 +308,7 @@ struct gsrad_batch {
         drop_graph();
         if (cap) (void)hipStreamDestroy(cap);
         delete F;
-        for (DevBuf *b : {&row_off, &val_off, &scene_C, &row_scene, &order, &counter, &temp, &Bt, &Lt, &lam0, &Bh, &Lh})
+        for (DevBuf *b : {&row_off, &val_off, &scene_C, &row_scene, &order, &counter, &temp, &scenes, &Bt, &Lt, &lam0, &Bh, &Lh})
             b->release();
     }
 };
@@ -976,6 +983,7 @@ gsrad_status gsrad_transport_solve(const gsrad_ff *ff, const float *rho, const f
             return fail(e);
     } else {
         float *slots = nullptr;
+        const RowScene scene{0, n, 0, C};
         if (tp) {
             if ((e = tp->B.ensure(row_bytes * n_bounces, "forward tape")) != GSRAD_OK) return fail(e);
             slots = tp->B.as<float>();
@@ -993,7 +1001,7 @@ gsrad_status gsrad_transport_solve(const gsrad_ff *ff, const float *rho, const f
             else if (tp) dst = slots + (size_t)(k + 1) * n * C;
             else dst = const_cast<gsrad_ff *>(ff)->slab.as<float>() + (size_t)(k & 1) * n * C;
             ProfScope ps("bounce", st);
-            if ((e = launch_bounce(F, C, src, E, rho, dst, st)) != GSRAD_OK) return fail(e);
+            if ((e = rows_bounce(F, scene, src, E, rho, dst, st)) != GSRAD_OK) return fail(e);
             src = dst;
         }
     }
@@ -1084,7 +1092,7 @@ gsrad_status gsrad_transport_solve_noalloc(const gsrad_ff *ff, const float *rho,
     const float *src = E;
     for (int k = 0; k < n_bounces; ++k) {
         float *dst = k == n_bounces - 1 ? B_out : slots + (size_t)(k & 1) * n * C;
-        GS_TRY(launch_bounce(F, C, src, E, rho, dst, st));
+        GS_TRY(rows_bounce(F, RowScene{0, n, 0, C}, src, E, rho, dst, st));
         src = dst;
     }
     return GSRAD_OK;
@@ -1121,19 +1129,24 @@ gsrad_status gsrad_transport_backward(const gsrad_ff *ff, const gsrad_tape *tape
         GS_TRY(ensure_transpose(f, st));
     }
     GS_TRY(tp->L.ensure(row_bytes * nb, "adjoint tape"));
-    GS_TRY(tp->lam0.ensure(row_bytes, "adjoint scratch"));
+    GS_TRY(tp->lam0.ensure(row_bytes, "adjoint scaled rows"));
+    GS_TRY(tp->pp.ensure(row_bytes, "adjoint scaled rows"));
     float *L = tp->L.as<float>();
     GS_TRY(check_hip(hipMemcpyAsync(L + (size_t)(nb - 1) * n * C, grad_B, row_bytes, hipMemcpyDeviceToDevice, st),
                      "adjoint seed"));
     const Csr FT = f->csr_t();
+    const RowScene scene{0, n, 0, C};
+    float *p = tp->pp.as<float>(), *p_next = tp->lam0.as<float>();   // rho lambda^(k+1), rho lambda^(k)
+    GS_TRY(rows_scale(scene, grad_B, rho, p, st));
     for (int k = nb - 1; k >= 0; --k) {
-        const float *lam_in = L + (size_t)k * n * C;   // lambda^(k+1)
-        float *lam_out = k >= 1 ? L + (size_t)(k - 1) * n * C : tp->lam0.as<float>();
         ProfScope ps("adjoint", st);
-        GS_TRY(launch_adjoint(FT, C, lam_in, rho, lam_out, grad_E, st));
+        GS_TRY(rows_adjoint(FT, scene, p, rho, k >= 1 ? L + (size_t)(k - 1) * n * C : nullptr, k >= 1 ? p_next : nullptr,
+                            grad_E, st));
+        std::swap(p, p_next);
     }
     ProfScope ps("sddmm", st);
-    if (grad_F || grad_rho) GS_TRY(launch_sddmm(ff->csr(), C, nb, tp->B.as<float>(), L, rho, grad_F, grad_rho, st));
+    if (grad_F || grad_rho)
+        GS_TRY(rows_sddmm(ff->csr(), scene, nb, (int64_t)n * C, tp->B.as<float>(), L, rho, grad_F, grad_rho, st));
     return GSRAD_OK;
 }
 
@@ -1641,9 +1654,12 @@ gsrad_status gsrad_batch_create(const gsrad_ff *const *ffs, int32_t n_scenes, co
     b->vals = voff[n_scenes];
     b->scene_rows.assign(roff.begin(), roff.end());
     b->scene_cols = Cs;
+    b->scene_vals = voff;
     if (!b->F) b->F = new gsrad_ff();
     gsrad_ff *F = b->F;
     const void *old_ptrs[3] = {F->row_ptr.p, F->col.p, F->val.p};
+    const bool old_order = F->has_order;
+    const void *const old_order_p = F->row_order.p;
     const int64_t rows = b->rows, nnz = eoff[n_scenes];
     if ((e = F->row_ptr.ensure((size_t)(rows + 1) * 8, "batch row_ptr")) != GSRAD_OK) return fail(e);
     if ((e = F->col.ensure((size_t)std::max<int64_t>(nnz, 1) * 4, "batch col")) != GSRAD_OK) return fail(e);
@@ -1669,7 +1685,6 @@ gsrad_status gsrad_batch_create(const gsrad_ff *const *ffs, int32_t n_scenes, co
     F->fill_gen = ++g_fill_gen;
     F->max_row = max_row;
     F->has_t = false;
-    F->has_order = false;
     if (old_ptrs[0] != F->row_ptr.p || old_ptrs[1] != F->col.p || old_ptrs[2] != F->val.p) b->drop_graph();
     if ((e = b->row_off.ensure((size_t)(n_scenes + 1) * 8, "scene rows")) != GSRAD_OK) return fail(e);
     if ((e = b->val_off.ensure((size_t)(n_scenes + 1) * 8, "scene values")) != GSRAD_OK) return fail(e);
@@ -1694,11 +1709,47 @@ gsrad_status gsrad_batch_create(const gsrad_ff *const *ffs, int32_t n_scenes, co
     // from one scene's nearby columns (replaces the cost order)
     bool all_ordered = true;
     for (int s = 0; s < n_scenes; ++s) all_ordered = all_ordered && ffs[s]->has_order;
+    if (all_ordered && (e = F->row_order.ensure((size_t)rows * 4, "row order")) != GSRAD_OK) return fail(e);
+    F->has_order = all_ordered;
+    if (old_order != all_ordered || old_order_p != F->row_order.p) b->drop_graph();
     if (all_ordered)
-        for (int s = 0; s < n_scenes; ++s)
+        for (int s = 0; s < n_scenes; ++s) {
+            if ((e = launch_offset_copy_i32(ffs[s]->row_order.as<int32_t>(), ffs[s]->n, (int32_t)roff[s],
+                                            F->row_order.as<int32_t>() + roff[s], st)) != GSRAD_OK)
+                return fail(e);
             if ((e = launch_offset_widen(ffs[s]->row_order.as<int32_t>(), ffs[s]->n, roff[s],
                                          b->order.as<int64_t>() + roff[s], st)) != GSRAD_OK)
                 return fail(e);
+        }
+    // the scenes as the FP32 row products take them
+    std::vector<RowScene> tab;
+    b->table.few.clear();
+    for (int s = 0; s < n_scenes; ++s) (rows_few(Cs[s]) ? b->table.few : tab).push_back(b->scene(s));
+    const size_t many = tab.size(), tab_bytes = many * sizeof(RowScene);
+    std::vector<int64_t> first(3 * many);
+    for (int g = 0; g < 3; ++g) {
+        int64_t at = 0;
+        for (size_t s = 0; s < many; ++s) {
+            first[g * many + s] = at;
+            at += rows_blocks(tab[s].n, tab[s].C, 16 << g);
+        }
+        b->table.blocks[g] = at;
+    }
+    if ((e = b->scenes.ensure(std::max<size_t>(tab_bytes + first.size() * 8, 8), "scene table")) != GSRAD_OK)
+        return fail(e);
+    b->table.tab = b->scenes.as<RowScene>();
+    b->table.count = (int)many;
+    for (int g = 0; g < 3; ++g)
+        b->table.first[g] = reinterpret_cast<const int64_t *>(b->scenes.as<char>() + tab_bytes) + g * many;
+    if (many > 0) {
+        if ((e = check_hip(hipMemcpyAsync(b->scenes.p, tab.data(), tab_bytes, hipMemcpyHostToDevice, st),
+                           "scene table copy")) != GSRAD_OK)
+            return fail(e);
+        if ((e = check_hip(hipMemcpyAsync(b->scenes.as<char>() + tab_bytes, first.data(), first.size() * 8,
+                                          hipMemcpyHostToDevice, st),
+                           "scene table copy")) != GSRAD_OK)
+            return fail(e);
+    }
     // the host vectors above are sources of asynchronous copies
     if ((e = check_hip(hipStreamSynchronize(st), "batch create sync")) != GSRAD_OK) return fail(e);
     b->nb = -1;
@@ -1727,8 +1778,17 @@ namespace {
 
 // Lanes per row for a ragged product: each candidate runs once on the
 // batch's own rows (into scratch) and the fastest is kept.
+// The products of the batch's precision are timed; BF16 rows are timed on
+// the bytes of `in` as they are.
 gsrad_status autotune_lanes_timed(gsrad_batch *b, const Csr &F, bool adjoint, const float *in, const float *rho,
                                   float *scratch, float *scratch2, hipStream_t st, int *best) {
+    auto product = [&](int lpr) {
+        if (b->precision == GSRAD_BF16)
+            return launch_ragged_spmm(b->dev(), F, lpr, adjoint, in, in, rho, scratch, scratch2,
+                                      b->counter.as<uint32_t>(), st);
+        return adjoint ? rows_adjoint_batch(F, b->table, lpr, in, rho, scratch, nullptr, scratch2, st)
+                       : rows_bounce_batch(F, b->table, lpr, in, in, rho, scratch, st);
+    };
     hipEvent_t e0, e1;
     GS_TRY(check_hip(hipEventCreate(&e0), "tune event"));
     if (hipEventCreate(&e1) != hipSuccess) {
@@ -1740,8 +1800,7 @@ gsrad_status autotune_lanes_timed(gsrad_batch *b, const Csr &F, bool adjoint, co
     for (int lpr : {64, 32, 16}) {
         for (int rep = 0; rep < 2 && e == GSRAD_OK; ++rep) {   // the first run warms the caches
             if ((e = check_hip(hipEventRecord(e0, st), "tune record")) != GSRAD_OK) break;
-            e = launch_ragged_spmm(b->dev(), F, lpr, adjoint, in, false, in, rho, scratch, scratch2,
-                                   b->counter.as<uint32_t>(), st);
+            e = product(lpr);
             if (e == GSRAD_OK) e = check_hip(hipEventRecord(e1, st), "tune record");
         }
         if (e != GSRAD_OK) break;
@@ -1759,14 +1818,14 @@ gsrad_status autotune_lanes_timed(gsrad_batch *b, const Csr &F, bool adjoint, co
 }
 
 // Lanes per row chosen by timing, remembered per batch shape (rows, stored
-// entries, values of the ragged arrays, direction) for the process, so a
+// entries, values of the ragged arrays, direction, precision) for the process, so a
 // new batch of a shape already seen skips the timing runs.
 std::mutex g_tune_mu;
-std::map<std::tuple<int64_t, int64_t, int64_t, bool>, int> g_tune_cache;
+std::map<std::tuple<int64_t, int64_t, int64_t, bool, int>, int> g_tune_cache;
 
 gsrad_status autotune_lanes(gsrad_batch *b, const Csr &F, bool adjoint, const float *in, const float *rho,
                             float *scratch, float *scratch2, hipStream_t st, int *best) {
-    const auto key = std::make_tuple(b->rows, F.nnz, b->vals, adjoint);
+    const auto key = std::make_tuple(b->rows, F.nnz, b->vals, adjoint, b->precision);
     {
         std::lock_guard<std::mutex> lock(g_tune_mu);
         const auto it = g_tune_cache.find(key);
@@ -1835,8 +1894,9 @@ gsrad_status gsrad_batch_transport_solve(gsrad_batch *b, const float *rho, const
             const void *in = in_bf ? static_cast<const void *>(bh + (size_t)(k & 1) * vals * 2)
                                    : static_cast<const void *>(tape + (size_t)k * vals);
             float *out = last ? B_out : tape + (size_t)(k + 1) * vals;
-            e = launch_ragged_spmm(b->dev(), F, b->lpr_fwd, false, in, in_bf, E, rho, out, nullptr,
-                                   b->counter.as<uint32_t>(), b->cap);
+            e = in_bf ? launch_ragged_spmm(b->dev(), F, b->lpr_fwd, false, in, E, rho, out, nullptr,
+                                           b->counter.as<uint32_t>(), b->cap)
+                      : rows_bounce_batch(F, b->table, b->lpr_fwd, static_cast<const float *>(in), E, rho, out, b->cap);
             if (e == GSRAD_OK && bf && k + 1 < n_bounces - 1)
                 e = launch_round_bf16(out, vals, bh + (size_t)((k + 1) & 1) * vals * 2, b->cap);
         }
@@ -1913,7 +1973,7 @@ gsrad_status gsrad_batch_transport_backward(gsrad_batch *b, const float *rho, co
         GS_TRY(b->Lh.ensure((size_t)vals * 4, "batch BF16 adjoint rows"));
     }
     char *lh = bf ? static_cast<char *>(b->Lh.p) : nullptr;   // two [vals] BF16 slots
-    const bool hit = b->aexec && b->a_rho == rho && b->a_gE == grad_E && b->a_L == L && b->a_lam0 == lam0 &&
+    const bool hit = b->aexec && b->a_rho == rho && b->a_gB == grad_B && b->a_gE == grad_E && b->a_L == L && b->a_lam0 == lam0 &&
                      b->a_nb == nb && b->a_lpr == b->lpr_adj && b->a_ft[0] == FT.row_ptr && b->a_ft[1] == FT.col &&
                      b->a_ft[2] == FT.val && b->a_prec == b->precision && b->a_h == lh;
     if (!hit) {
@@ -1925,16 +1985,22 @@ gsrad_status gsrad_batch_transport_backward(gsrad_batch *b, const float *rho, co
         if (!b->cap) GS_TRY(check_hip(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking), "capture stream"));
         GS_TRY(check_hip(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal), "begin capture"));
         gsrad_status e = GSRAD_OK;
+        float *p = L + (size_t)nb * vals, *p_next = lam0;   // rho lambda^(k+1), rho lambda^(k)
+        for (int s = 0; s < b->S && e == GSRAD_OK; ++s) e = rows_scale(b->scene(s), grad_B, rho, p, b->cap);
         // BF16: the adjoint of the forward above: its first step (the last
         // bounce's transpose) gathers the FP32 lambda^(n), the others
         // lambda^(k+1) rounded to BF16
         for (int k = nb - 1; k >= 0 && e == GSRAD_OK; --k) {
             const bool in_bf = bf && k < nb - 1;
-            const void *in = in_bf ? static_cast<const void *>(lh + (size_t)(k & 1) * vals * 2)
-                                   : static_cast<const void *>(L + (size_t)k * vals);   // lambda^(k+1)
             float *out = k >= 1 ? L + (size_t)(k - 1) * vals : lam0;
-            e = launch_ragged_spmm(b->dev(), FT, b->lpr_adj, true, in, in_bf, nullptr, rho, out, grad_E,
-                                   b->counter.as<uint32_t>(), b->cap);
+            if (in_bf) {
+                e = launch_ragged_spmm(b->dev(), FT, b->lpr_adj, true, lh + (size_t)(k & 1) * vals * 2, nullptr, rho, out,
+                                       grad_E, b->counter.as<uint32_t>(), b->cap);
+            } else {
+                e = rows_adjoint_batch(FT, b->table, b->lpr_adj, p, rho, k >= 1 ? out : nullptr,
+                                       k >= 1 && !bf ? p_next : nullptr, grad_E, b->cap);
+                std::swap(p, p_next);
+            }
             if (e == GSRAD_OK && bf && k >= 1) e = launch_round_bf16(out, vals, lh + (size_t)((k - 1) & 1) * vals * 2, b->cap);
         }
         hipGraph_t gr = nullptr;
@@ -1947,6 +2013,7 @@ gsrad_status gsrad_batch_transport_backward(gsrad_batch *b, const float *rho, co
         GS_TRY(check_hip(hipGraphInstantiate(&b->aexec, gr, nullptr, nullptr, 0), "graph instantiate"));
         b->a_rho = rho;
         b->a_gE = grad_E;
+        b->a_gB = grad_B;
         b->a_L = L;
         b->a_lam0 = lam0;
         b->a_nb = nb;
@@ -1963,9 +2030,9 @@ gsrad_status gsrad_batch_transport_backward(gsrad_batch *b, const float *rho, co
     }
     if (grad_F || grad_rho) {
         ProfScope ps("batch_sddmm", st);
-        const int max_C = *std::max_element(b->scene_cols.begin(), b->scene_cols.end());
-        GS_TRY(launch_ragged_sddmm(b->dev(), b->F->csr(), nb, vals, max_C, b->Bt.as<float>(), L, rho, grad_F, grad_rho,
-                                   b->counter.as<uint32_t>(), st));
+        for (int s = 0; s < b->S; ++s) {
+            GS_TRY(rows_sddmm(b->F->csr(), b->scene(s), nb, vals, b->Bt.as<float>(), L, rho, grad_F, grad_rho, st));
+        }
     }
     return GSRAD_OK;
 }
@@ -1977,6 +2044,8 @@ gsrad_status gsrad_batch_set_precision(gsrad_batch *b, int32_t precision) {
     if (precision != b->precision) {
         b->drop_graph();
         b->precision = precision;
+        b->lpr_fwd = b->force_fwd;   // tuned for the other precision's products
+        b->lpr_adj = b->force_adj;
         b->nb = -1;   // a forward solve of the new precision must come first
     }
     return GSRAD_OK;

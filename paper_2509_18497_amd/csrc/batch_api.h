@@ -21,17 +21,12 @@ size_t batch_order_temp_bytes(int64_t rows);
 // row_scene and order from the scene table and F's row lengths
 gsrad_status batch_order_rows(const BatchDev &bd, const int64_t *row_ptr, void *temp, size_t temp_bytes,
                               hipStream_t st);
-// bounce: out = E + rho * (F in);  adjoint (F given as F^T): out = F^T (rho in), gE += out.
-// One persistent launch; lpr = lanes per row (16, 32 or 64).  counter: one device uint32.
-// in: FP32 rows, or BF16 rows when in_bf16 (FP32 sums either way).
-gsrad_status launch_ragged_spmm(const BatchDev &bd, const Csr &F, int lpr, bool adjoint, const void *in, bool in_bf16,
+// bounce: out = E + rho * (F in);  adjoint (F given as F^T): out = F^T (rho in), gE += out,
+// of BF16 rows `in` with FP32 sums.  One persistent launch; lpr = lanes per
+// row (16, 32 or 64).  counter: one device uint32.
+gsrad_status launch_ragged_spmm(const BatchDev &bd, const Csr &F, int lpr, bool adjoint, const void *in,
                                 const float *E, const float *rho, float *out, float *gE, uint32_t *counter,
                                 hipStream_t st);
-// grad_F at the stored entries and grad_rho from the tapes [nb][vals]
-// (max_C: the largest C_s of the batch)
-gsrad_status launch_ragged_sddmm(const BatchDev &bd, const Csr &F, int nb, int64_t vals, int max_C, const float *Bt,
-                                 const float *Lt, const float *rho, float *grad_F, float *grad_rho, uint32_t *counter,
-                                 hipStream_t st);
 
 }  // namespace gsrad
 

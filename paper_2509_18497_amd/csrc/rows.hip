@@ -1,0 +1,485 @@
+// FP32 row products of the transport: B <- E + rho (F B), its adjoint on F^T
+// and the sampled products lambda_i . B_j at F's entries.
+//
+// Rows of B, E and the gradients hold C = 3 M contiguous floats, M = Lt K
+// RGB coefficients.  A lane owns one coefficient of a chunk (its three colours
+// in one 12-byte load, so no lane masks a colour) and G lanes a gathered row:
+// G = 1 for M = 1, 4 for M <= 4, else 16, more than 16 coefficients in chunks
+// of equal width.  A wave owns an output row and reads its entries 64 at a
+// time, one a lane; each of its 64 / G groups takes G of them, broadcast to
+// its lanes by DPP, and the groups' sums are added at the end.
+//
+// What bounds them is where the gathered rows come from and how many gathers
+// are in flight.  Measured on rows of 192 bytes: one instruction gathering
+// four rows takes a CU some 18 cycles, 25 TB/s over the chip, while the rows
+// come from the XCDs' L2, and 6.3 TB/s from the Infinity Cache; one row per
+// instruction takes 7.8 cycles, 15 TB/s.  So an instruction gathers 64 / G
+// rows, sixteen are in flight per lane with the next entries read ahead, and
+// the order keeps the rows in L2: rows in the receivers' Morton order, each
+// XCD a contiguous part, and the workgroups of one chunk of columns after the
+// other (100 lights: 1/57 of a row is in use at a time).
+//   16k-surfel room, 41.7 M entries, C = 27: bounce 0.87 -> 0.52 ms
+//   100k bowl, 50.5 M entries, C = 48: bounce 0.81 -> 0.77 ms
+// In L2 they run near its request rate (0.83 of one 64-byte request a cycle
+// and channel at C = 540, 96 % hits); the 100k bowl's bounce misses on 39 % of
+// its requests and runs at what the Infinity Cache gives.
+// Launches per tile of senders that fits L2, the row's position kept between
+// them, were slower (bowl: 1.27 ms a bounce with eight tiles): a row has too
+// few entries in a tile to pay for its start.
+#include <algorithm>
+#include <type_traits>
+#include <utility>
+
+#include "gsrad_internal.h"
+#include "rows.h"
+
+namespace gsrad {
+
+namespace {
+
+constexpr int kThreads = 256;
+
+__device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t g) {
+    const int64_t x = b & 7, q = b >> 3, per = g >> 3, rem = g & 7;
+    return x * per + (x < rem ? x : rem) + q;
+}
+
+// three floats at any 4-byte alignment
+struct __attribute__((packed, aligned(4))) F3 {
+    float x, y, z;
+};
+
+// chunks of a row of M coefficients and their width
+__host__ __device__ inline int row_chunks(int M, int g) { return (M + g - 1) / g; }
+__host__ __device__ inline int row_width(int M, int g) {
+    const int c = row_chunks(M, g);
+    return (M + c - 1) / c;
+}
+
+// Lane N's value in every lane of its row of 16 lanes, or of its quad
+template <int CTRL>
+__device__ __forceinline__ int dpp(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+template <int N, int W>
+__device__ __forceinline__ int bcast(int v) {
+    if constexpr (W == 16) return dpp<0x150 + N>(v);   // row_newbcast:N
+    else return dpp<N * 0x55>(v);                      // quad_perm [N, N, N, N]
+}
+template <int... I, typename Fn>
+__device__ __forceinline__ void unroll_seq(std::integer_sequence<int, I...>, Fn &&fn) {
+    (fn(std::integral_constant<int, I>{}), ...);
+}
+// fn(integral_constant 0) ... fn(integral_constant N - 1)
+template <int N, typename Fn>
+__device__ __forceinline__ void unroll(Fn &&fn) {
+    unroll_seq(std::make_integer_sequence<int, N>{}, fn);
+}
+
+// One entry a lane of the 64 entries from k on (the last one past e), of
+// which the group takes the G at `off`
+struct Entries {
+    int j;
+    float w;
+    __device__ __forceinline__ void read(const int32_t *__restrict__ col, const float *__restrict__ val, int64_t k,
+                                         int64_t e) {
+        const int64_t q = min(k, e - 1);
+        j = col[q];
+        w = val[q];
+    }
+    template <int N, int G>
+    __device__ __forceinline__ int column() const {
+        if constexpr (G == 1) return j;
+        else return bcast<N, G>(j);
+    }
+    template <int N, int G>
+    __device__ __forceinline__ float weight() const {
+        if constexpr (G == 1) return w;
+        else return __int_as_float(bcast<N, G>(__float_as_int(w)));
+    }
+};
+
+// acc += w_e * in[col_e] over the group's first m <= G entries
+template <int G, bool ALL>
+__device__ __forceinline__ void take(const Entries &now, int m, const float *__restrict__ in, int C, float (&acc)[3]) {
+    F3 x[G];
+    unroll<G>([&](auto u) {
+        const int j = now.column<u(), G>();
+        x[u()] = *reinterpret_cast<const F3 *>(in + (int64_t)j * C);   // past m: the row's last entry
+    });
+    unroll<G>([&](auto u) {
+        const float w = now.weight<u(), G>();
+        if (ALL || u() < m) {
+            acc[0] = __builtin_fmaf(w, x[u()].x, acc[0]);
+            acc[1] = __builtin_fmaf(w, x[u()].y, acc[1]);
+            acc[2] = __builtin_fmaf(w, x[u()].z, acc[2]);
+        }
+    });
+}
+
+// Sum of v over the groups of a row's LPR lanes, in every lane
+template <int G, int LPR>
+__device__ __forceinline__ float over_groups(float v) {
+#pragma unroll
+    for (int o = G; o < LPR; o <<= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+struct RowArgs {
+    const int64_t *row_ptr;
+    const int32_t *col;
+    const float *val;
+    const int32_t *order;   // rows of a scene in the order they are taken, or NULL
+    RowScene one;           // the scene, when tab is NULL
+    const RowScene *tab;
+    const int64_t *first;
+    int count;
+    const float *rho;
+};
+
+// The scene and the (chunk, row) of this lane; false past the scene's rows
+template <int G, int LPR>
+__device__ __forceinline__ bool find_row(const RowArgs &a, RowScene &s, int &m0, int64_t &row) {
+    int64_t b = blockIdx.x;
+    if (a.tab) {
+        int lo = 0, hi = a.count - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (a.first[mid] <= b) lo = mid;
+            else hi = mid - 1;
+        }
+        s = a.tab[lo];
+        b -= a.first[lo];
+    } else {
+        s = a.one;
+    }
+    constexpr int R = kThreads / LPR;
+    const int64_t per = (s.n + R - 1) / R;
+    const int chunk = (int)(b / per);
+    const int64_t idx = xcd_block(b - (int64_t)chunk * per, per) * R + threadIdx.x / LPR;
+    m0 = chunk * row_width(s.C / 3, G);
+    if (idx >= s.n) return false;
+    row = a.order ? (int64_t)a.order[s.row0 + idx] : s.row0 + idx;
+    return true;
+}
+
+// ADJ false: out = E + rho acc.  ADJ true: out = acc, p_out = rho acc,
+// gE += acc (out, p_out where not NULL).  LPR lanes per row: 64, or with
+// G = 16 also 32 or 16, which take the sums of two or four of the 64-entry
+// reading's groups one after the other; the sums are the same.
+template <int G, int LPR, bool ADJ>
+__global__ void __launch_bounds__(kThreads) k_rows(RowArgs a, const float *__restrict__ in,
+                                                   const float *__restrict__ E, float *__restrict__ out,
+                                                   float *__restrict__ p_out, float *__restrict__ gE) {
+    RowScene s;
+    int m0;
+    int64_t row;
+    if (!find_row<G, LPR>(a, s, m0, row)) return;
+    constexpr int A = 64 / LPR;   // groups of a reading that one group of lanes takes
+    const int M = s.C / 3, l = threadIdx.x % G, m = m0 + l;
+    const int sub = (threadIdx.x % LPR) / G;
+    const bool on = l < row_width(M, G) && m < M;
+    const int64_t b = a.row_ptr[row], e = a.row_ptr[row + 1];
+    float acc[A][3];
+#pragma unroll
+    for (int q = 0; q < A; ++q) acc[q][0] = acc[q][1] = acc[q][2] = 0.0f;
+    if (b < e) {
+        const float *src = in + s.vbase - s.row0 * s.C + 3 * (on ? m : 0);
+        Entries next[A];
+        auto first_of = [&](int64_t k, int q) { return k + (q * (LPR / G) + sub) * G; };
+#pragma unroll
+        for (int q = 0; q < A; ++q) next[q].read(a.col, a.val, first_of(b, q) + l, e);
+        int64_t k = b;
+        for (; k + 64 <= e; k += 64) {
+#pragma unroll
+            for (int q = 0; q < A; ++q) {
+                const Entries now = next[q];
+                if (k + 64 < e) next[q].read(a.col, a.val, first_of(k + 64, q) + l, e);
+                take<G, true>(now, G, src, s.C, acc[q]);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < A; ++q) {
+            const int n = (int)max<int64_t>(0, min<int64_t>(G, e - first_of(k, q)));
+            if (n > 0) take<G, false>(next[q], n, src, s.C, acc[q]);
+        }
+    }
+    // the groups' sums in one order whatever LPR: pairs at distance one
+    // group, then two, ...
+    float t[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        if constexpr (A == 1) t[c] = over_groups<G, 64>(acc[0][c]);
+        else if constexpr (A == 2) {
+            // lanes hold groups (0, 1) and (2, 3)
+            const float x = over_groups<G, LPR>(acc[0][c]), y = over_groups<G, LPR>(acc[1][c]);
+            t[c] = x + y;
+        } else {
+            t[c] = (acc[0][c] + acc[1][c]) + (acc[2][c] + acc[3][c]);
+        }
+    }
+    if (!on || sub != 0) return;
+    const int64_t at = s.vbase + (row - s.row0) * s.C + 3 * m;
+    const float r0 = a.rho[row * 3 + 0], r1 = a.rho[row * 3 + 1], r2 = a.rho[row * 3 + 2];
+    if (ADJ) {
+        if (out) *reinterpret_cast<F3 *>(out + at) = F3{t[0], t[1], t[2]};
+        if (p_out) *reinterpret_cast<F3 *>(p_out + at) = F3{r0 * t[0], r1 * t[1], r2 * t[2]};
+        const F3 g = *reinterpret_cast<const F3 *>(gE + at);
+        *reinterpret_cast<F3 *>(gE + at) = F3{g.x + t[0], g.y + t[1], g.z + t[2]};
+    } else {
+        const F3 x = *reinterpret_cast<const F3 *>(E + at);
+        *reinterpret_cast<F3 *>(out + at) = F3{__builtin_fmaf(r0, t[0], x.x), __builtin_fmaf(r1, t[1], x.y),
+                                               __builtin_fmaf(r2, t[2], x.z)};
+    }
+}
+
+// Sum over the G lanes of a group, in every lane (rotations within a row of
+// 16 lanes, or a quad)
+template <int G>
+__device__ __forceinline__ float group_sum(float v) {
+    auto add = [&](auto ctrl) { v += __int_as_float(dpp<decltype(ctrl)::value>(__float_as_int(v))); };
+    if constexpr (G == 16) {
+        add(std::integral_constant<int, 0x128>{});   // row_ror:8
+        add(std::integral_constant<int, 0x124>{});   // row_ror:4
+        add(std::integral_constant<int, 0x122>{});   // row_ror:2
+        add(std::integral_constant<int, 0x121>{});   // row_ror:1
+    } else if constexpr (G == 4) {
+        add(std::integral_constant<int, 0x4e>{});   // quad_perm [2,3,0,1]
+        add(std::integral_constant<int, 0xb1>{});   // quad_perm [1,0,3,2]
+    }
+    return v;
+}
+
+// For each stored entry e = (row, j), over this launch's chunk of columns
+// and its NQ bounces:
+//   s_c = sum_k sum_{columns of colour c} lambda^(k+1)[row] B^(k)[j]
+//   grad_F[e] (+)= sum_c rho[row, c] s_c;  grad_rho[row, c] (+)= sum_e F[e] s_c
+// A wave per row, the row's lambda in registers; a group gathers two of its
+// entries' NQ rows at a time.  Both results are linear in the lanes' shares of
+// s_c, so only the one value of dL/dF is summed over a group's lanes for each
+// entry; dL/drho's three are summed over the wave once per row.
+template <int G, int NQ>
+__global__ void __launch_bounds__(kThreads) k_sddmm3(RowArgs a, int m0, int64_t stride,
+                                                     const float *__restrict__ Bt, const float *__restrict__ Lt,
+                                                     float *__restrict__ grad_F, float *__restrict__ grad_rho,
+                                                     bool fresh) {
+    const RowScene s = a.one;
+    constexpr int R = kThreads / 64;
+    const int64_t idx = xcd_block(blockIdx.x, (s.n + R - 1) / R) * R + threadIdx.x / 64;
+    if (idx >= s.n) return;
+    const int64_t row = a.order ? (int64_t)a.order[s.row0 + idx] : s.row0 + idx;
+    const int lane = (int)__lane_id();
+    const int M = s.C / 3, l = lane % G, m = m0 + l;
+    const bool on = l < row_width(M, G) && m < M;
+    const int64_t b = a.row_ptr[row], e = a.row_ptr[row + 1];
+    float gr[3] = {0.0f, 0.0f, 0.0f};
+    if (b < e) {
+        const float r[3] = {a.rho[row * 3 + 0], a.rho[row * 3 + 1], a.rho[row * 3 + 2]};
+        float lam[NQ][3];
+        const int64_t at = s.vbase + (row - s.row0) * s.C + 3 * (on ? m : 0);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const F3 x = *reinterpret_cast<const F3 *>(Lt + q * stride + at);
+            lam[q][0] = x.x;
+            lam[q][1] = x.y;
+            lam[q][2] = x.z;
+        }
+        const float *base = Bt + s.vbase - s.row0 * s.C + 3 * (on ? m : 0);
+        Entries next;
+        next.read(a.col, a.val, b + lane, e);
+        for (int64_t k = b; k < e; k += 64) {
+            const Entries now = next;
+            if (k + 64 < e) next.read(a.col, a.val, k + 64 + lane, e);
+            const int n = (int)max<int64_t>(0, min<int64_t>(G, e - (k + lane - l)));
+            float keep = 0.0f;   // dL/dF of the entry this lane read
+            constexpr int P = G == 1 ? 1 : 2;
+            unroll<G / P>([&](auto h) {
+                constexpr int u0 = h() * P;
+                if (u0 < n) {
+                    F3 x[P][NQ];
+                    unroll<P>([&](auto u) {
+                        const float *src = base + (int64_t)now.column<u0 + u(), G>() * s.C;
+#pragma unroll
+                        for (int q = 0; q < NQ; ++q) x[u()][q] = *reinterpret_cast<const F3 *>(src + q * stride);
+                    });
+                    unroll<P>([&](auto u) {
+                        float t[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+                        for (int q = 0; q < NQ; ++q) {
+                            t[0] = __builtin_fmaf(lam[q][0], x[u()][q].x, t[0]);
+                            t[1] = __builtin_fmaf(lam[q][1], x[u()][q].y, t[1]);
+                            t[2] = __builtin_fmaf(lam[q][2], x[u()][q].z, t[2]);
+                        }
+                        float g = r[0] * t[0] + r[1] * t[1] + r[2] * t[2];
+                        if (G > 1) g = group_sum<G>(on ? g : 0.0f);
+                        const float f = now.weight<u0 + u(), G>();
+                        if (l == u0 + u()) keep = g;
+                        if (u0 + u() < n) {
+#pragma unroll
+                            for (int c = 0; c < 3; ++c) gr[c] = __builtin_fmaf(f, t[c], gr[c]);
+                        }
+                    });
+                }
+            });
+            if (grad_F && k + lane < e) grad_F[k + lane] = fresh ? keep : grad_F[k + lane] + keep;
+        }
+    }
+    if (!grad_rho) return;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const float t = over_groups<1, 64>(on ? gr[c] : 0.0f);
+        if (lane == 0) grad_rho[row * 3 + c] = fresh ? t : grad_rho[row * 3 + c] + t;
+    }
+}
+
+__global__ void __launch_bounds__(256) k_scale_rho(RowScene s, const float *__restrict__ in,
+                                                   const float *__restrict__ rho, float *__restrict__ out) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int M = s.C / 3;
+    if (t >= s.n * M) return;
+    const int64_t row = s.row0 + t / M;
+    const F3 x = *reinterpret_cast<const F3 *>(in + s.vbase + 3 * t);
+    *reinterpret_cast<F3 *>(out + s.vbase + 3 * t) =
+        F3{rho[row * 3] * x.x, rho[row * 3 + 1] * x.y, rho[row * 3 + 2] * x.z};
+}
+
+int row_lanes(int C) { return C == 3 ? 1 : C <= 12 ? 4 : 16; }
+
+// Bounces per launch of the sampled products.  One launch of all takes the
+// fewest instructions, but the chunk of all rows and bounces that it gathers
+// from has to stay in the XCDs' L2: with two against eight per launch 100k
+// rows of 192 bytes take 8.3 against 10.9 ms, 8k rows in 12 chunks 6.2
+// against 10.1, while 8k rows of 108 bytes take 0.33 against 0.27 and 16k
+// (four: 3.9) 4.5 against 3.9.  The line lies where these cross.
+constexpr int64_t kSddmmBytes = (int64_t)7 << 20;
+int sddmm_bounces(int64_t n, int width) {
+    return (int)std::min<int64_t>(8, std::max<int64_t>(2, kSddmmBytes / (n * width * 12)));
+}
+
+RowArgs row_args(const Csr &F, const float *rho) {
+    RowArgs a{};
+    a.row_ptr = F.row_ptr;
+    a.col = F.col;
+    a.val = F.val;
+    a.order = F.order;
+    a.rho = rho;
+    return a;
+}
+
+template <bool ADJ>
+gsrad_status run_scene(const Csr &F, const RowScene &s, const float *in, const float *E, const float *rho, float *out,
+                       float *p_out, float *gE, hipStream_t st) {
+    if (s.n == 0) return GSRAD_OK;
+    const int g = row_lanes(s.C);
+    RowArgs a = row_args(F, rho);
+    a.one = s;
+    const dim3 grid((unsigned)rows_blocks(s.n, s.C, 64));
+    auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, a, in, E, out, p_out, gE); };
+    if (g == 1) run(k_rows<1, 64, ADJ>);
+    else if (g == 4) run(k_rows<4, 64, ADJ>);
+    else run(k_rows<16, 64, ADJ>);
+    return check_hip(hipGetLastError(), ADJ ? "adjoint launch" : "bounce launch");
+}
+
+// The scenes of a batch in one launch; scenes of few columns (G < 16) in
+// launches of their own.
+template <bool ADJ>
+gsrad_status run_batch(const Csr &F, const RowTable &t, int lanes, const float *in, const float *E, const float *rho,
+                       float *out, float *p_out, float *gE, hipStream_t st) {
+    const int which = lanes == 16 ? 0 : lanes == 32 ? 1 : 2;
+    if (lanes != 16 && lanes != 32 && lanes != 64) {
+        set_error("ragged product: lanes per row must be 16, 32 or 64");
+        return GSRAD_EINVAL;
+    }
+    for (const RowScene &s : t.few) {
+        const gsrad_status e = run_scene<ADJ>(F, s, in, E, rho, out, p_out, gE, st);
+        if (e != GSRAD_OK) return e;
+    }
+    if (t.count == 0) return GSRAD_OK;
+    RowArgs a = row_args(F, rho);
+    a.tab = t.tab;
+    a.first = t.first[which];
+    a.count = t.count;
+    const dim3 grid((unsigned)t.blocks[which]);
+    auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, a, in, E, out, p_out, gE); };
+    if (which == 0) run(k_rows<16, 16, ADJ>);
+    else if (which == 1) run(k_rows<16, 32, ADJ>);
+    else run(k_rows<16, 64, ADJ>);
+    return check_hip(hipGetLastError(), "ragged product launch");
+}
+
+}  // namespace
+
+bool rows_few(int C) { return row_lanes(C) < 16; }
+
+int64_t rows_blocks(int64_t n, int C, int lanes) {
+    const int64_t r = kThreads / lanes;
+    return (n + r - 1) / r * row_chunks(C / 3, row_lanes(C));
+}
+
+gsrad_status rows_bounce(const Csr &F, const RowScene &s, const float *Bin, const float *E, const float *rho,
+                         float *Bout, hipStream_t st) {
+    return run_scene<false>(F, s, Bin, E, rho, Bout, nullptr, nullptr, st);
+}
+
+gsrad_status rows_adjoint(const Csr &FT, const RowScene &s, const float *p, const float *rho, float *lam,
+                          float *p_out, float *gE, hipStream_t st) {
+    return run_scene<true>(FT, s, p, nullptr, rho, lam, p_out, gE, st);
+}
+
+gsrad_status rows_bounce_batch(const Csr &F, const RowTable &t, int lanes, const float *Bin, const float *E,
+                               const float *rho, float *Bout, hipStream_t st) {
+    return run_batch<false>(F, t, lanes, Bin, E, rho, Bout, nullptr, nullptr, st);
+}
+
+gsrad_status rows_adjoint_batch(const Csr &FT, const RowTable &t, int lanes, const float *p, const float *rho,
+                                float *lam, float *p_out, float *gE, hipStream_t st) {
+    return run_batch<true>(FT, t, lanes, p, nullptr, rho, lam, p_out, gE, st);
+}
+
+gsrad_status rows_scale(const RowScene &s, const float *in, const float *rho, float *out, hipStream_t st) {
+    const int64_t lanes = s.n * (s.C / 3);
+    if (lanes == 0) return GSRAD_OK;
+    hipLaunchKernelGGL(k_scale_rho, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, st, s, in, rho, out);
+    return check_hip(hipGetLastError(), "rho scaling launch");
+}
+
+gsrad_status rows_sddmm(const Csr &F, const RowScene &s, int nb, int64_t stride, const float *Btape,
+                        const float *Ltape, const float *rho, float *grad_F, float *grad_rho, hipStream_t st) {
+    if (s.n == 0 || nb == 0) return GSRAD_OK;
+    const int g = row_lanes(s.C), M = s.C / 3, width = row_width(M, g);
+    RowArgs a = row_args(F, rho);
+    a.one = s;
+    const dim3 grid((unsigned)((s.n + kThreads / 64 - 1) / (kThreads / 64)));
+    const int per = sddmm_bounces(s.n, width);
+    bool fresh = true;
+    for (int m0 = 0; m0 < M; m0 += width) {
+        for (int q0 = 0; q0 < nb; q0 += per) {
+            const float *B = Btape + q0 * stride, *L = Ltape + q0 * stride;
+            auto run = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, a, m0, stride, B, L, grad_F, grad_rho, fresh);
+            };
+#define GS_NQ(N)                                 \
+    case N:                                      \
+        if (g == 1) run(k_sddmm3<1, N>);         \
+        else if (g == 4) run(k_sddmm3<4, N>);    \
+        else run(k_sddmm3<16, N>);               \
+        break
+            switch (std::min(per, nb - q0)) {
+                GS_NQ(1);
+                GS_NQ(2);
+                GS_NQ(3);
+                GS_NQ(4);
+                GS_NQ(5);
+                GS_NQ(6);
+                GS_NQ(7);
+                GS_NQ(8);
+            }
+#undef GS_NQ
+            fresh = false;
+        }
+    }
+    return check_hip(hipGetLastError(), "sddmm launch");
+}
+
+}  // namespace gsrad

@@ -69,18 +69,8 @@ struct Csr {
 size_t transpose_temp_bytes(int64_t n, int64_t nnz);
 gsrad_status csr_transpose(const Csr &A, int64_t *t_row_ptr, int32_t *t_col, float *t_val, void *temp,
                            size_t temp_bytes, hipStream_t st);
-// Bout = E + rho * (F Bin), rows of C columns
 // Morton-sorted position -> original surfel index (the sorted records' ids)
 gsrad_status launch_sorted_order(const BvhDev &bv, int32_t *order, hipStream_t st);
-gsrad_status launch_bounce(const Csr &F, int C, const float *Bin, const float *E, const float *rho, float *Bout,
-                           hipStream_t st);
-// lam_out = F^T (rho * lam_in) given FT = transpose(F); gE += lam_out
-gsrad_status launch_adjoint(const Csr &FT, int C, const float *lam_in, const float *rho, float *lam_out, float *gE,
-                            hipStream_t st);
-// grad_F[e] and grad_rho from the forward tape B^(k) and the adjoint tape
-// lambda^(k+1), both [nb][N][C]
-gsrad_status launch_sddmm(const Csr &F, int C, int nb, const float *Btape, const float *Ltape, const float *rho,
-                          float *grad_F, float *grad_rho, hipStream_t st);
 // reciprocity sums over the stored entries (areas [n] FP64): acc[0] +=
 // |A_i F_ij - A_j F_ji|, acc[1] += A_i F_ij, acc[2] = max relative difference
 gsrad_status launch_reciprocity(const Csr &F, const double *area, double *acc, hipStream_t st);
