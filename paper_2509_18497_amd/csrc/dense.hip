@@ -4,8 +4,8 @@
 // (B^(k))^T on split (hi + lo) operands.  Every product is one "NT" GEMM kernel: both operands are
 // row-major with the reduction index contiguous, C[i][j] = sum_k A[i][k] B[j][k].
 //
-// Tiles: a 256-thread workgroup computes a 256 x 256 block of C, its four
-// waves 128 x 128 each (4 x 4 MFMA tiles of 32 x 32, 256 accumulators per
+// Tiles: a 512-thread workgroup computes a 256 x 256 block of C, its eight
+// waves 128 x 64 each (4 x 2 MFMA tiles of 32 x 32, 128 accumulators per
 // lane), K advanced 64 at a time through two LDS stages filled by direct
 // global -> LDS buffer loads (no staging registers): the next K tile is in
 // flight while the current one is multiplied.  LDS rows are unpadded with
@@ -15,6 +15,18 @@
 // share an A row-block (the large operand) run on one XCD and share its L2;
 // the dL/dF product, whose operands are equally large, uses bands of eight
 // tile rows instead.
+//
+// Bound by the matrix cores at the clock they get, and by the gaps between
+// their instructions.  Measured at n = 32768, 2816 padded columns (2.4 GHz
+// nominal, 2.5 PFLOP/s): one wave of 128 x 128 per SIMD, bounce 7.49 ms (808
+// TFLOP/s issued) and dL/dF 129 ms (1.08 PFLOP/s); two waves per SIMD, which
+// fill each other's gaps, 5.73 ms (1.06 PFLOP/s; 8 % of it is the last,
+// half-empty round of workgroups) and 113 ms (1.23 PFLOP/s), the matrix cores
+// busy 65 % of the cycles at 1.8 GHz (a library product of the bounce's shape
+// runs at 1.27 PFLOP/s here).  Measured and not kept: one wave per SIMD with
+// the fragment reads and loads placed between its MFMAs, dL/dF 112 ms but
+// bounces 6.5 ms; K tiles of 32 in four or five stages, 123-125 ms and 7.0 ms
+// (half-line requests).
 //
 // A K range may be split into up to three segments with their own A and B
 // (the correction sweep sums F_hi X_hi + F_hi X_lo + F_lo X_hi in one pass).
@@ -32,6 +44,7 @@ typedef __attribute__((address_space(3))) void lds_void;
 constexpr int kWaitVm0 = 0x0F70;   // s_waitcnt vmcnt(0), other counters unconstrained
 
 constexpr int kBM = 256, kBN = 256, kBK = 64;
+constexpr int kGemmThreads = 512;
 constexpr int kRowBytes = kBK * 2;                         // one LDS row: 8 chunks of 16 bytes
 constexpr int kStageBytes = (kBM + kBN) * kRowBytes;      // A then B of one K tile (64 KiB)
 constexpr size_t kGemmSmem = (size_t)2 * kStageBytes;     // two stages
@@ -174,39 +187,34 @@ __device__ __forceinline__ void epi_tile(const Epi &epi, const f32x16 &a, int64_
 // 64 lanes x 16 bytes contiguously).
 __device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & 7; }
 
-// The 64-wide K tile of one wave's 128 x 128 block out of one stage: four
-// 16-wide steps of sixteen 32 x 32 x 16 MFMAs, each step's fragments read
-// while the previous step multiplies (two register sets).  Ab/Bb address
-// the wave's row frow of A and B; fsw = swz(frow) (rows 32 mi + frow add
-// 4 (mi & 1) to it), h = the lane's K half.
-__device__ __forceinline__ void gemm_k_tile(const unsigned char *Ab, const unsigned char *Bb, int fsw, int h,
-                                            f32x16 (&acc)[4][4]) {
-    bf16x8 af[2][4], bf[2][4];
-#define GEMM_FRAG(ks, i) (16 * ((2 * (ks) + h) ^ fsw ^ (((i) & 1) << 2)) + (i) * 32 * kRowBytes)
+// One wave's 128 x 64 block takes a 64-wide K tile in four 16-wide steps of
+// eight 32 x 32 x 16 MFMAs, the next step's fragments read while a step
+// multiplies (two register sets).  Ab/Bb address the wave's row frow of A and
+// B in the tile's stage; fsw = swz(frow) (rows 32 mi + frow add 4 (mi & 1) to
+// it), h = the lane's K half.
+constexpr int kMI = 4, kNI = 2;
+
+struct Frags {
+    bf16x8 a[kMI], b[kNI];
+    __device__ __forceinline__ void read(const unsigned char *Ab, const unsigned char *Bb, int ks, int fsw, int h) {
+#define GEMM_FRAG(i) (16 * ((2 * ks + h) ^ fsw ^ (((i) & 1) << 2)) + (i) * 32 * kRowBytes)
 #pragma unroll
-    for (int mi = 0; mi < 4; ++mi) af[0][mi] = *reinterpret_cast<const bf16x8 *>(Ab + GEMM_FRAG(0, mi));
+        for (int ni = 0; ni < kNI; ++ni) b[ni] = *reinterpret_cast<const bf16x8 *>(Bb + GEMM_FRAG(ni));
 #pragma unroll
-    for (int ni = 0; ni < 4; ++ni) bf[0][ni] = *reinterpret_cast<const bf16x8 *>(Bb + GEMM_FRAG(0, ni));
-#pragma unroll
-    for (int ks = 0; ks < kBK / 16; ++ks) {
-        const int cur = ks & 1, nxt = cur ^ 1;
-        if (ks + 1 < kBK / 16) {
-#pragma unroll
-            for (int mi = 0; mi < 4; ++mi)
-                af[nxt][mi] = *reinterpret_cast<const bf16x8 *>(Ab + GEMM_FRAG(ks + 1, mi));
-#pragma unroll
-            for (int ni = 0; ni < 4; ++ni)
-                bf[nxt][ni] = *reinterpret_cast<const bf16x8 *>(Bb + GEMM_FRAG(ks + 1, ni));
-        }
-#pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < 4; ++ni)
-                acc[mi][ni] =
-                    __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[cur][mi], bf[cur][ni], acc[mi][ni], 0, 0, 0);
-    }
+        for (int mi = 0; mi < kMI; ++mi) a[mi] = *reinterpret_cast<const bf16x8 *>(Ab + GEMM_FRAG(mi));
 #undef GEMM_FRAG
-}
+    }
+    template <int M0, int M1>
+    __device__ __forceinline__ void multiply(f32x16 (&acc)[kMI][kNI]) const {
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int mi = M0; mi < M1; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < kNI; ++ni)
+                acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mi], b[ni], acc[mi][ni], 0, 0, 0);
+        __builtin_amdgcn_s_setprio(0);
+    }
+};
 
 struct Segs {
     const __bf16 *a[3];
@@ -214,7 +222,7 @@ struct Segs {
 };
 
 template <class Epi>
-__global__ void __launch_bounds__(256) k_gemm_nt(Segs sg, int nseg, int64_t lda, int64_t ldb, int64_t kpad,
+__global__ void __launch_bounds__(kGemmThreads) k_gemm_nt(Segs sg, int nseg, int64_t lda, int64_t ldb, int64_t kpad,
                                                  int tiles_n, int64_t ntiles, int group_m, Epi epi) {
     extern __shared__ __align__(16) unsigned char gemm_smem[];   // [2 stages][A 256 rows | B 256 rows]
     const int64_t t = xcd_block(blockIdx.x, ntiles);
@@ -232,20 +240,20 @@ __global__ void __launch_bounds__(256) k_gemm_nt(Segs sg, int nseg, int64_t lda,
     }
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = w >> 1, wn = w & 1;
+    const int wm = w >> 2, wn = w & 3;
     const int kt_per = (int)(kpad / kBK);
     const int KT = nseg * kt_per;
-    f32x16 acc[4][4];
+    f32x16 acc[kMI][kNI];
 #pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
+    for (int mi = 0; mi < kMI; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < 4; ++ni)
+        for (int ni = 0; ni < kNI; ++ni)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.0f;
-    // Direct global -> LDS loads: wave w brings rows 64 w .. 64 w + 63 of
+    // Direct global -> LDS loads: wave w brings rows 32 w .. 32 w + 31 of
     // the A and the B tile, eight rows (1 KiB) per instruction; lane l
-    // fills row 64 w + 8 i + l / 8, physical chunk l % 8, so it fetches the
-    // logical chunk (l % 8) ^ swz(row) = (l % 8) ^ (l / 8) ^ i.  One buffer
+    // fills row 32 w + 8 i + l / 8, physical chunk l % 8, so it fetches the
+    // logical chunk (l % 8) ^ swz(row) = (l % 8) ^ (l / 8) ^ (4 w + i) % 8.  One buffer
     // resource per segment operand based at the workgroup's first row
     // (selected, not indexed: a dynamic index into the argument struct
     // would put it in scratch memory), the row step and K offset in SGPRs.
@@ -259,47 +267,59 @@ __global__ void __launch_bounds__(256) k_gemm_nt(Segs sg, int nseg, int64_t lda,
         const __bf16 *B_ = (s_ == 0 ? sg.b[0] : s_ == 1 ? sg.b[1] : sg.b[2]) + bn * kBN * ldb;           \
         const __amdgpu_buffer_rsrc_t ar_ = __builtin_amdgcn_make_buffer_rsrc((void *)A_, 0, nra, kBufFlags); \
         const __amdgpu_buffer_rsrc_t br_ = __builtin_amdgcn_make_buffer_rsrc((void *)B_, 0, nrb, kBufFlags); \
-        unsigned char *ls_ = gemm_smem + (stage) * kStageBytes + w * 64 * kRowBytes;                     \
+        unsigned char *ls_ = gemm_smem + (stage) * kStageBytes + w * 32 * kRowBytes;                     \
         GEMM_LOAD_ROWS(0); GEMM_LOAD_ROWS(1); GEMM_LOAD_ROWS(2); GEMM_LOAD_ROWS(3);                      \
-        GEMM_LOAD_ROWS(4); GEMM_LOAD_ROWS(5); GEMM_LOAD_ROWS(6); GEMM_LOAD_ROWS(7);                      \
     } while (0)
 #define GEMM_LOAD_ROWS(i)                                                                                \
     do {                                                                                                 \
-        const int r_ = w * 64 + 8 * (i);                                                                 \
+        const int r_ = w * 32 + 8 * (i);                                                                 \
         __builtin_amdgcn_raw_ptr_buffer_load_lds(ar_, (lds_void *)(ls_ + 8 * (i) * kRowBytes), 16,       \
-                                                 lr * (int)lda * 2 + 16 * (lc ^ lr ^ (i)),               \
+                                                 lr * (int)lda * 2 + 16 * (lc ^ lr ^ (4 * (w & 1) + (i))),               \
                                                  r_ * (int)lda * 2 + k0_, 0, 0);                         \
         __builtin_amdgcn_raw_ptr_buffer_load_lds(br_, (lds_void *)(ls_ + kBM * kRowBytes + 8 * (i) * kRowBytes), \
-                                                 16, lr * (int)ldb * 2 + 16 * (lc ^ lr ^ (i)),           \
+                                                 16, lr * (int)ldb * 2 + 16 * (lc ^ lr ^ (4 * (w & 1) + (i))),           \
                                                  r_ * (int)ldb * 2 + k0_, 0, 0);                         \
     } while (0)
     const int frow = lane & 31, h = lane >> 5, fsw = swz(frow);
     const unsigned char *Aw = gemm_smem + (wm * 128 + frow) * kRowBytes;
-    const unsigned char *Bw = gemm_smem + kBM * kRowBytes + (wn * 128 + frow) * kRowBytes;
+    const unsigned char *Bw = gemm_smem + kBM * kRowBytes + (wn * 64 + frow) * kRowBytes;
+    // A tile's last step is multiplied after the barrier that ends the reads
+    // of its stage and finds the next tile in the other one, so the next
+    // tile's first fragments and the loads into the freed stage are issued
+    // while it multiplies, and a load has a whole tile's time to arrive.
+    Frags f0, f1;
     GEMM_LOAD(0, 0);
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
     __syncthreads();
+    if (KT > 1) GEMM_LOAD(1, 1);
+    f0.read(Aw, Bw, 0, fsw, h);
     for (int kt = 0; kt < KT; ++kt) {
         const int st = kt & 1;
-        // the next tile (the last one again at the end: in bounds, unused)
-        // goes into the other stage, free since the previous barrier
-        GEMM_LOAD(min(kt + 1, KT - 1), st ^ 1);
-        gemm_k_tile(Aw + st * kStageBytes, Bw + st * kStageBytes, fsw, h, acc);
+        const unsigned char *Ab = Aw + st * kStageBytes, *Bb = Bw + st * kStageBytes;
+        f1.read(Ab, Bb, 1, fsw, h);
+        f0.multiply<0, kMI>(acc);
+        f0.read(Ab, Bb, 2, fsw, h);
+        f1.multiply<0, kMI>(acc);
+        f1.read(Ab, Bb, 3, fsw, h);
+        f0.multiply<0, kMI>(acc);
         __builtin_amdgcn_s_waitcnt(kWaitVm0);
         __syncthreads();
+        // (past the last tile: the stage's old bytes, not used)
+        f0.read(Aw + (st ^ 1) * kStageBytes, Bw + (st ^ 1) * kStageBytes, 0, fsw, h);
+        f1.multiply<0, kMI / 2>(acc);
+        if (kt + 2 < KT) GEMM_LOAD(kt + 2, st);
+        f1.multiply<kMI / 2, kMI>(acc);
     }
 #undef GEMM_LOAD_ROWS
 #undef GEMM_LOAD
     // accumulator register r of lane l holds row (r/4)*8 + (l/32)*4 + r%4,
     // column l%32 of its 32 x 32 tile
-    const int64_t i0 = bm * kBM + wm * 128 + (lane >> 5) * 4, j0 = bn * kBN + wn * 128 + (lane & 31);
-    // sixteen explicit tile calls: a loop over the accumulator array that
+    const int64_t i0 = bm * kBM + wm * 128 + (lane >> 5) * 4, j0 = bn * kBN + wn * 64 + (lane & 31);
+    // eight explicit tile calls: a loop over the accumulator array that
     // the compiler does not unroll would leave it in scratch memory
 #define GEMM_EPI(mi, ni) epi_tile(epi, acc[mi][ni], i0 + (mi) * 32, j0 + (ni) * 32)
-    GEMM_EPI(0, 0); GEMM_EPI(0, 1); GEMM_EPI(0, 2); GEMM_EPI(0, 3);
-    GEMM_EPI(1, 0); GEMM_EPI(1, 1); GEMM_EPI(1, 2); GEMM_EPI(1, 3);
-    GEMM_EPI(2, 0); GEMM_EPI(2, 1); GEMM_EPI(2, 2); GEMM_EPI(2, 3);
-    GEMM_EPI(3, 0); GEMM_EPI(3, 1); GEMM_EPI(3, 2); GEMM_EPI(3, 3);
+    GEMM_EPI(0, 0); GEMM_EPI(0, 1); GEMM_EPI(1, 0); GEMM_EPI(1, 1);
+    GEMM_EPI(2, 0); GEMM_EPI(2, 1); GEMM_EPI(3, 0); GEMM_EPI(3, 1);
 #undef GEMM_EPI
 }
 
@@ -421,7 +441,7 @@ gsrad_status launch_gemm(const Segs &sg, int nseg, int64_t lda, int64_t ldb, int
                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGemmSmem),
                                "dense product LDS attribute");
     if (e != GSRAD_OK) return e;
-    hipLaunchKernelGGL(k_gemm_nt<Epi>, dim3((unsigned)ntiles), dim3(256), kGemmSmem, st, sg, nseg, lda, ldb, kpad,
+    hipLaunchKernelGGL(k_gemm_nt<Epi>, dim3((unsigned)ntiles), dim3(kGemmThreads), kGemmSmem, st, sg, nseg, lda, ldb, kpad,
                        tiles_n, ntiles, group_m, epi);
     return check_hip(hipGetLastError(), "dense product launch");
 }
