@@ -320,7 +320,7 @@ struct gsrad_mc {
     int G = 0;
     float rmin2 = 0.0f;
     DevBuf cent, gnrm, L, key, ids, skey, members, count, goff, rtemp, stemp;
-    DevBuf S, S2, B, delta, var, D, q, maxbits, recv, cdf, err;
+    DevBuf S, S2, B, delta, var, D, q, maxbits, recv, cdf, err, mem, jsel, pj;
     gsrad::McBuffers mb() const {
         gsrad::McBuffers m;
         m.cent = cent.as<float>();
@@ -346,11 +346,14 @@ struct gsrad_mc {
         m.maxbits = maxbits.as<uint32_t>();
         m.recv = recv.as<int32_t>();
         m.cdf = cdf.as<int64_t>();
+        m.mem = mem.p;
+        m.jsel = jsel.as<int32_t>();
+        m.pj = pj.as<float>();
         return m;
     }
     ~gsrad_mc() {
         for (DevBuf *b : {&cent, &gnrm, &L, &key, &ids, &skey, &members, &count, &goff, &rtemp, &stemp, &S, &S2, &B,
-                          &delta, &var, &D, &q, &maxbits, &recv, &cdf, &err})
+                          &delta, &var, &D, &q, &maxbits, &recv, &cdf, &err, &mem, &jsel, &pj})
             b->release();
     }
 };
@@ -2134,6 +2137,9 @@ static gsrad_status mc_ready(gsrad_mc *mc, int Lt, int K, const char *fn) {
     GS_TRY(mc->maxbits.ensure(64, "mc max"));
     GS_TRY(mc->recv.ensure((size_t)mc->n * 4, "mc receivers"));
     GS_TRY(mc->cdf.ensure(((size_t)mc->n + 1) * 8, "mc cdf"));
+    GS_TRY(mc->mem.ensure(mc_member_bytes(mc->n), "mc members"));
+    GS_TRY(mc->jsel.ensure((size_t)mc->n * 4, "mc draws"));
+    GS_TRY(mc->pj.ensure((size_t)mc->n * 4, "mc draws"));
     return GSRAD_OK;
 }
 

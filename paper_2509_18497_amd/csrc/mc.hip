@@ -1,6 +1,8 @@
 // Monte-Carlo TD(0) radiosity solver (Sec. 7, App. D): K-Means groups of
 // the surfels, next-event sampling of a group and a member, the one-point
 // estimate with the centre-to-centre decay and the running averages.
+#include <utility>
+
 #include "gsrad_internal.h"
 #include "sh_api.h"
 #include "trace_api.h"
@@ -135,86 +137,245 @@ __device__ __forceinline__ float group_weight(const SurfRec &ra, const float *ce
     return Lg * (ca + kMcBeta) * (cg + kMcBeta) / r2;
 }
 
-// One next event per slot: receiver recv[slot] (slot itself when recv is
-// NULL), current radiance B, writes delta [slots][C].
-__global__ void __launch_bounds__(kCenterThreads) k_mc_ne(BvhDev bv, int G, const int64_t *__restrict__ goff,
-                                                          const uint32_t *__restrict__ members,
-                                                          const float *__restrict__ cent,
-                                                          const float *__restrict__ gnrm, const float *__restrict__ Lg,
-                                                          float rmin2, const int32_t *__restrict__ recv,
-                                                          int64_t slots, const float *__restrict__ lambda,
-                                                          const float *__restrict__ rho, const float *__restrict__ E,
-                                                          const float *__restrict__ B, int Lt, int K, uint64_t seed,
-                                                          int step, float *__restrict__ delta, int *err) {
-    extern __shared__ uint32_t stack_mem[];
-    const int64_t s = (int64_t)blockIdx.x * kCenterThreads + threadIdx.x;
+// What the member draws read of a surfel, in the groups' member order:
+// centre and the luminance of its current radiance, normal and index.  Made
+// once a round, so that a draw streams its group's members instead of
+// following three indices to each.
+struct McMember {
+    float4 p, n;
+};
+
+__global__ void __launch_bounds__(256) k_mc_members(BvhDev bv, const uint32_t *__restrict__ members,
+                                                    const float *__restrict__ B, int Lt, int K,
+                                                    McMember *__restrict__ mem) {
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (k >= bv.n) return;
+    const uint32_t j = members[k];
+    const SurfRec r = bv.rec[bv.inv[j]];
+    const float *bj = B + (int64_t)j * Lt * K * 3;
+    float lj = 0.0f;
+    for (int l = 0; l < Lt; ++l) lj += lum3(bj + l * K * 3);
+    mem[k].p = make_float4(r.a.x, r.a.y, r.a.z, lj);
+    mem[k].n = make_float4(r.b.x, r.b.y, r.b.z, __uint_as_float(j));
+}
+
+// Lane N's value in every lane of its row of 16 lanes
+template <int N>
+__device__ __forceinline__ float row_bcast(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + N, 0xf, 0xf, true));
+}
+template <int... I, typename Fn>
+__device__ __forceinline__ void each_lane(std::integer_sequence<int, I...>, float v, Fn &&fn) {
+    (fn(I, row_bcast<I>(v)), ...);
+}
+
+// Inverse CDF of weight(0 .. n) by a row of 16 lanes: `at`, the first w > 0
+// whose running sum exceeds u times the total (else the last w > 0; -1: the
+// total is not positive).  Each lane forms the weight of every 16th entry, and
+// all lanes add them in order, broadcast lane by lane, so the sums are those
+// of one lane that walks the list.  The running sum is kept at 16 points of
+// the list, one per lane, and the pick starts from the last point before it
+// instead of forming all weights again.
+struct RowPick {
+    int64_t at = -1;
+    float w = 0.0f, total = 0.0f;
+};
+
+template <typename Weight>
+__device__ __forceinline__ RowPick row_pick(int64_t n, float u, Weight &&weight) {
+    constexpr auto kRow = std::make_integer_sequence<int, 16>{};
+    const int l = threadIdx.x & 15, row = (int)__lane_id() & 48;
+    auto lane_weight = [&](int64_t k) { return k < n ? weight(k) : 0.0f; };
+    const int64_t part = ((n + 255) / 256) * 16;   // entries between two points
+    RowPick p;
+    float run = 0.0f, mine = 0.0f;   // sum of the positive weights; at the end of part l
+    for (int64_t k0 = 0, end = part; k0 < n; k0 += 16) {
+        each_lane(kRow, lane_weight(k0 + l), [&](int, float x) {
+            p.total += x;
+            run += x <= 0.0f ? 0.0f : x;
+        });
+        if (k0 + 16 == end || k0 + 16 >= n) {
+            if ((end / part - 1) == l) mine = run;
+            end += part;
+        }
+    }
+    if (!(p.total > 0.0f)) return p;
+    const float target = u * p.total;
+    const uint32_t over = (uint32_t)(__ballot(mine > target) >> row) & 0xffffu;
+    const int first = over ? __ffs((int)over) - 1 : 0;
+    const float before = __shfl(mine, row + max(first - 1, 0));
+    float acc = first > 0 ? before : 0.0f;
+    bool found = false;
+    for (int64_t k0 = first * part; k0 < n && !found; k0 += 16) {
+        each_lane(kRow, lane_weight(k0 + l), [&](int i, float x) {
+            if (found || x <= 0.0f) return;
+            acc += x;
+            p.at = k0 + i;
+            p.w = x;
+            found = acc > target;
+        });
+    }
+    return p;
+}
+
+// One draw per slot: receiver recv[slot] (slot itself when recv is NULL) draws
+// a group and a member of it; jsel (-1: none) and its probability.  16 lanes
+// per receiver.  One lane per receiver left most of the chip without work and
+// waited for each member's record in turn: draw and walk 1.65 ms for 50k
+// receivers, now 0.11 and 0.24 ms.
+constexpr int kRowThreads = 256;
+
+__global__ void __launch_bounds__(kRowThreads) k_mc_select(BvhDev bv, int G, const int64_t *__restrict__ goff,
+                                                           const McMember *__restrict__ mem,
+                                                           const float *__restrict__ cent,
+                                                           const float *__restrict__ gnrm,
+                                                           const float *__restrict__ Lg, float rmin2,
+                                                           const int32_t *__restrict__ recv, int64_t slots,
+                                                           uint64_t seed, int step, int32_t *__restrict__ jsel_out,
+                                                           float *__restrict__ pj_out) {
+    const int64_t s = (int64_t)blockIdx.x * (kRowThreads / 16) + threadIdx.x / 16;
     if (s >= slots) return;
     const int64_t a = recv ? (int64_t)recv[s] : s;
-    const int C = Lt * K * 3;
+    const SurfRec ra = bv.rec[bv.inv[a]];
+    uint64_t w[4];
+    philox4x64_10((uint64_t)s, (uint64_t)step, 0ull, 2ull, seed, 0ull, w);
+    const RowPick g = row_pick(G, u01(w[0]), [&](int64_t i) {
+        return group_weight(ra, cent + 3 * i, gnrm + 3 * i, Lg[i], rmin2);
+    });
+    int64_t jsel = -1;
+    float pj = 0.0f;
+    if (g.at >= 0) {
+        const McMember *list = mem + goff[g.at];
+        const RowPick m = row_pick(goff[g.at + 1] - goff[g.at], u01(w[1]), [&](int64_t k) {
+            const McMember r = list[k];
+            if ((int64_t)__float_as_uint(r.n.w) == a) return 0.0f;
+            SurfRec rj;
+            rj.a = r.p;
+            rj.b = r.n;
+            return member_weight(ra, rj, r.p.w);
+        });
+        if (m.at >= 0) {
+            jsel = (int64_t)__float_as_uint(list[m.at].n.w);
+            pj = (g.w / g.total) * (m.w / m.total);
+        }
+    }
+    if ((threadIdx.x & 15) == 0) {
+        jsel_out[s] = (int32_t)jsel;
+        pj_out[s] = pj;
+    }
+}
+
+// Transmittance of a segment by a row of 16 lanes.  The row keeps the walk's
+// stack in LDS, next entry on top: a node to open, a leaf to test, or the
+// factor of a crossing found while nodes before it were still closed.  A
+// round takes the top entries, one per lane, with one load for nodes and
+// leaves alike (both are 64 bytes); what they leave goes back in their order,
+// and the factors that have come to the top are multiplied in.  So T is the
+// product in the order of trace_segment, factor by factor, but the loads that
+// trace_segment waits for one by one are up to 16 at a time, and a wave waits
+// for the longest of four segments, not of 64.  50k segments across a bowl of
+// 50k surfels: 1.0 ms with a lane each (whether 64 or 16 of them share a
+// wave), 0.24 ms with a row each.
+// A tree no higher than trace_segment takes never fills the stack: near its
+// end a round opens one entry only, which needs kStackDeep more of them.
+constexpr int kRowStack = 192;
+
+__device__ __forceinline__ float row_transmittance(const BvhDev &bv, const Segment &g, uint32_t skip_a,
+                                                   uint32_t skip_b, uint64_t *stack, int *err) {
+    constexpr auto kRow = std::make_integer_sequence<int, 16>{};
+    constexpr uint32_t kNode = 0, kLeaf = 1, kFactor = 2;
+    auto entry = [](uint32_t kind, uint32_t v) { return (uint64_t)kind << 32 | v; };
+    auto child = [&](int c) { return c < 0 ? entry(kLeaf, (uint32_t)~c) : entry(kNode, (uint32_t)c); };
+    const int l = threadIdx.x & 15, row = (int)__lane_id() & 48;
+    const float ix = safe_inv(g.dx), iy = safe_inv(g.dy), iz = safe_inv(g.dz);
+    const float t0 = g.t_lo * 0.99999f, t1 = g.t_hi * 1.00001f;
+    float T = 1.0f;
+    if (l == 0) stack[0] = entry(bv.n == 1 ? kLeaf : kNode, 0);
+    int sp = 1;
+    while (sp > 0) {
+        const int m = sp + 16 <= kRowStack - kStackDeep ? min(sp, 16) : 1;
+        if (sp >= kRowStack) {
+            if (l == 0) atomicOr(err, kErrStack);
+            break;
+        }
+        uint64_t e = entry(kFactor, __float_as_uint(1.0f));
+        __builtin_amdgcn_wave_barrier();
+        if (l < m) e = stack[sp - 1 - l];
+        __builtin_amdgcn_wave_barrier();
+        const uint32_t kind = (uint32_t)(e >> 32), v = (uint32_t)e;
+        uint64_t keep0 = 0, keep1 = 0;   // what the entry leaves, keep0 first
+        int keep = 0;
+        float f = 1.0f;
+        if (kind == kFactor) {
+            f = __uint_as_float(v);
+        } else {
+            const float4 *q = kind == kNode ? reinterpret_cast<const float4 *>(bv.nodes + v)
+                                            : reinterpret_cast<const float4 *>(bv.rec + v);
+            const float4 q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
+            if (kind == kNode) {
+                float tn;
+                const bool h0 = slab(q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, g.ox, g.oy, g.oz, ix, iy, iz, t0, t1, tn);
+                const bool h1 = slab(q1.z, q1.w, q2.x, q2.y, q2.z, q2.w, g.ox, g.oy, g.oz, ix, iy, iz, t0, t1, tn);
+                const int c0 = __float_as_int(q3.x), c1 = __float_as_int(q3.y);
+                const bool swap = c0 >= 0 && c1 < 0;   // a node's leaves come before its nodes
+                keep = (h0 ? 1 : 0) + (h1 ? 1 : 0);
+                keep0 = child(h0 && !(h1 && swap) ? c0 : c1);
+                keep1 = child(swap ? c0 : c1);
+            } else {
+                SurfRec r;
+                r.a = q0;
+                r.b = q1;
+                r.c = q2;
+                r.d = q3;
+                const uint32_t j = __float_as_uint(r.d.w);
+                float t, r2;
+                bool front;
+                if (j != skip_a && j != skip_b &&
+                    hit_test(r, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, g.t_lo, g.t_hi, true, t, r2, front))
+                    f = transmit(r.c.w, kernel_gamma(hit_r2_exact(r, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz)));
+            }
+        }
+        // lanes before the row's first node: their factors are next in order
+        const uint32_t nodes = (uint32_t)(__ballot(kind == kNode) >> row) & 0xffffu;
+        const int first = nodes ? __ffs((int)nodes) - 1 : 16;
+        if (kind != kNode && l >= first && __float_as_uint(f) != __float_as_uint(1.0f)) {
+            keep = 1;
+            keep0 = entry(kFactor, __float_as_uint(f));
+        }
+        each_lane(kRow, l < first ? f : 1.0f, [&](int, float x) { T = __fmul_rn(T, x); });
+        const uint32_t k1 = (uint32_t)(__ballot(keep >= 1) >> row) & 0xffffu;
+        const uint32_t k2 = (uint32_t)(__ballot(keep >= 2) >> row) & 0xffffu;
+        int at = sp - m + __popc(k1 >> (l + 1)) + __popc(k2 >> (l + 1));
+        if (keep >= 2) stack[at++] = keep1;
+        if (keep >= 1) stack[at] = keep0;
+        sp += __popc(k1) + __popc(k2) - m;
+    }
+    return T;
+}
+
+// The estimates of the drawn pairs: current radiance B, writes delta
+// [slots][C], 16 lanes per slot.
+__global__ void __launch_bounds__(kRowThreads) k_mc_ne(BvhDev bv, const int32_t *__restrict__ recv, int64_t slots,
+                                                       const int32_t *__restrict__ jsel_in,
+                                                       const float *__restrict__ pj_in,
+                                                       const float *__restrict__ lambda,
+                                                       const float *__restrict__ rho, const float *__restrict__ E,
+                                                       const float *__restrict__ B, int C, float *__restrict__ delta,
+                                                       int *err) {
+    __shared__ uint64_t stack[kRowThreads / 16][kRowStack];
+    const int64_t s = (int64_t)blockIdx.x * (kRowThreads / 16) + threadIdx.x / 16;
+    if (s >= slots) return;
+    const int64_t a = recv ? (int64_t)recv[s] : s;
     const SurfRec ra = bv.rec[bv.inv[a]];
     const float *Ea = E + a * C;
     float *out = delta + s * C;
-    uint64_t w[4];
-    philox4x64_10((uint64_t)s, (uint64_t)step, 0ull, 2ull, seed, 0ull, w);
-    // group: two passes (total, then the inverse CDF)
-    float WG = 0.0f;
-    for (int g = 0; g < G; ++g) WG += group_weight(ra, cent + 3 * g, gnrm + 3 * g, Lg[g], rmin2);
-    int gsel = -1;
-    float wg = 0.0f;
-    if (WG > 0.0f) {
-        const float target = u01(w[0]) * WG;
-        float acc = 0.0f;
-        for (int g = 0; g < G; ++g) {
-            const float x = group_weight(ra, cent + 3 * g, gnrm + 3 * g, Lg[g], rmin2);
-            if (x <= 0.0f) continue;
-            acc += x;
-            gsel = g;
-            wg = x;
-            if (acc > target) break;
-        }
-    }
-    int64_t jsel = -1;
-    float pj = 0.0f;
-    if (gsel >= 0) {
-        const int64_t b = goff[gsel], e = goff[gsel + 1];
-        float Wg = 0.0f;
-        for (int64_t k = b; k < e; ++k) {
-            const uint32_t j = members[k];
-            if ((int64_t)j == a) continue;
-            const SurfRec rj = bv.rec[bv.inv[j]];
-            float lj = 0.0f;
-            for (int l = 0; l < Lt; ++l) lj += lum3(B + (int64_t)j * C + l * K * 3);
-            Wg += member_weight(ra, rj, lj);
-        }
-        if (Wg > 0.0f) {
-            const float target = u01(w[1]) * Wg;
-            float acc = 0.0f, wj = 0.0f;
-            for (int64_t k = b; k < e; ++k) {
-                const uint32_t j = members[k];
-                if ((int64_t)j == a) continue;
-                const SurfRec rj = bv.rec[bv.inv[j]];
-                float lj = 0.0f;
-                for (int l = 0; l < Lt; ++l) lj += lum3(B + (int64_t)j * C + l * K * 3);
-                const float x = member_weight(ra, rj, lj);
-                if (x <= 0.0f) continue;
-                acc += x;
-                jsel = j;
-                wj = x;
-                if (acc > target) break;
-            }
-            pj = (wg / WG) * (wj / Wg);
-        }
-    }
+    const int64_t jsel = jsel_in[s];
+    const float pj = pj_in[s];
     float scale = 0.0f;
     if (jsel >= 0 && pj > 0.0f) {
         const SurfRec rj = bv.rec[bv.inv[jsel]];
         const Segment g = make_segment(ra, rj, bv.bounds[6]);
-        float T = 1.0f;
-        trace_segment<kStackDeep>(bv, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, (uint32_t)a, (uint32_t)jsel, g.t_lo, g.t_hi,
-                      stack_mem + threadIdx.x, kCenterThreads, err, [&](const SurfRec &r, int) {
-                          T = __fmul_rn(T, transmit(r.c.w, kernel_gamma(hit_r2_exact(r, g.ox, g.oy, g.oz, g.dx,
-                                                                                     g.dy, g.dz))));
-                      });
+        const float T = row_transmittance(bv, g, (uint32_t)a, (uint32_t)jsel, stack[threadIdx.x / 16], err);
         const float aa = fabsf(ra.b.x * g.dx + ra.b.y * g.dy + ra.b.z * g.dz);
         const float bb = fabsf(rj.b.x * g.dx + rj.b.y * g.dy + rj.b.z * g.dz);
         const float r2 = g.dx * g.dx + g.dy * g.dy + g.dz * g.dz;
@@ -222,7 +383,7 @@ __global__ void __launch_bounds__(kCenterThreads) k_mc_ne(BvhDev bv, int G, cons
         scale = F / pj;
     }
     const float *Bj = jsel >= 0 ? B + jsel * C : nullptr;
-    for (int c = 0; c < C; ++c) {
+    for (int c = threadIdx.x & 15; c < C; c += 16) {
         const float add = Bj ? rho[3 * a + c % 3] * scale * Bj[c] : 0.0f;
         out[c] = Ea[c] + add;
     }
@@ -237,44 +398,30 @@ __global__ void __launch_bounds__(256) k_mc_mean(const float *__restrict__ S, co
     B[t] = d ? S[t] / (float)d : 0.0f;
 }
 
-// receiver a adds its slots' estimates (slots sorted by receiver; NULL recv:
-// slot a is receiver a) in slot order
+// Receivers add their slots' estimates in slot order (slots sorted by
+// receiver; NULL recv: slot a is receiver a).  The first slot of a receiver
+// adds them all, so that no receiver looks for its slots: by binary search
+// 50 us for 50k slots, now 35 us.
 __global__ void __launch_bounds__(256) k_mc_accum(const int32_t *__restrict__ recv, int64_t slots,
-                                                  const float *__restrict__ delta, int64_t n, int C,
-                                                  float *__restrict__ S, float *__restrict__ S2,
-                                                  uint32_t *__restrict__ D) {
-    const int64_t a = (int64_t)blockIdx.x * 4 + threadIdx.x / 64;
-    if (a >= n) return;
-    const int lane = __lane_id();
-    int64_t lo = a, hi = a + 1;
-    if (recv) {
-        int64_t l = 0, h = slots;
-        while (l < h) {
-            const int64_t m = (l + h) >> 1;
-            if (recv[m] < a) l = m + 1;
-            else h = m;
-        }
-        lo = l;
-        h = slots;
-        while (l < h) {
-            const int64_t m = (l + h) >> 1;
-            if (recv[m] <= a) l = m + 1;
-            else h = m;
-        }
-        hi = l;
-    }
-    if (hi <= lo) return;
-    for (int c = lane; c < C; c += 64) {
-        float s = S[a * C + c], s2 = S2[a * C + c];
-        for (int64_t k = lo; k < hi; ++k) {
-            const float d = delta[k * C + c];
-            s += d;
-            s2 = __builtin_fmaf(d, d, s2);
-        }
-        S[a * C + c] = s;
-        S2[a * C + c] = s2;
-    }
-    if (lane == 0) D[a] += (uint32_t)(hi - lo);
+                                                  const float *__restrict__ delta, int C, float *__restrict__ S,
+                                                  float *__restrict__ S2, uint32_t *__restrict__ D) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t first = t / C;
+    const int c = (int)(t % C);
+    if (first >= slots) return;
+    const int64_t a = recv ? (int64_t)recv[first] : first;
+    if (recv && first > 0 && recv[first - 1] == a) return;
+    float s = S[a * C + c], s2 = S2[a * C + c];
+    int64_t k = first;
+    do {
+        const float d = delta[k * C + c];
+        s += d;
+        s2 = __builtin_fmaf(d, d, s2);
+        ++k;
+    } while (recv && k < slots && recv[k] == a);
+    S[a * C + c] = s;
+    S2[a * C + c] = s2;
+    if (c == 0) D[a] += (uint32_t)(k - first);
 }
 
 // per-receiver variance of the estimates, summed over the columns, and its
@@ -331,6 +478,8 @@ __global__ void __launch_bounds__(256) k_mc_draw(const int64_t *__restrict__ cdf
 }  // namespace
 
 // --- Monte-Carlo solver host side ---------------------------------------
+size_t mc_member_bytes(int64_t n) { return (size_t)n * sizeof(McMember); }
+
 gsrad_status mc_kmeans(const BvhDev &bv, int G, int iters, McBuffers &mb, hipStream_t st) {
     const int64_t n = bv.n;
     const unsigned gn = (unsigned)((n + 255) / 256);
@@ -357,9 +506,12 @@ gsrad_status mc_step(const BvhDev &bv, const McBuffers &mb, int G, float rmin2, 
     const int64_t n = bv.n;
     hipLaunchKernelGGL(k_mc_lum, dim3((unsigned)((G + 3) / 4)), dim3(256), 0, st, G, mb.goff, mb.members, B, Lt, K,
                        mb.L);
-    hipLaunchKernelGGL(k_mc_ne, dim3((unsigned)((n + kCenterThreads - 1) / kCenterThreads)), dim3(kCenterThreads),
-                       walk_bytes(kStackDeep), st, bv, G, mb.goff, mb.members, mb.cent,
-                       mb.gnrm, mb.L, rmin2, recv, n, lambda, rho, E, B, Lt, K, seed, step, delta, err);
+    McMember *mem = static_cast<McMember *>(mb.mem);
+    hipLaunchKernelGGL(k_mc_members, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, bv, mb.members, B, Lt, K, mem);
+    hipLaunchKernelGGL(k_mc_select, dim3((unsigned)((n + kRowThreads / 16 - 1) / (kRowThreads / 16))), dim3(kRowThreads),
+                       0, st, bv, G, mb.goff, mem, mb.cent, mb.gnrm, mb.L, rmin2, recv, n, seed, step, mb.jsel, mb.pj);
+    hipLaunchKernelGGL(k_mc_ne, dim3((unsigned)((n + kRowThreads / 16 - 1) / (kRowThreads / 16))), dim3(kRowThreads), 0,
+                       st, bv, recv, n, mb.jsel, mb.pj, lambda, rho, E, B, Lt * K * 3, delta, err);
     return check_hip(hipGetLastError(), "next event launch");
 }
 
@@ -387,8 +539,7 @@ gsrad_status mc_solve(const BvhDev &bv, const McBuffers &mb, int G, float rmin2,
         }
         if ((e = mc_step(bv, mb, G, rmin2, lambda, rho, E, mb.B, Lt, K, seed, t, recv, mb.delta, err, st)) != GSRAD_OK)
             return e;
-        hipLaunchKernelGGL(k_mc_accum, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, recv, n, mb.delta, n, C,
-                           mb.S, mb.S2, mb.D);
+        hipLaunchKernelGGL(k_mc_accum, dim3(gv), dim3(256), 0, st, recv, n, mb.delta, C, mb.S, mb.S2, mb.D);
     }
     hipLaunchKernelGGL(k_mc_mean, dim3(gv), dim3(256), 0, st, mb.S, mb.D, n, C, B_out);
     return check_hip(hipGetLastError(), "mc solve launch");

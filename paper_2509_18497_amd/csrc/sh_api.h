@@ -63,7 +63,11 @@ struct McBuffers {
     uint32_t *D = nullptr, *q = nullptr, *maxbits = nullptr;
     int32_t *recv = nullptr;
     int64_t *cdf = nullptr;                                   // [n + 1]
+    void *mem = nullptr;                                      // [n] member records (mc_member_bytes)
+    int32_t *jsel = nullptr;                                  // [n] drawn senders and their probabilities
+    float *pj = nullptr;
 };
+size_t mc_member_bytes(int64_t n);
 gsrad_status mc_kmeans(const BvhDev &bv, int G, int iters, McBuffers &mb, hipStream_t st);
 gsrad_status mc_step(const BvhDev &bv, const McBuffers &mb, int G, float rmin2, const float *lambda, const float *rho,
                      const float *E, const float *B, int Lt, int K, uint64_t seed, int step, const int32_t *recv,

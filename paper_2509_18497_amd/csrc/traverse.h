@@ -30,9 +30,8 @@ constexpr uint32_t kEmpty = 0xffffffffu;
 // a CU to ten waves (10 M segments of a 20k-surfel bowl: F 29.6 ms, with a
 // head of 20 24.2 ms; their gradients 183 and 156 ms).  A launch that does
 // not reach ten waves a CU (kWalkFill lanes) walks faster without the choice
-// of memory and takes HEAD = 64 (16 Monte-Carlo rounds of 50k receivers, three
-// waves a CU: 27.7 ms, with a head of 20 29.6 ms; the direct light of 512
-// surfels 49 and 60 us).
+// of memory and takes HEAD = 64 (the direct light of 512 surfels 49 us, with
+// a head of 20 60 us).
 constexpr int kWalkHead = 20;
 constexpr int64_t kWalkFill = (int64_t)256 * 10 * 64;
 

@@ -93,3 +93,57 @@ def test_walks_below_the_stack_in_lds(g, orc):
     F = g.ff_center(bvh, P, dev(lam)).csr()[2].cpu().numpy()
     Fo, _ = center.center_ff(sur, rows, cols.astype(np.int32), lam.astype(np.float64), t_eps=orc.default_t_eps(sur))
     assert rel_err(F[~same], Fo[~same]) < TOL
+
+
+@pytest.mark.parametrize("n", [9, 16, 17, 256, 257, 530])
+def test_monte_carlo_draws_pick_by_the_running_sum(g, n):
+    """One group of n members: each receiver's draw is known from the counter
+    generator and the FP64 running sum of the member weights, and its estimate
+    from the oracle's centre form factor.  Lists end inside a row of 16 lanes
+    and at its edge, and are longer than 16 rows.  Tolerances: an FP32 running
+    sum of n terms is off by at most n 2^-24 of the total and its terms by some
+    20 roundings, so draws closer than (n + 50) 2^-23 to a step of the sum are
+    left out; an estimate has in addition the transmittance's product of at
+    most 200 factors, and cosines n . v that lose digits as they near 0."""
+    from oracle import center
+    from oracle import oracle as orc
+    sc = scenes.make_config("box_room", n=n)
+    sur, n = sc.surfels, sc.n
+    bvh = g.build_bvh(dev_surfels(sur))
+    mc = g.mc_create(bvh, groups=1, kmeans_iters=1)
+    lam = scenes.seeded_array((n,), seed=5, lo=0.5, hi=1.5).astype(np.float32)
+    rho = orc.rho(sur["opacity"], sc.albedo).astype(np.float32)
+    E = orc.direct_light(sur, sc.albedo, sc.light_pos, sc.light_I, 1).astype(np.float32)
+    B = (E + 0.05 * scenes.seeded_array(E.shape, seed=3, lo=0.5, hi=1.5)).astype(np.float32)
+    seed, step = 77, 3
+    got = g.mc_estimate(mc, dev(lam), dev(rho), dev(E), dev(B), seed=seed, step=step).cpu().numpy()
+
+    p = np.stack([sur[k] for k in ("px", "py", "pz")], 1).astype(np.float64)
+    nrm = np.stack([sur[k] for k in ("nx", "ny", "nz")], 1).astype(np.float64)
+    lum = np.maximum(B.astype(np.float64) @ [0.2126, 0.7152, 0.0722], 0).sum((1, 2))
+    v = p[None] - p[:, None]
+    r2 = (v ** 2).sum(2)
+    np.fill_diagonal(r2, 1.0)
+    ca, cj = np.abs((nrm[:, None] * v).sum(2)), np.abs((nrm[None] * v).sum(2))
+    w = lum[None] * ca * cj / r2 ** 2
+    np.fill_diagonal(w, 0.0)
+    u = np.empty(n)
+    for a in range(n):
+        counter = (a | step << 64 | 2 << 192) - 1
+        word = np.random.Philox(key=seed, counter=counter).random_raw(2)[1]
+        u[a] = (int(word) >> 40) * 2.0 ** -24
+    cdf = np.cumsum(w, 1)
+    total = cdf[:, -1]
+    pick = (cdf <= (u * total)[:, None]).sum(1)
+    pick = np.minimum(pick, n - 1)
+    gap = np.abs(cdf - (u * total)[:, None]).min(1) / total
+    sure = (gap > (n + 50) * 2.0 ** -23) & (u > (n + 50) * 2.0 ** -23)
+    assert sure.mean() > 0.9
+    rows = np.arange(n)
+    F, _ = center.center_ff(sur, rows, pick.astype(np.int32), lam)
+    pj = w[rows, pick] / total
+    want = E + (rho[:, None, None, :] * (F / pj)[:, None, None, None] * B[pick])
+    lost = 8 * np.sqrt(r2[rows, pick]) * (1 / ca[rows, pick] + 1 / cj[rows, pick])
+    tol = (n + 250 + lost[:, None, None, None]) * 2.0 ** -23 * np.abs(want - E) + 2.0 ** -23 * np.abs(want)
+    bad = np.abs(got - want) > tol
+    assert not bad[sure].any(), (np.abs(got - want) / np.abs(want))[sure].max()
