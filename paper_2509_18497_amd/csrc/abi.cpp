@@ -1391,7 +1391,7 @@ gsrad_status gsrad_ff_center_backward(const gsrad_bvh *bvh, const gsrad_ff *ff, 
     hipStream_t st = S(stream);
     gsrad_ff *f = const_cast<gsrad_ff *>(ff);
     const size_t bytes = center_acc_bytes(ff->n);
-    GS_TRY(f->cacc.ensure(bytes, "centre-to-centre gradient accumulators"));
+    GS_TRY(f->cacc.ensure(bytes + center_list_bytes(ff->n), "centre-to-centre gradient accumulators"));
     GS_TRY(check_hip(hipMemsetAsync(f->cacc.p, 0, bytes, st), "accumulators zero"));
     GS_TRY(f->err.ensure(128, "flags"));
     CenterOutputs out;

@@ -1,10 +1,11 @@
 // Gradient kernels through the centre-to-centre form factors (Sec. 8), the
 // ray-cast form factors' geometry (recorded hits) and the direct light.
 //
-// k_ff_center       one wave per row of a pattern: the centre-to-centre F
-//                   with the learnable decay scale lambda.
-// k_center_bwd      its gradient with respect to lambda and every surfel
-//                   field on each segment (endpoints and occluders).
+// k_ff_center       one workgroup per row of a pattern: the centre-to-centre
+//                   F with the learnable decay scale lambda.
+// k_center_rows     its gradient with respect to lambda and every surfel
+//                   field on each segment (endpoints and occluders);
+//                   k_center_bwd what does not fit its lists.
 // k_geometry_rec    dL/dF through the recorded hits to centres, frames,
 //                   scales and opacities.
 // k_direct_bwd      the direct light's gradient: lights, albedo, receivers
@@ -12,6 +13,7 @@
 // All sums are 64-bit fixed point with per-field scales (bit-identical
 // between runs), one copy per XCD.
 #include <algorithm>
+#include <cstring>
 #include <functional>
 
 #include "gsrad_internal.h"
@@ -27,35 +29,30 @@ namespace {
 // centre-to-centre form factors (Sec. 8) and their gradients
 // ---------------------------------------------------------------------------
 // F_ij = lambda_j A_j T_ij |n_i . v| |n_j . v| / (pi |v|^4) per stored entry
-// of the pattern (v = p_j - p_i); one wave per row, lanes over entries.
-__global__ void __launch_bounds__(kCenterThreads) k_ff_center(BvhDev bv, const int64_t *__restrict__ row_ptr,
-                                                              const int32_t *__restrict__ col, int64_t n,
-                                                              const float *__restrict__ lambda,
-                                                              float *__restrict__ val, int64_t nblocks,
-                                                              const int32_t *__restrict__ order, int *err) {
-    extern __shared__ uint32_t stack_mem[];
-    const int64_t idx = xcd_block(blockIdx.x, nblocks) * (kCenterThreads / 64) + threadIdx.x / 64;
-    if (idx >= n) return;
+// of the pattern (v = p_j - p_i); one workgroup per row, 16 lanes per entry.
+// Bound by the walks' nodes and leaves (200 and 96 a segment on a 20k-surfel
+// bowl): 10 M segments in 19.4 ms, with a segment a lane 24.2 ms.
+__global__ void __launch_bounds__(kRowThreads) k_ff_center(BvhDev bv, const int64_t *__restrict__ row_ptr,
+                                                           const int32_t *__restrict__ col, int64_t n,
+                                                           const float *__restrict__ lambda,
+                                                           float *__restrict__ val, int64_t nblocks,
+                                                           const int32_t *__restrict__ order, int *err) {
+    __shared__ uint64_t stack[kRowThreads / 16][kRowStack];
+    const int64_t idx = xcd_block(blockIdx.x, nblocks);
     const int64_t row = order ? (int64_t)order[idx] : idx;
-    const int lane = __lane_id();
     const SurfRec ri = bv.rec[bv.inv[row]];
     const int64_t b = row_ptr[row], e = row_ptr[row + 1];
     const float t_eps = bv.bounds[6];
-    for (int64_t kk = b + lane; kk < e; kk += 64) {
+    for (int64_t kk = b + threadIdx.x / 16; kk < e; kk += kRowThreads / 16) {
         const int32_t j = col[kk];
         const SurfRec rj = bv.rec[bv.inv[j]];
         const Segment g = make_segment(ri, rj, t_eps);
-        float T = 1.0f;
-        trace_segment<kWalkHead>(bv, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, (uint32_t)row, (uint32_t)j, g.t_lo, g.t_hi,
-                      stack_mem + threadIdx.x, kCenterThreads, err, [&](const SurfRec &r, int) {
-                          T = __fmul_rn(T, transmit(r.c.w, kernel_gamma(hit_r2_exact(r, g.ox, g.oy, g.oz, g.dx,
-                                                                                     g.dy, g.dz))));
-                      });
+        const float T = row_segment<false>(bv, g, (uint32_t)row, (uint32_t)j, stack[threadIdx.x / 16], err, [](int) {});
         const float a = ri.b.x * g.dx + ri.b.y * g.dy + ri.b.z * g.dz;
         const float bb = rj.b.x * g.dx + rj.b.y * g.dy + rj.b.z * g.dz;
         const float r2 = g.dx * g.dx + g.dy * g.dy + g.dz * g.dz;
         const float phi = (fabsf(a) * fabsf(bb)) / (r2 * r2);
-        val[kk] = lambda[j] * (float)bv.area[j] * T * phi * kInvPi;
+        if ((threadIdx.x & 15) == 0) val[kk] = lambda[j] * (float)bv.area[j] * T * phi * kInvPi;
     }
 }
 
@@ -206,6 +203,115 @@ struct SharedSurfelAcc {
     }
 };
 
+// Crossings' sums of a workgroup in LDS: open addressing on the surfel, ten
+// 64-bit fixed-point sums each (fields kFdu ... kFdu + 8 and kFo); a surfel
+// that finds no place within kProbes adds to the global sums.
+template <int SLOTS>
+struct CrossTable {
+    static constexpr int kProbes = 8, kSums = 10;
+    uint32_t key[SLOTS];
+    unsigned long long sum[kSums][SLOTS];
+    static __device__ __forceinline__ int field(int q) { return q < 9 ? kFdu + q : kFo; }
+    __device__ __forceinline__ void clear(int tid, int threads) {
+        for (int z = tid; z < SLOTS; z += threads) {
+            key[z] = kEmpty;
+#pragma unroll
+            for (int q = 0; q < kSums; ++q) sum[q][z] = 0;
+        }
+    }
+    template <typename Sink>
+    __device__ __forceinline__ void add(Sink &sink, uint32_t k, const float (&x)[kSums]) {
+        const uint32_t h = (k * 0x9e3779b1u) >> 16;
+        int at = -1;
+        for (int p = 0; p < kProbes && at < 0; ++p) {
+            const int z = (int)((h + (uint32_t)p) & (uint32_t)(SLOTS - 1));
+            uint32_t old = key[z];
+            if (old == kEmpty) old = atomicCAS(&key[z], kEmpty, k);
+            if (old == kEmpty || old == k) at = z;
+        }
+#pragma unroll
+        for (int q = 0; q < kSums; ++q) {
+            const long long v = sink.scaled(field(q), x[q]);
+            if (v == 0) continue;
+            if (at >= 0) atomicAdd(&sum[q][at], (unsigned long long)v);
+            else sink.add_scaled(field(q), k, v);
+        }
+    }
+    template <typename Sink>
+    __device__ __forceinline__ void flush(Sink &sink, int tid, int threads) {
+        for (int z = tid; z < SLOTS; z += threads) {
+            const uint32_t k = key[z];
+            if (k == kEmpty) continue;
+#pragma unroll
+            for (int q = 0; q < kSums; ++q)
+                if (sum[q][z] != 0) sink.add_scaled(field(q), k, (long long)sum[q][z]);
+        }
+    }
+};
+
+// One crossing of a segment o + t d with weight W: the crossed surfel's ten
+// sums x, and the shares ge and gs of the segment's end and start.
+__device__ __forceinline__ void crossing(const BvhDev &bv, const SurfRec &r, float ox, float oy, float oz,
+                                         float dx, float dy, float dz, float W, float (&x)[10], float (&ge)[3],
+                                               float (&gs)[3]) {
+    const float ok = bv.raw_op[__float_as_uint(r.d.w)];
+    const float gam = kernel_gamma(hit_r2_exact(r, ox, oy, oz, dx, dy, dz));
+    const float qx = r.a.x - ox, qy = r.a.y - oy, qz = r.a.z - oz;
+    const float den = dx * r.b.x + dy * r.b.y + dz * r.b.z;
+    const float tk = (qx * r.b.x + qy * r.b.y + qz * r.b.z) / den;
+    const float hx = tk * dx - qx, hy = tk * dy - qy, hz = tk * dz - qz;
+    const float u = (hx * r.c.x + hy * r.c.y + hz * r.c.z) * r.a.w;
+    const float w = (hx * r.d.x + hy * r.d.y + hz * r.d.z) * r.b.w;
+    const float f = W * 3.4f * r.c.w * gam;
+    const float fu = f * u * r.a.w, fw = f * w * r.b.w;
+    const float ghx = fu * r.c.x + fw * r.d.x, ghy = fu * r.c.y + fw * r.d.y, ghz = fu * r.c.z + fw * r.d.z;
+    const float beta = (ghx * dx + ghy * dy + ghz * dz) / den;
+    const float gqx = beta * r.b.x - ghx, gqy = beta * r.b.y - ghy, gqz = beta * r.b.z - ghz;
+    cross_terms(r, fu, fw, beta, hx, hy, hz, x);
+    x[9] = ok > 0.0f && ok < kOpacityMax ? -W * gam / (1.0f - ok) : 0.0f;
+    ge[0] = -tk * gqx;
+    ge[1] = -tk * gqy;
+    ge[2] = -tk * gqz;
+    gs[0] = -(1.0f - tk) * gqx;
+    gs[1] = -(1.0f - tk) * gqy;
+    gs[2] = -(1.0f - tk) * gqz;
+}
+
+// The pair's own terms of a centre-to-centre segment: Phi = |a| |b| / r^4,
+// kappa = lambda_j A_j / pi; the shares of p_j (-: of p_i), n_i and n_j and
+// the term of the chain through lambda_j A_j.
+struct PairTerm {
+    float dp[3], ni[3], nj[3], chain;
+    __device__ __forceinline__ PairTerm(const SurfRec &ri, const SurfRec &rj, const Segment &g, float G, float lambda_j,
+                                        float A, float T) {
+        const float a = ri.b.x * g.dx + ri.b.y * g.dy + ri.b.z * g.dz;
+        const float bb = rj.b.x * g.dx + rj.b.y * g.dy + rj.b.z * g.dz;
+        const float r2 = g.dx * g.dx + g.dy * g.dy + g.dz * g.dz;
+        const float r4 = r2 * r2;
+        const float aa = fabsf(a), ab = fabsf(bb);
+        const float sa = a > 0.0f ? 1.0f : (a < 0.0f ? -1.0f : 0.0f);
+        const float sb = bb > 0.0f ? 1.0f : (bb < 0.0f ? -1.0f : 0.0f);
+        const float kT = G * lambda_j * A * T * kInvPi;
+        const float c1 = kT * sa * ab / r4, c2 = kT * aa * sb / r4, c3 = 4.0f * kT * aa * ab / (r4 * r2);
+        dp[0] = c1 * ri.b.x + c2 * rj.b.x - c3 * g.dx;
+        dp[1] = c1 * ri.b.y + c2 * rj.b.y - c3 * g.dy;
+        dp[2] = c1 * ri.b.z + c2 * rj.b.z - c3 * g.dz;
+        ni[0] = c1 * g.dx;
+        ni[1] = c1 * g.dy;
+        ni[2] = c1 * g.dz;
+        nj[0] = c2 * g.dx;
+        nj[1] = c2 * g.dy;
+        nj[2] = c2 * g.dz;
+        chain = G * T * (aa * ab / r4) * kInvPi;
+    }
+};
+
+// Crossings of the accumulating pass (64 bits), words after maxbits
+constexpr int kCrossings = 3 * kFields + 3;
+static_assert(kCrossings % 2 == 0, "aligned");
+
+// What k_center_rows left of its rows (each from entry done[row]), a segment a
+// lane.
 template <int PASS>
 __global__ void __launch_bounds__(kCenterThreads) k_center_bwd(BvhDev bv, const int64_t *__restrict__ row_ptr,
                                                                const int32_t *__restrict__ col,
@@ -214,89 +320,230 @@ __global__ void __launch_bounds__(kCenterThreads) k_center_bwd(BvhDev bv, const 
                                                                const float *__restrict__ gF, uint32_t *maxbits,
                                                                const int *fx, unsigned long long *acc,
                                                                int64_t nblocks, const int32_t *__restrict__ order,
-                                                               int stride, int *err) {
+                                                               int stride, const int32_t *__restrict__ done,
+                                                               int *err) {
     extern __shared__ uint32_t stack_mem[];
     const int64_t idx = (xcd_block(blockIdx.x, nblocks) * (kCenterThreads / 64) + threadIdx.x / 64) * stride;
+    if (idx >= n) return;
+    const int64_t row = order ? (int64_t)order[idx] : idx;
+    const int64_t b = row_ptr[row] + (int64_t)done[row], e = row_ptr[row + 1];
+    if (b >= e) return;
     FieldSink<PASS> sink;
     sink.init(acc, fx, n);
-    const float t_eps = bv.bounds[6];
     SharedSurfelAcc<6> accI;   // the row's receiver: p and n
     accI.zero();
-    uint32_t i = 0;
-    if (idx < n) {
+    const uint32_t i = (uint32_t)row;
+    unsigned long long hits = 0;
+    const SurfRec ri = bv.rec[bv.inv[row]];
+    for (int64_t kk = b + __lane_id(); kk < e; kk += 64) {
+        const float G = gF[kk];
+        if (G == 0.0f) continue;
+        const uint32_t j = (uint32_t)col[kk];
+        const SurfRec rj = bv.rec[bv.inv[j]];
+        const Segment g = make_segment(ri, rj, bv.bounds[6]);
+        const float W = G * fval[kk];
+        float T = 1.0f;
+        float gpi[3] = {0.0f, 0.0f, 0.0f}, gpj[3] = {0.0f, 0.0f, 0.0f};
+        trace_segment<kWalkHead>(bv, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, i, j, g.t_lo, g.t_hi, stack_mem + threadIdx.x,
+                                 kCenterThreads, err, [&](const SurfRec &r, int) {
+                                     T = __fmul_rn(T, transmit(r.c.w, kernel_gamma(hit_r2_exact(r, g.ox, g.oy, g.oz,
+                                                                                                g.dx, g.dy, g.dz))));
+                                     float x[10], ge[3], gs[3];
+                                     crossing(bv, r, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, W, x, ge, gs);
+#pragma unroll
+                                     for (int q = 0; q < 10; ++q)
+                                         sink.add(CrossTable<1>::field(q), __float_as_uint(r.d.w), x[q]);
+                                     // (pass 0: each share alone, as k_center_rows)
+#pragma unroll
+                                     for (int c = 0; c < 3; ++c) {
+                                         gpi[c] = PASS == 0 ? fmaxf(gpi[c], fabsf(gs[c])) : gpi[c] + gs[c];
+                                         gpj[c] = PASS == 0 ? fmaxf(gpj[c], fabsf(ge[c])) : gpj[c] + ge[c];
+                                     }
+                                     ++hits;
+                                 });
+        const PairTerm t(ri, rj, g, G, lambda[j], (float)bv.area[j], T);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            if (PASS == 0) {
+                sink.add(kFp + c, j, fmaxf(fabsf(t.dp[c]), fmaxf(gpi[c], gpj[c])));
+            } else {
+                sink.add(kFp + c, j, t.dp[c] + gpj[c]);
+                accI.add<PASS>(sink, c, kFp + c, gpi[c] - t.dp[c]);
+            }
+            accI.add<PASS>(sink, 3 + c, kFn + c, t.ni[c]);
+            sink.add(kFn + c, j, t.nj[c]);
+        }
+        sink.add(kFpair, j, t.chain);
+    }
+    const int fI[6] = {kFp, kFp + 1, kFp + 2, kFn, kFn + 1, kFn + 2};
+    accI.flush<PASS>(sink.acc, n, i, fI);
+    sink.report(maxbits);
+    if (PASS == 1) {
+        for (int off = 32; off > 0; off >>= 1) hits += __shfl_xor(hits, off, 64);
+        if (__lane_id() == 0) atomicAdd(reinterpret_cast<unsigned long long *>(maxbits + kCrossings), hits);
+    }
+}
+
+// A workgroup takes a row, kRowSegs entries of it at a
+// time.  Rows of 16 lanes walk the segments and list their crossings (the
+// segment and the surfel's sorted position) in kRowParts parts by a hash of
+// the surfel; then part after part is dealt evenly to the lanes and summed in
+// a table in LDS.  A row of 512 entries crosses some 1,900 surfels 17,000
+// times, so ten sums per surfel and row go to memory instead of ten per
+// crossing.  Bound by the walks (19 of 29 ms for 10 M segments of a 20k-surfel
+// bowl, as long as k_ff_center), then by the LDS atomics.  A segment a lane
+// and ten global atomics a crossing took 108 ms.
+// The lists lie in the workgroup's own stretch of the workspace; a row that
+// crosses more surfels than fit is left to k_center_bwd from there (done[row],
+// zeroed before).
+constexpr int kCenterRowThreads = 512, kRowSegs = 512, kRowParts = 5, kRowSlots = 512;
+constexpr int kRowPart = 13312;        // list places of a part
+constexpr int64_t kCenterGroups = 512;   // workgroups, two a CU
+
+struct RowShared {
+    union {
+        uint64_t stack[kCenterRowThreads / 16][kRowStack];
+        CrossTable<kRowSlots> table;
+    };
+    float d[3][kRowSegs], W[kRowSegs], T[kRowSegs];
+    unsigned long long end[3][kRowSegs];   // shares of the segments' ends, fixed point
+    uint32_t count[kRowParts];
+};
+
+template <int PASS>
+__global__ void __launch_bounds__(kCenterRowThreads, 4) k_center_rows(BvhDev bv, const int64_t *__restrict__ row_ptr,
+                                                                   const int32_t *__restrict__ col,
+                                                                   const float *__restrict__ fval, int64_t n,
+                                                                   const float *__restrict__ lambda,
+                                                                   const float *__restrict__ gF, uint32_t *maxbits,
+                                                                   const int *fx, unsigned long long *acc,
+                                                                   const int32_t *__restrict__ order, int stride,
+                                                                   uint2 *__restrict__ lists,
+                                                                   int32_t *__restrict__ done, int *err) {
+    extern __shared__ __align__(16) char row_mem[];
+    RowShared &sh = *reinterpret_cast<RowShared *>(row_mem);
+    const int tid = threadIdx.x;
+    uint2 *list = lists + (int64_t)blockIdx.x * kRowParts * kRowPart;
+    FieldSink<PASS> sink;
+    sink.init(acc, fx, n);
+    unsigned long long hits = 0;
+    for (int64_t idx = (int64_t)blockIdx.x * stride; idx < n; idx += (int64_t)gridDim.x * stride) {
         const int64_t row = order ? (int64_t)order[idx] : idx;
-        i = (uint32_t)row;
         const SurfRec ri = bv.rec[bv.inv[row]];
         const int64_t b = row_ptr[row], e = row_ptr[row + 1];
-        for (int64_t kk = b + __lane_id(); kk < e; kk += 64) {
-            const float G = gF[kk];
-            if (G == 0.0f) continue;
-            const uint32_t j = (uint32_t)col[kk];
-            const SurfRec rj = bv.rec[bv.inv[j]];
-            const Segment g = make_segment(ri, rj, t_eps);
-            const float W = G * fval[kk];
-            float T = 1.0f;
-            float gpi[3] = {0.0f, 0.0f, 0.0f}, gpj[3] = {0.0f, 0.0f, 0.0f};
-            trace_segment<kWalkHead>(bv, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, i, j, g.t_lo, g.t_hi, stack_mem + threadIdx.x,
-                          kCenterThreads, err, [&](const SurfRec &r, int) {
-                              // exact kernel value for T, FP32 geometry for the derivatives
-                              const float gam = kernel_gamma(hit_r2_exact(r, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz));
-                              T = __fmul_rn(T, transmit(r.c.w, gam));
-                              const uint32_t k = __float_as_uint(r.d.w);
-                              const float qx = r.a.x - g.ox, qy = r.a.y - g.oy, qz = r.a.z - g.oz;
-                              const float den = g.dx * r.b.x + g.dy * r.b.y + g.dz * r.b.z;
-                              const float tk = (qx * r.b.x + qy * r.b.y + qz * r.b.z) / den;
-                              const float hx = tk * g.dx - qx, hy = tk * g.dy - qy, hz = tk * g.dz - qz;
-                              const float u = (hx * r.c.x + hy * r.c.y + hz * r.c.z) * r.a.w;
-                              const float w = (hx * r.d.x + hy * r.d.y + hz * r.d.z) * r.b.w;
-                              const float f = W * 3.4f * r.c.w * gam;
-                              const float fu = f * u * r.a.w, fw = f * w * r.b.w;
-                              const float ghx = fu * r.c.x + fw * r.d.x, ghy = fu * r.c.y + fw * r.d.y,
-                                          ghz = fu * r.c.z + fw * r.d.z;
-                              const float beta = (ghx * g.dx + ghy * g.dy + ghz * g.dz) / den;
-                              const float gqx = beta * r.b.x - ghx, gqy = beta * r.b.y - ghy,
-                                          gqz = beta * r.b.z - ghz;
-                              sink.cross(k, r, fu, fw, beta, hx, hy, hz);
-                              const float ok = bv.raw_op[k];
-                              if (ok > 0.0f && ok < kOpacityMax) sink.add(kFo, k, -W * gam / (1.0f - ok));
-                              gpi[0] -= (1.0f - tk) * gqx;
-                              gpi[1] -= (1.0f - tk) * gqy;
-                              gpi[2] -= (1.0f - tk) * gqz;
-                              gpj[0] -= tk * gqx;
-                              gpj[1] -= tk * gqy;
-                              gpj[2] -= tk * gqz;
-                          });
-            // the pair's own terms: Phi = |a| |b| / r^4, kappa = lambda_j A_j / pi
-            const float a = ri.b.x * g.dx + ri.b.y * g.dy + ri.b.z * g.dz;
-            const float bb = rj.b.x * g.dx + rj.b.y * g.dy + rj.b.z * g.dz;
-            const float r2 = g.dx * g.dx + g.dy * g.dy + g.dz * g.dz;
-            const float r4 = r2 * r2;
-            const float aa = fabsf(a), ab = fabsf(bb);
-            const float sa = a > 0.0f ? 1.0f : (a < 0.0f ? -1.0f : 0.0f);
-            const float sb = bb > 0.0f ? 1.0f : (bb < 0.0f ? -1.0f : 0.0f);
-            const float A = (float)bv.area[j];
-            const float kT = G * lambda[j] * A * T * kInvPi;
-            const float c1 = kT * sa * ab / r4, c2 = kT * aa * sb / r4, c3 = 4.0f * kT * aa * ab / (r4 * r2);
-            const float dpx = c1 * ri.b.x + c2 * rj.b.x - c3 * g.dx;
-            const float dpy = c1 * ri.b.y + c2 * rj.b.y - c3 * g.dy;
-            const float dpz = c1 * ri.b.z + c2 * rj.b.z - c3 * g.dz;
-            sink.add3(kFp, j, dpx + gpj[0], dpy + gpj[1], dpz + gpj[2]);
-            accI.add<PASS>(sink, 0, kFp, gpi[0] - dpx);
-            accI.add<PASS>(sink, 1, kFp + 1, gpi[1] - dpy);
-            accI.add<PASS>(sink, 2, kFp + 2, gpi[2] - dpz);
-            accI.add<PASS>(sink, 3, kFn, c1 * g.dx);
-            accI.add<PASS>(sink, 4, kFn + 1, c1 * g.dy);
-            accI.add<PASS>(sink, 5, kFn + 2, c1 * g.dz);
-            sink.add3(kFn, j, c2 * g.dx, c2 * g.dy, c2 * g.dz);
-            sink.add(kFpair, j, G * T * (aa * ab / r4) * kInvPi);
+        SharedSurfelAcc<6> accI;   // the row's receiver: p and n
+        accI.zero();
+        int64_t k0 = b;
+        for (; k0 < e; k0 += kRowSegs) {
+            const int segs = (int)min<int64_t>(kRowSegs, e - k0);
+            if (tid < kRowParts) sh.count[tid] = 0;
+            __syncthreads();
+            for (int q = tid / 16; q < segs; q += kCenterRowThreads / 16) {
+                const float G = gF[k0 + q];
+                const int32_t j = col[k0 + q];
+                const Segment g = make_segment(ri, bv.rec[bv.inv[j]], bv.bounds[6]);
+                float T = 1.0f;
+                if (G != 0.0f)
+                    T = row_segment<false>(bv, g, (uint32_t)row, (uint32_t)j, sh.stack[tid / 16], err, [&](int s) {
+                        const uint32_t part = __umulhi((uint32_t)s * 0x85ebca6bu, (uint32_t)kRowParts);
+                        const uint32_t at = atomicAdd(&sh.count[part], 1u);
+                        if (at < (uint32_t)kRowPart) list[part * kRowPart + at] = make_uint2((uint32_t)q, (uint32_t)s);
+                    });
+                if ((tid & 15) == 0) {
+                    sh.d[0][q] = g.dx;
+                    sh.d[1][q] = g.dy;
+                    sh.d[2][q] = g.dz;
+                    sh.W[q] = G * fval[k0 + q];
+                    sh.T[q] = T;
+                }
+            }
+            __syncthreads();
+            bool fits = true;
+            for (int part = 0; part < kRowParts; ++part) fits = fits && sh.count[part] <= (uint32_t)kRowPart;
+            if (!fits) break;
+            if (tid < segs) {
+                const float G = gF[k0 + tid];
+                const uint32_t j = (uint32_t)col[k0 + tid];
+                long long own[3] = {0, 0, 0};
+                if (G != 0.0f) {
+                    const SurfRec rj = bv.rec[bv.inv[j]];
+                    const PairTerm t(ri, rj, make_segment(ri, rj, bv.bounds[6]), G, lambda[j], (float)bv.area[j],
+                                     sh.T[tid]);
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        if (PASS == 1) own[c] = sink.scaled(kFp + c, t.dp[c]);
+                        accI.add<PASS>(sink, c, kFp + c, -t.dp[c]);
+                        accI.add<PASS>(sink, 3 + c, kFn + c, t.ni[c]);
+                        sink.add(kFn + c, j, t.nj[c]);
+                    }
+                    sink.add(kFpair, j, t.chain);
+                }
+#pragma unroll
+                for (int c = 0; c < 3; ++c) sh.end[c][tid] = (unsigned long long)own[c];
+            }
+            // parts share the table while they cannot fill it
+            bool open = false;
+            uint32_t used = 0;
+            for (int part = 0; part < kRowParts; ++part) {
+                const uint32_t count = sh.count[part];
+                hits += count;
+                if (count == 0) continue;
+                if (PASS == 1 && (!open || used + count > (uint32_t)kRowSlots)) {
+                    if (open) {
+                        __syncthreads();
+                        sh.table.flush(sink, tid, kCenterRowThreads);
+                        __syncthreads();
+                    }
+                    sh.table.clear(tid, kCenterRowThreads);
+                    __syncthreads();
+                    open = true;
+                    used = 0;
+                }
+                used += count;
+                for (uint32_t h = tid; h < count; h += kCenterRowThreads) {
+                    const uint2 hit = list[part * kRowPart + h];
+                    const SurfRec r = bv.rec[hit.y];
+                    float x[10], ge[3], gs[3];
+                    crossing(bv, r, ri.a.x, ri.a.y, ri.a.z, sh.d[0][hit.x], sh.d[1][hit.x], sh.d[2][hit.x],
+                             sh.W[hit.x], x, ge, gs);
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        accI.add<PASS>(sink, c, kFp + c, gs[c]);
+                        if (PASS == 0) {
+                            sink.add(kFp + c, 0, ge[c]);
+                        } else {
+                            const long long v = sink.scaled(kFp + c, ge[c]);
+                            if (v != 0) atomicAdd(&sh.end[c][hit.x], (unsigned long long)v);
+                        }
+                    }
+                    if (PASS == 0) {
+#pragma unroll
+                        for (int q = 0; q < 10; ++q) sink.add(sh.table.field(q), 0, x[q]);
+                    } else {
+                        sh.table.add(sink, __float_as_uint(r.d.w), x);
+                    }
+                }
+            }
+            if (open) {
+                __syncthreads();
+                sh.table.flush(sink, tid, kCenterRowThreads);
+                __syncthreads();
+            }
+            if (PASS == 1 && tid < segs) {
+                const uint32_t j = (uint32_t)col[k0 + tid];
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    if (sh.end[c][tid] != 0) sink.add_scaled(kFp + c, j, (long long)sh.end[c][tid]);
+            }
+            __syncthreads();
         }
-    }
-    // one row per wave: every lane's receiver is the row's
-    if (idx < n) {
+        if (tid == 0) done[row] = (int32_t)(min(k0, e) - b);
         const int fI[6] = {kFp, kFp + 1, kFp + 2, kFn, kFn + 1, kFn + 2};
-        accI.flush<PASS>(sink.acc, n, i, fI);
+        accI.flush<PASS>(sink.acc, n, (uint32_t)row, fI);
+        __syncthreads();
     }
     sink.report(maxbits);
+    if (PASS == 1 && tid == 0) atomicAdd(reinterpret_cast<unsigned long long *>(maxbits + kCrossings), hits);
 }
 
 // per-field exponent: (max contribution) * count * 2^margin < 2^62 (count
@@ -543,52 +790,6 @@ struct SegLists {
     static constexpr int64_t words_per_lane = 3 + kSegHits + kSegMore / kSegShare;
 };
 
-// Crossings' sums of a workgroup in LDS: open addressing on the surfel, ten
-// 64-bit fixed-point sums each (fields kFdu ... kFdu + 8 and kFo); a surfel
-// that finds no place within kProbes adds to the global sums.
-template <int SLOTS>
-struct CrossTable {
-    static constexpr int kProbes = 8, kSums = 10;
-    uint32_t key[SLOTS];
-    unsigned long long sum[kSums][SLOTS];
-    static __device__ __forceinline__ int field(int q) { return q < 9 ? kFdu + q : kFo; }
-    __device__ __forceinline__ void clear(int tid, int threads) {
-        for (int z = tid; z < SLOTS; z += threads) {
-            key[z] = kEmpty;
-#pragma unroll
-            for (int q = 0; q < kSums; ++q) sum[q][z] = 0;
-        }
-    }
-    template <typename Sink>
-    __device__ __forceinline__ void add(Sink &sink, uint32_t k, const float (&x)[kSums]) {
-        const uint32_t h = (k * 0x9e3779b1u) >> 16;
-        int at = -1;
-        for (int p = 0; p < kProbes && at < 0; ++p) {
-            const int z = (int)((h + (uint32_t)p) & (uint32_t)(SLOTS - 1));
-            uint32_t old = key[z];
-            if (old == kEmpty) old = atomicCAS(&key[z], kEmpty, k);
-            if (old == kEmpty || old == k) at = z;
-        }
-#pragma unroll
-        for (int q = 0; q < kSums; ++q) {
-            const long long v = sink.scaled(field(q), x[q]);
-            if (v == 0) continue;
-            if (at >= 0) atomicAdd(&sum[q][at], (unsigned long long)v);
-            else sink.add_scaled(field(q), k, v);
-        }
-    }
-    template <typename Sink>
-    __device__ __forceinline__ void flush(Sink &sink, int tid, int threads) {
-        for (int z = tid; z < SLOTS; z += threads) {
-            const uint32_t k = key[z];
-            if (k == kEmpty) continue;
-#pragma unroll
-            for (int q = 0; q < kSums; ++q)
-                if (sum[q][z] != 0) sink.add_scaled(field(q), k, (long long)sum[q][z]);
-        }
-    }
-};
-
 // The light's side of one (receiver, light): nothing to do where !on.
 struct LightTerm {
     float dx, dy, dz, dd, ndot, len, S;
@@ -648,35 +849,6 @@ __global__ void __launch_bounds__(kCenterThreads) k_light_walk(BvhDev bv, const 
 
 constexpr int kTermThreads = 256;
 constexpr int kLightSlots = 512;   // 43 KB
-
-// One crossing of a shadow segment o + t d with weight W: the surfel's ten
-// sums x, the light's share gl and the receiver's share gp of its centre's
-// gradient.
-__device__ __forceinline__ void light_crossing(const BvhDev &bv, const SurfRec &r, float ox, float oy, float oz,
-                                               float dx, float dy, float dz, float W, float (&x)[10], float (&gl)[4],
-                                               float (&gp)[3]) {
-    const float ok = bv.raw_op[__float_as_uint(r.d.w)];
-    const float gam = kernel_gamma(hit_r2_exact(r, ox, oy, oz, dx, dy, dz));
-    const float qx = r.a.x - ox, qy = r.a.y - oy, qz = r.a.z - oz;
-    const float den = dx * r.b.x + dy * r.b.y + dz * r.b.z;
-    const float tk = (qx * r.b.x + qy * r.b.y + qz * r.b.z) / den;
-    const float hx = tk * dx - qx, hy = tk * dy - qy, hz = tk * dz - qz;
-    const float u = (hx * r.c.x + hy * r.c.y + hz * r.c.z) * r.a.w;
-    const float w = (hx * r.d.x + hy * r.d.y + hz * r.d.z) * r.b.w;
-    const float f = W * 3.4f * r.c.w * gam;
-    const float fu = f * u * r.a.w, fw = f * w * r.b.w;
-    const float ghx = fu * r.c.x + fw * r.d.x, ghy = fu * r.c.y + fw * r.d.y, ghz = fu * r.c.z + fw * r.d.z;
-    const float beta = (ghx * dx + ghy * dy + ghz * dz) / den;
-    const float gqx = beta * r.b.x - ghx, gqy = beta * r.b.y - ghy, gqz = beta * r.b.z - ghz;
-    cross_terms(r, fu, fw, beta, hx, hy, hz, x);
-    x[9] = ok > 0.0f && ok < kOpacityMax ? -W * gam / (1.0f - ok) : 0.0f;
-    gl[0] -= tk * gqx;
-    gl[1] -= tk * gqy;
-    gl[2] -= tk * gqz;
-    gp[0] = -(1.0f - tk) * gqx;
-    gp[1] = -(1.0f - tk) * gqy;
-    gp[2] = -(1.0f - tk) * gqz;
-}
 
 // The light's fields: largest |value| of the wave's lanes (pass 0), or one
 // wave sum and one fixed-point add per field
@@ -784,9 +956,10 @@ __global__ void __launch_bounds__(kTermThreads) k_light_terms(BvhDev bv, const f
                                ? seg.hit[(at0 + g) * kSegHits + h]
                                : seg.more[(int64_t)seg.block[at0 + g] * kSegMore + (h - kSegHits)];
         const SurfRec r = bv.rec[s];
-        float x[10], gp[3];
-        light_crossing(bv, r, sh.o[0][g], sh.o[1][g], sh.o[2][g], sh.d[0][g], sh.d[1][g], sh.d[2][g], sh.W[g], x, gl,
-                       gp);
+        float x[10], ge[3], gp[3];
+        crossing(bv, r, sh.o[0][g], sh.o[1][g], sh.o[2][g], sh.d[0][g], sh.d[1][g], sh.d[2][g], sh.W[g], x, ge, gp);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) gl[c] += ge[c];
         if (PASS == 0) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) sink.add(kFp + c, 0, gp[c]);
@@ -839,8 +1012,9 @@ __global__ void __launch_bounds__(kCenterThreads) k_light_again(BvhDev bv, const
         const float W = t.S * bv.op[i] * (1.1283791670955126f * lI[l] * t.ndot * seg.T[at] / (t.dd * t.len));
         trace_segment<kWalkHead>(bv, rr.a.x, rr.a.y, rr.a.z, t.dx, t.dy, t.dz, i, i, __fdiv_rn(bv.bounds[6], t.len),
                                  1.0f, stack_mem + threadIdx.x, kCenterThreads, err, [&](const SurfRec &r, int) {
-                                     float x[10], gp[3];
-                                     light_crossing(bv, r, rr.a.x, rr.a.y, rr.a.z, t.dx, t.dy, t.dz, W, x, gl, gp);
+                                     float x[10], ge[3], gp[3];
+                                     crossing(bv, r, rr.a.x, rr.a.y, rr.a.z, t.dx, t.dy, t.dz, W, x, ge, gp);
+                                     for (int c = 0; c < 3; ++c) gl[c] += ge[c];
                                      sink.add3(kFp, i, gp[0], gp[1], gp[2]);
 #pragma unroll
                                      for (int q = 0; q < 10; ++q)
@@ -915,10 +1089,8 @@ __global__ void k_light_finish(const unsigned long long *__restrict__ lacc, cons
 gsrad_status launch_ff_center(const BvhDev &bv, const Csr &P, const float *lambda, float *val, int *err,
                               hipStream_t st) {
     if (P.n == 0) return GSRAD_OK;
-    const int64_t nb = (P.n + 1) / 2;
-    hipLaunchKernelGGL(k_ff_center, dim3((unsigned)nb), dim3(kCenterThreads),
-                       walk_bytes(kWalkHead), st, bv, P.row_ptr, P.col, P.n, lambda,
-                       val, nb, P.order, err);
+    hipLaunchKernelGGL(k_ff_center, dim3((unsigned)P.n), dim3(kRowThreads), 0, st, bv, P.row_ptr, P.col, P.n, lambda,
+                       val, P.n, P.order, err);
     return check_hip(hipGetLastError(), "centre-to-centre form factor launch");
 }
 
@@ -930,11 +1102,15 @@ gsrad_status launch_ff_center(const BvhDev &bv, const Csr &P, const float *lambd
 constexpr int kScaleStride = 64;
 constexpr int kScaleMargin = 12;
 
+size_t center_list_bytes(int64_t n) {
+    return (size_t)std::min(n, kCenterGroups) * kRowParts * kRowPart * sizeof(uint2) + (size_t)n * 4;
+}
+
 size_t center_acc_bytes(int64_t n) { return (size_t)8 * kFields * n * 8 + 512; }
 
 // accumulator layout: [8 XCD copies][kFields][n] u64, then maxbits[kFields],
 // fx[kFields], the largest scaled contribution of the accumulating pass (as
-// float bits) at maxbits[2 kFields]
+// float bits) at maxbits[2 kFields], its crossings at maxbits[kCrossings]
 static gsrad_status center_scaled_passes(int64_t n, int64_t count, void *acc, hipStream_t st,
                                          const std::function<void(int pass, int stride)> &run) {
     unsigned long long *a = static_cast<unsigned long long *>(acc);
@@ -943,20 +1119,20 @@ static gsrad_status center_scaled_passes(int64_t n, int64_t count, void *acc, hi
     run(0, kScaleStride);
     hipLaunchKernelGGL(k_fields_exp, dim3(1), dim3(64), 0, st, maxbits, count, kScaleMargin, fx);
     run(1, 1);
-    uint32_t qbits = 0;
-    gsrad_status e = check_hip(hipMemcpyAsync(&qbits, maxbits + 2 * kFields, 4, hipMemcpyDeviceToHost, st),
+    uint32_t words[kCrossings + 2 - 2 * kFields];
+    gsrad_status e = check_hip(hipMemcpyAsync(words, maxbits + 2 * kFields, sizeof(words), hipMemcpyDeviceToHost, st),
                                "scale check copy");
     if (e != GSRAD_OK) return e;
     if ((e = check_hip(hipStreamSynchronize(st), "scale check sync")) != GSRAD_OK) return e;
     // every |scaled contribution| times the count below 2^62: no sum overflows
-    const double qmax = (double)reinterpret_cast<const float &>(qbits);
+    const double qmax = (double)reinterpret_cast<const float &>(words[0]);
+    uint64_t crossings;
+    memcpy(&crossings, words + (kCrossings - 2 * kFields), 8);
+    count += (int64_t)crossings;   // a crossing adds to its segment's ends once
     if (!(qmax * (double)count < 4.6e18)) {
         // the sampled rows missed the largest contributions: exact maxima from
         // every row, then the sums again
-        const size_t bytes = (size_t)8 * kFields * n * 8;
-        if ((e = check_hip(hipMemsetAsync(a, 0, bytes + 3 * kFields * 4, st), "accumulators zero")) !=
-            GSRAD_OK)
-            return e;
+        if ((e = check_hip(hipMemsetAsync(a, 0, center_acc_bytes(n), st), "accumulators zero")) != GSRAD_OK) return e;
         run(0, 1);
         hipLaunchKernelGGL(k_fields_exp, dim3(1), dim3(64), 0, st, maxbits, count, 0, fx);
         run(1, 1);
@@ -970,16 +1146,33 @@ gsrad_status launch_center_backward(const BvhDev &bv, const Csr &F, const float 
     unsigned long long *a = static_cast<unsigned long long *>(acc);
     uint32_t *maxbits = reinterpret_cast<uint32_t *>(a + (size_t)8 * kFields * F.n);
     int *fx = reinterpret_cast<int *>(maxbits + kFields);
+    static bool attr_set = false;
+    if (!attr_set) {
+        for (const void *fn : {reinterpret_cast<const void *>(&k_center_rows<0>),
+                               reinterpret_cast<const void *>(&k_center_rows<1>)})
+            (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(RowShared));
+        attr_set = true;
+    }
     const size_t smem = walk_bytes(kWalkHead);
+    const int64_t groups = std::min(F.n, kCenterGroups);
+    char *lists = reinterpret_cast<char *>(acc) + center_acc_bytes(F.n);
+    int32_t *done = reinterpret_cast<int32_t *>(lists + groups * kRowParts * kRowPart * (int64_t)sizeof(uint2));
     auto run = [&](int pass, int stride) {
         const int64_t rows = (F.n + stride - 1) / stride;
         const int64_t nb = (rows + 1) / 2;
-        if (pass == 0)
+        const unsigned grid = (unsigned)std::min(rows, kCenterGroups);
+        uint2 *lp = reinterpret_cast<uint2 *>(lists);
+        if (pass == 0) {
+            hipLaunchKernelGGL(k_center_rows<0>, dim3(grid), dim3(kCenterRowThreads), sizeof(RowShared), st, bv,
+                               F.row_ptr, F.col, F.val, F.n, lambda, gF, maxbits, fx, a, F.order, stride, lp, done, err);
             hipLaunchKernelGGL(k_center_bwd<0>, dim3((unsigned)nb), dim3(kCenterThreads), smem, st, bv, F.row_ptr,
-                               F.col, F.val, F.n, lambda, gF, maxbits, fx, a, nb, F.order, stride, err);
-        else
+                               F.col, F.val, F.n, lambda, gF, maxbits, fx, a, nb, F.order, stride, done, err);
+        } else {
+            hipLaunchKernelGGL(k_center_rows<1>, dim3(grid), dim3(kCenterRowThreads), sizeof(RowShared), st, bv,
+                               F.row_ptr, F.col, F.val, F.n, lambda, gF, maxbits, fx, a, F.order, stride, lp, done, err);
             hipLaunchKernelGGL(k_center_bwd<1>, dim3((unsigned)nb), dim3(kCenterThreads), smem, st, bv, F.row_ptr,
-                               F.col, F.val, F.n, lambda, gF, maxbits, fx, a, nb, F.order, stride, err);
+                               F.col, F.val, F.n, lambda, gF, maxbits, fx, a, nb, F.order, stride, done, err);
+        }
     };
     gsrad_status e = center_scaled_passes(F.n, 2 * F.nnz + 2, acc, st, run);
     if (e != GSRAD_OK) return e;

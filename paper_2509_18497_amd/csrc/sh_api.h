@@ -35,6 +35,7 @@ struct CenterOutputs {
     float *p[16];
 };
 size_t center_acc_bytes(int64_t n);
+size_t center_list_bytes(int64_t n);
 gsrad_status launch_center_backward(const BvhDev &bv, const Csr &F, const float *lambda, const float *gF, void *acc,
                                     const CenterOutputs &out, int *err, hipStream_t st);
 

@@ -7,6 +7,8 @@
 // inlined copy.
 #pragma once
 
+#include <utility>
+
 #include "gsrad_internal.h"
 
 namespace gsrad {
@@ -27,7 +29,7 @@ constexpr uint32_t kEmpty = 0xffffffffu;
 // walks reach (an LBVH of 100k surfels is some 20 levels high), in the lane's
 // private memory.  The walks wait for dependent node and leaf loads, so where
 // a launch fills the chip, waves in flight count: all 64 entries in LDS hold
-// a CU to ten waves (10 M segments of a 20k-surfel bowl: F 29.6 ms, with a
+// a CU to ten waves (10 M segments of a 20k-surfel bowl, a lane each: F 29.6 ms, with a
 // head of 20 24.2 ms; their gradients 183 and 156 ms).  A launch that does
 // not reach ten waves a CU (kWalkFill lanes) walks faster without the choice
 // of memory and takes HEAD = 64 (the direct light of 512 surfels 49 us, with
@@ -341,6 +343,120 @@ __device__ __forceinline__ Segment make_segment(const SurfRec &ri, const SurfRec
     g.t_lo = __fdiv_rn(t_eps, len);
     g.t_hi = __fsub_rn(1.0f, g.t_lo);
     return g;
+}
+
+// Lane N's value in every lane of its row of 16 lanes
+template <int N>
+__device__ __forceinline__ float row_bcast(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + N, 0xf, 0xf, true));
+}
+template <int... I, typename Fn>
+__device__ __forceinline__ void each_lane(std::integer_sequence<int, I...>, float v, Fn &&fn) {
+    (fn(I, row_bcast<I>(v)), ...);
+}
+
+// The crossings of a segment by a row of 16 lanes: on_hit(sorted position) in
+// the lane that finds one, in no order; returns the transmittance.  The row
+// keeps the walk's stack in LDS, next entry on top: a node to open, a leaf to
+// test, or (ORDERED) the factor of a crossing found while nodes before it were
+// still closed.  A round takes the top entries, one per lane, with one load
+// for nodes and leaves alike (both are 64 bytes); what they leave goes back in
+// their order.  ORDERED multiplies the factors as they come to the top, so T
+// is the product in the order of trace_segment, bit by bit; otherwise each
+// lane multiplies those it finds, and the lanes' products are multiplied at
+// the end.  The loads that trace_segment waits for one by one are up to 16 at
+// a time, and a wave waits for the longest of four segments, not of 64.  50k
+// segments across a bowl of 50k surfels (ORDERED): 1.0 ms with a lane each
+// (whether 64 or 16 of them share a wave), 0.24 ms with a row each; 10 M
+// segments of a 20k-surfel bowl: 24.2 ms with a lane each, 22.7 ms ORDERED,
+// 19.4 ms.
+// A tree no higher than trace_segment takes never fills the stack: near its
+// end a round opens one entry only, which needs kStackDeep more of them.
+constexpr int kRowThreads = 256;   // 16 rows a workgroup
+constexpr int kRowStack = 192;
+
+template <bool ORDERED, typename OnHit>
+__device__ __forceinline__ float row_segment(const BvhDev &bv, const Segment &g, uint32_t skip_a, uint32_t skip_b,
+                                             uint64_t *stack, int *err, OnHit &&on_hit) {
+    constexpr auto kRow = std::make_integer_sequence<int, 16>{};
+    constexpr uint32_t kNode = 0, kLeaf = 1, kFactor = 2;
+    auto entry = [](uint32_t kind, uint32_t v) { return (uint64_t)kind << 32 | v; };
+    auto child = [&](int c) { return c < 0 ? entry(kLeaf, (uint32_t)~c) : entry(kNode, (uint32_t)c); };
+    const int l = threadIdx.x & 15, row = (int)__lane_id() & 48;
+    const float ix = safe_inv(g.dx), iy = safe_inv(g.dy), iz = safe_inv(g.dz);
+    const float t0 = g.t_lo * 0.99999f, t1 = g.t_hi * 1.00001f;
+    float T = 1.0f;
+    if (l == 0) stack[0] = entry(bv.n == 1 ? kLeaf : kNode, 0);
+    int sp = 1;
+    while (sp > 0) {
+        const int m = sp + 16 <= kRowStack - kStackDeep ? min(sp, 16) : 1;
+        if (sp >= kRowStack) {
+            if (l == 0) atomicOr(err, kErrStack);
+            break;
+        }
+        uint64_t e = entry(kFactor, __float_as_uint(1.0f));
+        __builtin_amdgcn_wave_barrier();
+        if (l < m) e = stack[sp - 1 - l];
+        __builtin_amdgcn_wave_barrier();
+        const uint32_t kind = (uint32_t)(e >> 32), v = (uint32_t)e;
+        uint64_t keep0 = 0, keep1 = 0;   // what the entry leaves, keep0 first
+        int keep = 0;
+        float f = 1.0f;
+        if (kind == kFactor) {
+            f = __uint_as_float(v);
+        } else {
+            const float4 *q = kind == kNode ? reinterpret_cast<const float4 *>(bv.nodes + v)
+                                            : reinterpret_cast<const float4 *>(bv.rec + v);
+            const float4 q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
+            if (kind == kNode) {
+                float tn;
+                const bool h0 = slab(q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, g.ox, g.oy, g.oz, ix, iy, iz, t0, t1, tn);
+                const bool h1 = slab(q1.z, q1.w, q2.x, q2.y, q2.z, q2.w, g.ox, g.oy, g.oz, ix, iy, iz, t0, t1, tn);
+                const int c0 = __float_as_int(q3.x), c1 = __float_as_int(q3.y);
+                const bool swap = c0 >= 0 && c1 < 0;   // a node's leaves come before its nodes
+                keep = (h0 ? 1 : 0) + (h1 ? 1 : 0);
+                keep0 = child(h0 && !(h1 && swap) ? c0 : c1);
+                keep1 = child(swap ? c0 : c1);
+            } else {
+                SurfRec r;
+                r.a = q0;
+                r.b = q1;
+                r.c = q2;
+                r.d = q3;
+                const uint32_t j = __float_as_uint(r.d.w);
+                float t, r2;
+                bool front;
+                if (j != skip_a && j != skip_b &&
+                    hit_test(r, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, g.t_lo, g.t_hi, true, t, r2, front)) {
+                    f = transmit(r.c.w, kernel_gamma(hit_r2_exact(r, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz)));
+                    on_hit((int)v);
+                }
+            }
+        }
+        if (ORDERED) {
+            // lanes before the row's first node: their factors are next in order
+            const uint32_t nodes = (uint32_t)(__ballot(kind == kNode) >> row) & 0xffffu;
+            const int first = nodes ? __ffs((int)nodes) - 1 : 16;
+            if (kind != kNode && l >= first && __float_as_uint(f) != __float_as_uint(1.0f)) {
+                keep = 1;
+                keep0 = entry(kFactor, __float_as_uint(f));
+            }
+            each_lane(kRow, l < first ? f : 1.0f, [&](int, float x) { T = __fmul_rn(T, x); });
+        } else {
+            T = __fmul_rn(T, f);
+        }
+        const uint32_t k1 = (uint32_t)(__ballot(keep >= 1) >> row) & 0xffffu;
+        const uint32_t k2 = (uint32_t)(__ballot(keep >= 2) >> row) & 0xffffu;
+        int at = sp - m + __popc(k1 >> (l + 1)) + __popc(k2 >> (l + 1));
+        if (keep >= 2) stack[at++] = keep1;
+        if (keep >= 1) stack[at] = keep0;
+        sp += __popc(k1) + __popc(k2) - m;
+    }
+    if (!ORDERED) {
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) T = __fmul_rn(T, __shfl_xor(T, off));
+    }
+    return T;
 }
 
 }  // namespace

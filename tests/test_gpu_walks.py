@@ -147,3 +147,57 @@ def test_monte_carlo_draws_pick_by_the_running_sum(g, n):
     tol = (n + 250 + lost[:, None, None, None]) * 2.0 ** -23 * np.abs(want - E) + 2.0 ** -23 * np.abs(want)
     bad = np.abs(got - want) > tol
     assert not bad[sure].any(), (np.abs(got - want) / np.abs(want))[sure].max()
+
+
+def _sheets(before, beyond, layers, seed=0):
+    """Surfel 0 looks at `layers` wide thin sheets and at small surfels, some
+    before and some beyond them."""
+    rng = np.random.default_rng(seed)
+    n = 1 + before + beyond + layers
+    p = rng.uniform(-0.3, 0.3, (n, 3))
+    p[0] = 0.0
+    p[1:1 + before, 2] = rng.uniform(0.5, 0.9, before)
+    p[1 + before:1 + before + beyond, 2] = rng.uniform(3.5, 4.0, beyond)
+    p[1 + before + beyond:, 2] = 1.0 + 0.005 * np.arange(layers)
+    nrm = rng.normal(0.0, 0.05, (n, 3)) + [0.0, 0.0, 1.0]
+    nrm /= np.linalg.norm(nrm, axis=1, keepdims=True)
+    tu = np.cross(nrm, [0.0, 1.0, 0.0])
+    tu /= np.linalg.norm(tu, axis=1, keepdims=True)
+    tv = np.cross(nrm, tu)
+    size = np.full(n, 0.01)
+    size[1 + before + beyond:] = 0.8
+    op = np.full(n, 0.5)
+    op[1 + before + beyond:] = 0.01
+    cols = {"su": size, "sv": size, "opacity": op}
+    for name, v in (("p", p), ("tu", tu), ("tv", tv), ("n", nrm)):
+        for k, a in enumerate("xyz"):
+            cols[name + a] = v[:, k]
+    return {k: np.ascontiguousarray(v, np.float32) for k, v in cols.items()}
+
+
+@pytest.mark.parametrize("before,beyond,layers", [(1, 0, 1), (0, 33, 3), (500, 12, 40), (300, 213, 40), (0, 600, 150),
+                                                  (512, 200, 400)])
+def test_center_gradients_of_long_rows_and_lists(g, orc, before, beyond, layers):
+    """Rows of one segment, of a chunk and one more, and rows whose crossings
+    (90,000 and, in the second chunk, 80,000) do not fit the lists."""
+    from oracle import center
+    sur = _sheets(before, beyond, layers)
+    n, m = sur["px"].shape[0], before + beyond
+    bvh = g.build_bvh(dev_surfels(sur))
+    ptr = np.full(n + 1, m, np.int64)
+    ptr[0] = 0
+    cols = np.arange(1, 1 + m, dtype=np.int32)
+    P = g.ff_from_csr(dev(ptr), dev(cols), dev(np.ones(m, np.float32)))
+    lam = scenes.seeded_array((n,), 7, 0.2, 0.8)
+    gF = scenes.seeded_array((m,), 8, -1.0, 1.0)
+    F = g.ff_center(bvh, P, dev(lam))
+    rows, te = np.zeros(m, np.int64), orc.default_t_eps(sur)
+    Fo, _ = center.center_ff(sur, rows, cols, lam.astype(np.float64), t_eps=te)
+    assert rel_err(F.csr()[2].cpu().numpy(), Fo) < TOL
+    gl, gf = g.ff_center_backward(bvh, F, dev(lam), dev(gF))
+    glo, gfo = center.center_backward(sur, rows, cols, lam.astype(np.float64), gF.astype(np.float64), t_eps=te)
+    assert rel_err(gl.cpu().numpy(), glo) < TOL
+    for f in center.FIELDS:
+        assert rel_err(gf[f].cpu().numpy(), gfo[f]) < TOL, f
+    again = g.ff_center_backward(bvh, F, dev(lam), dev(gF))
+    assert all(torch.equal(gf[f], again[1][f]) for f in gf) and torch.equal(gl, again[0])
