@@ -191,7 +191,7 @@ struct gsrad_ff {
     // scratch of the ray-cast path
     DevBuf slab, ell_col, ell_val, row_len, err, scan_temp, redo, pools;
     // opacity backward: per-XCD fixed-point accumulators and scale
-    DevBuf opac, cacc;
+    DevBuf opac, cacc, lists;
     // dense BF16 copies (gsrad_ff_dense): F and F^T, hi and lo parts
     bool has_dense = false;
     int64_t Np = 0;
@@ -220,7 +220,7 @@ struct gsrad_ff {
     ~gsrad_ff() {
         for (DevBuf *b : {&row_ptr, &col, &val, &t_row_ptr, &t_col, &t_val, &t_temp, &slab, &ell_col, &redo, &row_order,
                           &ell_val, &row_len, &err, &scan_temp, &pools, &recs, &rcnt, &d_hi, &d_lo, &dt_hi, &dt_lo, &xa, &xb, &xl, &opac,
-                          &cacc})
+                          &cacc, &lists})
             b->release();
     }
 };
@@ -1429,6 +1429,13 @@ gsrad_status gsrad_direct_light_backward(const gsrad_bvh *bvh, const float *albe
                                   grad_light_pos, grad_light_I, grad_albedo, out, h->height.as<int>() + 12, st);
 }
 
+// The hit lists' workspace; NULL (the sums are then added directly) where none
+// is wanted or the memory is not there.
+static void *list_workspace(gsrad_ff *f, size_t bytes) {
+    if (bytes == 0 || f->lists.ensure(bytes, "hit lists") != GSRAD_OK) return nullptr;
+    return f->lists.p;
+}
+
 gsrad_status gsrad_geometry_backward(const gsrad_bvh *bvh, const gsrad_ff *ff, const float *grad_F,
                                      const gsrad_surfel_grads *grads, void *stream) {
     if (!bvh || !ff || !grad_F || !grads) return einval("gsrad_geometry_backward: null argument");
@@ -1460,7 +1467,7 @@ gsrad_status gsrad_geometry_backward(const gsrad_bvh *bvh, const gsrad_ff *ff, c
     ProfScope ps("geometry_backward", st);
     return launch_geometry_rec(bvh->dev(), f->R, f->seed, f->recs.as<uint2>(), f->rcnt.as<uint32_t>(), f->rec_cap,
                                f->row_ptr.as<int64_t>(), f->col.as<int32_t>(), grad_F, std::max(f->max_row, 1),
-                               f->cacc.p, out, st);
+                               f->cacc.p, list_workspace(f, geometry_list_bytes(ff->n, f->R)), out, st);
 }
 
 gsrad_status gsrad_opacity_backward(const gsrad_bvh *bvh, const gsrad_ff *ff, const float *grad_F,
@@ -1489,9 +1496,10 @@ gsrad_status gsrad_opacity_backward(const gsrad_bvh *bvh, const gsrad_ff *ff, co
             return einval("gsrad_opacity_backward: row too long for the LDS row cache");
         if (f->has_records) {
             ProfScope ps("opacity_records", st);
+            void *ws = list_workspace(f, opacity_list_bytes(n, f->R));
             GS_TRY(launch_opacity_rec(bvh->dev(), f->R, f->recs.as<uint2>(), f->rcnt.as<uint32_t>(), f->rec_cap,
                                       f->row_ptr.as<int64_t>(), f->col.as<int32_t>(), grad_F, std::max(f->max_row, 1),
-                                      acc, st));
+                                      acc, ws, st));
         } else {
             // recompute the rays without (complete) records by traversal
             GS_TRY(f->slab.ensure(std::max(f->slab.bytes, (size_t)n * f->R * sizeof(float2)), "ray sums"));

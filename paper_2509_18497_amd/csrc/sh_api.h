@@ -43,7 +43,9 @@ gsrad_status launch_center_backward(const BvhDev &bv, const Csr &F, const float 
 // (accumulators of center_acc_bytes(n) zeroed first; out.p[0..14])
 gsrad_status launch_geometry_rec(const BvhDev &bv, int R, uint64_t seed, const uint2 *recs, const uint32_t *rcnt,
                                  int rcap, const int64_t *row_ptr, const int32_t *col, const float *gF, int max_row,
-                                 void *acc, const CenterOutputs &out, hipStream_t st);
+                                 void *acc, void *ws, const CenterOutputs &out, hipStream_t st);
+// workspace of launch_geometry_rec (0: none taken; NULL ws is always accepted)
+size_t geometry_list_bytes(int64_t n, int R);
 
 // direct-light gradients (workspace of light_acc_bytes + light_seg_bytes,
 // its first light_acc_bytes zeroed; out.p[0..14] surfel fields)

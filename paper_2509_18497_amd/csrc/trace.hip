@@ -17,6 +17,7 @@
 #include "sh_basis.h"
 #include "trace_api.h"
 #include "traverse.h"
+#include "hit_lists.h"
 
 namespace gsrad {
 
@@ -426,16 +427,6 @@ __global__ void __launch_bounds__(256) k_ray_pools(BvhDev bv, int R, uint64_t se
         list[b * kPoolRays + p] = make_uint4((uint32_t)k, __float_as_uint(pool_d[k][0]), __float_as_uint(pool_d[k][1]),
                                              __float_as_uint(pool_d[k][2]));
     }
-}
-
-__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
-    const int lane = __lane_id();
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t u = __shfl_up(v, o, 64);
-        if (lane >= o) v += u;
-    }
-    return v;
 }
 
 __device__ __forceinline__ uint64_t badness(uint32_t j, float v) {
@@ -868,15 +859,17 @@ __device__ __forceinline__ float row_lookup(const uint32_t *lc, const float *lg,
 // the workgroup: every workgroup that touches copy x runs on XCD x), and
 // k_opacity_finish adds the copies.
 // One hit of the second walk: the sender's contribution to dL/do.
-// The same with the sender's c_j and raw opacity already loaded.
-__device__ __forceinline__ void opacity_hit_c(uint32_t j, float G, float alpha, float f, float T, float g, float cj,
-                                              float oraw, DF W, DF &P, unsigned long long *acc, float scale) {
+// The same with the sender's c_j and raw opacity already loaded, returned
+// instead of added; false: none.
+__device__ __forceinline__ bool opacity_term(float G, float alpha, float f, float T, float g, float cj, float oraw,
+                                             DF W, DF &P, float &v) {
     if (G != 0.0f) P = df_add(P, df_prod3(G, alpha, T));
-    if (!(oraw > 0.0f && oraw < kOpacityMax)) return;
+    if (!(oraw > 0.0f && oraw < kOpacityMax)) return false;
     const DF Sd = df_add(W, DF{-P.hi, -P.lo});
     const float dLda = G * T - Sd.hi / f;
     const float dado = g * expf(cj * (1.0f - g));
-    fx_add(acc + j, dLda * dado, scale);
+    v = dLda * dado;
+    return true;
 }
 
 __device__ __forceinline__ void opacity_hit(const BvhDev &bv, uint32_t j, float G, float alpha, float f, float T,
@@ -968,18 +961,20 @@ __global__ void __launch_bounds__(256) k_opacity_bwd(BvhDev bv, int R, uint64_t 
     }
 }
 
+// Bound by the records' latency and the lists' stores: 356 M hits of a
+// 100k-surfel bowl 12.7 ms with the sums (16.5 ms with an atomic each), 105 M
+// of a 16k-surfel room 4.9 ms (14.5 ms, also for the larger row table).
 // Compositing backward from the recorded hits: the same FP32 alpha and T
-// sequence as the forward trace, G from an LDS hash of row i of dL/dF.
+// sequence as the forward trace, G from row i of dL/dF in LDS.
 __global__ void __launch_bounds__(256) k_opacity_rec(BvhDev bv, int R, const uint2 *__restrict__ recs,
-                                                     const uint32_t *__restrict__ rcnt, int rcap, int64_t nblocks,
+                                                     const uint32_t *__restrict__ rcnt, int rcap, int64_t s0, int64_t nblocks,
                                                      const int64_t *__restrict__ row_ptr,
                                                      const int32_t *__restrict__ col, const float *__restrict__ gF,
-                                                     int log2h, const int *fx_exp, unsigned long long *acc) {
+                                                     int max_row, const int *fx_exp, unsigned long long *acc,
+                                                     HitLists lists) {
     extern __shared__ uint32_t sm3[];
-    const int H = 1 << log2h;
-    uint32_t *hk = sm3;
-    float *hv = reinterpret_cast<float *>(sm3 + H);
-    const int64_t b = xcd_block(blockIdx.x, nblocks);
+    RowIndex row(sm3, max_row, bv.n);
+    const int64_t b = s0 + xcd_block(blockIdx.x, nblocks);
     const int tid = threadIdx.x;
     const uint32_t i = __float_as_uint(bv.rec[b].d.w);
     // With one ray per thread, the threads take the rays in ascending order
@@ -990,7 +985,6 @@ __global__ void __launch_bounds__(256) k_opacity_rec(BvhDev bv, int R, const uin
     __shared__ uint32_t bucket[64], ray_of[256];
     const bool by_len = R == (int)blockDim.x;
     if (by_len && tid < 64) bucket[tid] = 0;
-    for (int k = tid; k < H; k += blockDim.x) hk[k] = kEmpty;
     __syncthreads();
     uint32_t bk = 0;
     if (by_len) {
@@ -999,17 +993,9 @@ __global__ void __launch_bounds__(256) k_opacity_rec(BvhDev bv, int R, const uin
         atomicAdd(&bucket[bk], 1u);
     }
     const int64_t e0 = row_ptr[i];
-    const int len = (int)(row_ptr[i + 1] - e0);
-    const float invR = 1.0f / (float)R;
     const float scale = __builtin_ldexpf(1.0f, *fx_exp);
     unsigned long long *my = acc + (int64_t)xcc_id() * bv.n;
-    for (int k = tid; k < len; k += blockDim.x) {
-        const uint32_t j = (uint32_t)col[e0 + k];
-        uint32_t h = hash_slot(j, log2h);
-        while (atomicCAS(&hk[h], kEmpty, j) != kEmpty) h = (h + 1) & (uint32_t)(H - 1);
-        hv[h] = gF[e0 + k] * invR;
-    }
-    __syncthreads();
+    row.load(col + e0, gF + e0, (int)(row_ptr[i + 1] - e0), 1.0f / (float)R, tid, blockDim.x);
     if (by_len) {
         if (tid < 64) {
             const uint32_t v = bucket[tid];
@@ -1019,16 +1005,22 @@ __global__ void __launch_bounds__(256) k_opacity_rec(BvhDev bv, int R, const uin
         ray_of[atomicAdd(&bucket[bk], 1u)] = (uint32_t)tid;
         __syncthreads();
     }
-    for (int t = tid; t < R; t += blockDim.x) {
-        const int r = by_len ? (int)ray_of[t] : t;
-        const uint32_t m = rcnt[(int64_t)i * R + r];
-        if (m > (uint32_t)rcap) continue;
+    const int batches = (R + (int)blockDim.x - 1) / (int)blockDim.x;
+    uint32_t *next = sm3 + row_index_bytes(max_row) / 4;
+    for (int batch = 0; batch < batches; ++batch) {
+        const int t = batch * (int)blockDim.x + tid;
+        ListStretch out(lists, next, (int64_t)blockIdx.x * batches + batch);
+        out.clear(tid, blockDim.x);
+        __syncthreads();
+        const int r = by_len ? (int)ray_of[tid] : t;
+        uint32_t m = t < R ? rcnt[(int64_t)i * R + r] : 0u;
+        if (m > (uint32_t)rcap) m = 0;
         const uint2 *in = recs + (int64_t)i * rcap * R + r;
         // Records are loaded two hits ahead and the sender's constants one
         // ahead.  In the second pass those loads are issued before the
-        // current hit's atomic add: the memory counter the waits use is in
-        // order, so a load issued after an atomic could only be waited for
-        // together with the atomic.
+        // current hit's store or atomic add: the memory counter the waits use
+        // is in order, so a load issued after it could only be waited for
+        // together with it.
         DF W{0.0f, 0.0f};
         float T = 1.0f;
         {
@@ -1041,19 +1033,21 @@ __global__ void __launch_bounds__(256) k_opacity_rec(BvhDev bv, int R, const uin
                 h1 = h2;
                 if (q + 2 < m) h2 = in[(int64_t)(q + 2) * R];
                 if (q + 1 < m) c1 = bv.c[h1.x];
+                out.count(h.x);
                 const float gs = __uint_as_float(h.y);
                 const float x = cq * fabsf(gs);
                 if (gs > 0.0f) {
-                    const float G = row_hash_lookup(hk, hv, log2h, h.x);
+                    const float G = row.find(h.x);
                     if (G != 0.0f) W = df_add(W, df_prod3(G, -expm1f(-x), T));
                 }
                 T = __fmul_rn(T, exp_fx(-x));
             }
         }
-        if (W.hi == 0.0f) continue;   // every G_q alpha_q T_q is 0: no contribution
+        out.open(tid, blockDim.x);
+        if (W.hi == 0.0f) m = 0;   // every G_q alpha_q T_q is 0: no contribution
         DF P{0.0f, 0.0f};
         T = 1.0f;
-        uint2 h1 = in[0];
+        uint2 h1 = m > 0 ? in[0] : make_uint2(0u, 0u);
         uint2 h2 = m > 1 ? in[(int64_t)R] : make_uint2(0u, 0u);
         float c1 = bv.c[h1.x], o1 = bv.raw_op[h1.x];
         for (uint32_t q = 0; q < m; ++q) {
@@ -1069,12 +1063,55 @@ __global__ void __launch_bounds__(256) k_opacity_rec(BvhDev bv, int R, const uin
             const float g = fabsf(gs);
             const float x = cq * g;
             const float f = exp_fx(-x);
-            const float G = gs > 0.0f ? row_hash_lookup(hk, hv, log2h, h.x) : 0.0f;
-            opacity_hit_c(h.x, G, -expm1f(-x), f, T, g, cq, oq, W, P, my, scale);
+            const float G = gs > 0.0f ? row.find(h.x) : 0.0f;
+            float v;
+            if (opacity_term(G, -expm1f(-x), f, T, g, cq, oq, W, P, v)) {
+                if (out.on) reinterpret_cast<uint2 *>(lists.entry)[out.place(h.x)] = make_uint2(h.x, __float_as_uint(v));
+                else fx_add(my + h.x, v, scale);
+            }
             T = __fmul_rn(T, f);
         }
+        out.close(tid, blockDim.x);
     }
 }
+
+// The listed contributions of one chunk: workgroup (block of surfels, share of
+// the stretches), 16 lanes per stretch.  Blocks of up to 4,096 surfels: fewer
+// blocks fill the lists' lines faster, larger tables leave fewer workgroups a
+// CU (2,048 / 4,096 / 8,192 on a 100k-surfel bowl: 11.1 + 2.7, 10.0 + 2.7,
+// 9.0 + 4.3 ms).
+constexpr int kOpacityShift = 12;
+constexpr int kListSumThreads = 256;
+constexpr int kListSumWgs = 1024;   // workgroups aimed at
+
+__global__ void __launch_bounds__(kListSumThreads) k_opacity_sum(HitLists lists, int64_t stretches, int64_t n,
+                                                                 const int *fx_exp, unsigned long long *acc) {
+    __shared__ unsigned long long table[1 << kOpacityShift];
+    const int tid = threadIdx.x;
+    for (int z = tid; z < (1 << kOpacityShift); z += kListSumThreads) table[z] = 0;
+    __syncthreads();
+    const float scale = __builtin_ldexpf(1.0f, *fx_exp);
+    const uint2 *entry = reinterpret_cast<const uint2 *>(lists.entry);
+    const int block = blockIdx.x;
+    constexpr int kRows = kListSumThreads / 16;
+    for (int64_t s = (int64_t)blockIdx.y * kRows + tid / 16; s < stretches; s += (int64_t)gridDim.y * kRows) {
+        const uint2 p = lists.part[(s << lists.bits) + block];
+        for (uint32_t k = p.x + (tid & 15); k < p.y; k += 16) {
+            const uint2 e = entry[k];
+            const long long q = __float2ll_rn(__uint_as_float(e.y) * scale);
+            if (q != 0) atomicAdd(&table[e.x >> lists.bits], (unsigned long long)q);
+        }
+    }
+    __syncthreads();
+    unsigned long long *my = acc + (int64_t)xcc_id() * n;
+    for (int z = tid; z < (1 << kOpacityShift); z += kListSumThreads) {
+        const int64_t j = ((int64_t)z << lists.bits) + block;
+        if (j < n && table[z] != 0)
+            __hip_atomic_fetch_add(my + j, table[z], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+}
+
+__global__ void k_list_reset(unsigned long long *used) { *used = 0; }
 
 __global__ void __launch_bounds__(256) k_opacity_finish(BvhDev bv, const unsigned long long *__restrict__ acc,
                                                         const int *fx_exp, const float *__restrict__ grad_rho,
@@ -1309,24 +1346,44 @@ gsrad_status launch_opacity_bwd(const BvhDev &bv, int R, uint64_t seed, float t_
 
 gsrad_status launch_opacity_rec(const BvhDev &bv, int R, const uint2 *recs, const uint32_t *rcnt, int rcap,
                                 const int64_t *row_ptr, const int32_t *col, const float *gF, int max_row,
-                                void *acc, hipStream_t st) {
+                                void *acc, void *ws, hipStream_t st) {
     const int threads = R >= 256 ? 256 : ((R + 63) / 64) * 64;
-    int log2h = 4;
-    while ((1 << log2h) < 2 * max_row) ++log2h;
-    const size_t smem = (size_t)(1 << log2h) * 8;
+    const size_t smem = row_index_bytes(max_row);
     static bool attr_set = false;
     if (!attr_set) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_opacity_rec), hipFuncAttributeMaxDynamicSharedMemorySize,
                             160 * 1024 - 4096);
         attr_set = true;
     }
-    if (smem > 150 * 1024) {
+    if (max_row > kRowIndexMax) {
         set_error("opacity backward: row of %d entries is too long for the LDS row table", max_row);
         return GSRAD_EINVAL;
     }
-    hipLaunchKernelGGL(k_opacity_rec, dim3((unsigned)bv.n), dim3(threads), smem, st, bv, R, recs, rcnt, rcap, bv.n,
-                       row_ptr, col, gF, log2h, fx_exp_ptr(bv, acc), static_cast<unsigned long long *>(acc));
+    const int *fx = fx_exp_ptr(bv, acc);
+    unsigned long long *a = static_cast<unsigned long long *>(acc);
+    const int64_t batches = (R + threads - 1) / threads;
+    const ListLayout lay(bv.n, R, threads, kOpacityShift, sizeof(uint2));
+    HitLists lists{};
+    if (ws) lists = lay.view(ws);
+    const int64_t chunk = ws ? lay.stretches / batches : bv.n;
+    for (int64_t s0 = 0; s0 < bv.n; s0 += chunk) {
+        const int64_t m = std::min(chunk, bv.n - s0);
+        if (ws) hipLaunchKernelGGL(k_list_reset, dim3(1), dim3(1), 0, st, lists.used);
+        hipLaunchKernelGGL(k_opacity_rec, dim3((unsigned)m), dim3(threads), smem + (ws ? (size_t)lists.blocks() * 4 : 0), st, bv, R,
+                           recs, rcnt, rcap, s0, m, row_ptr, col, gF, max_row, fx, a, lists);
+        if (ws) {
+            const int64_t rows = (m * batches + 15) / 16;
+            const unsigned split = (unsigned)std::max<int64_t>(1, std::min<int64_t>(rows, kListSumWgs / lists.blocks()));
+            hipLaunchKernelGGL(k_opacity_sum, dim3((unsigned)lists.blocks(), split), dim3(kListSumThreads), 0, st, lists,
+                               m * batches, bv.n, fx, a);
+        }
+    }
     return check_hip(hipGetLastError(), "opacity records launch");
+}
+
+size_t opacity_list_bytes(int64_t n, int R) {
+    const int threads = R >= 256 ? 256 : ((R + 63) / 64) * 64;
+    return lists_pay(n, R, kOpacityShift) ? (size_t)ListLayout(n, R, threads, kOpacityShift, sizeof(uint2)).bytes : 0;
 }
 
 gsrad_status launch_opacity_finish(const BvhDev &bv, const void *acc, const float *grad_rho, const float *albedo,

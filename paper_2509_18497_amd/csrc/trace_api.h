@@ -46,7 +46,9 @@ gsrad_status launch_opacity_bwd(const BvhDev &bv, int R, uint64_t seed, float t_
                                 void *acc, int pass, const uint32_t *rcnt, int rcap, int *err, hipStream_t st);
 gsrad_status launch_opacity_rec(const BvhDev &bv, int R, const uint2 *recs, const uint32_t *rcnt, int rcap,
                                 const int64_t *row_ptr, const int32_t *col, const float *gF, int max_row,
-                                void *acc, hipStream_t st);
+                                void *acc, void *ws, hipStream_t st);
+// workspace of launch_opacity_rec (0: none taken; NULL ws is always accepted)
+size_t opacity_list_bytes(int64_t n, int R);
 gsrad_status launch_opacity_finish(const BvhDev &bv, const void *acc, const float *grad_rho, const float *albedo,
                                    float *grad_o, float *grad_a, hipStream_t st);
 gsrad_status launch_ray_hits(const BvhDev &bv, int R, uint64_t seed, float t_eps, float t_min, const int64_t *recv,
