@@ -191,7 +191,7 @@ struct gsrad_ff {
     // scratch of the ray-cast path
     DevBuf slab, ell_col, ell_val, row_len, err, scan_temp, redo, pools;
     // opacity backward: per-XCD fixed-point accumulators and scale
-    DevBuf opac, cacc, lists;
+    DevBuf opac, cacc, lists, frames;
     // dense BF16 copies (gsrad_ff_dense): F and F^T, hi and lo parts
     bool has_dense = false;
     int64_t Np = 0;
@@ -220,7 +220,7 @@ struct gsrad_ff {
     ~gsrad_ff() {
         for (DevBuf *b : {&row_ptr, &col, &val, &t_row_ptr, &t_col, &t_val, &t_temp, &slab, &ell_col, &redo, &row_order,
                           &ell_val, &row_len, &err, &scan_temp, &pools, &recs, &rcnt, &d_hi, &d_lo, &dt_hi, &dt_lo, &xa, &xb, &xl, &opac,
-                          &cacc, &lists})
+                          &cacc, &lists, &frames})
             b->release();
     }
 };
@@ -234,6 +234,7 @@ struct gsrad_tape {
     const gsrad_bvh *bvh = nullptr;   // directional transfer: the geometry it used
     uint64_t bvh_gen = 0;
     DevBuf B, L, lam0, pp;
+    DevBuf frames;                    // directional transfer: the solve's surfel frames
     // GSRAD_BF16: Q^(k) = F B^(k) (FP32 [nb][n][C]), B^(k) in BF16 as
     // [Np][Kp] rows (k-major columns), the adjoint's BF16 rows
     // rho lambda^(k+1), its FP32 iterates, and the dense dL/dF [n][n]
@@ -241,7 +242,7 @@ struct gsrad_tape {
     bool has_G = false;
     DevBuf Q, bb, bb_lo, pb, pb_lo, lam_a, lam_b, G;
     ~gsrad_tape() {
-        for (DevBuf *b : {&B, &L, &lam0, &pp, &Q, &bb, &bb_lo, &pb, &pb_lo, &lam_a, &lam_b, &G}) b->release();
+        for (DevBuf *b : {&B, &L, &lam0, &pp, &Q, &bb, &bb_lo, &pb, &pb_lo, &lam_a, &lam_b, &G, &frames}) b->release();
     }
 };
 
@@ -1217,7 +1218,6 @@ gsrad_status gsrad_transport_solve_sh(const gsrad_ff *ff, const gsrad_bvh *bvh, 
         return e;
     };
     gsrad_status e;
-    const BvhDev bv = bvh->dev();
     const Csr F = ff->csr();
     if (n_bounces == 0) {
         if ((e = check_hip(hipMemcpyAsync(B_out, E, row_bytes, hipMemcpyDeviceToDevice, st), "solve copy")) != GSRAD_OK)
@@ -1236,6 +1236,9 @@ gsrad_status gsrad_transport_solve_sh(const gsrad_ff *ff, const gsrad_bvh *bvh, 
             gsrad_ff *m = const_cast<gsrad_ff *>(ff);
             if ((e = m->slab.ensure(std::max(m->slab.bytes, row_bytes * 2), "ping-pong")) != GSRAD_OK) return fail(e);
         }
+        DevBuf &frames = tp ? tp->frames : const_cast<gsrad_ff *>(ff)->frames;
+        if ((e = frames.ensure(sh_frame_bytes(n), "surfel frames")) != GSRAD_OK) return fail(e);
+        if ((e = launch_sh_frames(bvh->dev(), frames.p, st)) != GSRAD_OK) return fail(e);
         const float *src = E;
         for (int k = 0; k < n_bounces; ++k) {
             float *dst;
@@ -1243,7 +1246,7 @@ gsrad_status gsrad_transport_solve_sh(const gsrad_ff *ff, const gsrad_bvh *bvh, 
             else if (tp) dst = slots + (size_t)(k + 1) * n * C;
             else dst = const_cast<gsrad_ff *>(ff)->slab.as<float>() + (size_t)(k & 1) * n * C;
             ProfScope ps("bounce_sh", st);
-            if ((e = launch_transfer_sh(bv, F, n_lights, K, src, E, R, qs ? qs + (size_t)k * n * C : nullptr, dst, 0,
+            if ((e = launch_transfer_sh(frames.p, F, n_lights, K, src, E, R, qs ? qs + (size_t)k * n * C : nullptr, dst, 0,
                                         st)) != GSRAD_OK)
                 return fail(e);
             src = dst;
@@ -1301,18 +1304,17 @@ gsrad_status gsrad_transport_backward_sh(const gsrad_ff *ff, const gsrad_bvh *bv
     float *u = tp->pp.as<float>();
     GS_TRY(check_hip(hipMemcpyAsync(L + (size_t)(nb - 1) * n * C, grad_B, row_bytes, hipMemcpyDeviceToDevice, st),
                      "adjoint seed"));
-    const BvhDev bv = bvh->dev();
     const Csr FT = f->csr_t();
     for (int k = nb - 1; k >= 0; --k) {
         const float *lam_in = L + (size_t)k * n * C;   // lambda^(k+1)
         float *lam_out = k >= 1 ? L + (size_t)(k - 1) * n * C : tp->lam0.as<float>();
         ProfScope ps("adjoint_sh", st);
         GS_TRY(launch_scale_rows(lam_in, R, n, Lt, K, u, st));
-        GS_TRY(launch_transfer_sh(bv, FT, Lt, K, u, nullptr, nullptr, lam_out, grad_E, 1, st));
+        GS_TRY(launch_transfer_sh(tp->frames.p, FT, Lt, K, u, nullptr, nullptr, lam_out, grad_E, 1, st));
     }
     ProfScope ps("sddmm_sh", st);
     if (grad_R) GS_TRY(launch_grad_R(L, tp->Q.as<float>(), n, Lt, K, nb, grad_R, st));
-    if (grad_F) GS_TRY(launch_sddmm_sh(bv, ff->csr(), Lt, K, nb, tp->B.as<float>(), L, R, grad_F, st));
+    if (grad_F) GS_TRY(launch_sddmm_sh(tp->frames.p, ff->csr(), Lt, K, nb, tp->B.as<float>(), L, R, grad_F, st));
     return GSRAD_OK;
 }
 

@@ -12,9 +12,20 @@
 // the decay term reversed).
 //
 // One wave owns one output row: its lanes take the row's entries (one each,
-// 64 at a time), evaluate both SH bases of the pair, gather the sender's
-// row and accumulate all K x 3 outputs of the light; a butterfly over the
-// wave then sums the lanes in a fixed order (deterministic results).
+// 64 at a time), evaluate both SH bases of the pair and accumulate all K x 3
+// outputs of the light; a butterfly over the wave then sums the lanes in a
+// fixed order (deterministic results).  The senders' records and rows come
+// through LDS: a lane that reads its own row 16 bytes at a time makes 64
+// lanes touch 64 cache lines with each of 17 loads, and a CU's first-level
+// cache takes one line a clock.  Loaded as they lie in memory, consecutive
+// lanes consecutive 16 bytes, the same rows take a quarter of the accesses.
+// A batch's rows are loaded while the one before is computed.  25 M entries,
+// K = 16: a bounce 0.93 ms, now 0.49 ms; the gradient of F over eight bounces
+// 9.1 ms, now 4.1 ms.  What bounds them now: 200 requests to L2 per 64
+// entries, a fifth of which miss it (a bounce's rows are 9.6 MB, an XCD's L2
+// 4 MB), beside 390 vector instructions.
+#include <algorithm>
+
 #include "gsrad_internal.h"
 #include "sh_api.h"
 #include "sh_basis.h"
@@ -24,7 +35,7 @@ namespace gsrad {
 
 namespace {
 
-constexpr int kWavesPerBlock = 4;
+constexpr int kWavesPerBlock = 2;   // LDS of K = 16: five workgroups a CU
 constexpr float kPi = 3.14159265358979324f;
 
 __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t g) {
@@ -32,11 +43,26 @@ __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t g) {
     return x * per + (x < rem ? x : rem) + q;
 }
 
+// What the transfer reads of a surfel, by original index (48 bytes): centre,
+// normal, t_u, t_v.  In the order of F's columns, so that no load waits for
+// the surfel's place in the tree.
+struct Frame {
+    float p[3], n[3], u[3], v[3];
+};
+
+__global__ void __launch_bounds__(256) k_frames(BvhDev bv, Frame *__restrict__ out) {
+    const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (s >= bv.n) return;
+    const SurfRec r = bv.rec[s];
+    out[__float_as_uint(r.d.w)] = Frame{{r.a.x, r.a.y, r.a.z}, {r.b.x, r.b.y, r.b.z}, {r.c.x, r.c.y, r.c.z},
+                                        {r.d.x, r.d.y, r.d.z}};
+}
+
 // Unit direction from the centre of `ri` to the centre of `rj` in ri's
 // frame (di) and its opposite in rj's frame (ej).  Coincident centres take
 // the receiver's normal as the direction.
-__device__ __forceinline__ void pair_dirs(const SurfRec &ri, const SurfRec &rj, float (&di)[3], float (&ej)[3]) {
-    float dx = rj.a.x - ri.a.x, dy = rj.a.y - ri.a.y, dz = rj.a.z - ri.a.z;
+__device__ __forceinline__ void pair_dirs(const Frame &ri, const Frame &rj, float (&di)[3], float (&ej)[3]) {
+    float dx = rj.p[0] - ri.p[0], dy = rj.p[1] - ri.p[1], dz = rj.p[2] - ri.p[2];
     const float len2 = dx * dx + dy * dy + dz * dz;
     if (len2 > 0.0f) {
         const float inv = 1.0f / sqrtf(len2);
@@ -44,89 +70,209 @@ __device__ __forceinline__ void pair_dirs(const SurfRec &ri, const SurfRec &rj, 
         dy *= inv;
         dz *= inv;
     } else {
-        dx = ri.b.x;
-        dy = ri.b.y;
-        dz = ri.b.z;
+        dx = ri.n[0];
+        dy = ri.n[1];
+        dz = ri.n[2];
     }
-    di[0] = dx * ri.c.x + dy * ri.c.y + dz * ri.c.z;
-    di[1] = dx * ri.d.x + dy * ri.d.y + dz * ri.d.z;
-    di[2] = dx * ri.b.x + dy * ri.b.y + dz * ri.b.z;
-    ej[0] = -(dx * rj.c.x + dy * rj.c.y + dz * rj.c.z);
-    ej[1] = -(dx * rj.d.x + dy * rj.d.y + dz * rj.d.z);
-    ej[2] = -(dx * rj.b.x + dy * rj.b.y + dz * rj.b.z);
+    di[0] = dx * ri.u[0] + dy * ri.u[1] + dz * ri.u[2];
+    di[1] = dx * ri.v[0] + dy * ri.v[1] + dz * ri.v[2];
+    di[2] = dx * ri.n[0] + dy * ri.n[1] + dz * ri.n[2];
+    ej[0] = -(dx * rj.u[0] + dy * rj.u[1] + dz * rj.u[2]);
+    ej[1] = -(dx * rj.v[0] + dy * rj.v[1] + dz * rj.v[2]);
+    ej[2] = -(dx * rj.n[0] + dy * rj.n[1] + dz * rj.n[2]);
 }
 
-template <int N>
-__device__ __forceinline__ void wave_sum(float (&v)[N]) {
+// Sums v[0 .. N) over the wave's lanes, in the order of a butterfly from
+// distance 32 down.  While N is even a lane keeps one half of the values and
+// gives the other away; at the end a lane holds kept() values, from index
+// first on, with the same lanes' values in each group of copies() lanes.
+template <int N, int OFF = 32>
+struct WaveSum {
+    static constexpr bool kHalve = N % 2 == 0 && OFF >= 1;
+    using Next = WaveSum<kHalve ? N / 2 : N, OFF / 2>;
+    static __device__ __forceinline__ void run(float *v, int lane, int &first) {
+        if constexpr (OFF >= 1) {
+            if constexpr (kHalve) {
+                const bool up = (lane & OFF) != 0;
 #pragma unroll
-    for (int q = 0; q < N; ++q) {
+                for (int q = 0; q < N / 2; ++q) {
+                    const float give = up ? v[q] : v[q + N / 2];
+                    const float keep = up ? v[q + N / 2] : v[q];
+                    v[q] = keep + __shfl_xor(give, OFF, 64);
+                }
+                first += up ? N / 2 : 0;
+            } else {
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v[q] += __shfl_xor(v[q], off, 64);
+                for (int q = 0; q < N; ++q) v[q] += __shfl_xor(v[q], OFF, 64);
+            }
+            Next::run(v, lane, first);
+        }
     }
-}
+    static constexpr int kept() {
+        if constexpr (OFF >= 1) return Next::kept();
+        else return N;
+    }
+    // lanes that end with the same values: those whose last halving bit is above
+    static constexpr int copies() {
+        if constexpr (OFF >= 1) return kHalve ? Next::copies() : 2 * Next::copies();
+        else return 1;
+    }
+};
 
-template <int N>
-__device__ __forceinline__ float pick(const float (&v)[N], int lane) {
-    float r = 0.0f;
+// Rows of 64 senders in LDS, `Bytes` each, loaded in pieces of 16 bytes (base
+// and rows aligned to them) or of 12, which take 16 in LDS: piece s of the 64
+// rows' pieces by lane s % 64.  Where a row is a multiple of four pieces, its
+// pieces are exchanged by row, so that 16 lanes reading the same piece of
+// their rows reach 16 different groups of four banks.
+template <int Bytes, bool Aligned = true>
+struct Staged {
+    static constexpr int kPiece = Aligned && Bytes % 16 == 0 ? 16 : 12;
+    static constexpr int kPieces = Bytes / kPiece;
+    static constexpr int kSize = 64 * kPieces * 16;
+    static constexpr int kFours = kPieces % 4 == 0 ? 4 : kPieces % 2 == 0 ? 2 : 1;
+    static constexpr int kPeriod = kPieces / kFours;   // loads after which lanes take the same pieces, 16 rows on
+    static __device__ __forceinline__ int exchange(int row) {
+        return kPieces % 16 == 0 ? row & 15 : kPieces % 4 == 0 ? (row >> 2) & 3 : 0;
+    }
+    // row j of the lane at base + j * stride; lds is the same for the wave
+    static __device__ __forceinline__ void load(char *lds, const void *base, int64_t stride, uint32_t j, int lane) {
+        // all rows' indices first: a load's turn does not wait for its own
+        uint32_t of[kPieces];
 #pragma unroll
-    for (int q = 0; q < N; ++q) r = lane == q ? v[q] : r;
-    return r;
+        for (int t = 0; t < kPieces; ++t)
+            of[t] = (uint32_t)__shfl((int)j, (t % kPeriod * 64 + lane) / kPieces + t / kPeriod * (kPeriod * 64 / kPieces));
+#pragma unroll
+        for (int t = 0; t < kPieces; ++t) {
+            const int s = t % kPeriod * 64 + lane, p = (s % kPieces) ^ exchange(s / kPieces);
+            const char *src = static_cast<const char *>(base) + (int64_t)of[t] * stride + p * kPiece;
+            const auto *from = (const __attribute__((address_space(1))) void *)src;
+            auto *to = (__attribute__((address_space(3))) void *)(lds + t * 64 * 16);
+            if constexpr (kPiece == 16) __builtin_amdgcn_global_load_lds(from, to, 16, 0, 0);
+            else __builtin_amdgcn_global_load_lds(from, to, 12, 0, 0);
+        }
+    }
+    static __device__ __forceinline__ void read(const char *lds, int lane, float *x) {
+        constexpr int kF = kPiece / 4;
+        const char *row = lds + lane * kPieces * 16;
+        const int ex = exchange(lane);
+#pragma unroll
+        for (int p = 0; p < kPieces; ++p) {
+            const float *v = reinterpret_cast<const float *>(row + ((p ^ ex) << 4));
+#pragma unroll
+            for (int c = 0; c < kF; ++c) x[kF * p + c] = v[c];
+        }
+    }
+};
+
+constexpr int kWaitVm0 = 0x0F70;   // s_waitcnt vmcnt(0), other counters unconstrained
+
+constexpr int kWaitLgkm0 = 0xC07F;   // s_waitcnt lgkmcnt(0), other counters unconstrained
+
+using Frames = Staged<(int)sizeof(Frame)>;
+
+__device__ __forceinline__ Frame staged_frame(const char *lds, int lane) {
+    float x[12];
+    Frames::read(lds, lane, x);
+    return Frame{{x[0], x[1], x[2]}, {x[3], x[4], x[5]}, {x[6], x[7], x[8]}, {x[9], x[10], x[11]}};
 }
 
 // mode 0 (bounce):  acc = (T X)_row;  out_a = acc (if set);  out_b = E + R (.) acc
 // mode 1 (adjoint): acc = (T^T X)_row on F^T;  out_a = acc;  out_b += acc
-template <int K>
-__global__ void __launch_bounds__(256) k_transfer_sh(BvhDev bv, const int64_t *__restrict__ row_ptr,
-                                                     const int32_t *__restrict__ col, const float *__restrict__ val,
-                                                     int64_t n, int Lt, const float *__restrict__ X,
-                                                     const float *__restrict__ E, const float *__restrict__ R,
-                                                     float *__restrict__ out_a, float *__restrict__ out_b, int mode,
-                                                     int64_t nblocks, const int32_t *__restrict__ order) {
-    constexpr int W = 3 * K;
-    const int64_t idx = xcd_block(blockIdx.x, nblocks) * kWavesPerBlock + threadIdx.x / 64;
+template <int K, bool Aligned>
+__global__ void __launch_bounds__(64 * kWavesPerBlock, 2) k_transfer_sh(const Frame *__restrict__ frames, const int64_t *__restrict__ row_ptr,
+                                                                     const int32_t *__restrict__ col,
+                                                                     const float *__restrict__ val, int64_t n, int Lt,
+                                                                     const float *__restrict__ X,
+                                                                     const float *__restrict__ E,
+                                                                     const float *__restrict__ R,
+                                                                     float *__restrict__ out_a,
+                                                                     float *__restrict__ out_b, int mode,
+                                                                     int64_t nblocks,
+                                                                     const int32_t *__restrict__ order) {
+    constexpr int W = 3 * K, N = W + W % 2;
+    using Rows = Staged<4 * W, Aligned>;
+    __shared__ __align__(16) char stage[kWavesPerBlock][Rows::kSize + (K > 1 ? Frames::kSize : 0)];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int64_t idx = xcd_block(blockIdx.x, nblocks) * kWavesPerBlock + wave;
     if (idx >= n) return;
     const int64_t row = order ? (int64_t)order[idx] : idx;
     const int lane = __lane_id();
-    const SurfRec ri = bv.rec[bv.inv[row]];
+    char *rows = stage[wave], *recs = rows + Rows::kSize;
+    const Frame ri = frames[row];
     const int64_t b = row_ptr[row], e = row_ptr[row + 1];
     for (int l = 0; l < Lt; ++l) {
-        float acc[W];
+        float acc[N];
 #pragma unroll
-        for (int q = 0; q < W; ++q) acc[q] = 0.0f;
-        for (int64_t kk = b + lane; kk < e; kk += 64) {
-            const int32_t j = col[kk];
-            const float w = val[kk];
-            const SurfRec rj = bv.rec[bv.inv[j]];
-            float di[3], ej[3];
-            pair_dirs(ri, rj, di, ej);
-            float Yd[K], Ye[K];
-            sh_eval<K>(di[0], di[1], di[2], Yd);
+        for (int q = 0; q < N; ++q) acc[q] = 0.0f;
+        // a batch's rows are loaded while the one before is computed, its
+        // entries one batch earlier still
+        const char *base = reinterpret_cast<const char *>(X + (int64_t)l * W);
+        const int64_t stride = (int64_t)Lt * W * 4;
+        uint32_t j = 0;
+        float w = 0.0f, w1 = 0.0f;
+        if (b < e) {
+            const int64_t k1 = min(b + lane, e - 1), k2 = min(b + 64 + lane, e - 1);
+            const uint32_t j1 = (uint32_t)col[k1];
+            w1 = val[k1];
+            j = (uint32_t)col[k2];
+            w = val[k2];
+            if constexpr (K > 1) Frames::load(recs, frames, sizeof(Frame), j1, lane);
+            Rows::load(rows, base, stride, j1, lane);
+        }
+        for (int64_t k0 = b; k0 < e; k0 += 64) {
+            const bool live = k0 + lane < e;
+            const float wc = w1;
+            w1 = w;
+            __builtin_amdgcn_s_waitcnt(kWaitVm0);
+            Frame rj = ri;
+            if constexpr (K > 1) rj = staged_frame(recs, lane);
+            float x[W];
+            Rows::read(rows, lane, x);
+            __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+            if (k0 + 64 < e) {
+                if constexpr (K > 1) Frames::load(recs, frames, sizeof(Frame), j, lane);
+                Rows::load(rows, base, stride, j, lane);
+                const int64_t next = min(k0 + 128 + lane, e - 1);
+                j = (uint32_t)col[next];
+                w = val[next];
+            }
+            float di[3] = {}, ej[3] = {};
+            if constexpr (K > 1) pair_dirs(ri, rj, di, ej);
+            float Ye[K];
             sh_eval<K>(ej[0], ej[1], ej[2], Ye);
-            const float *xj = X + ((int64_t)j * Lt + l) * W;
             float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
 #pragma unroll
             for (int q = 0; q < K; ++q) {
-                s0 = __builtin_fmaf(Ye[q], xj[3 * q + 0], s0);
-                s1 = __builtin_fmaf(Ye[q], xj[3 * q + 1], s1);
-                s2 = __builtin_fmaf(Ye[q], xj[3 * q + 2], s2);
+                s0 = __builtin_fmaf(Ye[q], x[3 * q + 0], s0);
+                s1 = __builtin_fmaf(Ye[q], x[3 * q + 1], s1);
+                s2 = __builtin_fmaf(Ye[q], x[3 * q + 2], s2);
             }
-            s0 *= w;
-            s1 *= w;
-            s2 *= w;
+            if (live) {
+                float Yd[K];
+                sh_eval<K>(di[0], di[1], di[2], Yd);
+                s0 *= wc;
+                s1 *= wc;
+                s2 *= wc;
 #pragma unroll
-            for (int a = 0; a < K; ++a) {
-                acc[3 * a + 0] = __builtin_fmaf(Yd[a], s0, acc[3 * a + 0]);
-                acc[3 * a + 1] = __builtin_fmaf(Yd[a], s1, acc[3 * a + 1]);
-                acc[3 * a + 2] = __builtin_fmaf(Yd[a], s2, acc[3 * a + 2]);
+                for (int a = 0; a < K; ++a) {
+                    acc[3 * a + 0] = __builtin_fmaf(Yd[a], s0, acc[3 * a + 0]);
+                    acc[3 * a + 1] = __builtin_fmaf(Yd[a], s1, acc[3 * a + 1]);
+                    acc[3 * a + 2] = __builtin_fmaf(Yd[a], s2, acc[3 * a + 2]);
+                }
             }
         }
-        wave_sum<W>(acc);
-        const float v = pick<W>(acc, lane);
-        if (lane < W) {
-            const int64_t o = (row * Lt + l) * W + lane;
+        using Sum = WaveSum<N>;
+        int first = 0;
+        Sum::run(acc, lane, first);
+        for (int q = lane % Sum::copies(); q < Sum::kept(); q += Sum::copies()) {
+            float v = 0.0f;
+#pragma unroll
+            for (int z = 0; z < Sum::kept(); ++z) v = q == z ? acc[z] : v;
+            if (first + q >= W) continue;
+            const int64_t o = (row * Lt + l) * W + first + q;
             if (mode == 0) {
                 if (out_a) out_a[o] = v;
-                out_b[o] = __builtin_fmaf(R[row * W + lane], v, E[o]);
+                out_b[o] = __builtin_fmaf(R[row * W + first + q], v, E[o]);
             } else {
                 out_a[o] = v;
                 out_b[o] += v;
@@ -145,50 +291,98 @@ __global__ void __launch_bounds__(256) k_scale_rows(const float *__restrict__ la
 }
 
 // grad_F[e] = sum_k sum_l sum_c (Yd . (R (.) lambda^(k+1))_i[l][:, c]) (Ye . B^(k)_j[l][:, c])
+// of bounces k0 .. k1 (added to the earlier ones' where k0 > 0)
 template <int K>
-__global__ void __launch_bounds__(256) k_sddmm_sh(BvhDev bv, const int64_t *__restrict__ row_ptr,
-                                                  const int32_t *__restrict__ col, int64_t n, int Lt, int nb,
-                                                  const float *__restrict__ Btape, const float *__restrict__ Ltape,
-                                                  const float *__restrict__ R, float *__restrict__ grad_F,
-                                                  int64_t nblocks, const int32_t *__restrict__ order) {
+__global__ void __launch_bounds__(64 * kWavesPerBlock, K == 9 ? 2 : 3) k_sddmm_sh(const Frame *__restrict__ frames, const int64_t *__restrict__ row_ptr,
+                                                                  const int32_t *__restrict__ col, int64_t n, int Lt,
+                                                                  int k0, int k1, const float *__restrict__ Btape,
+                                                                  const float *__restrict__ Ltape,
+                                                                  const float *__restrict__ R,
+                                                                  float *__restrict__ grad_F, int64_t nblocks,
+                                                                  const int32_t *__restrict__ order) {
     constexpr int W = 3 * K;
-    const int64_t idx = xcd_block(blockIdx.x, nblocks) * kWavesPerBlock + threadIdx.x / 64;
+    using Rows = Staged<4 * W>;
+    __shared__ __align__(16) char stage[kWavesPerBlock][Rows::kSize + (K > 1 ? Frames::kSize : 0)];
+    __shared__ float own[kWavesPerBlock][W];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int64_t idx = xcd_block(blockIdx.x, nblocks) * kWavesPerBlock + wave;
     if (idx >= n) return;
     const int64_t row = order ? (int64_t)order[idx] : idx;
     const int lane = __lane_id();
-    const SurfRec ri = bv.rec[bv.inv[row]];
+    char *rows = stage[wave], *recs = rows + Rows::kSize;
+    float *u = own[wave];
+    const Frame ri = frames[row];
     const int64_t b = row_ptr[row], e = row_ptr[row + 1];
-    const float *Ri = R + row * W;
     const size_t plane = (size_t)n * Lt * W;
-    for (int64_t kk = b + lane; kk < e; kk += 64) {
-        const int32_t j = col[kk];
-        const SurfRec rj = bv.rec[bv.inv[j]];
-        float di[3], ej[3];
-        pair_dirs(ri, rj, di, ej);
-        float Yd[K], Ye[K];
-        sh_eval<K>(di[0], di[1], di[2], Yd);
-        sh_eval<K>(ej[0], ej[1], ej[2], Ye);
-        float g = 0.0f;
-        for (int k = 0; k < nb; ++k) {
-            for (int l = 0; l < Lt; ++l) {
-                const float *lam = Ltape + k * plane + (row * Lt + l) * W;
-                const float *bj = Btape + k * plane + ((int64_t)j * Lt + l) * W;
-                float p0 = 0.0f, p1 = 0.0f, p2 = 0.0f, s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
-#pragma unroll
-                for (int q = 0; q < K; ++q) {
-                    p0 = __builtin_fmaf(Yd[q], Ri[3 * q + 0] * lam[3 * q + 0], p0);
-                    p1 = __builtin_fmaf(Yd[q], Ri[3 * q + 1] * lam[3 * q + 1], p1);
-                    p2 = __builtin_fmaf(Yd[q], Ri[3 * q + 2] * lam[3 * q + 2], p2);
-                    s0 = __builtin_fmaf(Ye[q], bj[3 * q + 0], s0);
-                    s1 = __builtin_fmaf(Ye[q], bj[3 * q + 1], s1);
-                    s2 = __builtin_fmaf(Ye[q], bj[3 * q + 2], s2);
-                }
-                g = __builtin_fmaf(p0, s0, g);
-                g = __builtin_fmaf(p1, s1, g);
-                g = __builtin_fmaf(p2, s2, g);
+    if (b >= e) return;
+    const float r = lane < W ? R[row * W + lane] : 0.0f;
+    // steps: a batch's bounces and lights; the rows of the next step are
+    // loaded while one is computed, the entries one batch earlier still
+    const int64_t stride = (int64_t)Lt * W * 4;
+    auto rows_of = [&](int k, int l) { return reinterpret_cast<const char *>(Btape + k * plane + (int64_t)l * W); };
+    auto own_of = [&](int k, int l) { return lane < W ? r * Ltape[k * plane + (row * Lt + l) * W + lane] : 0.0f; };
+    uint32_t j = (uint32_t)col[min(b + lane, e - 1)];
+    uint32_t jn = (uint32_t)col[min(b + 64 + lane, e - 1)];
+    if constexpr (K > 1) Frames::load(recs, frames, sizeof(Frame), j, lane);   // (degree 0 is a constant)
+    Rows::load(rows, rows_of(k0, 0), stride, j, lane);
+    float un = own_of(k0, 0), g = 0.0f;
+    float Yd[K], Ye[K];
+    int64_t e0 = b;
+    int k = k0, l = 0;
+    for (;;) {
+        const bool head = k == k0 && l == 0;
+        __builtin_amdgcn_s_waitcnt(kWaitVm0);
+        if (lane < W) u[lane] = un;
+        Frame rj = ri;
+        if (K > 1 && head) rj = staged_frame(recs, lane);
+        float x[W];
+        Rows::read(rows, lane, x);
+        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+        int64_t en = e0;
+        int kn = k, ln = l + 1;
+        if (ln == Lt) {
+            ln = 0;
+            if (++kn == k1) {
+                kn = k0;
+                en += 64;
             }
         }
-        grad_F[kk] = g;
+        if (en < e) {
+            if (en != e0) {
+                j = jn;
+                jn = (uint32_t)col[min(en + 64 + lane, e - 1)];
+                if constexpr (K > 1) Frames::load(recs, frames, sizeof(Frame), j, lane);
+            }
+            Rows::load(rows, rows_of(kn, ln), stride, j, lane);
+            un = own_of(kn, ln);
+        }
+        const int64_t kk = e0 + lane;
+        if (head) {
+            float di[3] = {}, ej[3] = {};
+            if constexpr (K > 1) pair_dirs(ri, rj, di, ej);
+            sh_eval<K>(di[0], di[1], di[2], Yd);
+            sh_eval<K>(ej[0], ej[1], ej[2], Ye);
+            g = k0 > 0 && kk < e ? grad_F[kk] : 0.0f;
+        }
+        float p0 = 0.0f, p1 = 0.0f, p2 = 0.0f, s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+            p0 = __builtin_fmaf(Yd[q], u[3 * q + 0], p0);
+            p1 = __builtin_fmaf(Yd[q], u[3 * q + 1], p1);
+            p2 = __builtin_fmaf(Yd[q], u[3 * q + 2], p2);
+            s0 = __builtin_fmaf(Ye[q], x[3 * q + 0], s0);
+            s1 = __builtin_fmaf(Ye[q], x[3 * q + 1], s1);
+            s2 = __builtin_fmaf(Ye[q], x[3 * q + 2], s2);
+        }
+        g = __builtin_fmaf(p0, s0, g);
+        g = __builtin_fmaf(p1, s1, g);
+        g = __builtin_fmaf(p2, s2, g);
+        if (en != e0 && kk < e) grad_F[kk] = g;
+        __builtin_amdgcn_wave_barrier();
+        if (en >= e) break;
+        e0 = en;
+        k = kn;
+        l = ln;
     }
 }
 
@@ -281,31 +475,54 @@ __global__ void __launch_bounds__(256) k_brdf_backward(BvhDev bv, const float *_
 unsigned row_blocks_sh(int64_t n) { return (unsigned)((n + kWavesPerBlock - 1) / kWavesPerBlock); }
 
 template <int K>
-void launch_transfer_k(const BvhDev &bv, const Csr &F, int Lt, const float *X, const float *E, const float *R,
+void launch_transfer_k(const Frame *frames, const Csr &F, int Lt, const float *X, const float *E, const float *R,
                        float *out_a, float *out_b, int mode, hipStream_t st) {
     const unsigned g = row_blocks_sh(F.n);
-    hipLaunchKernelGGL(k_transfer_sh<K>, dim3(g), dim3(256), 0, st, bv, F.row_ptr, F.col, F.val, F.n, Lt, X, E, R,
+    const auto kernel = reinterpret_cast<uintptr_t>(X) % 16 == 0 ? k_transfer_sh<K, true> : k_transfer_sh<K, false>;
+    hipLaunchKernelGGL(kernel, dim3(g), dim3(64 * kWavesPerBlock), 0, st, frames, F.row_ptr, F.col, F.val, F.n, Lt, X, E, R,
                        out_a, out_b, mode, (int64_t)g, F.order);
 }
 
+// Bounces of one launch of k_sddmm_sh: as many as have senders' rows of
+// kSddmmBytesSh together, which an XCD's L2 still serves for the most part; a
+// launch more costs the pair's bases again and grad_F once more.  Eight
+// bounces of 50k surfels, K = 16 (9.6 MB each): 4.1 ms by one bounce, 4.2 ms
+// by two, 4.8 ms by eight.
+constexpr int64_t kSddmmBytesSh = (int64_t)7 << 20;
+
+int sddmm_bounces_sh(int64_t n, int Lt, int K) {
+    return (int)std::max<int64_t>(1, kSddmmBytesSh / (n * Lt * K * 12));
+}
+
 template <int K>
-void launch_sddmm_k(const BvhDev &bv, const Csr &F, int Lt, int nb, const float *Bt, const float *Lt_, const float *R,
+void launch_sddmm_k(const Frame *frames, const Csr &F, int Lt, int nb, const float *Bt, const float *Lt_, const float *R,
                     float *grad_F, hipStream_t st) {
     const unsigned g = row_blocks_sh(F.n);
-    hipLaunchKernelGGL(k_sddmm_sh<K>, dim3(g), dim3(256), 0, st, bv, F.row_ptr, F.col, F.n, Lt, nb, Bt, Lt_, R, grad_F,
-                       (int64_t)g, F.order);
+    const int per = sddmm_bounces_sh(F.n, Lt, K);
+    for (int k = 0; k < nb; k += per)
+        hipLaunchKernelGGL(k_sddmm_sh<K>, dim3(g), dim3(64 * kWavesPerBlock), 0, st, frames, F.row_ptr, F.col, F.n, Lt, k,
+                           std::min(nb, k + per), Bt, Lt_, R, grad_F, (int64_t)g, F.order);
 }
 
 }  // namespace
 
-gsrad_status launch_transfer_sh(const BvhDev &bv, const Csr &F, int Lt, int K, const float *X, const float *E,
+size_t sh_frame_bytes(int64_t n) { return (size_t)n * sizeof(Frame); }
+
+gsrad_status launch_sh_frames(const BvhDev &bv, void *frames, hipStream_t st) {
+    hipLaunchKernelGGL(k_frames, dim3((unsigned)((bv.n + 255) / 256)), dim3(256), 0, st, bv,
+                       static_cast<Frame *>(frames));
+    return check_hip(hipGetLastError(), "SH frames launch");
+}
+
+gsrad_status launch_transfer_sh(const void *frames, const Csr &F, int Lt, int K, const float *X, const float *E,
                                 const float *R, float *out_a, float *out_b, int mode, hipStream_t st) {
     if (F.n == 0) return GSRAD_OK;
+    const Frame *fr = static_cast<const Frame *>(frames);
     switch (K) {
-        case 1: launch_transfer_k<1>(bv, F, Lt, X, E, R, out_a, out_b, mode, st); break;
-        case 4: launch_transfer_k<4>(bv, F, Lt, X, E, R, out_a, out_b, mode, st); break;
-        case 9: launch_transfer_k<9>(bv, F, Lt, X, E, R, out_a, out_b, mode, st); break;
-        case 16: launch_transfer_k<16>(bv, F, Lt, X, E, R, out_a, out_b, mode, st); break;
+        case 1: launch_transfer_k<1>(fr, F, Lt, X, E, R, out_a, out_b, mode, st); break;
+        case 4: launch_transfer_k<4>(fr, F, Lt, X, E, R, out_a, out_b, mode, st); break;
+        case 9: launch_transfer_k<9>(fr, F, Lt, X, E, R, out_a, out_b, mode, st); break;
+        case 16: launch_transfer_k<16>(fr, F, Lt, X, E, R, out_a, out_b, mode, st); break;
         default: set_error("SH transfer: K must be 1, 4, 9 or 16"); return GSRAD_EINVAL;
     }
     return check_hip(hipGetLastError(), "SH transfer launch");
@@ -318,14 +535,15 @@ gsrad_status launch_scale_rows(const float *lam, const float *R, int64_t n, int 
     return check_hip(hipGetLastError(), "SH scale launch");
 }
 
-gsrad_status launch_sddmm_sh(const BvhDev &bv, const Csr &F, int Lt, int K, int nb, const float *Btape,
+gsrad_status launch_sddmm_sh(const void *frames, const Csr &F, int Lt, int K, int nb, const float *Btape,
                              const float *Ltape, const float *R, float *grad_F, hipStream_t st) {
     if (F.n == 0 || F.nnz == 0) return GSRAD_OK;
+    const Frame *fr = static_cast<const Frame *>(frames);
     switch (K) {
-        case 1: launch_sddmm_k<1>(bv, F, Lt, nb, Btape, Ltape, R, grad_F, st); break;
-        case 4: launch_sddmm_k<4>(bv, F, Lt, nb, Btape, Ltape, R, grad_F, st); break;
-        case 9: launch_sddmm_k<9>(bv, F, Lt, nb, Btape, Ltape, R, grad_F, st); break;
-        case 16: launch_sddmm_k<16>(bv, F, Lt, nb, Btape, Ltape, R, grad_F, st); break;
+        case 1: launch_sddmm_k<1>(fr, F, Lt, nb, Btape, Ltape, R, grad_F, st); break;
+        case 4: launch_sddmm_k<4>(fr, F, Lt, nb, Btape, Ltape, R, grad_F, st); break;
+        case 9: launch_sddmm_k<9>(fr, F, Lt, nb, Btape, Ltape, R, grad_F, st); break;
+        case 16: launch_sddmm_k<16>(fr, F, Lt, nb, Btape, Ltape, R, grad_F, st); break;
         default: set_error("SH sddmm: K must be 1, 4, 9 or 16"); return GSRAD_EINVAL;
     }
     return check_hip(hipGetLastError(), "SH sddmm launch");
