@@ -137,13 +137,14 @@ struct gsrad_bvh {
     int64_t n = 0;               // 0 after a failed (re)build: unusable
     uint64_t gen = 0;            // unique per successful build
     hipStream_t stream = nullptr;
-    DevBuf rec, nodes, leafbox, leaf_parent, inv, cst, opc, opraw, area, dado, bounds, height, temp, lacc;
+    DevBuf rec, nodes, wide, leafbox, leaf_parent, inv, cst, opc, opraw, area, dado, bounds, height, temp, lacc;
     BvhBuffers B;
     BvhDev dev() const {
         BvhDev d;
         d.n = n;
         d.rec = B.rec;
         d.nodes = B.nodes;
+        d.wide = B.wide;
         d.inv = B.inv;
         d.c = B.cst;
         d.op = B.opc;
@@ -155,7 +156,7 @@ struct gsrad_bvh {
         return d;
     }
     ~gsrad_bvh() {
-        for (DevBuf *b : {&rec, &nodes, &leafbox, &leaf_parent, &inv, &cst, &opc, &opraw, &area, &dado, &bounds, &height,
+        for (DevBuf *b : {&rec, &nodes, &wide, &leafbox, &leaf_parent, &inv, &cst, &opc, &opraw, &area, &dado, &bounds, &height,
                           &temp, &lacc})
             b->release();
     }
@@ -471,6 +472,7 @@ gsrad_status gsrad_build_bvh(const gsrad_surfels *s, gsrad_bvh **bvh, void *stre
     if ((e = h->buf.ensure((size_t)(bytes), what)) != GSRAD_OK) return fail(e);
     ENS(rec, n * sizeof(SurfRec), "surfel records");
     ENS(nodes, std::max<int64_t>(n - 1, 1) * sizeof(Node), "bvh nodes");
+    ENS(wide, std::max<int64_t>(n - 1, 1) * sizeof(WideNode), "bvh wide nodes");
     ENS(leafbox, n * 6 * sizeof(float), "leaf boxes");
     ENS(leaf_parent, n * 4, "leaf parents");
     ENS(inv, n * 4, "inverse order");
@@ -487,6 +489,7 @@ gsrad_status gsrad_build_bvh(const gsrad_surfels *s, gsrad_bvh **bvh, void *stre
     BvhBuffers &B = h->B;
     B.rec = h->rec.as<SurfRec>();
     B.nodes = h->nodes.as<Node>();
+    B.wide = h->wide.as<WideNode>();
     B.leafbox = h->leafbox.as<float>();
     B.leaf_parent = h->leaf_parent.as<int32_t>();
     B.inv = h->inv.as<int32_t>();

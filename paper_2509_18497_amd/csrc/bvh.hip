@@ -268,16 +268,56 @@ __global__ void __launch_bounds__(kThreads) k_refit(const Node *__restrict__ nod
     }
 }
 
-__global__ void __launch_bounds__(kThreads) k_pack(Node *__restrict__ nodes, const float *__restrict__ leafbox,
-                                                   const float *__restrict__ nodebox, int64_t n) {
+// The children's boxes into the nodes, and the WideNodes beside them: planes in
+// steps of 1/65520 of the scene's box, moved out by one to two steps.  A step
+// is at least 2^-21 of the box's largest coordinate: what FP32 loses in
+// base + q step, and in the trace's (base - o) / d + q (step / d), is then at
+// most a fifth of a step.
+__global__ void __launch_bounds__(kThreads) k_pack(Node *__restrict__ nodes, WideNode *__restrict__ wide,
+                                                   const float *__restrict__ leafbox,
+                                                   const float *__restrict__ nodebox, float *__restrict__ bounds,
+                                                   int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= n - 1) return;
-    const int c0 = nodes[i].ch.x, c1 = nodes[i].ch.y;
-    const float *b0 = c0 < 0 ? leafbox + (int64_t)(~c0) * 6 : nodebox + (int64_t)c0 * 6;
-    const float *b1 = c1 < 0 ? leafbox + (int64_t)(~c1) * 6 : nodebox + (int64_t)c1 * 6;
+    auto box = [&](int c) { return c < 0 ? leafbox + (int64_t)(~c) * 6 : nodebox + (int64_t)c * 6; };
+    const int c[2] = {nodes[i].ch.x, nodes[i].ch.y};
+    const float *b0 = box(c[0]), *b1 = box(c[1]);
     nodes[i].b0 = make_float4(b0[0], b0[1], b0[2], b0[3]);
     nodes[i].b1 = make_float4(b0[4], b0[5], b1[0], b1[1]);
     nodes[i].b2 = make_float4(b1[2], b1[3], b1[4], b1[5]);
+    WideNode w;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        w.ch[2 * h] = c[h] < 0 ? c[h] : nodes[c[h]].ch.x;
+        w.ch[2 * h + 1] = c[h] < 0 ? kNoChild : nodes[c[h]].ch.y;
+    }
+    float base[3], step[3];   // (nodebox[0]: the root's; planes that are not finite end at the grid's)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const float lo = fmaxf(nodebox[k], -1e30f), hi = fminf(nodebox[3 + k], 1e30f);
+        step[k] = fmaxf(fmaxf((hi - lo) * (1.0f / 65520.0f), fmaxf(fabsf(lo), fabsf(hi)) * 0x1p-21f), 1e-35f);
+        base[k] = lo - 4.0f * step[k];
+        if (i == 0) {
+            bounds[8 + k] = base[k];
+            bounds[11 + k] = step[k];
+        }
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const float *b = box(w.ch[g] == kNoChild ? c[g / 2] : w.ch[g]);
+        uint32_t q[6];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const float lo = floorf((b[k] - base[k]) / step[k]) - 1.0f;
+            const float hi = ceilf((b[3 + k] - base[k]) / step[k]) + 1.0f;
+            q[k] = (uint32_t)fminf(fmaxf(lo, 0.0f), 65535.0f);
+            q[3 + k] = (uint32_t)fmaxf(fminf(hi, 65535.0f), 0.0f);
+        }
+        w.box[3 * g] = q[0] | q[1] << 16;
+        w.box[3 * g + 1] = q[2] | q[3] << 16;
+        w.box[3 * g + 2] = q[4] | q[5] << 16;
+    }
+    wide[i] = w;
 }
 
 inline unsigned nblk(int64_t n) { return (unsigned)((n + kThreads - 1) / kThreads); }
@@ -339,7 +379,8 @@ gsrad_status bvh_build(const gsrad_surfels &sf, BvhBuffers &B, hipStream_t st) {
         if (s != GSRAD_OK) return s;
         hipLaunchKernelGGL(k_refit, dim3(nblk(n)), dim3(kThreads), 0, st, B.nodes, B.leaf_parent, B.leafbox, nodebox,
                            height, counter, B.height, n);
-        hipLaunchKernelGGL(k_pack, dim3(nblk(n - 1)), dim3(kThreads), 0, st, B.nodes, B.leafbox, nodebox, n);
+        hipLaunchKernelGGL(k_pack, dim3(nblk(n - 1)), dim3(kThreads), 0, st, B.nodes, B.wide,
+                           B.leafbox, nodebox, B.bounds, n);
     }
     return check_hip(hipGetLastError(), "bvh build");
 }

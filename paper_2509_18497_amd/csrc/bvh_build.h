@@ -10,6 +10,7 @@ namespace gsrad {
 struct BvhBuffers {
     SurfRec *rec = nullptr;         // [n] sorted order
     Node *nodes = nullptr;          // [max(n-1,1)]
+    WideNode *wide = nullptr;       // [max(n-1,1)]
     float *leafbox = nullptr;       // [n][6] sorted order
     int32_t *leaf_parent = nullptr; // [n]
     int32_t *inv = nullptr;         // [n] original -> sorted
@@ -18,7 +19,7 @@ struct BvhBuffers {
     float *opraw = nullptr;         // [n] opacity as given
     double *area = nullptr;         // [n] App. E effective area
     float *dado = nullptr;          // [n] d area / d opacity (0 where the clamp is active)
-    float *bounds = nullptr;        // [8]
+    float *bounds = nullptr;        // [14]
     int *height = nullptr;          // [1] tree height
     void *temp = nullptr;
     size_t temp_bytes = 0;

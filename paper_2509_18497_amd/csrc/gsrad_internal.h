@@ -43,15 +43,27 @@ struct __align__(16) Node {
     int4 ch;
 };
 
+// What the form-factor trace reads instead: a node's four grandchildren (a
+// child that is a leaf stands for itself, its second place empty) in the same
+// 64 bytes, box planes in steps of a grid over the scene (bounds[8..10] base,
+// [11..13] step), rounded outwards.  Box k in words 3 k ... 3 k + 2:
+//   lo.x | lo.y << 16, lo.z | hi.x << 16, hi.y | hi.z << 16
+struct __align__(16) WideNode {
+    uint32_t box[12];
+    int32_t ch[4];   // as Node's, or kNoChild
+};
+constexpr int kNoChild = 0x7fffffff;
+
 struct BvhDev {
     int64_t n;
     const SurfRec *rec;      // [n] in sorted (Morton) order
     const Node *nodes;       // [n-1]
+    const WideNode *wide;    // [n-1]
     const int32_t *inv;      // [n] original index -> sorted position
     const float *c;          // [n] opacity constant c_j, original order
     const float *op;         // [n] clamped opacity, original order
     const float *raw_op;     // [n] opacity as given, original order
-    const float *bounds;     // [8]: lo.xyz, hi.xyz, t_eps, diag
+    const float *bounds;     // [14]: lo.xyz, hi.xyz, t_eps, diag, WideNode's base.xyz, step.xyz
     const double *area;      // [n] App. E effective area, original order
     const float *dado;       // [n] d area / d opacity, original order
     float leaf_box_r;        // unused padding for alignment
@@ -234,6 +246,20 @@ __device__ __forceinline__ bool slab(float lox, float loy, float loz, float hix,
     const float az = __builtin_fmaf(loz, iz, -oz_), bz = __builtin_fmaf(hiz, iz, -oz_);
     const float tmin = fmaxf(fmaxf(fminf(ax, bx), fminf(ay, by)), fmaxf(fminf(az, bz), t0));
     const float tmax = fminf(fminf(fmaxf(ax, bx), fmaxf(ay, by)), fminf(fmaxf(az, bz), t1));
+    tn = tmin;
+    return tmin <= tmax * 1.00001f + 1e-30f;
+}
+
+// The slab test on a WideNode's planes q: with s = step / d and b = (base - o) / d
+// a plane is at fma(q, s, b).
+__device__ __forceinline__ bool wide_slab(float lox, float loy, float loz, float hix, float hiy, float hiz, float sx,
+                                          float sy, float sz, float bx, float by, float bz, float t0, float t1,
+                                          float &tn) {
+    const float ax = __builtin_fmaf(lox, sx, bx), cx = __builtin_fmaf(hix, sx, bx);
+    const float ay = __builtin_fmaf(loy, sy, by), cy = __builtin_fmaf(hiy, sy, by);
+    const float az = __builtin_fmaf(loz, sz, bz), cz = __builtin_fmaf(hiz, sz, bz);
+    const float tmin = fmaxf(fmaxf(fminf(ax, cx), fminf(ay, cy)), fmaxf(fminf(az, cz), t0));
+    const float tmax = fminf(fminf(fmaxf(ax, cx), fmaxf(ay, cy)), fminf(fmaxf(az, cz), t1));
     tn = tmin;
     return tmin <= tmax * 1.00001f + 1e-30f;
 }

@@ -51,16 +51,21 @@ constexpr int kPoolBits = 8;
 constexpr int kPoolRays = 1 << kPoolBits;   // rays sorted and pooled per batch
 constexpr int kCompChunk = 5;     // buffered hits whose kernel values are found together
 // a wave composites once kFlushNum / kFlushDen of its lanes holding rays wait
-constexpr int kFlushNum = 3, kFlushDen = 8;
-// leaf children found by a node step wait in a per-lane queue of kLeafQ;
+constexpr int kFlushNum = 1, kFlushDen = 2;
+// leaf children found by a node step wait in a per-lane queue of kLeafQ (LDS);
 // a wave tests one queued leaf per lane once kLeafNum / kLeafDen of its
 // lanes holding rays have one (or a queue is full, or no lane can step), so
 // the costly leaf test and k-buffer insertion run with more lanes at once.
-// Measured on the 100k fruit bowl: queues of 8 and a composite at 3/8 best
-// (queue 6: +0.6 ms; composite at 1/2: +1.4 ms, at 1/4: +3.7 ms; leaf
-// steps at 3/4 as good as at 1/2, at 1/4 +6 ms).
-constexpr int kLeafQ = 8;
+// Measured on the 100k fruit bowl: queues of 8 / 12 / 16 / 20 48.7, 45.6, 44.4,
+// 43.9 ms; leaf steps at 1/2 as good as at 3/4, at 1/4 +2.5 ms; composite at
+// 1/4 +1.8 ms, at 3/8 +0.3, at 5/8 +0.9; a k-buffer of 16 +0.8, of 24 +2.6.
+constexpr int kLeafQ = 20;
 constexpr int kLeafNum = 1, kLeafDen = 2;
+// stack entries a lane of the trace: up to three a level of four grandchildren,
+// mostly one (a bowl of 1 M surfels, 29 levels of the binary tree, stays below
+// 29); a tree that needs more is traced again with the deep stack
+constexpr int kWideShallow = 32, kWideDeep = 96;
+constexpr size_t ff_trace_bytes(int stack) { return (size_t)(stack + kLeafQ) * 256 * sizeof(uint32_t); }
 
 // Lane index within the wave, recomputed at each use (volatile: not hoisted
 // out of the traversal loop into a register of its own).
@@ -114,6 +119,13 @@ __device__ __forceinline__ uint32_t next_pool(uint32_t *queue, int64_t npools, i
 // installed once, and a wave ends when all of its lanes have found kNoPool
 // and hold no ray.
 //
+// Bound by the latency of dependent node and leaf loads (12 waves a CU) and, at
+// half of the lanes on average, by the tests' vector instructions.  A node
+// step tests four grandchildren (WideNode), so a ray waits for half as many nodes: 12.8 M
+// rays of a 100k-surfel bowl 43.9 ms, one child pair of 64 bytes a step
+// 54.9 ms, of 32 bytes 53.9 ms (the lines fetched from L2 fell by a third, so
+// these do not bound it).
+//
 // Each lane walks its ray one node per iteration, queueing the leaves it
 // reaches; the wave tests queued leaves once half of its lanes hold one; a
 // lane whose k-buffer round ends waits until enough lanes of its wave
@@ -151,7 +163,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))
         uint32_t i = 0, q = 0;
         uint2 *rec_out = nullptr;
         uint32_t *cnt_out = nullptr;
-        float ox = 0.0f, oy = 0.0f, oz = 0.0f, dx = 0.0f, dy = 0.0f, dz = 0.0f, ix = 0.0f, iy = 0.0f, iz = 0.0f;
+        float ox = 0.0f, oy = 0.0f, oz = 0.0f, dx = 0.0f, dy = 0.0f, dz = 0.0f;
+        float sx = 0.0f, sy = 0.0f, sz = 0.0f, bx = 0.0f, by = 0.0f, bz = 0.0f;   // grid_slab's step / d, (base - o) / d
         float T = 1.0f, t0 = 0.0f, t1 = INFINITY;
         uint64_t last = 0;
         double key[kKB];
@@ -161,9 +174,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))
         // queued leaves (LIFO; the order of the leaf tests does not change
         // the round's buffer: it keeps the KB smallest keys whatever the
         // order), and whether the round's walk of the tree is done
-        int lq[kLeafQ];
-#pragma unroll
-        for (int k = 0; k < kLeafQ; ++k) lq[k] = 0;
         int qn = 0;
         bool walked = false;
         // a new k-buffer round from the root, beyond the last composited key
@@ -226,9 +236,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))
                         dx = __uint_as_float(ent.y);
                         dy = __uint_as_float(ent.z);
                         dz = __uint_as_float(ent.w);
-                        ix = safe_inv(dx);
-                        iy = safe_inv(dy);
-                        iz = safe_inv(dz);
+                        const float ix = safe_inv(dx), iy = safe_inv(dy), iz = safe_inv(dz);
+                        sx = bv.bounds[11] * ix;
+                        sy = bv.bounds[12] * iy;
+                        sz = bv.bounds[13] * iz;
+                        bx = (bv.bounds[8] - ox) * ix;
+                        by = (bv.bounds[9] - oy) * iy;
+                        bz = (bv.bounds[10] - oz) * iz;
                         q = 0;
                         T = 1.0f;
                         last = 0;
@@ -294,59 +308,67 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))
             }
             // node and leaf steps until a flush is due or a lane needs a ray
             for (;;) {
-                const bool can = trav && !walked && qn <= kLeafQ - 2;
+                const bool can = trav && !walked && qn <= kLeafQ - 4;
                 const int nq = __popcll(__ballot(qn > 0));
                 const bool leaf_step =
-                    nq > 0 && (kLeafDen * nq >= kLeafNum * nact || !__ballot(can) || __ballot(qn > kLeafQ - 2));
+                    nq > 0 && (kLeafDen * nq >= kLeafNum * nact || !__ballot(can) || __ballot(qn > kLeafQ - 4));
                 // per-lane conditions (a uniform if / else here made the
                 // compiler copy the k-buffer between register sets)
                 const bool do_leaf = leaf_step && qn > 0, do_node = !leaf_step && can;
                 if (do_leaf) {
                     --qn;
-                    int s = lq[0];
-#pragma unroll
-                    for (int k = 1; k < kLeafQ; ++k) s = qn == k ? lq[k] : s;
+                    const int s = (int)stack_mem[wave_base + lane_index() + (STK + qn) * 256];
                     visit_leaf<kKB>(bv.rec, s, i, ox, oy, oz, dx, dy, dz, t_eps, last, key, found, t1);
                 }
                 if (do_node) {
-                    const Node nd = bv.nodes[node];
-                    float tn0, tn1;
-                    bool h0 = slab(nd.b0.x, nd.b0.y, nd.b0.z, nd.b0.w, nd.b1.x, nd.b1.y, ox, oy, oz, ix, iy, iz, t0, t1, tn0);
-                    bool h1 = slab(nd.b1.z, nd.b1.w, nd.b2.x, nd.b2.y, nd.b2.z, nd.b2.w, ox, oy, oz, ix, iy, iz, t0, t1, tn1);
-                    const int c0 = nd.ch.x, c1 = nd.ch.y;
-                    auto queue_leaf = [&](int leaf) {
-#pragma unroll
-                        for (int k = 0; k < kLeafQ; ++k) lq[k] = qn == k ? leaf : lq[k];
-                        ++qn;
+                    const uint4 *nd = reinterpret_cast<const uint4 *>(bv.wide + node);
+                    const uint4 q0 = nd[0], q1 = nd[1], q2 = nd[2], q3 = nd[3];
+                    auto low = [](uint32_t v) { return (float)(v & 0xffffu); };
+                    auto high = [](uint32_t v) { return (float)(v >> 16); };
+                    auto test = [&](uint32_t x, uint32_t y, uint32_t z, float &tn) {
+                        return wide_slab(low(x), high(x), low(y), high(y), low(z), high(z), sx, sy, sz, bx, by, bz, t0,
+                                         t1, tn);
                     };
-                    if (h0 && c0 < 0) {
-                        queue_leaf(~c0);
-                        h0 = false;
+                    const int ch[4] = {(int)q3.x, (int)q3.y, (int)q3.z, (int)q3.w};
+                    float tn[4];
+                    bool h[4] = {test(q0.x, q0.y, q0.z, tn[0]), test(q0.w, q1.x, q1.y, tn[1]),
+                                 test(q1.z, q1.w, q2.x, tn[2]), test(q2.y, q2.z, q2.w, tn[3])};
+                    h[1] = h[1] && ch[1] != kNoChild;
+                    h[3] = h[3] && ch[3] != kNoChild;
+                    // leaves to the queue; the nearest node is next, the
+                    // others go on the stack; with none left, pop; an empty
+                    // stack ends the walk (the round ends once the queued
+                    // leaves are tested too).  A push past the stack's end
+                    // ends the ray with an error (the launch is repeated with
+                    // the deep stack).  The lane's column: the wave's base
+                    // (uniform) plus the lane index, read again here rather
+                    // than held in a register across the loop
+                    uint32_t *column = stack_mem + wave_base + lane_index();
+                    const bool ovf = sp > STK - 3;
+                    int next = -1;
+                    float near_t = 0.0f;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        if (!h[k]) continue;
+                        if (ch[k] < 0) {
+                            column[(STK + qn) * 256] = (uint32_t)~ch[k];
+                            ++qn;
+                            continue;
+                        }
+                        const bool nearer = next < 0 || tn[k] < near_t;
+                        if (next >= 0 && !ovf) {
+                            column[sp * 256] = (uint32_t)(nearer ? next : ch[k]);
+                            ++sp;
+                        }
+                        next = nearer ? ch[k] : next;
+                        near_t = nearer ? tn[k] : near_t;
                     }
-                    if (h1 && c1 < 0) {
-                        queue_leaf(~c1);
-                        h1 = false;
-                    }
-                    // descend into the nearer hit child and push the other;
-                    // with no child left, pop; an empty stack ends the walk
-                    // (the round ends once the queued leaves are tested too).
-                    // A push past the stack's end ends the ray with an error
-                    // (the launch is repeated with the deep stack).
-                    const bool both = h0 && h1;
-                    const bool n0 = !h1 || (h0 && tn0 <= tn1);
-                    const bool ovf = both && sp >= STK;
-                    // the lane's stack column: the wave's base (uniform) plus
-                    // the lane index, read again here rather than held in a
-                    // register across the loop
-                    uint32_t *stack = stack_mem + wave_base + lane_index();
-                    if (both) stack[min(sp, STK - 1) * 256] = (uint32_t)(n0 ? c1 : c0);
-                    sp += both ? 1 : 0;
-                    node = n0 ? c0 : c1;
-                    if (!h0 && !h1) {
+                    node = next;
+                    if (next < 0) {
                         if (sp == 0) walked = true;
                         else {
                             --sp;
-                            node = (int)stack[sp * 256];
+                            node = (int)column[sp * 256];
                         }
                     }
                     if (ovf) {
@@ -1220,15 +1242,15 @@ gsrad_status launch_ff_trace(const BvhDev &bv, int R, float t_eps, float t_min, 
         return s;
     const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(npools, 3 * (int64_t)cus));
     if (deep) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_ff_trace<kStackDeep>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, kStackDeep * 256 * 4);
-        hipLaunchKernelGGL(k_ff_trace<kStackDeep>, dim3((unsigned)grid), dim3(256),
-                           (size_t)kStackDeep * 256 * sizeof(uint32_t), st, bv, R, t_eps, t_min, s_begin, count,
-                           pool_rays, npools, list, queue, by_orig, recs, rcnt, rcap, err);
+        const size_t smem = ff_trace_bytes(kWideDeep);
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_ff_trace<kWideDeep>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        hipLaunchKernelGGL(k_ff_trace<kWideDeep>, dim3((unsigned)grid), dim3(256), smem, st, bv, R, t_eps, t_min,
+                           s_begin, count, pool_rays, npools, list, queue, by_orig, recs, rcnt, rcap, err);
     } else {
-        hipLaunchKernelGGL(k_ff_trace<kStackShallow>, dim3((unsigned)grid), dim3(256),
-                           (size_t)kStackShallow * 256 * sizeof(uint32_t), st, bv, R, t_eps, t_min, s_begin, count,
-                           pool_rays, npools, list, queue, by_orig, recs, rcnt, rcap, err);
+        hipLaunchKernelGGL(k_ff_trace<kWideShallow>, dim3((unsigned)grid), dim3(256), ff_trace_bytes(kWideShallow), st,
+                           bv, R, t_eps, t_min, s_begin, count, pool_rays, npools, list, queue, by_orig, recs, rcnt,
+                           rcap, err);
     }
     return check_hip(hipGetLastError(), "ff trace launch");
 }
