@@ -31,14 +31,14 @@ namespace {
 // ---------------------------------------------------------------------------
 // F_ij = lambda_j A_j T_ij |n_i . v| |n_j . v| / (pi |v|^4) per stored entry
 // of the pattern (v = p_j - p_i); one workgroup per row, 16 lanes per entry.
-// Bound by the walks' nodes and leaves (200 and 96 a segment on a 20k-surfel
-// bowl): 10 M segments in 19.4 ms, with a segment a lane 24.2 ms.
+// Bound by the walks (row_crossings): 10 M segments of a 20k-surfel bowl in
+// 14.6 ms, with a segment a lane 24.2 ms.
 __global__ void __launch_bounds__(kRowThreads) k_ff_center(BvhDev bv, const int64_t *__restrict__ row_ptr,
                                                            const int32_t *__restrict__ col, int64_t n,
                                                            const float *__restrict__ lambda,
                                                            float *__restrict__ val, int64_t nblocks,
                                                            const int32_t *__restrict__ order, int *err) {
-    __shared__ uint64_t stack[kRowThreads / 16][kRowStack];
+    __shared__ int32_t stack[kRowThreads / 16][kCrossNodes + kCrossLeaves];
     const int64_t idx = xcd_block(blockIdx.x, nblocks);
     const int64_t row = order ? (int64_t)order[idx] : idx;
     const SurfRec ri = bv.rec[bv.inv[row]];
@@ -48,7 +48,7 @@ __global__ void __launch_bounds__(kRowThreads) k_ff_center(BvhDev bv, const int6
         const int32_t j = col[kk];
         const SurfRec rj = bv.rec[bv.inv[j]];
         const Segment g = make_segment(ri, rj, t_eps);
-        const float T = row_segment<false>(bv, g, (uint32_t)row, (uint32_t)j, stack[threadIdx.x / 16], err, [](int) {});
+        const float T = row_crossings(bv, g, (uint32_t)row, (uint32_t)j, stack[threadIdx.x / 16], err, [](int) {});
         const float a = ri.b.x * g.dx + ri.b.y * g.dy + ri.b.z * g.dz;
         const float bb = rj.b.x * g.dx + rj.b.y * g.dy + rj.b.z * g.dz;
         const float r2 = g.dx * g.dx + g.dy * g.dy + g.dz * g.dz;
@@ -345,7 +345,7 @@ __global__ void __launch_bounds__(kCenterThreads) k_center_bwd(BvhDev bv, const 
         const float W = G * fval[kk];
         float T = 1.0f;
         float gpi[3] = {0.0f, 0.0f, 0.0f}, gpj[3] = {0.0f, 0.0f, 0.0f};
-        trace_segment<kWalkHead>(bv, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, i, j, g.t_lo, g.t_hi, stack_mem + threadIdx.x,
+        trace_segment(bv, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, i, j, g.t_lo, g.t_hi, stack_mem + threadIdx.x,
                                  kCenterThreads, err, [&](const SurfRec &r, int) {
                                      T = __fmul_rn(T, transmit(r.c.w, kernel_gamma(hit_r2_exact(r, g.ox, g.oy, g.oz,
                                                                                                 g.dx, g.dy, g.dz))));
@@ -391,7 +391,7 @@ __global__ void __launch_bounds__(kCenterThreads) k_center_bwd(BvhDev bv, const 
 // the surfel; then part after part is dealt evenly to the lanes and summed in
 // a table in LDS.  A row of 512 entries crosses some 1,900 surfels 17,000
 // times, so ten sums per surfel and row go to memory instead of ten per
-// crossing.  Bound by the walks (19 of 29 ms for 10 M segments of a 20k-surfel
+// crossing.  Bound by the walks (14.6 of 23.8 ms for 10 M segments of a 20k-surfel
 // bowl, as long as k_ff_center), then by the LDS atomics.  A segment a lane
 // and ten global atomics a crossing took 108 ms.
 // The lists lie in the workgroup's own stretch of the workspace; a row that
@@ -403,7 +403,7 @@ constexpr int64_t kCenterGroups = 512;   // workgroups, two a CU
 
 struct RowShared {
     union {
-        uint64_t stack[kCenterRowThreads / 16][kRowStack];
+        int32_t stack[kCenterRowThreads / 16][kCrossNodes + kCrossLeaves];
         CrossTable<kRowSlots> table;
     };
     float d[3][kRowSegs], W[kRowSegs], T[kRowSegs];
@@ -445,7 +445,7 @@ __global__ void __launch_bounds__(kCenterRowThreads, 4) k_center_rows(BvhDev bv,
                 const Segment g = make_segment(ri, bv.rec[bv.inv[j]], bv.bounds[6]);
                 float T = 1.0f;
                 if (G != 0.0f)
-                    T = row_segment<false>(bv, g, (uint32_t)row, (uint32_t)j, sh.stack[tid / 16], err, [&](int s) {
+                    T = row_crossings(bv, g, (uint32_t)row, (uint32_t)j, sh.stack[tid / 16], err, [&](int s) {
                         const uint32_t part = __umulhi((uint32_t)s * 0x85ebca6bu, (uint32_t)kRowParts);
                         const uint32_t at = atomicAdd(&sh.count[part], 1u);
                         if (at < (uint32_t)kRowPart) list[part * kRowPart + at] = make_uint2((uint32_t)q, (uint32_t)s);
@@ -823,7 +823,7 @@ __global__ void __launch_bounds__(kGeometryThreads) k_geometry_sum(HitLists list
 // Bound by the walks' latency and by the sums' atomics.  One lane per
 // receiver that walked its lights in turn, twice in each of two passes, left
 // most of the chip idle: 458 ms for 16k surfels x 100 lights.  Here
-// k_light_walk walks every (receiver, light) segment once, in its own lane,
+// k_light_walk walks every (receiver, light) segment once, 16 lanes to one,
 // and keeps T and the positions of the surfels crossed (kSegHits places per
 // lane and for the lanes with more a block of kSegMore from a pool); the two
 // passes (largest contributions, then the sums) read those lists.  A segment
@@ -867,12 +867,14 @@ struct LightTerm {
     }
 };
 
-template <int HEAD>
-__global__ void __launch_bounds__(kCenterThreads) k_light_walk(BvhDev bv, const float *__restrict__ albedo,
-                                                               const float *__restrict__ lpos, int l0, int Lt, int K,
-                                                               const float *__restrict__ gE, SegLists seg, int *err) {
-    extern __shared__ uint32_t stack_mem[];
-    const int64_t slot = (int64_t)blockIdx.x * kCenterThreads + threadIdx.x;
+__global__ void __launch_bounds__(kRowThreads) k_light_walk(BvhDev bv, const float *__restrict__ albedo,
+                                                            const float *__restrict__ lpos, int l0, int Lt, int K,
+                                                            const float *__restrict__ gE, SegLists seg, int *err) {
+    constexpr int kRows = kRowThreads / 16, kListed = kSegHits + kSegMore;
+    __shared__ int32_t stack[kRows][kCrossNodes + kCrossLeaves];
+    __shared__ uint32_t list[kRows][kListed], hits[kRows];
+    const int row = threadIdx.x / 16, lane = threadIdx.x & 15;
+    const int64_t slot = (int64_t)blockIdx.x * kRows + row;
     if (slot >= bv.n) return;
     const int l = l0 + (int)blockIdx.y;
     const int64_t at = (int64_t)blockIdx.y * seg.pad + slot;
@@ -880,29 +882,34 @@ __global__ void __launch_bounds__(kCenterThreads) k_light_walk(BvhDev bv, const 
     const uint32_t i = __float_as_uint(rr.d.w);
     const LightTerm t(rr, true, lpos, l, gE + (((int64_t)i * Lt + l) * K) * 3, albedo + 3 * (int64_t)i);
     float T = 1.0f;
-    uint32_t hits = 0, block = 0;
-    const uint32_t blocks = (uint32_t)(seg.lanes / kSegShare);
-    if (t.on)
-        trace_segment<HEAD>(bv, rr.a.x, rr.a.y, rr.a.z, t.dx, t.dy, t.dz, i, i, __fdiv_rn(bv.bounds[6], t.len), 1.0f,
-                            stack_mem + threadIdx.x, kCenterThreads, err, [&](const SurfRec &r, int s) {
-                                T = __fmul_rn(T, transmit(r.c.w, kernel_gamma(hit_r2_exact(r, rr.a.x, rr.a.y, rr.a.z,
-                                                                                           t.dx, t.dy, t.dz))));
-                                if (hits < (uint32_t)kSegHits) {
-                                    seg.hit[at * kSegHits + hits] = (uint32_t)s;
-                                } else {
-                                    if (hits == (uint32_t)kSegHits) block = atomicAdd(seg.used, 1u);
-                                    const uint32_t h = hits - kSegHits;
-                                    if (h < (uint32_t)kSegMore && block < blocks)
-                                        seg.more[(int64_t)block * kSegMore + h] = (uint32_t)s;
-                                }
-                                ++hits;
-                            });
-    seg.T[at] = T;
-    if (hits > (uint32_t)kSegHits) {
-        if (block >= blocks || hits > (uint32_t)(kSegHits + kSegMore)) hits = kSegAgain;
-        else seg.block[at] = block;
+    if (lane == 0) hits[row] = 0;
+    __builtin_amdgcn_wave_barrier();
+    if (t.on) {
+        const Segment g{rr.a.x, rr.a.y, rr.a.z, t.dx, t.dy, t.dz, __fdiv_rn(bv.bounds[6], t.len), 1.0f};
+        T = row_crossings(bv, g, i, i, stack[row], err, [&](int s) {
+            const uint32_t h = atomicAdd(&hits[row], 1u);
+            if (h < (uint32_t)kListed) list[row][h] = (uint32_t)s;
+        });
     }
-    seg.count[at] = hits;
+    __builtin_amdgcn_wave_barrier();
+    uint32_t count = hits[row];
+    for (uint32_t h = lane; h < min(count, (uint32_t)kSegHits); h += 16) seg.hit[at * kSegHits + h] = list[row][h];
+    if (count > (uint32_t)kSegHits) {
+        uint32_t block = 0;
+        if (lane == 0) block = atomicAdd(seg.used, 1u);
+        block = (uint32_t)__shfl((int)block, (int)__lane_id() & 48);
+        if (block >= (uint32_t)(seg.lanes / kSegShare) || count > (uint32_t)kListed) {
+            count = kSegAgain;
+        } else {
+            for (uint32_t h = kSegHits + lane; h < count; h += 16)
+                seg.more[(int64_t)block * kSegMore + (h - kSegHits)] = list[row][h];
+            if (lane == 0) seg.block[at] = block;
+        }
+    }
+    if (lane == 0) {
+        seg.T[at] = T;
+        seg.count[at] = count;
+    }
 }
 
 constexpr int kTermThreads = 256;
@@ -1068,7 +1075,7 @@ __global__ void __launch_bounds__(kCenterThreads) k_light_again(BvhDev bv, const
         const uint32_t i = __float_as_uint(rr.d.w);
         const LightTerm t(rr, true, lpos, l, gE + (((int64_t)i * Lt + l) * K) * 3, albedo + 3 * (int64_t)i);
         const float W = t.S * bv.op[i] * (1.1283791670955126f * lI[l] * t.ndot * seg.T[at] / (t.dd * t.len));
-        trace_segment<kWalkHead>(bv, rr.a.x, rr.a.y, rr.a.z, t.dx, t.dy, t.dz, i, i, __fdiv_rn(bv.bounds[6], t.len),
+        trace_segment(bv, rr.a.x, rr.a.y, rr.a.z, t.dx, t.dy, t.dz, i, i, __fdiv_rn(bv.bounds[6], t.len),
                                  1.0f, stack_mem + threadIdx.x, kCenterThreads, err, [&](const SurfRec &r, int) {
                                      float x[10], ge[3], gp[3];
                                      crossing(bv, r, rr.a.x, rr.a.y, rr.a.z, t.dx, t.dy, t.dz, W, x, ge, gp);
@@ -1216,7 +1223,7 @@ gsrad_status launch_center_backward(const BvhDev &bv, const Csr &F, const float 
             (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(RowShared));
         attr_set = true;
     }
-    const size_t smem = walk_bytes(kWalkHead);
+    const size_t smem = kWalkBytes;
     const int64_t groups = std::min(F.n, kCenterGroups);
     char *lists = reinterpret_cast<char *>(acc) + center_acc_bytes(F.n);
     int32_t *done = reinterpret_cast<int32_t *>(lists + groups * kRowParts * kRowPart * (int64_t)sizeof(uint2));
@@ -1329,11 +1336,9 @@ gsrad_status launch_direct_backward(const BvhDev &bv, const float *albedo, const
     const unsigned gw = (unsigned)((bv.n + kCenterThreads - 1) / kCenterThreads), gt = (unsigned)(seg.pad / kTermThreads);
     auto walk = [&](int l0) {
         const int m = std::min(slice, Lt - l0);
-        const bool fills = bv.n * m > kWalkFill;
         hipLaunchKernelGGL(k_seg_reset, dim3(1), dim3(1), 0, st, seg.used);
-        hipLaunchKernelGGL(fills ? k_light_walk<kWalkHead> : k_light_walk<kStackDeep>, dim3(gw, (unsigned)m),
-                           dim3(kCenterThreads), walk_bytes(fills ? kWalkHead : kStackDeep), st, bv, albedo, lpos, l0,
-                           Lt, K, gE, seg, err);
+        hipLaunchKernelGGL(k_light_walk, dim3((unsigned)((bv.n + kRowThreads / 16 - 1) / (kRowThreads / 16)), (unsigned)m),
+                           dim3(kRowThreads), 0, st, bv, albedo, lpos, l0, Lt, K, gE, seg, err);
         return m;
     };
     for (int l0 = 0; l0 < Lt; l0 += slice) {
@@ -1343,7 +1348,7 @@ gsrad_status launch_direct_backward(const BvhDev &bv, const float *albedo, const
                                lI, l0, l0 + m, Lt, K, gE, seg, g_alb);
         hipLaunchKernelGGL(k_light_terms<0>, dim3(gt, (unsigned)m), dim3(kTermThreads), 0, st, bv, albedo, lpos, lI, l0,
                            Lt, K, gE, seg, maxbits, fx, a, la);
-        hipLaunchKernelGGL(k_light_again<0>, dim3(gw, (unsigned)m), dim3(kCenterThreads), walk_bytes(kWalkHead), st,
+        hipLaunchKernelGGL(k_light_again<0>, dim3(gw, (unsigned)m), dim3(kCenterThreads), kWalkBytes, st,
                            bv, albedo, lpos, lI, l0, Lt, K, gE, seg, maxbits, fx, a, la, err);
     }
     hipLaunchKernelGGL(k_light_exp, dim3(1), dim3(64), 0, st, maxbits,
@@ -1352,7 +1357,7 @@ gsrad_status launch_direct_backward(const BvhDev &bv, const float *albedo, const
         const int m = slice < Lt ? walk(l0) : Lt;
         hipLaunchKernelGGL(k_light_terms<1>, dim3(gt, (unsigned)m), dim3(kTermThreads), 0, st, bv, albedo, lpos, lI, l0,
                            Lt, K, gE, seg, maxbits, fx, a, la);
-        hipLaunchKernelGGL(k_light_again<1>, dim3(gw, (unsigned)m), dim3(kCenterThreads), walk_bytes(kWalkHead), st,
+        hipLaunchKernelGGL(k_light_again<1>, dim3(gw, (unsigned)m), dim3(kCenterThreads), kWalkBytes, st,
                            bv, albedo, lpos, lI, l0, Lt, K, gE, seg, maxbits, fx, a, la, err);
     }
     CenterOutputs o15 = out;

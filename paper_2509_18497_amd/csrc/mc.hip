@@ -273,7 +273,7 @@ __global__ void __launch_bounds__(kRowThreads) k_mc_ne(BvhDev bv, const int32_t 
     if (jsel >= 0 && pj > 0.0f) {
         const SurfRec rj = bv.rec[bv.inv[jsel]];
         const Segment g = make_segment(ra, rj, bv.bounds[6]);
-        const float T = row_segment<true>(bv, g, (uint32_t)a, (uint32_t)jsel, stack[threadIdx.x / 16], err, [](int) {});
+        const float T = row_segment(bv, g, (uint32_t)a, (uint32_t)jsel, stack[threadIdx.x / 16], err);
         const float aa = fabsf(ra.b.x * g.dx + ra.b.y * g.dy + ra.b.z * g.dz);
         const float bb = fabsf(rj.b.x * g.dx + rj.b.y * g.dy + rj.b.z * g.dz);
         const float r2 = g.dx * g.dx + g.dy * g.dy + g.dz * g.dz;

@@ -10,7 +10,7 @@
 //                 table with 2^-40 fixed-point sums (integer adds are order
 //                 independent, so F is bit-deterministic), radix select of
 //                 the top-k entries, bitonic sort by column, one ELL row.
-// k_direct        one thread per (surfel, light): shadow-ray transmittance.
+// k_direct        16 lanes per (surfel, light): shadow-ray transmittance.
 // k_opacity_bwd   compositing backward, two recomputing passes.
 #include "gsrad_internal.h"
 #include "sh_api.h"
@@ -760,33 +760,27 @@ __global__ void __launch_bounds__(256) k_ell_to_csr(const int32_t *__restrict__ 
 // ---------------------------------------------------------------------------
 // direct light
 // ---------------------------------------------------------------------------
-// Transmittance of receiver i's shadow segment to the light at o + d.
-template <int HEAD>
+// Transmittance of receiver i's shadow segment to the light at o + d, by a row
+// of 16 lanes.
 __device__ __forceinline__ float shadow(const BvhDev &bv, const SurfRec &rr, float dx, float dy, float dz, float len,
-                                        uint32_t *column, int *err) {
+                                        uint64_t *stack, int *err) {
     const uint32_t i = __float_as_uint(rr.d.w);
-    float T = 1.0f;
-    // kernel values from the exact intersection (the FP32 hit point loses
-    // the offset from the centre when the centre is many radii away)
-    trace_segment<HEAD>(bv, rr.a.x, rr.a.y, rr.a.z, dx, dy, dz, i, i, __fdiv_rn(bv.bounds[6], len), 1.0f, column,
-                        kCenterThreads, err, [&](const SurfRec &r, int) {
-                            T = __fmul_rn(T, transmit(r.c.w, kernel_gamma(hit_r2_exact(r, rr.a.x, rr.a.y, rr.a.z, dx,
-                                                                                       dy, dz))));
-                        });
-    return T;
+    const Segment g{rr.a.x, rr.a.y, rr.a.z, dx, dy, dz, __fdiv_rn(bv.bounds[6], len), 1.0f};
+    return row_segment(bv, g, i, i, stack, err);
 }
 
-// One lane per (receiver, light); a wave's lanes are receivers that follow
-// each other in Morton order and one light, so their walks are alike (lanes
-// of one receiver and successive lights: 6.8 ms for 16k surfels x 100 lights,
-// 4.9 so, both with the same stacks).
-template <int HEAD>
-__global__ void __launch_bounds__(kCenterThreads) k_direct(BvhDev bv, const float *__restrict__ albedo,
-                                                           const float *__restrict__ lpos,
-                                                           const float *__restrict__ lI, int l0, int Lt, int K,
-                                                           float *__restrict__ E, int *err) {
-    extern __shared__ uint32_t stack_mem[];
-    const int64_t slot = (int64_t)blockIdx.x * kCenterThreads + threadIdx.x;
+// A row of 16 lanes per (receiver, light); a workgroup's receivers follow each
+// other in Morton order and have one light, so their walks are alike.  16k
+// surfels x 100 lights: 4.1 ms with a lane each, 3.3 ms so; 100k surfels and one
+// light, a wave and a half per SIMD with a lane each: 0.69 ms, 0.18 ms
+// so.  (The product in a fixed order: the light drives the Monte-Carlo draws,
+// which one bit changes; a sum in any order, row_crossings, takes 2.2 ms and
+// 0.13 ms.)
+__global__ void __launch_bounds__(kRowThreads) k_direct(BvhDev bv, const float *__restrict__ albedo,
+                                                        const float *__restrict__ lpos, const float *__restrict__ lI,
+                                                        int l0, int Lt, int K, float *__restrict__ E, int *err) {
+    __shared__ uint64_t stack[kRowThreads / 16][kRowStack];
+    const int64_t slot = (int64_t)blockIdx.x * (kRowThreads / 16) + threadIdx.x / 16;
     if (slot >= bv.n) return;
     const int l = l0 + (int)blockIdx.y;
     const SurfRec rr = bv.rec[slot];
@@ -801,22 +795,19 @@ __global__ void __launch_bounds__(kCenterThreads) k_direct(BvhDev bv, const floa
     float base = 0.0f;
     if (ndot > 0.0f && dd > 0.0f)
         base = bv.op[i] * 1.1283791670955126f * lI[l] * (ndot / len) / dd *
-               shadow<HEAD>(bv, rr, dx, dy, dz, len, stack_mem + threadIdx.x, err);
-    e[0] = base * albedo[3 * i + 0];
-    e[1] = base * albedo[3 * i + 1];
-    e[2] = base * albedo[3 * i + 2];
-    for (int c = 3; c < 3 * K; ++c) e[c] = 0.0f;
+               shadow(bv, rr, dx, dy, dz, len, stack[threadIdx.x / 16], err);
+    for (int c = threadIdx.x & 15; c < 3 * K; c += 16) e[c] = c < 3 ? base * albedo[3 * i + c] : 0.0f;
 }
 
 // Direct light with the BRDF: E_i,l = (R_i / pi) (.) Y(w^(i)) I_l max(0, n_i . w) / r^2 T_il
 // with w the unit direction to the light expressed in i's tangent frame.
-template <int K, int HEAD>
-__global__ void __launch_bounds__(kCenterThreads) k_direct_sh(BvhDev bv, const float *__restrict__ R,
-                                                              const float *__restrict__ lpos,
-                                                              const float *__restrict__ lI, int l0, int Lt,
-                                                              float *__restrict__ E, int *err) {
-    extern __shared__ uint32_t stack_mem[];
-    const int64_t slot = (int64_t)blockIdx.x * kCenterThreads + threadIdx.x;
+template <int K>
+__global__ void __launch_bounds__(kRowThreads) k_direct_sh(BvhDev bv, const float *__restrict__ R,
+                                                           const float *__restrict__ lpos,
+                                                           const float *__restrict__ lI, int l0, int Lt,
+                                                           float *__restrict__ E, int *err) {
+    __shared__ uint64_t stack[kRowThreads / 16][kRowStack];
+    const int64_t slot = (int64_t)blockIdx.x * (kRowThreads / 16) + threadIdx.x / 16;
     if (slot >= bv.n) return;
     const int l = l0 + (int)blockIdx.y;
     const SurfRec rr = bv.rec[slot];
@@ -831,7 +822,7 @@ __global__ void __launch_bounds__(kCenterThreads) k_direct_sh(BvhDev bv, const f
     float base = 0.0f;
     float Y[K];
     if (ndot > 0.0f && dd > 0.0f) {
-        const float T = shadow<HEAD>(bv, rr, dx, dy, dz, len, stack_mem + threadIdx.x, err);
+        const float T = shadow(bv, rr, dx, dy, dz, len, stack[threadIdx.x / 16], err);
         base = lI[l] * (ndot / len) / dd * T * 0.318309886183791f;
         const float il = 1.0f / len;
         sh_eval<K>((dx * rr.c.x + dy * rr.c.y + dz * rr.c.z) * il, (dx * rr.d.x + dy * rr.d.y + dz * rr.d.z) * il,
@@ -843,7 +834,8 @@ __global__ void __launch_bounds__(kCenterThreads) k_direct_sh(BvhDev bv, const f
     const float *Ri = R + i * K * 3;
 #pragma unroll
     for (int a = 0; a < K; ++a)
-        for (int c = 0; c < 3; ++c) e[3 * a + c] = Ri[3 * a + c] * Y[a] * base;
+        for (int c = 0; c < 3; ++c)
+            if (((3 * a + c) & 15) == (int)(threadIdx.x & 15)) e[3 * a + c] = Ri[3 * a + c] * Y[a] * base;
 }
 
 // ---------------------------------------------------------------------------
@@ -1302,11 +1294,10 @@ constexpr int kLightGrid = 32768;
 
 gsrad_status launch_direct(const BvhDev &bv, const float *albedo, const float *lpos, const float *lI, int Lt, int K,
                            float *E, int *err, hipStream_t st) {
-    const bool fills = bv.n * Lt > kWalkFill;
     for (int l0 = 0; l0 < Lt; l0 += kLightGrid) {
-        const dim3 grid((unsigned)((bv.n + kCenterThreads - 1) / kCenterThreads), (unsigned)std::min(kLightGrid, Lt - l0));
-        hipLaunchKernelGGL(fills ? k_direct<kWalkHead> : k_direct<kStackDeep>, grid, dim3(kCenterThreads),
-                           walk_bytes(fills ? kWalkHead : kStackDeep), st, bv, albedo, lpos, lI, l0, Lt, K, E, err);
+        const dim3 grid((unsigned)((bv.n + kRowThreads / 16 - 1) / (kRowThreads / 16)),
+                        (unsigned)std::min(kLightGrid, Lt - l0));
+        hipLaunchKernelGGL(k_direct, grid, dim3(kRowThreads), 0, st, bv, albedo, lpos, lI, l0, Lt, K, E, err);
     }
     return check_hip(hipGetLastError(), "direct light launch");
 }
@@ -1330,20 +1321,18 @@ static const int *fx_exp_ptr(const BvhDev &bv, const void *acc) {
 
 gsrad_status launch_direct_sh(const BvhDev &bv, const float *R, const float *lpos, const float *lI, int Lt, int K,
                               float *E, int *err, hipStream_t st) {
-    const bool fills = bv.n * Lt > kWalkFill;
-    auto run = [&](auto small, auto large) {
+    auto run = [&](auto kernel) {
         for (int l0 = 0; l0 < Lt; l0 += kLightGrid) {
-            const dim3 grid((unsigned)((bv.n + kCenterThreads - 1) / kCenterThreads),
+            const dim3 grid((unsigned)((bv.n + kRowThreads / 16 - 1) / (kRowThreads / 16)),
                             (unsigned)std::min(kLightGrid, Lt - l0));
-            hipLaunchKernelGGL(fills ? large : small, grid, dim3(kCenterThreads),
-                               walk_bytes(fills ? kWalkHead : kStackDeep), st, bv, R, lpos, lI, l0, Lt, E, err);
+            hipLaunchKernelGGL(kernel, grid, dim3(kRowThreads), 0, st, bv, R, lpos, lI, l0, Lt, E, err);
         }
     };
     switch (K) {
-        case 1: run(k_direct_sh<1, kStackDeep>, k_direct_sh<1, kWalkHead>); break;
-        case 4: run(k_direct_sh<4, kStackDeep>, k_direct_sh<4, kWalkHead>); break;
-        case 9: run(k_direct_sh<9, kStackDeep>, k_direct_sh<9, kWalkHead>); break;
-        case 16: run(k_direct_sh<16, kStackDeep>, k_direct_sh<16, kWalkHead>); break;
+        case 1: run(k_direct_sh<1>); break;
+        case 4: run(k_direct_sh<4>); break;
+        case 9: run(k_direct_sh<9>); break;
+        case 16: run(k_direct_sh<16>); break;
         default: set_error("direct light: K must be 1, 4, 9 or 16"); return GSRAD_EINVAL;
     }
     return check_hip(hipGetLastError(), "SH direct light launch");

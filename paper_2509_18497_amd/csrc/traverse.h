@@ -1,6 +1,6 @@
 // Device-side traversal helpers shared by the ray-cast, gradient and
 // Monte-Carlo kernels: the k-buffer all-hit walk (trace_sorted), the shadow
-// walk (trace_shadow), the segment walk between two surfel centres
+// walk (row_crossings), the segment walks between two surfel centres
 // (trace_segment), the open-addressing slot hash of surfel indices, and the
 // double-float and fixed-point helpers of the deterministic gradient sums.
 // Everything sits in an unnamed namespace: each kernel source gets its own
@@ -24,31 +24,25 @@ constexpr int kStackDeep = 64;
 constexpr int kKB = 20;   // k-buffer entries per traversal round (measured best of 8-32)
 constexpr uint32_t kEmpty = 0xffffffffu;
 
-// Stack of the shadow and segment walks, 64 entries a lane: the first HEAD in
-// LDS (column `lds`, entries `stride` apart), the deeper ones, which few
-// walks reach (an LBVH of 100k surfels is some 20 levels high), in the lane's
-// private memory.  The walks wait for dependent node and leaf loads, so where
-// a launch fills the chip, waves in flight count: all 64 entries in LDS hold
-// a CU to ten waves (10 M segments of a 20k-surfel bowl, a lane each: F 29.6 ms, with a
-// head of 20 24.2 ms; their gradients 183 and 156 ms).  A launch that does
-// not reach ten waves a CU (kWalkFill lanes) walks faster without the choice
-// of memory and takes HEAD = 64 (the direct light of 512 surfels 49 us, with
-// a head of 20 60 us).
+// Stack of the segment walks that take a lane each, kStackDeep entries: the
+// first kWalkHead in LDS (column `lds`, entries `stride` apart), the deeper
+// ones, which few walks reach (an LBVH of 100k surfels is some 20 levels high),
+// in the lane's private memory.  The walks wait for dependent node and leaf
+// loads, so waves in flight count: all 64 entries in LDS hold a CU to ten waves
+// (10 M segments of a 20k-surfel bowl: F 29.6 ms, with a head of 20 24.2 ms).
 constexpr int kWalkHead = 20;
-constexpr int64_t kWalkFill = (int64_t)256 * 10 * 64;
 
-template <int HEAD>
 struct WalkStack {
     uint32_t *lds;
     int stride;
-    uint32_t tail[HEAD < kStackDeep ? kStackDeep - HEAD : 1];
+    uint32_t tail[kStackDeep - kWalkHead];
     __device__ __forceinline__ WalkStack(uint32_t *column, int stride_) : lds(column), stride(stride_) {}
     __device__ __forceinline__ void put(int k, uint32_t v) {
-        if (HEAD >= kStackDeep || k < HEAD) lds[k * stride] = v;
-        else tail[k - HEAD] = v;
+        if (k < kWalkHead) lds[k * stride] = v;
+        else tail[k - kWalkHead] = v;
     }
     __device__ __forceinline__ uint32_t get(int k) const {
-        return HEAD >= kStackDeep || k < HEAD ? lds[k * stride] : tail[k - HEAD];
+        return k < kWalkHead ? lds[k * stride] : tail[k - kWalkHead];
     }
 };
 
@@ -313,7 +307,7 @@ struct RowIndex {
 // Every surfel other than skip_a and skip_b whose support the segment
 // o + t d, t in (t_lo, t_hi), crosses (D_hit, both faces occlude);
 // on_hit(record, sorted position) per crossing, in traversal order.
-template <int HEAD, typename OnHit>
+template <typename OnHit>
 __device__ __forceinline__ void trace_segment(const BvhDev &bv, float ox, float oy, float oz, float dx, float dy,
                                               float dz, uint32_t skip_a, uint32_t skip_b, float t_lo, float t_hi,
                                               uint32_t *column, int stride, int *err, OnHit &&on_hit) {
@@ -333,7 +327,7 @@ __device__ __forceinline__ void trace_segment(const BvhDev &bv, float ox, float 
         leaf(0);
         return;
     }
-    WalkStack<HEAD> stack(column, stride);
+    WalkStack stack(column, stride);
     int sp = 0, node = 0;
     bool ovf = false;
     for (;;) {
@@ -368,8 +362,7 @@ __device__ __forceinline__ void trace_segment(const BvhDev &bv, float ox, float 
 }
 
 constexpr int kCenterThreads = 128;   // two rows (waves) per workgroup
-// LDS of a workgroup's walks
-constexpr size_t walk_bytes(int head) { return (size_t)head * kCenterThreads * sizeof(uint32_t); }
+constexpr size_t kWalkBytes = (size_t)kWalkHead * kCenterThreads * sizeof(uint32_t);   // LDS of its walks
 constexpr float kInvPi = 0.318309886183790672f;
 
 struct Segment {
@@ -401,29 +394,24 @@ __device__ __forceinline__ void each_lane(std::integer_sequence<int, I...>, floa
     (fn(I, row_bcast<I>(v)), ...);
 }
 
-// The crossings of a segment by a row of 16 lanes: on_hit(sorted position) in
-// the lane that finds one, in no order; returns the transmittance.  The row
-// keeps the walk's stack in LDS, next entry on top: a node to open, a leaf to
-// test, or (ORDERED) the factor of a crossing found while nodes before it were
-// still closed.  A round takes the top entries, one per lane, with one load
-// for nodes and leaves alike (both are 64 bytes); what they leave goes back in
-// their order.  ORDERED multiplies the factors as they come to the top, so T
-// is the product in the order of trace_segment, bit by bit; otherwise each
-// lane multiplies those it finds, and the lanes' products are multiplied at
-// the end.  The loads that trace_segment waits for one by one are up to 16 at
-// a time, and a wave waits for the longest of four segments, not of 64.  50k
-// segments across a bowl of 50k surfels (ORDERED): 1.0 ms with a lane each
-// (whether 64 or 16 of them share a wave), 0.24 ms with a row each; 10 M
-// segments of a 20k-surfel bowl: 24.2 ms with a lane each, 22.7 ms ORDERED,
-// 19.4 ms.
+// Transmittance of a segment by a row of 16 lanes, bit by bit as from
+// trace_segment.  The row keeps the walk's stack in LDS, next entry on top: a
+// node to open, a leaf to test, or the factor of a crossing found while nodes
+// before it were still closed.  A round takes the top entries, one per lane,
+// with one load for nodes and leaves alike (both are 64 bytes); what they leave
+// goes back in their order, and the factors that have come to the top are
+// multiplied in.  The loads that trace_segment waits for one by one are up to
+// 16 at a time, and a wave waits for the longest of four segments, not of 64.
+// 50k segments across a bowl of 50k surfels: 1.0 ms with a lane each (whether
+// 64 or 16 of them share a wave), 0.24 ms with a row each (with
+// WideNodes the same).
 // A tree no higher than trace_segment takes never fills the stack: near its
 // end a round opens one entry only, which needs kStackDeep more of them.
 constexpr int kRowThreads = 256;   // 16 rows a workgroup
 constexpr int kRowStack = 192;
 
-template <bool ORDERED, typename OnHit>
 __device__ __forceinline__ float row_segment(const BvhDev &bv, const Segment &g, uint32_t skip_a, uint32_t skip_b,
-                                             uint64_t *stack, int *err, OnHit &&on_hit) {
+                                             uint64_t *stack, int *err) {
     constexpr auto kRow = std::make_integer_sequence<int, 16>{};
     constexpr uint32_t kNode = 0, kLeaf = 1, kFactor = 2;
     auto entry = [](uint32_t kind, uint32_t v) { return (uint64_t)kind << 32 | v; };
@@ -473,24 +461,18 @@ __device__ __forceinline__ float row_segment(const BvhDev &bv, const Segment &g,
                 float t, r2;
                 bool front;
                 if (j != skip_a && j != skip_b &&
-                    hit_test(r, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, g.t_lo, g.t_hi, true, t, r2, front)) {
+                    hit_test(r, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, g.t_lo, g.t_hi, true, t, r2, front))
                     f = transmit(r.c.w, kernel_gamma(hit_r2_exact(r, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz)));
-                    on_hit((int)v);
-                }
             }
         }
-        if (ORDERED) {
-            // lanes before the row's first node: their factors are next in order
-            const uint32_t nodes = (uint32_t)(__ballot(kind == kNode) >> row) & 0xffffu;
-            const int first = nodes ? __ffs((int)nodes) - 1 : 16;
-            if (kind != kNode && l >= first && __float_as_uint(f) != __float_as_uint(1.0f)) {
-                keep = 1;
-                keep0 = entry(kFactor, __float_as_uint(f));
-            }
-            each_lane(kRow, l < first ? f : 1.0f, [&](int, float x) { T = __fmul_rn(T, x); });
-        } else {
-            T = __fmul_rn(T, f);
+        // lanes before the row's first node: their factors are next in order
+        const uint32_t nodes = (uint32_t)(__ballot(kind == kNode) >> row) & 0xffffu;
+        const int first = nodes ? __ffs((int)nodes) - 1 : 16;
+        if (kind != kNode && l >= first && __float_as_uint(f) != __float_as_uint(1.0f)) {
+            keep = 1;
+            keep0 = entry(kFactor, __float_as_uint(f));
         }
+        each_lane(kRow, l < first ? f : 1.0f, [&](int, float x) { T = __fmul_rn(T, x); });
         const uint32_t k1 = (uint32_t)(__ballot(keep >= 1) >> row) & 0xffffu;
         const uint32_t k2 = (uint32_t)(__ballot(keep >= 2) >> row) & 0xffffu;
         int at = sp - m + __popc(k1 >> (l + 1)) + __popc(k2 >> (l + 1));
@@ -498,11 +480,120 @@ __device__ __forceinline__ float row_segment(const BvhDev &bv, const Segment &g,
         if (keep >= 1) stack[at] = keep0;
         sp += __popc(k1) + __popc(k2) - m;
     }
-    if (!ORDERED) {
-#pragma unroll
-        for (int off = 8; off > 0; off >>= 1) T = __fmul_rn(T, __shfl_xor(T, off));
-    }
     return T;
+}
+
+// The crossings of a segment by a row of 16 lanes, in no order: on_hit(sorted
+// position) in the lane that finds one; returns the transmittance, e to the
+// minus sum of c gamma.  The sum is in steps of 2^-40, so that it does not
+// depend on the order (which the other rows of the wave have a part in).  Nodes are WideNodes; a round opens up to 16 nodes or
+// tests up to 16 leaves, and the rows of a wave do the same kind, so that a
+// wave does not step through both.  Bound by the vector instructions of the
+// tests: 10 M segments of a 20k-surfel bowl (200 binary nodes and 96 leaves
+// each) 24.2 ms with a lane each, 19.4 ms with a row each taking nodes and
+// leaves as they come, 17.5 ms with WideNodes, 14.6 ms with rounds of one kind.
+// The stack never fills in a tree no higher than trace_segment takes: near its
+// end a round opens fewer nodes, at last one, which needs kWideReserve more.
+constexpr int kCrossNodes = 224, kCrossLeaves = 160;   // 1.5 KB a row
+constexpr int kWideReserve = 96;                       // three a level of four grandchildren
+
+template <typename OnHit>
+__device__ __forceinline__ float row_crossings(const BvhDev &bv, const Segment &g, uint32_t skip_a, uint32_t skip_b,
+                                               int32_t *nodes, int *err, OnHit &&on_hit) {
+    int32_t *leaves = nodes + kCrossNodes;
+    const int l = threadIdx.x & 15, row = (int)__lane_id() & 48;
+    const float ix = safe_inv(g.dx), iy = safe_inv(g.dy), iz = safe_inv(g.dz);
+    const float sx = bv.bounds[11] * ix, sy = bv.bounds[12] * iy, sz = bv.bounds[13] * iz;
+    const float bx = (bv.bounds[8] - g.ox) * ix, by = (bv.bounds[9] - g.oy) * iy, bz = (bv.bounds[10] - g.oz) * iz;
+    const float t0 = g.t_lo * 0.99999f, t1 = g.t_hi * 1.00001f;
+    long long depth = 0;
+    int sp = bv.n > 1 ? 1 : 0, nl = 1 - sp;
+    if (l == 0) {
+        nodes[0] = 0;
+        leaves[0] = 0;
+    }
+    while (sp > 0 || nl > 0) {
+        // (sp and nl are the row's; rows that are done take no part)
+        const int rows = __popcll(__ballot(true)), want = __popcll(__ballot(nl >= 16 || sp == 0));
+        __builtin_amdgcn_wave_barrier();
+        if (2 * want >= rows || __any(nl > kCrossLeaves - 64)) {
+            const int m = min(nl, 16);
+            if (l < m) {
+                const int s = leaves[nl - 1 - l];
+                const SurfRec r = bv.rec[s];
+                asm volatile("" : : "v"(r.a.x), "v"(r.b.x), "v"(r.c.x), "v"(r.d.w));   // whole record in one latency
+                const uint32_t j = __float_as_uint(r.d.w);
+                float t, r2;
+                bool front;
+                if (j != skip_a && j != skip_b &&
+                    hit_test(r, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz, g.t_lo, g.t_hi, true, t, r2, front)) {
+                    const float x = __fmul_rn(r.c.w, kernel_gamma(hit_r2_exact(r, g.ox, g.oy, g.oz, g.dx, g.dy, g.dz)));
+                    depth += __float2ll_rn(x * 0x1p40f);
+                    on_hit(s);
+                }
+            }
+            nl -= m;
+        } else {
+            if (sp > kCrossNodes - 4) {
+                if (l == 0) atomicOr(err, kErrStack);
+                break;
+            }
+            const int m = min(min(sp, 16), max(1, (kCrossNodes - kWideReserve - sp) / 3));
+            int c[4] = {};
+            bool h[4] = {};
+            if (l < m) {
+                const uint4 *q = reinterpret_cast<const uint4 *>(bv.wide + nodes[sp - 1 - l]);
+                const uint4 q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
+                auto low = [](uint32_t x) { return (float)(x & 0xffffu); };
+                auto high = [](uint32_t x) { return (float)(x >> 16); };
+                auto test = [&](uint32_t x, uint32_t y, uint32_t z) {
+                    float tn;
+                    return wide_slab(low(x), high(x), low(y), high(y), low(z), high(z), sx, sy, sz, bx, by, bz, t0, t1,
+                                     tn);
+                };
+                c[0] = (int)q3.x;
+                c[1] = (int)q3.y;
+                c[2] = (int)q3.z;
+                c[3] = (int)q3.w;
+                h[0] = test(q0.x, q0.y, q0.z);
+                h[1] = test(q0.w, q1.x, q1.y) && c[1] != kNoChild;
+                h[2] = test(q1.z, q1.w, q2.x);
+                h[3] = test(q2.y, q2.z, q2.w) && c[3] != kNoChild;
+            }
+            __builtin_amdgcn_wave_barrier();
+            // (counts of the lanes before and of all, through the counts' bits)
+            int cn = 0, cl = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                cn += h[k] && c[k] >= 0 ? 1 : 0;
+                cl += h[k] && c[k] < 0 ? 1 : 0;
+            }
+            const uint32_t below = (1u << l) - 1u;
+            int an = 0, al = 0, tn = 0, tl = 0;
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const uint32_t kn = (uint32_t)(__ballot((cn >> b) & 1) >> row) & 0xffffu;
+                const uint32_t kl = (uint32_t)(__ballot((cl >> b) & 1) >> row) & 0xffffu;
+                an += __popc(kn & below) << b;
+                al += __popc(kl & below) << b;
+                tn += __popc(kn) << b;
+                tl += __popc(kl) << b;
+            }
+            an += sp - m;
+            al += nl;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (!h[k]) continue;
+                if (c[k] >= 0) nodes[an++] = c[k];
+                else leaves[al++] = ~c[k];
+            }
+            sp += tn - m;
+            nl += tl;
+        }
+    }
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) depth += __shfl_xor(depth, off);
+    return exp_fx(-(__ll2float_rn(depth) * 0x1p-40f));
 }
 
 }  // namespace
