@@ -137,7 +137,7 @@ struct gsrad_bvh {
     int64_t n = 0;               // 0 after a failed (re)build: unusable
     uint64_t gen = 0;            // unique per successful build
     hipStream_t stream = nullptr;
-    DevBuf rec, nodes, wide, leafbox, leaf_parent, inv, cst, opc, opraw, area, dado, bounds, height, temp, lacc;
+    DevBuf rec, nodes, wide, leafbox, leaf_parent, inv, cst, opc, opraw, area, dado, bounds, height, temp, lacc, frames;
     BvhBuffers B;
     BvhDev dev() const {
         BvhDev d;
@@ -157,7 +157,7 @@ struct gsrad_bvh {
     }
     ~gsrad_bvh() {
         for (DevBuf *b : {&rec, &nodes, &wide, &leafbox, &leaf_parent, &inv, &cst, &opc, &opraw, &area, &dado, &bounds, &height,
-                          &temp, &lacc})
+                          &temp, &lacc, &frames})
             b->release();
     }
 };
@@ -192,7 +192,8 @@ struct gsrad_ff {
     // scratch of the ray-cast path
     DevBuf slab, ell_col, ell_val, row_len, err, scan_temp, redo, pools;
     // opacity backward: per-XCD fixed-point accumulators and scale
-    DevBuf opac, cacc, lists, frames;
+    DevBuf opac, cacc;
+    DevBuf opac_lists, geo_lists;   // listed hit contributions, one buffer per gradient call
     // dense BF16 copies (gsrad_ff_dense): F and F^T, hi and lo parts
     bool has_dense = false;
     int64_t Np = 0;
@@ -221,7 +222,7 @@ struct gsrad_ff {
     ~gsrad_ff() {
         for (DevBuf *b : {&row_ptr, &col, &val, &t_row_ptr, &t_col, &t_val, &t_temp, &slab, &ell_col, &redo, &row_order,
                           &ell_val, &row_len, &err, &scan_temp, &pools, &recs, &rcnt, &d_hi, &d_lo, &dt_hi, &dt_lo, &xa, &xb, &xl, &opac,
-                          &cacc, &lists, &frames})
+                          &cacc, &opac_lists, &geo_lists})
             b->release();
     }
 };
@@ -235,7 +236,6 @@ struct gsrad_tape {
     const gsrad_bvh *bvh = nullptr;   // directional transfer: the geometry it used
     uint64_t bvh_gen = 0;
     DevBuf B, L, lam0, pp;
-    DevBuf frames;                    // directional transfer: the solve's surfel frames
     // GSRAD_BF16: Q^(k) = F B^(k) (FP32 [nb][n][C]), B^(k) in BF16 as
     // [Np][Kp] rows (k-major columns), the adjoint's BF16 rows
     // rho lambda^(k+1), its FP32 iterates, and the dense dL/dF [n][n]
@@ -243,7 +243,7 @@ struct gsrad_tape {
     bool has_G = false;
     DevBuf Q, bb, bb_lo, pb, pb_lo, lam_a, lam_b, G;
     ~gsrad_tape() {
-        for (DevBuf *b : {&B, &L, &lam0, &pp, &Q, &bb, &bb_lo, &pb, &pb_lo, &lam_a, &lam_b, &G, &frames}) b->release();
+        for (DevBuf *b : {&B, &L, &lam0, &pp, &Q, &bb, &bb_lo, &pb, &pb_lo, &lam_a, &lam_b, &G}) b->release();
     }
 };
 
@@ -1239,7 +1239,8 @@ gsrad_status gsrad_transport_solve_sh(const gsrad_ff *ff, const gsrad_bvh *bvh, 
             gsrad_ff *m = const_cast<gsrad_ff *>(ff);
             if ((e = m->slab.ensure(std::max(m->slab.bytes, row_bytes * 2), "ping-pong")) != GSRAD_OK) return fail(e);
         }
-        DevBuf &frames = tp ? tp->frames : const_cast<gsrad_ff *>(ff)->frames;
+        // (the same values by every call on this BVH)
+        DevBuf &frames = const_cast<gsrad_bvh *>(bvh)->frames;
         if ((e = frames.ensure(sh_frame_bytes(n), "surfel frames")) != GSRAD_OK) return fail(e);
         if ((e = launch_sh_frames(bvh->dev(), frames.p, st)) != GSRAD_OK) return fail(e);
         const float *src = E;
@@ -1313,11 +1314,11 @@ gsrad_status gsrad_transport_backward_sh(const gsrad_ff *ff, const gsrad_bvh *bv
         float *lam_out = k >= 1 ? L + (size_t)(k - 1) * n * C : tp->lam0.as<float>();
         ProfScope ps("adjoint_sh", st);
         GS_TRY(launch_scale_rows(lam_in, R, n, Lt, K, u, st));
-        GS_TRY(launch_transfer_sh(tp->frames.p, FT, Lt, K, u, nullptr, nullptr, lam_out, grad_E, 1, st));
+        GS_TRY(launch_transfer_sh(bvh->frames.p, FT, Lt, K, u, nullptr, nullptr, lam_out, grad_E, 1, st));
     }
     ProfScope ps("sddmm_sh", st);
     if (grad_R) GS_TRY(launch_grad_R(L, tp->Q.as<float>(), n, Lt, K, nb, grad_R, st));
-    if (grad_F) GS_TRY(launch_sddmm_sh(tp->frames.p, ff->csr(), Lt, K, nb, tp->B.as<float>(), L, R, grad_F, st));
+    if (grad_F) GS_TRY(launch_sddmm_sh(bvh->frames.p, ff->csr(), Lt, K, nb, tp->B.as<float>(), L, R, grad_F, st));
     return GSRAD_OK;
 }
 
@@ -1436,9 +1437,8 @@ gsrad_status gsrad_direct_light_backward(const gsrad_bvh *bvh, const float *albe
 
 // The hit lists' workspace; NULL (the sums are then added directly) where none
 // is wanted or the memory is not there.
-static void *list_workspace(gsrad_ff *f, size_t bytes) {
-    if (bytes == 0 || f->lists.ensure(bytes, "hit lists") != GSRAD_OK) return nullptr;
-    return f->lists.p;
+static void *list_workspace(DevBuf &buf, size_t bytes) {
+    return bytes > 0 && buf.ensure(bytes, "hit lists") == GSRAD_OK ? buf.p : nullptr;
 }
 
 gsrad_status gsrad_geometry_backward(const gsrad_bvh *bvh, const gsrad_ff *ff, const float *grad_F,
@@ -1472,7 +1472,7 @@ gsrad_status gsrad_geometry_backward(const gsrad_bvh *bvh, const gsrad_ff *ff, c
     ProfScope ps("geometry_backward", st);
     return launch_geometry_rec(bvh->dev(), f->R, f->seed, f->recs.as<uint2>(), f->rcnt.as<uint32_t>(), f->rec_cap,
                                f->row_ptr.as<int64_t>(), f->col.as<int32_t>(), grad_F, std::max(f->max_row, 1),
-                               f->cacc.p, list_workspace(f, geometry_list_bytes(ff->n, f->R)), out, st);
+                               f->cacc.p, list_workspace(f->geo_lists, geometry_list_bytes(ff->n, f->R)), out, st);
 }
 
 gsrad_status gsrad_opacity_backward(const gsrad_bvh *bvh, const gsrad_ff *ff, const float *grad_F,
@@ -1501,7 +1501,7 @@ gsrad_status gsrad_opacity_backward(const gsrad_bvh *bvh, const gsrad_ff *ff, co
             return einval("gsrad_opacity_backward: row too long for the LDS row cache");
         if (f->has_records) {
             ProfScope ps("opacity_records", st);
-            void *ws = list_workspace(f, opacity_list_bytes(n, f->R));
+            void *ws = list_workspace(f->opac_lists, opacity_list_bytes(n, f->R));
             GS_TRY(launch_opacity_rec(bvh->dev(), f->R, f->recs.as<uint2>(), f->rcnt.as<uint32_t>(), f->rec_cap,
                                       f->row_ptr.as<int64_t>(), f->col.as<int32_t>(), grad_F, std::max(f->max_row, 1),
                                       acc, ws, st));

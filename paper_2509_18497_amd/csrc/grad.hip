@@ -8,7 +8,7 @@
 //                   k_center_bwd what does not fit its lists.
 // k_geometry_rec    dL/dF through the recorded hits to centres, frames,
 //                   scales and opacities.
-// k_direct_bwd      the direct light's gradient: lights, albedo, receivers
+// k_light_*         the direct light's gradient: lights, albedo, receivers
 //                   and shadow-segment occluders.
 // All sums are 64-bit fixed point with per-field scales (bit-identical
 // between runs), one copy per XCD.

@@ -1,7 +1,7 @@
 // Device-side traversal helpers shared by the ray-cast, gradient and
-// Monte-Carlo kernels: the k-buffer all-hit walk (trace_sorted), the shadow
-// walk (row_crossings), the segment walks between two surfel centres
-// (trace_segment), the open-addressing slot hash of surfel indices, and the
+// Monte-Carlo kernels: the k-buffer all-hit walk (trace_sorted), the segment
+// walks (trace_segment by a lane, row_segment and row_crossings by 16), a row
+// of dL/dF in LDS (RowIndex), the slot hash of surfel indices, and the
 // double-float and fixed-point helpers of the deterministic gradient sums.
 // Everything sits in an unnamed namespace: each kernel source gets its own
 // inlined copy.
@@ -15,11 +15,8 @@ namespace gsrad {
 
 namespace {
 
-// Traversal stack entries per lane (LDS).  The form-factor trace first runs
-// with the shallow stack (it keeps three workgroups per CU resident); a
-// tree deep enough to overflow it is traced again with the deep one, which
-// covers any LBVH of 30-bit Morton codes plus 32 index bits.
-constexpr int kStackShallow = 32;
+// Traversal stack entries per lane of the walks over binary nodes: covers any
+// LBVH of 30-bit Morton codes plus 32 index bits.
 constexpr int kStackDeep = 64;
 constexpr int kKB = 20;   // k-buffer entries per traversal round (measured best of 8-32)
 constexpr uint32_t kEmpty = 0xffffffffu;
