@@ -652,7 +652,7 @@ __global__ void __launch_bounds__(256) k_fields_finish(BvhDev bv, const unsigned
 // 64-bit fixed point with per-field scales from a first pass (bit-identical
 // between runs), one copy per XCD; pass 1 lists a hit's ten contributions
 // (hit_lists.h) and k_geometry_sum adds them: 107 M hits of a 30k-surfel bowl
-// 33.6 ms with ten atomics a hit, 8.1 + 3.0 ms listed.
+// 33.6 ms with ten atomics a hit, 6.7 + 2.1 ms listed.
 
 // zeroes a counter
 __global__ void k_seg_reset(uint32_t *used) { used[threadIdx.x] = 0; }

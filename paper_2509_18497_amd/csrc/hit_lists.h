@@ -37,8 +37,13 @@ struct HitLists {
 // opacity 402 us and geometry 744 us listed, 508 and 2,122 us added directly;
 // 512 of 64 rays, the opacity's 37 us of direct adds leave nothing to gain.
 constexpr int64_t kListRays = (int64_t)1 << 16;
-constexpr int64_t kListBytes = (int64_t)1 << 30;   // entries of a chunk
-constexpr int64_t kListStretches = 1 << 15;        // stretches of a chunk, at most
+// Bytes of a chunk's entries, and its stretches at most.  A chunk's two launches
+// end with a few workgroups each, so few large chunks: 30k surfels' geometry
+// 11.0 ms with 1 GiB, 8.8 with 2, 7.4 with 4; 100k surfels' opacity 12.7, 11.9
+// and 11.3 ms.  An allocation of 4 GiB took up to 1.6 s at a handle's first
+// call, of 2 GiB it is not seen.  Scenes of few rays take less.
+constexpr int64_t kListBytes = (int64_t)1 << 31;
+constexpr int64_t kListStretches = 1 << 16;
 
 inline bool lists_pay(int64_t n, int R, int shift) {
     return n * R >= kListRays && ((n - 1) >> shift) < kListBlocks;

@@ -986,8 +986,8 @@ __global__ void __launch_bounds__(256) k_opacity_bwd(BvhDev bv, int R, uint64_t 
 }
 
 // Bound by the records' latency and the lists' stores: 356 M hits of a
-// 100k-surfel bowl 12.7 ms with the sums (16.5 ms with an atomic each), 105 M
-// of a 16k-surfel room 4.9 ms (14.5 ms, also for the larger row table).
+// 100k-surfel bowl 11.9 ms with the sums (16.5 ms with an atomic each), 105 M
+// of a 16k-surfel room 4.6 ms (14.5 ms, also for the larger row table).
 // Compositing backward from the recorded hits: the same FP32 alpha and T
 // sequence as the forward trace, G from row i of dL/dF in LDS.
 __global__ void __launch_bounds__(256) k_opacity_rec(BvhDev bv, int R, const uint2 *__restrict__ recs,
@@ -1102,8 +1102,8 @@ __global__ void __launch_bounds__(256) k_opacity_rec(BvhDev bv, int R, const uin
 // The listed contributions of one chunk: workgroup (block of surfels, share of
 // the stretches), 16 lanes per stretch.  Blocks of up to 4,096 surfels: fewer
 // blocks fill the lists' lines faster, larger tables leave fewer workgroups a
-// CU (2,048 / 4,096 / 8,192 on a 100k-surfel bowl: 11.1 + 2.7, 10.0 + 2.7,
-// 9.0 + 4.3 ms).
+// CU (2,048 / 4,096 / 8,192 on a 100k-surfel bowl in chunks of 1 GiB: 11.1 +
+// 2.7, 10.0 + 2.7, 9.0 + 4.3 ms).
 constexpr int kOpacityShift = 12;
 constexpr int kListSumThreads = 256;
 constexpr int kListSumWgs = 1024;   // workgroups aimed at
