@@ -40,9 +40,9 @@ FLOP_COMP = 30     # compositing one hit (two exponentials, weights)
 # FETCH_SIZE, x1.0000 for WRITE_SIZE), valid only for the kernel sources
 # they were taken on (sha256 over the listed files, in order).
 TRAFFIC = {
-    "ff_trace": {"fetch": 117217.57e6, "write": 11135.94e6,
+    "ff_trace": {"fetch": 117103.97e6, "write": 11135.33e6,
                  "files": ["trace.hip", "traverse.h", "gsrad_internal.h", "trace_api.h"],
-                 "sha256": "367973663a068583b776d378e8d45ffbd005557c80769e8c8f89bc18d5509cef",
+                 "sha256": "9a64b837a92eefb5da112eecb09d82b98958d0c271371fcee07633f415c0da54",
                  "summary": "profiles/fruit_bowl_100k_hbm_counters.txt"},
     "dense_grad_F": {"fetch": 236949.39e6, "write": 4294.97e6,
                      "files": ["dense.hip", "dense_api.h", "gsrad_internal.h"],
