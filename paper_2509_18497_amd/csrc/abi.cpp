@@ -473,6 +473,7 @@ gsrad_status gsrad_build_bvh(const gsrad_surfels *s, gsrad_bvh **bvh, void *stre
     ENS(rec, n * sizeof(SurfRec), "surfel records");
     ENS(nodes, std::max<int64_t>(n - 1, 1) * sizeof(Node), "bvh nodes");
     ENS(wide, std::max<int64_t>(n - 1, 1) * sizeof(WideNode), "bvh wide nodes");
+    ENS(frames, sh_frame_bytes(n), "surfel frames");
     ENS(leafbox, n * 6 * sizeof(float), "leaf boxes");
     ENS(leaf_parent, n * 4, "leaf parents");
     ENS(inv, n * 4, "inverse order");
@@ -1239,9 +1240,9 @@ gsrad_status gsrad_transport_solve_sh(const gsrad_ff *ff, const gsrad_bvh *bvh, 
             gsrad_ff *m = const_cast<gsrad_ff *>(ff);
             if ((e = m->slab.ensure(std::max(m->slab.bytes, row_bytes * 2), "ping-pong")) != GSRAD_OK) return fail(e);
         }
-        // (the same values by every call on this BVH)
-        DevBuf &frames = const_cast<gsrad_bvh *>(bvh)->frames;
-        if ((e = frames.ensure(sh_frame_bytes(n), "surfel frames")) != GSRAD_OK) return fail(e);
+        // (the same values by every call on this BVH, in memory its build took:
+        // threads and streams may share the BVH)
+        const DevBuf &frames = bvh->frames;
         if ((e = launch_sh_frames(bvh->dev(), frames.p, st)) != GSRAD_OK) return fail(e);
         const float *src = E;
         for (int k = 0; k < n_bounces; ++k) {
