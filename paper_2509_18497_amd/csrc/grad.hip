@@ -849,6 +849,7 @@ __global__ void __launch_bounds__(kGeometryThreads) k_geometry_sum(HitLists list
 // are formed in a table in LDS first (CrossTable).  The lists hold one slice
 // of the lights at a time (kSegLanes); more slices are walked once per pass.
 constexpr int kLightFields = kFields + 4;
+constexpr int kLightCrossings = 28;   // word of maxbits: crossings of pass 0 (64 bits)
 constexpr uint32_t kSegAgain = 0xffffffffu;   // count of a lane whose list is not complete
 constexpr int kSegHits = 64, kSegMore = 96, kSegShare = 8;   // a block for every eighth lane
 constexpr int64_t kSegLanes = (int64_t)1 << 21;
@@ -910,10 +911,12 @@ __global__ void __launch_bounds__(kRowThreads) k_light_walk(BvhDev bv, const flo
     uint32_t count = hits[row];
     for (uint32_t h = lane; h < min(count, (uint32_t)kSegHits); h += 16) seg.hit[at * kSegHits + h] = list[row][h];
     if (count > (uint32_t)kSegHits) {
-        uint32_t block = 0;
-        if (lane == 0) block = atomicAdd(seg.used, 1u);
-        block = (uint32_t)__shfl((int)block, (int)__lane_id() & 48);
-        if (block >= (uint32_t)(seg.lanes / kSegShare) || count > (uint32_t)kListed) {
+        uint32_t block = kSegAgain;
+        if (count <= (uint32_t)kListed) {
+            if (lane == 0) block = atomicAdd(seg.used, 1u);
+            block = (uint32_t)__shfl((int)block, (int)__lane_id() & 48);
+        }
+        if (block >= (uint32_t)(seg.lanes / kSegShare)) {
             count = kSegAgain;
         } else {
             for (uint32_t h = kSegHits + lane; h < count; h += 16)
@@ -930,20 +933,40 @@ __global__ void __launch_bounds__(kRowThreads) k_light_walk(BvhDev bv, const flo
 constexpr int kTermThreads = 256;
 constexpr int kLightSlots = 512;   // 43 KB
 
+// A lane's terms of a light's fields: its segment's own, and the shares of the
+// light's position of the crossings it takes.  Which lane takes a crossing
+// depends on which lists found a block, so each share enters the fixed-point
+// sum by itself: an FP32 sum of a lane's shares would round differently from
+// run to run.
+template <int PASS>
+struct LightSum {
+    float own[4], top[3];   // top: largest |share| (pass 0)
+    long long q[3];         // the shares' sums (pass 1)
+    __device__ __forceinline__ LightSum() : own{}, top{}, q{} {}
+    __device__ __forceinline__ void share(const float (&ge)[3], const int *fx) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            if (PASS == 0) top[c] = fmaxf(top[c], fabsf(ge[c]));
+            else q[c] += __float2ll_rn(ge[c] * __builtin_ldexpf(1.0f, fx[kFields + c]));
+        }
+    }
+};
+
 // The light's fields: largest |value| of the wave's lanes (pass 0), or one
 // wave sum and one fixed-point add per field
 template <int PASS>
-__device__ __forceinline__ void add_light(const float (&gl)[4], uint32_t *maxbits, const int *fx,
+__device__ __forceinline__ void add_light(const LightSum<PASS> &gl, uint32_t *maxbits, const int *fx,
                                           unsigned long long *lacc, int Lt, int l) {
     unsigned long long *lsum = lacc + (int64_t)xcc_id() * 4 * Lt;   // this XCD's light fields [4][Lt]
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         if (PASS == 0) {
-            const float v = wave_max(fabsf(gl[q]));
+            const float v = wave_max(fmaxf(fabsf(gl.own[q]), q < 3 ? gl.top[q < 3 ? q : 0] : 0.0f));
             if (__lane_id() == 0) raise(maxbits + kFields + q, v);
         } else {
             unsigned long long tot =
-                (unsigned long long)__float2ll_rn(gl[q] * __builtin_ldexpf(1.0f, fx[kFields + q]));
+                (unsigned long long)__float2ll_rn(gl.own[q] * __builtin_ldexpf(1.0f, fx[kFields + q]));
+            if (q < 3) tot += (unsigned long long)gl.q[q < 3 ? q : 0];
             for (int off = 32; off > 0; off >>= 1) tot += (unsigned long long)__shfl_xor((long long)tot, off, 64);
             if (__lane_id() == 0 && tot != 0)
                 __hip_atomic_fetch_add(lsum + (int64_t)q * Lt + l, tot, __ATOMIC_RELAXED,
@@ -979,7 +1002,7 @@ __global__ void __launch_bounds__(kTermThreads) k_light_terms(BvhDev bv, const f
     const uint32_t i = __float_as_uint(rr.d.w);
     const LightTerm t(rr, live, lpos, l, gE + (((int64_t)i * Lt + l) * K) * 3, albedo + 3 * (int64_t)i);
     if (PASS == 1) table.clear(tid, kTermThreads);
-    float gl[4] = {0.0f, 0.0f, 0.0f, 0.0f};   // the light's terms of this lane
+    LightSum<PASS> gl;
     uint32_t count = 0;
     sh.W[tid] = 0.0f;
     if (t.on) {
@@ -989,13 +1012,13 @@ __global__ void __launch_bounds__(kTermThreads) k_light_terms(BvhDev bv, const f
         const float r3 = t.dd * t.len, r5 = r3 * t.dd;
         const float kI = 1.1283791670955126f * lI[l];
         const float base = kI * t.ndot * T / r3;
-        gl[3] = t.S * oc * 1.1283791670955126f * t.ndot * T / r3;
+        gl.own[3] = t.S * oc * 1.1283791670955126f * t.ndot * T / r3;
         if (oraw > 0.0f && oraw < kOpacityMax) sink.add(kFo, i, t.S * base);
         const float Q = t.S * oc * kI * T;
-        gl[0] = Q * (rr.b.x / r3 - 3.0f * t.ndot * t.dx / r5);
-        gl[1] = Q * (rr.b.y / r3 - 3.0f * t.ndot * t.dy / r5);
-        gl[2] = Q * (rr.b.z / r3 - 3.0f * t.ndot * t.dz / r5);
-        sink.add3(kFp, i, -gl[0], -gl[1], -gl[2]);
+        gl.own[0] = Q * (rr.b.x / r3 - 3.0f * t.ndot * t.dx / r5);
+        gl.own[1] = Q * (rr.b.y / r3 - 3.0f * t.ndot * t.dy / r5);
+        gl.own[2] = Q * (rr.b.z / r3 - 3.0f * t.ndot * t.dz / r5);
+        sink.add3(kFp, i, -gl.own[0], -gl.own[1], -gl.own[2]);
         sink.add3(kFn, i, Q * t.dx / r3, Q * t.dy / r3, Q * t.dz / r3);
         sh.W[tid] = t.S * oc * base;
     }
@@ -1037,8 +1060,7 @@ __global__ void __launch_bounds__(kTermThreads) k_light_terms(BvhDev bv, const f
         const SurfRec r = bv.rec[s];
         float x[10], ge[3], gp[3];
         crossing(bv, r, sh.o[0][g], sh.o[1][g], sh.o[2][g], sh.d[0][g], sh.d[1][g], sh.d[2][g], sh.W[g], x, ge, gp);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) gl[c] += ge[c];
+        gl.share(ge, fx);
         if (PASS == 0) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) sink.add(kFp + c, 0, gp[c]);
@@ -1056,6 +1078,8 @@ __global__ void __launch_bounds__(kTermThreads) k_light_terms(BvhDev bv, const f
     add_light<PASS>(gl, maxbits, fx, lacc, Lt, l);
     if (PASS == 0) {
         sink.report(maxbits);
+        if (tid == 0 && total != 0)
+            atomicAdd(reinterpret_cast<unsigned long long *>(maxbits + kLightCrossings), (unsigned long long)total);
     } else {
         __syncthreads();
 #pragma unroll
@@ -1083,7 +1107,8 @@ __global__ void __launch_bounds__(kCenterThreads) k_light_again(BvhDev bv, const
     if (!__any(mine)) return;
     FieldSink<PASS> sink;
     sink.init(acc, fx, bv.n);
-    float gl[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    LightSum<PASS> gl;
+    unsigned long long hits = 0;
     if (mine) {
         const SurfRec rr = bv.rec[slot];
         const uint32_t i = __float_as_uint(rr.d.w);
@@ -1093,7 +1118,8 @@ __global__ void __launch_bounds__(kCenterThreads) k_light_again(BvhDev bv, const
                                  1.0f, stack_mem + threadIdx.x, kCenterThreads, err, [&](const SurfRec &r, int) {
                                      float x[10], ge[3], gp[3];
                                      crossing(bv, r, rr.a.x, rr.a.y, rr.a.z, t.dx, t.dy, t.dz, W, x, ge, gp);
-                                     for (int c = 0; c < 3; ++c) gl[c] += ge[c];
+                                     gl.share(ge, fx);
+                                     ++hits;
                                      sink.add3(kFp, i, gp[0], gp[1], gp[2]);
 #pragma unroll
                                      for (int q = 0; q < 10; ++q)
@@ -1101,7 +1127,12 @@ __global__ void __launch_bounds__(kCenterThreads) k_light_again(BvhDev bv, const
                                  });
     }
     add_light<PASS>(gl, maxbits, fx, lacc, Lt, l);
-    if (PASS == 0) sink.report(maxbits);
+    if (PASS == 0) {
+        sink.report(maxbits);
+        for (int off = 32; off > 0; off >>= 1) hits += __shfl_xor(hits, off, 64);
+        if (__lane_id() == 0)
+            atomicAdd(reinterpret_cast<unsigned long long *>(maxbits + kLightCrossings), hits);
+    }
 }
 
 // dL/dalbedo of a slice's lights, in their order (added to the earlier
@@ -1132,6 +1163,8 @@ __global__ void __launch_bounds__(256) k_light_albedo(BvhDev bv, const float *__
 __global__ void k_light_exp(const uint32_t *maxbits, int64_t count_surfel, int64_t count_light, int *fx) {
     const int f = threadIdx.x;
     if (f >= kLightFields) return;
+    // (a crossing adds to its light's position once)
+    count_light += 2 * (int64_t)*reinterpret_cast<const unsigned long long *>(maxbits + kLightCrossings);
     const float m = __uint_as_float(maxbits[f]);
     int e = 0;
     if (!(m <= 3.0e38f)) {
@@ -1332,7 +1365,8 @@ size_t light_seg_bytes(int64_t n, int Lt) { return (size_t)light_slice(n, Lt) * 
 gsrad_status launch_direct_backward(const BvhDev &bv, const float *albedo, const float *lpos, const float *lI, int Lt,
                                     int K, const float *gE, void *acc, float *g_lpos, float *g_lI, float *g_alb,
                                     const CenterOutputs &out, int *err, hipStream_t st) {
-    static_assert(kLightFields < 32, "maxbits and fx hold 32 entries each, the last of maxbits counts blocks");
+    static_assert(kLightFields <= kLightCrossings && kLightCrossings % 2 == 0,
+                  "maxbits and fx hold 32 entries each; crossings are counted at kLightCrossings, blocks in the last");
     unsigned long long *a = static_cast<unsigned long long *>(acc);
     unsigned long long *la = a + (size_t)8 * kFields * bv.n;
     uint32_t *maxbits = reinterpret_cast<uint32_t *>(la + (size_t)8 * 4 * Lt);
