@@ -61,3 +61,27 @@ def test_more_long_segments_than_blocks(g, orc, layers, per_layer):
         again = g.direct_light_backward(*args)
         assert all(torch.equal(a, b) for a, b in zip(got[:3], again[:3]))
         assert all(torch.equal(got[3][f], again[3][f]) for f in orc.GEOMETRY_FIELDS)
+
+
+def test_more_lights_than_one_slice(g, orc):
+    """63 surfels are padded to 256 places a light, so 8,192 lights fill the
+    lists: eight more are a slice of their own, the albedo's sum goes on from
+    the first, and both are walked again between the passes."""
+    sur = scenes.random_frame_surfels(63, seed=4, scale=(0.1, 0.4))
+    lights = 8200
+    rng = np.random.default_rng(5)
+    lp = (rng.uniform(-0.5, 0.5, (lights, 3)) + [0.0, 0.0, 2.5]).astype(np.float32)
+    lI = rng.uniform(1.0, 4.0, lights).astype(np.float32)
+    alb = scenes.seeded_array((63, 3), 1, 0.2, 0.9)
+    gE = scenes.seeded_array((63, lights, 1, 3), 2, -1.0, 1.0)
+    bvh = g.build_bvh(dev_surfels(sur))
+    args = (bvh, dev(alb), dev(lp), dev(lI), dev(gE))
+    got = g.direct_light_backward(*args)
+    want = orc.direct_light_backward(sur, alb, lp, lI, gE, t_eps=orc.default_t_eps(sur))
+    for a, b in zip(got[:3], want[:3]):
+        assert rel_err(a.cpu().numpy(), b) < TOL
+    for f in orc.GEOMETRY_FIELDS:
+        assert rel_err(got[3][f].cpu().numpy(), want[3][f]) < TOL, f
+    again = g.direct_light_backward(*args)
+    assert all(torch.equal(a, b) for a, b in zip(got[:3], again[:3]))
+    assert all(torch.equal(got[3][f], again[3][f]) for f in orc.GEOMETRY_FIELDS)
