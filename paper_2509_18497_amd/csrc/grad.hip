@@ -36,10 +36,10 @@ namespace {
 __global__ void __launch_bounds__(kRowThreads) k_ff_center(BvhDev bv, const int64_t *__restrict__ row_ptr,
                                                            const int32_t *__restrict__ col, int64_t n,
                                                            const float *__restrict__ lambda,
-                                                           float *__restrict__ val, int64_t nblocks,
+                                                           float *__restrict__ val, int64_t block0, int64_t nblocks,
                                                            const int32_t *__restrict__ order, int *err) {
     __shared__ int32_t stack[kRowThreads / 16][kCrossNodes + kCrossLeaves];
-    const int64_t idx = xcd_block(blockIdx.x, nblocks);
+    const int64_t idx = xcd_block(block0 + blockIdx.x, nblocks);
     const int64_t row = order ? (int64_t)order[idx] : idx;
     const SurfRec ri = bv.rec[bv.inv[row]];
     const int64_t b = row_ptr[row], e = row_ptr[row + 1];
@@ -1201,8 +1201,10 @@ __global__ void k_light_finish(const unsigned long long *__restrict__ lacc, cons
 gsrad_status launch_ff_center(const BvhDev &bv, const Csr &P, const float *lambda, float *val, int *err,
                               hipStream_t st) {
     if (P.n == 0) return GSRAD_OK;
-    hipLaunchKernelGGL(k_ff_center, dim3((unsigned)P.n), dim3(kRowThreads), 0, st, bv, P.row_ptr, P.col, P.n, lambda,
-                       val, P.n, P.order, err);
+    each_launch(P.n, kRowThreads, [&](int64_t first, unsigned blocks) {
+        hipLaunchKernelGGL(k_ff_center, dim3(blocks), dim3(kRowThreads), 0, st, bv, P.row_ptr, P.col, P.n, lambda, val,
+                           first, P.n, P.order, err);
+    });
     return check_hip(hipGetLastError(), "centre-to-centre form factor launch");
 }
 

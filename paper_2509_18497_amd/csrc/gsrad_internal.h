@@ -274,6 +274,15 @@ __device__ __forceinline__ float safe_inv(float d) {
 void set_error(const char *fmt, ...);
 gsrad_status check_hip(hipError_t e, const char *what);
 
+// fn(first group, groups) for launches that together run all groups of
+// `threads`: one launch holds fewer than 2^32 threads in a dimension.  The
+// first group of a launch is a multiple of 8, so a group's XCD stays the same.
+template <typename Fn>
+inline void each_launch(int64_t groups, int threads, Fn &&fn) {
+    const int64_t most = ((int64_t)1 << 31) / threads;
+    for (int64_t g0 = 0; g0 < groups; g0 += most) fn(g0, (unsigned)(groups - g0 < most ? groups - g0 : most));
+}
+
 // scan_sort.hip
 size_t scan_temp_bytes(int64_t n);
 // exclusive prefix sum of n uint32 counts into int64 out[n+1] (out[n] = total)

@@ -216,10 +216,10 @@ __global__ void __launch_bounds__(kRowThreads) k_mc_select(BvhDev bv, int G, con
                                                            const float *__restrict__ cent,
                                                            const float *__restrict__ gnrm,
                                                            const float *__restrict__ Lg, float rmin2,
-                                                           const int32_t *__restrict__ recv, int64_t slots,
-                                                           uint64_t seed, int step, int32_t *__restrict__ jsel_out,
+                                                           const int32_t *__restrict__ recv, int64_t block0,
+                                                           int64_t slots, uint64_t seed, int step, int32_t *__restrict__ jsel_out,
                                                            float *__restrict__ pj_out) {
-    const int64_t s = (int64_t)blockIdx.x * (kRowThreads / 16) + threadIdx.x / 16;
+    const int64_t s = (block0 + blockIdx.x) * (kRowThreads / 16) + threadIdx.x / 16;
     if (s >= slots) return;
     const int64_t a = recv ? (int64_t)recv[s] : s;
     const SurfRec ra = bv.rec[bv.inv[a]];
@@ -253,7 +253,8 @@ __global__ void __launch_bounds__(kRowThreads) k_mc_select(BvhDev bv, int G, con
 
 // The estimates of the drawn pairs: current radiance B, writes delta
 // [slots][C], 16 lanes per slot.
-__global__ void __launch_bounds__(kRowThreads) k_mc_ne(BvhDev bv, const int32_t *__restrict__ recv, int64_t slots,
+__global__ void __launch_bounds__(kRowThreads) k_mc_ne(BvhDev bv, const int32_t *__restrict__ recv, int64_t block0,
+                                                       int64_t slots,
                                                        const int32_t *__restrict__ jsel_in,
                                                        const float *__restrict__ pj_in,
                                                        const float *__restrict__ lambda,
@@ -261,7 +262,7 @@ __global__ void __launch_bounds__(kRowThreads) k_mc_ne(BvhDev bv, const int32_t 
                                                        const float *__restrict__ B, int C, float *__restrict__ delta,
                                                        int *err) {
     __shared__ uint64_t stack[kRowThreads / 16][kRowStack];
-    const int64_t s = (int64_t)blockIdx.x * (kRowThreads / 16) + threadIdx.x / 16;
+    const int64_t s = (block0 + blockIdx.x) * (kRowThreads / 16) + threadIdx.x / 16;
     if (s >= slots) return;
     const int64_t a = recv ? (int64_t)recv[s] : s;
     const SurfRec ra = bv.rec[bv.inv[a]];
@@ -406,10 +407,15 @@ gsrad_status mc_step(const BvhDev &bv, const McBuffers &mb, int G, float rmin2, 
                        mb.L);
     McMember *mem = static_cast<McMember *>(mb.mem);
     hipLaunchKernelGGL(k_mc_members, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, bv, mb.members, B, Lt, K, mem);
-    hipLaunchKernelGGL(k_mc_select, dim3((unsigned)((n + kRowThreads / 16 - 1) / (kRowThreads / 16))), dim3(kRowThreads),
-                       0, st, bv, G, mb.goff, mem, mb.cent, mb.gnrm, mb.L, rmin2, recv, n, seed, step, mb.jsel, mb.pj);
-    hipLaunchKernelGGL(k_mc_ne, dim3((unsigned)((n + kRowThreads / 16 - 1) / (kRowThreads / 16))), dim3(kRowThreads), 0,
-                       st, bv, recv, n, mb.jsel, mb.pj, lambda, rho, E, B, Lt * K * 3, delta, err);
+    const int64_t groups = (n + kRowThreads / 16 - 1) / (kRowThreads / 16);
+    each_launch(groups, kRowThreads, [&](int64_t first, unsigned blocks) {
+        hipLaunchKernelGGL(k_mc_select, dim3(blocks), dim3(kRowThreads), 0, st, bv, G, mb.goff, mem, mb.cent, mb.gnrm,
+                           mb.L, rmin2, recv, first, n, seed, step, mb.jsel, mb.pj);
+    });
+    each_launch(groups, kRowThreads, [&](int64_t first, unsigned blocks) {
+        hipLaunchKernelGGL(k_mc_ne, dim3(blocks), dim3(kRowThreads), 0, st, bv, recv, first, n, mb.jsel, mb.pj, lambda,
+                           rho, E, B, Lt * K * 3, delta, err);
+    });
     return check_hip(hipGetLastError(), "next event launch");
 }
 

@@ -134,13 +134,14 @@ struct RowArgs {
     const RowScene *tab;
     const int64_t *first;
     int count;
+    int64_t block0;         // first workgroup of this launch
     const float *rho;
 };
 
 // The scene and the (chunk, row) of this lane; false past the scene's rows
 template <int G, int LPR>
 __device__ __forceinline__ bool find_row(const RowArgs &a, RowScene &s, int &m0, int64_t &row) {
-    int64_t b = blockIdx.x;
+    int64_t b = a.block0 + blockIdx.x;
     if (a.tab) {
         int lo = 0, hi = a.count - 1;
         while (lo < hi) {
@@ -332,9 +333,9 @@ __global__ void __launch_bounds__(kThreads) k_sddmm3(RowArgs a, int m0, int64_t 
     }
 }
 
-__global__ void __launch_bounds__(256) k_scale_rho(RowScene s, const float *__restrict__ in,
+__global__ void __launch_bounds__(256) k_scale_rho(RowScene s, int64_t block0, const float *__restrict__ in,
                                                    const float *__restrict__ rho, float *__restrict__ out) {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t t = (block0 + blockIdx.x) * 256 + threadIdx.x;
     const int M = s.C / 3;
     if (t >= s.n * M) return;
     const int64_t row = s.row0 + t / M;
@@ -373,8 +374,12 @@ gsrad_status run_scene(const Csr &F, const RowScene &s, const float *in, const f
     const int g = row_lanes(s.C);
     RowArgs a = row_args(F, rho);
     a.one = s;
-    const dim3 grid((unsigned)rows_blocks(s.n, s.C, 64));
-    auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, a, in, E, out, p_out, gE); };
+    auto run = [&](auto kernel) {
+        each_launch(rows_blocks(s.n, s.C, 64), kThreads, [&](int64_t first, unsigned blocks) {
+            a.block0 = first;
+            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), 0, st, a, in, E, out, p_out, gE);
+        });
+    };
     if (g == 1) run(k_rows<1, 64, ADJ>);
     else if (g == 4) run(k_rows<4, 64, ADJ>);
     else run(k_rows<16, 64, ADJ>);
@@ -400,8 +405,12 @@ gsrad_status run_batch(const Csr &F, const RowTable &t, int lanes, const float *
     a.tab = t.tab;
     a.first = t.first[which];
     a.count = t.count;
-    const dim3 grid((unsigned)t.blocks[which]);
-    auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, a, in, E, out, p_out, gE); };
+    auto run = [&](auto kernel) {
+        each_launch(t.blocks[which], kThreads, [&](int64_t first, unsigned blocks) {
+            a.block0 = first;
+            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), 0, st, a, in, E, out, p_out, gE);
+        });
+    };
     if (which == 0) run(k_rows<16, 16, ADJ>);
     else if (which == 1) run(k_rows<16, 32, ADJ>);
     else run(k_rows<16, 64, ADJ>);
@@ -440,7 +449,9 @@ gsrad_status rows_adjoint_batch(const Csr &FT, const RowTable &t, int lanes, con
 gsrad_status rows_scale(const RowScene &s, const float *in, const float *rho, float *out, hipStream_t st) {
     const int64_t lanes = s.n * (s.C / 3);
     if (lanes == 0) return GSRAD_OK;
-    hipLaunchKernelGGL(k_scale_rho, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, st, s, in, rho, out);
+    each_launch((lanes + 255) / 256, 256, [&](int64_t first, unsigned blocks) {
+        hipLaunchKernelGGL(k_scale_rho, dim3(blocks), dim3(256), 0, st, s, first, in, rho, out);
+    });
     return check_hip(hipGetLastError(), "rho scaling launch");
 }
 

@@ -778,9 +778,9 @@ __device__ __forceinline__ float shadow(const BvhDev &bv, const SurfRec &rr, flo
 // 0.13 ms.)
 __global__ void __launch_bounds__(kRowThreads) k_direct(BvhDev bv, const float *__restrict__ albedo,
                                                         const float *__restrict__ lpos, const float *__restrict__ lI,
-                                                        int l0, int Lt, int K, float *__restrict__ E, int *err) {
+                                                        int64_t block0, int l0, int Lt, int K, float *__restrict__ E, int *err) {
     __shared__ uint64_t stack[kRowThreads / 16][kRowStack];
-    const int64_t slot = (int64_t)blockIdx.x * (kRowThreads / 16) + threadIdx.x / 16;
+    const int64_t slot = (block0 + blockIdx.x) * (kRowThreads / 16) + threadIdx.x / 16;
     if (slot >= bv.n) return;
     const int l = l0 + (int)blockIdx.y;
     const SurfRec rr = bv.rec[slot];
@@ -804,10 +804,10 @@ __global__ void __launch_bounds__(kRowThreads) k_direct(BvhDev bv, const float *
 template <int K>
 __global__ void __launch_bounds__(kRowThreads) k_direct_sh(BvhDev bv, const float *__restrict__ R,
                                                            const float *__restrict__ lpos,
-                                                           const float *__restrict__ lI, int l0, int Lt,
+                                                           const float *__restrict__ lI, int64_t block0, int l0, int Lt,
                                                            float *__restrict__ E, int *err) {
     __shared__ uint64_t stack[kRowThreads / 16][kRowStack];
-    const int64_t slot = (int64_t)blockIdx.x * (kRowThreads / 16) + threadIdx.x / 16;
+    const int64_t slot = (block0 + blockIdx.x) * (kRowThreads / 16) + threadIdx.x / 16;
     if (slot >= bv.n) return;
     const int l = l0 + (int)blockIdx.y;
     const SurfRec rr = bv.rec[slot];
@@ -1304,11 +1304,11 @@ constexpr int kLightGrid = 32768;
 
 gsrad_status launch_direct(const BvhDev &bv, const float *albedo, const float *lpos, const float *lI, int Lt, int K,
                            float *E, int *err, hipStream_t st) {
-    for (int l0 = 0; l0 < Lt; l0 += kLightGrid) {
-        const dim3 grid((unsigned)((bv.n + kRowThreads / 16 - 1) / (kRowThreads / 16)),
-                        (unsigned)std::min(kLightGrid, Lt - l0));
-        hipLaunchKernelGGL(k_direct, grid, dim3(kRowThreads), 0, st, bv, albedo, lpos, lI, l0, Lt, K, E, err);
-    }
+    for (int l0 = 0; l0 < Lt; l0 += kLightGrid)
+        each_launch((bv.n + kRowThreads / 16 - 1) / (kRowThreads / 16), kRowThreads, [&](int64_t first, unsigned blocks) {
+            hipLaunchKernelGGL(k_direct, dim3(blocks, (unsigned)std::min(kLightGrid, Lt - l0)), dim3(kRowThreads), 0, st,
+                               bv, albedo, lpos, lI, first, l0, Lt, K, E, err);
+        });
     return check_hip(hipGetLastError(), "direct light launch");
 }
 
@@ -1332,11 +1332,12 @@ static const int *fx_exp_ptr(const BvhDev &bv, const void *acc) {
 gsrad_status launch_direct_sh(const BvhDev &bv, const float *R, const float *lpos, const float *lI, int Lt, int K,
                               float *E, int *err, hipStream_t st) {
     auto run = [&](auto kernel) {
-        for (int l0 = 0; l0 < Lt; l0 += kLightGrid) {
-            const dim3 grid((unsigned)((bv.n + kRowThreads / 16 - 1) / (kRowThreads / 16)),
-                            (unsigned)std::min(kLightGrid, Lt - l0));
-            hipLaunchKernelGGL(kernel, grid, dim3(kRowThreads), 0, st, bv, R, lpos, lI, l0, Lt, E, err);
-        }
+        for (int l0 = 0; l0 < Lt; l0 += kLightGrid)
+            each_launch((bv.n + kRowThreads / 16 - 1) / (kRowThreads / 16), kRowThreads,
+                        [&](int64_t first, unsigned blocks) {
+                            hipLaunchKernelGGL(kernel, dim3(blocks, (unsigned)std::min(kLightGrid, Lt - l0)),
+                                               dim3(kRowThreads), 0, st, bv, R, lpos, lI, first, l0, Lt, E, err);
+                        });
     };
     switch (K) {
         case 1: run(k_direct_sh<1>); break;
