@@ -137,7 +137,7 @@ struct gsrad_bvh {
     int64_t n = 0;               // 0 after a failed (re)build: unusable
     uint64_t gen = 0;            // unique per successful build
     hipStream_t stream = nullptr;
-    DevBuf rec, nodes, wide, leafbox, leaf_parent, inv, cst, opc, opraw, area, dado, bounds, height, temp, lacc, frames;
+    DevBuf rec, nodes, wide, leafbox, leaf_parent, inv, cst, opc, opraw, area, dado, bounds, height, temp, lacc, light_lists, frames;
     BvhBuffers B;
     BvhDev dev() const {
         BvhDev d;
@@ -157,7 +157,7 @@ struct gsrad_bvh {
     }
     ~gsrad_bvh() {
         for (DevBuf *b : {&rec, &nodes, &wide, &leafbox, &leaf_parent, &inv, &cst, &opc, &opraw, &area, &dado, &bounds, &height,
-                          &temp, &lacc, &frames})
+                          &temp, &lacc, &light_lists, &frames})
             b->release();
     }
 };
@@ -193,7 +193,7 @@ struct gsrad_ff {
     DevBuf slab, ell_col, ell_val, row_len, err, scan_temp, redo, pools;
     // opacity backward: per-XCD fixed-point accumulators and scale
     DevBuf opac, cacc;
-    DevBuf opac_lists, geo_lists;   // listed hit contributions, one buffer per gradient call
+    DevBuf opac_lists, geo_lists, center_lists;   // listed contributions, one buffer per gradient call
     // dense BF16 copies (gsrad_ff_dense): F and F^T, hi and lo parts
     bool has_dense = false;
     int64_t Np = 0;
@@ -222,7 +222,7 @@ struct gsrad_ff {
     ~gsrad_ff() {
         for (DevBuf *b : {&row_ptr, &col, &val, &t_row_ptr, &t_col, &t_val, &t_temp, &slab, &ell_col, &redo, &row_order,
                           &ell_val, &row_len, &err, &scan_temp, &pools, &recs, &rcnt, &d_hi, &d_lo, &dt_hi, &dt_lo, &xa, &xb, &xl, &opac,
-                          &cacc, &opac_lists, &geo_lists})
+                          &cacc, &opac_lists, &geo_lists, &center_lists})
             b->release();
     }
 };
@@ -1387,6 +1387,35 @@ gsrad_status gsrad_ff_center(const gsrad_bvh *bvh, const gsrad_ff *pattern, cons
     return GSRAD_OK;
 }
 
+// Bytes of the workspace `buf` that a gradient call may use, of `want` it would
+// like: whole multiples of `unit`, at most an eighth of the free memory where it
+// has to be allocated (a handle keeps it, so with many handles alive the lists
+// leave room for what cannot do without), and what is there while the stream is
+// being captured.  0 and no error where there is no memory: every caller has a
+// slower path that takes none.
+static size_t list_workspace(DevBuf &buf, size_t want, size_t unit, hipStream_t st) {
+    if (want == 0 || (want <= buf.bytes && buf.p)) return want;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    size_t free_b = 0, total_b = 0;
+    if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone ||
+        hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+        (void)hipGetLastError();
+        return buf.bytes;
+    }
+    const size_t take = std::min(want, (free_b + buf.bytes) / 8 / unit * unit);
+    if (take < want && take < 2 * buf.bytes) return buf.bytes;   // (not for a little more)
+    buf.release();
+    if (take == 0) return 0;
+    void *p = nullptr;
+    if (hipMalloc(&p, take) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    buf.p = p;
+    buf.bytes = take;
+    return take;
+}
+
 gsrad_status gsrad_ff_center_backward(const gsrad_bvh *bvh, const gsrad_ff *ff, const float *lambda,
                                       const float *grad_F, float *grad_lambda, const gsrad_surfel_grads *grads,
                                       void *stream) {
@@ -1398,7 +1427,8 @@ gsrad_status gsrad_ff_center_backward(const gsrad_bvh *bvh, const gsrad_ff *ff, 
     hipStream_t st = S(stream);
     gsrad_ff *f = const_cast<gsrad_ff *>(ff);
     const size_t bytes = center_acc_bytes(ff->n);
-    GS_TRY(f->cacc.ensure(bytes + center_list_bytes(ff->n), "centre-to-centre gradient accumulators"));
+    GS_TRY(f->cacc.ensure(bytes + (size_t)ff->n * 4, "centre-to-centre gradient accumulators"));
+    const size_t room = list_workspace(f->center_lists, center_list_bytes(ff->n), center_group_bytes(), st);
     GS_TRY(check_hip(hipMemsetAsync(f->cacc.p, 0, bytes, st), "accumulators zero"));
     GS_TRY(f->err.ensure(128, "flags"));
     CenterOutputs out;
@@ -1408,7 +1438,9 @@ gsrad_status gsrad_ff_center_backward(const gsrad_bvh *bvh, const gsrad_ff *ff, 
                          g.opacity, grad_lambda};
     for (int k = 0; k < 16; ++k) out.p[k] = fields[k];
     ProfScope ps("ff_center_backward", st);
-    return launch_center_backward(bvh->dev(), ff->csr(), lambda, grad_F, f->cacc.p, out, f->err.as<int>() + 8, st);
+    return launch_center_backward(bvh->dev(), ff->csr(), lambda, grad_F, f->cacc.p,
+                                  reinterpret_cast<int32_t *>(f->cacc.as<char>() + bytes), f->center_lists.p, room, out,
+                                  f->err.as<int>() + 8, st);
 }
 
 gsrad_status gsrad_direct_light_backward(const gsrad_bvh *bvh, const float *albedo, const float *light_pos,
@@ -1422,7 +1454,8 @@ gsrad_status gsrad_direct_light_backward(const gsrad_bvh *bvh, const float *albe
     hipStream_t st = S(stream);
     gsrad_bvh *h = const_cast<gsrad_bvh *>(bvh);
     const size_t bytes = light_acc_bytes(bvh->n, n_lights);
-    GS_TRY(h->lacc.ensure(bytes + light_seg_bytes(bvh->n, n_lights), "direct light gradient accumulators"));
+    GS_TRY(h->lacc.ensure(bytes, "direct light gradient accumulators"));
+    const size_t room = list_workspace(h->light_lists, light_list_bytes(bvh->n, n_lights), light_one_bytes(bvh->n), st);
     GS_TRY(check_hip(hipMemsetAsync(h->lacc.p, 0, bytes, st), "accumulators zero"));
     GS_TRY(h->height.ensure(64, "flags"));
     const gsrad_surfel_grads z{};
@@ -1433,31 +1466,8 @@ gsrad_status gsrad_direct_light_backward(const gsrad_bvh *bvh, const float *albe
     for (int k = 0; k < 16; ++k) out.p[k] = fields[k];
     ProfScope ps("direct_light_backward", st);
     return launch_direct_backward(bvh->dev(), albedo, light_pos, light_I, n_lights, K, grad_E, h->lacc.p,
-                                  grad_light_pos, grad_light_I, grad_albedo, out, h->height.as<int>() + 12, st);
-}
-
-// The hit lists' workspace; NULL (the sums are then added directly, 1.3 to 4
-// times slower) where none is wanted or it would take more than an eighth of
-// the free memory: a handle keeps it, so with many handles alive the lists
-// leave room for what cannot do without.  No error either way.
-static void *list_workspace(DevBuf &buf, size_t bytes) {
-    if (bytes == 0) return nullptr;
-    if (bytes <= buf.bytes && buf.p) return buf.p;
-    size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    if (bytes > free_b / 8) return nullptr;
-    buf.release();
-    void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    buf.p = p;
-    buf.bytes = bytes;
-    return p;
+                                  h->light_lists.p, room, grad_light_pos, grad_light_I, grad_albedo, out,
+                                  h->height.as<int>() + 12, st);
 }
 
 gsrad_status gsrad_geometry_backward(const gsrad_bvh *bvh, const gsrad_ff *ff, const float *grad_F,
@@ -1488,10 +1498,12 @@ gsrad_status gsrad_geometry_backward(const gsrad_bvh *bvh, const gsrad_ff *ff, c
             if (fields[k]) GS_TRY(check_hip(hipMemsetAsync(fields[k], 0, (size_t)ff->n * 4, st), "zero gradient"));
         return GSRAD_OK;
     }
+    const size_t want = geometry_list_bytes(ff->n, f->R);
+    void *lists = want > 0 && list_workspace(f->geo_lists, want, want, st) >= want ? f->geo_lists.p : nullptr;
     ProfScope ps("geometry_backward", st);
     return launch_geometry_rec(bvh->dev(), f->R, f->seed, f->recs.as<uint2>(), f->rcnt.as<uint32_t>(), f->rec_cap,
                                f->row_ptr.as<int64_t>(), f->col.as<int32_t>(), grad_F, std::max(f->max_row, 1),
-                               f->cacc.p, list_workspace(f->geo_lists, geometry_list_bytes(ff->n, f->R)), out, st);
+                               f->cacc.p, lists, out, st);
 }
 
 gsrad_status gsrad_opacity_backward(const gsrad_bvh *bvh, const gsrad_ff *ff, const float *grad_F,
@@ -1519,8 +1531,9 @@ gsrad_status gsrad_opacity_backward(const gsrad_bvh *bvh, const gsrad_ff *ff, co
         if ((size_t)f->max_row * 8 + ff_stack_bytes(256) > 150 * 1024)
             return einval("gsrad_opacity_backward: row too long for the LDS row cache");
         if (f->has_records) {
+            const size_t want = opacity_list_bytes(n, f->R);
+            void *ws = want > 0 && list_workspace(f->opac_lists, want, want, st) >= want ? f->opac_lists.p : nullptr;
             ProfScope ps("opacity_records", st);
-            void *ws = list_workspace(f->opac_lists, opacity_list_bytes(n, f->R));
             GS_TRY(launch_opacity_rec(bvh->dev(), f->R, f->recs.as<uint2>(), f->rcnt.as<uint32_t>(), f->rec_cap,
                                       f->row_ptr.as<int64_t>(), f->col.as<int32_t>(), grad_F, std::max(f->max_row, 1),
                                       acc, ws, st));

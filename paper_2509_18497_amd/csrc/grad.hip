@@ -410,8 +410,7 @@ __global__ void __launch_bounds__(kCenterThreads) k_center_bwd(BvhDev bv, const 
 // bowl, as long as k_ff_center), then by the LDS atomics.  A segment a lane
 // and ten global atomics a crossing took 108 ms.
 // The lists lie in the workgroup's own stretch of the workspace; a row that
-// crosses more surfels than fit is left to k_center_bwd from there (done[row],
-// zeroed before).
+// crosses more surfels than fit is left to k_center_bwd from there (done[row]).
 constexpr int kCenterRowThreads = 512, kRowSegs = 512, kRowParts = 5, kRowSlots = 512;
 constexpr int kRowPart = 13312;        // list places of a part
 constexpr int64_t kCenterGroups = 512;   // workgroups, two a CU
@@ -860,9 +859,10 @@ struct SegLists {
     uint32_t *count;   // [lanes] surfels crossed
     uint32_t *hit;     // [lanes][kSegHits] their sorted positions
     uint32_t *block;   // [lanes] block of a lane with more than kSegHits
-    uint32_t *more;    // [lanes / kSegShare][kSegMore]
+    uint32_t *more;    // [blocks][kSegMore]
     uint32_t *used;    // blocks given out (zeroed before each slice's walk)
     int64_t pad, lanes;
+    uint32_t hits, blocks;   // kSegHits and lanes / kSegShare; without memory for lists 0, and every crossing is walked again
     static constexpr int64_t words_per_lane = 3 + kSegHits + kSegMore / kSegShare;
 };
 
@@ -909,14 +909,14 @@ __global__ void __launch_bounds__(kRowThreads) k_light_walk(BvhDev bv, const flo
     }
     __builtin_amdgcn_wave_barrier();
     uint32_t count = hits[row];
-    for (uint32_t h = lane; h < min(count, (uint32_t)kSegHits); h += 16) seg.hit[at * kSegHits + h] = list[row][h];
-    if (count > (uint32_t)kSegHits) {
+    for (uint32_t h = lane; h < min(count, seg.hits); h += 16) seg.hit[at * kSegHits + h] = list[row][h];
+    if (count > seg.hits) {
         uint32_t block = kSegAgain;
-        if (count <= (uint32_t)kListed) {
+        if (seg.blocks > 0 && count <= (uint32_t)kListed) {
             if (lane == 0) block = atomicAdd(seg.used, 1u);
             block = (uint32_t)__shfl((int)block, (int)__lane_id() & 48);
         }
-        if (block >= (uint32_t)(seg.lanes / kSegShare)) {
+        if (block >= seg.blocks) {
             count = kSegAgain;
         } else {
             for (uint32_t h = kSegHits + lane; h < count; h += 16)
@@ -1221,9 +1221,8 @@ size_t geometry_list_bytes(int64_t n, int R) {
     return lists_pay(n, R, kGeometryShift) ? (size_t)ListLayout(n, R, threads, kGeometryShift, kGeometryEntry).bytes : 0;
 }
 
-size_t center_list_bytes(int64_t n) {
-    return (size_t)std::min(n, kCenterGroups) * kRowParts * kRowPart * sizeof(uint2) + (size_t)n * 4;
-}
+size_t center_group_bytes() { return (size_t)kRowParts * kRowPart * sizeof(uint2); }
+size_t center_list_bytes(int64_t n) { return (size_t)std::min(n, kCenterGroups) * center_group_bytes(); }
 
 size_t center_acc_bytes(int64_t n) { return (size_t)8 * kFields * n * 8 + 512; }
 
@@ -1260,7 +1259,8 @@ static gsrad_status center_scaled_passes(int64_t n, int64_t count, void *acc, hi
 }
 
 gsrad_status launch_center_backward(const BvhDev &bv, const Csr &F, const float *lambda, const float *gF, void *acc,
-                                    const CenterOutputs &out, int *err, hipStream_t st) {
+                                    int32_t *done, void *lists, size_t list_bytes, const CenterOutputs &out, int *err,
+                                    hipStream_t st) {
     if (F.n == 0) return GSRAD_OK;
     unsigned long long *a = static_cast<unsigned long long *>(acc);
     uint32_t *maxbits = reinterpret_cast<uint32_t *>(a + (size_t)8 * kFields * F.n);
@@ -1273,22 +1273,29 @@ gsrad_status launch_center_backward(const BvhDev &bv, const Csr &F, const float 
         attr_set = true;
     }
     const size_t smem = kWalkBytes;
-    const int64_t groups = std::min(F.n, kCenterGroups);
-    char *lists = reinterpret_cast<char *>(acc) + center_acc_bytes(F.n);
-    int32_t *done = reinterpret_cast<int32_t *>(lists + groups * kRowParts * kRowPart * (int64_t)sizeof(uint2));
+    // as many workgroups as have lists; with none, every row is k_center_bwd's
+    const int64_t groups = std::min(std::min(F.n, kCenterGroups), (int64_t)(list_bytes / center_group_bytes()));
+    if (groups == 0) {
+        const gsrad_status e = check_hip(hipMemsetAsync(done, 0, (size_t)F.n * 4, st), "rows zero");
+        if (e != GSRAD_OK) return e;
+    }
     auto run = [&](int pass, int stride) {
         const int64_t rows = (F.n + stride - 1) / stride;
         const int64_t nb = (rows + 1) / 2;
-        const unsigned grid = (unsigned)std::min(rows, kCenterGroups);
-        uint2 *lp = reinterpret_cast<uint2 *>(lists);
+        const unsigned grid = (unsigned)std::min(rows, groups);
+        uint2 *lp = static_cast<uint2 *>(lists);
         if (pass == 0) {
-            hipLaunchKernelGGL(k_center_rows<0>, dim3(grid), dim3(kCenterRowThreads), sizeof(RowShared), st, bv,
-                               F.row_ptr, F.col, F.val, F.n, lambda, gF, maxbits, fx, a, F.order, stride, lp, done, err);
+            if (groups > 0)
+                hipLaunchKernelGGL(k_center_rows<0>, dim3(grid), dim3(kCenterRowThreads), sizeof(RowShared), st, bv,
+                                   F.row_ptr, F.col, F.val, F.n, lambda, gF, maxbits, fx, a, F.order, stride, lp, done,
+                                   err);
             hipLaunchKernelGGL(k_center_bwd<0>, dim3((unsigned)nb), dim3(kCenterThreads), smem, st, bv, F.row_ptr,
                                F.col, F.val, F.n, lambda, gF, maxbits, fx, a, nb, F.order, stride, done, err);
         } else {
-            hipLaunchKernelGGL(k_center_rows<1>, dim3(grid), dim3(kCenterRowThreads), sizeof(RowShared), st, bv,
-                               F.row_ptr, F.col, F.val, F.n, lambda, gF, maxbits, fx, a, F.order, stride, lp, done, err);
+            if (groups > 0)
+                hipLaunchKernelGGL(k_center_rows<1>, dim3(grid), dim3(kCenterRowThreads), sizeof(RowShared), st, bv,
+                                   F.row_ptr, F.col, F.val, F.n, lambda, gF, maxbits, fx, a, F.order, stride, lp, done,
+                                   err);
             hipLaunchKernelGGL(k_center_bwd<1>, dim3((unsigned)nb), dim3(kCenterThreads), smem, st, bv, F.row_ptr,
                                F.col, F.val, F.n, lambda, gF, maxbits, fx, a, nb, F.order, stride, done, err);
         }
@@ -1353,31 +1360,39 @@ gsrad_status launch_geometry_rec(const BvhDev &bv, int R, uint64_t seed, const u
     return check_hip(hipGetLastError(), "geometry backward launch");
 }
 
-// [8 XCD copies][kFields][n] u64, the lights' [8][4][Lt] u64, maxbits[32],
-// fx[32]
-size_t light_acc_bytes(int64_t n, int Lt) { return (size_t)8 * kFields * n * 8 + (size_t)8 * 4 * Lt * 8 + 256; }
-
 // receivers padded to the workgroups of k_light_terms, lights of a slice
 static int64_t light_pad(int64_t n) { return (n + kTermThreads - 1) / kTermThreads * kTermThreads; }
 static int light_slice(int64_t n, int Lt) {
     return (int)std::min<int64_t>({(int64_t)Lt, 32768, std::max<int64_t>(1, kSegLanes / light_pad(n))});
 }
-size_t light_seg_bytes(int64_t n, int Lt) { return (size_t)light_slice(n, Lt) * light_pad(n) * SegLists::words_per_lane * 4; }
+
+// [8 XCD copies][kFields][n] u64, the lights' [8][4][Lt] u64, maxbits[32],
+// fx[32]; behind them a light's T, counts and blocks, for where there is no
+// memory for its lists
+static size_t light_sum_bytes(int64_t n, int Lt) { return (size_t)8 * kFields * n * 8 + (size_t)8 * 4 * Lt * 8 + 256; }
+size_t light_acc_bytes(int64_t n, int Lt) { return light_sum_bytes(n, Lt) + (size_t)light_pad(n) * 12; }
+size_t light_one_bytes(int64_t n) { return (size_t)light_pad(n) * SegLists::words_per_lane * 4; }
+size_t light_list_bytes(int64_t n, int Lt) { return (size_t)light_slice(n, Lt) * light_one_bytes(n); }
 
 gsrad_status launch_direct_backward(const BvhDev &bv, const float *albedo, const float *lpos, const float *lI, int Lt,
-                                    int K, const float *gE, void *acc, float *g_lpos, float *g_lI, float *g_alb,
-                                    const CenterOutputs &out, int *err, hipStream_t st) {
+                                    int K, const float *gE, void *acc, void *lists, size_t list_bytes, float *g_lpos,
+                                    float *g_lI, float *g_alb, const CenterOutputs &out, int *err, hipStream_t st) {
     static_assert(kLightFields <= kLightCrossings && kLightCrossings % 2 == 0,
                   "maxbits and fx hold 32 entries each; crossings are counted at kLightCrossings, blocks in the last");
     unsigned long long *a = static_cast<unsigned long long *>(acc);
     unsigned long long *la = a + (size_t)8 * kFields * bv.n;
     uint32_t *maxbits = reinterpret_cast<uint32_t *>(la + (size_t)8 * 4 * Lt);
     int *fx = reinterpret_cast<int *>(maxbits + 32);
-    const int slice = light_slice(bv.n, Lt);
+    // as many lights a slice as have lists
+    const bool listed = list_bytes >= light_one_bytes(bv.n);
+    const int slice =
+        listed ? (int)std::min<int64_t>(light_slice(bv.n, Lt), (int64_t)(list_bytes / light_one_bytes(bv.n))) : 1;
     SegLists seg;
     seg.pad = light_pad(bv.n);
     seg.lanes = seg.pad * slice;
-    seg.T = reinterpret_cast<float *>(fx + 32);
+    seg.hits = listed ? kSegHits : 0;
+    seg.blocks = listed ? (uint32_t)(seg.lanes / kSegShare) : 0;
+    seg.T = listed ? static_cast<float *>(lists) : reinterpret_cast<float *>(fx + 32);
     seg.count = reinterpret_cast<uint32_t *>(seg.T + seg.lanes);
     seg.block = seg.count + seg.lanes;
     seg.hit = seg.block + seg.lanes;

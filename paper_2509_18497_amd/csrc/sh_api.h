@@ -38,9 +38,12 @@ struct CenterOutputs {
     float *p[16];
 };
 size_t center_acc_bytes(int64_t n);
+// the lists' workspace (any number of center_group_bytes, also none), done: n words
 size_t center_list_bytes(int64_t n);
+size_t center_group_bytes();
 gsrad_status launch_center_backward(const BvhDev &bv, const Csr &F, const float *lambda, const float *gF, void *acc,
-                                    const CenterOutputs &out, int *err, hipStream_t st);
+                                    int32_t *done, void *lists, size_t list_bytes, const CenterOutputs &out, int *err,
+                                    hipStream_t st);
 
 // geometry gradients through the ray-cast F from the recorded hits
 // (accumulators of center_acc_bytes(n) zeroed first; out.p[0..14])
@@ -50,13 +53,15 @@ gsrad_status launch_geometry_rec(const BvhDev &bv, int R, uint64_t seed, const u
 // workspace of launch_geometry_rec (0: none taken; NULL ws is always accepted)
 size_t geometry_list_bytes(int64_t n, int R);
 
-// direct-light gradients (workspace of light_acc_bytes + light_seg_bytes,
-// its first light_acc_bytes zeroed; out.p[0..14] surfel fields)
+// direct-light gradients (acc: light_acc_bytes, zeroed first; the lists'
+// workspace: up to light_list_bytes in light_one_bytes a light, also none;
+// out.p[0..14] surfel fields)
 size_t light_acc_bytes(int64_t n, int Lt);
-size_t light_seg_bytes(int64_t n, int Lt);
+size_t light_list_bytes(int64_t n, int Lt);
+size_t light_one_bytes(int64_t n);
 gsrad_status launch_direct_backward(const BvhDev &bv, const float *albedo, const float *lpos, const float *lI, int Lt,
-                                    int K, const float *gE, void *acc, float *g_lpos, float *g_lI, float *g_alb,
-                                    const CenterOutputs &out, int *err, hipStream_t st);
+                                    int K, const float *gE, void *acc, void *lists, size_t list_bytes, float *g_lpos,
+                                    float *g_lI, float *g_alb, const CenterOutputs &out, int *err, hipStream_t st);
 
 // Monte-Carlo TD(0) solver (trace.hip): device buffers owned by the handle
 struct McBuffers {
