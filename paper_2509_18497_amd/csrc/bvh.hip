@@ -316,15 +316,12 @@ __global__ void __launch_bounds__(1024) k_refit_small(const Node *__restrict__ n
     for (int k = tid; k < 6 * (n - 1); k += threads) nodebox[k] = box[k];
 }
 
-// The children's boxes into the nodes, and the WideNodes beside them: planes in
-// steps of 1/65520 of the scene's box, moved out by one to two steps.  A step
-// is at least 2^-21 of the box's largest coordinate: what FP32 loses in
-// base + q step, and in the trace's (base - o) / d + q (step / d), is then at
-// most a fifth of a step.
+// The children's boxes into the nodes, and the WideNodes beside them.  A
+// node's grid starts a little below its box and reaches a little beyond it, so
+// that the outer planes too are moved out by at least a thousandth of a step.
 __global__ void __launch_bounds__(kThreads) k_pack(Node *__restrict__ nodes, WideNode *__restrict__ wide,
                                                    const float *__restrict__ leafbox,
-                                                   const float *__restrict__ nodebox, float *__restrict__ bounds,
-                                                   int64_t n) {
+                                                   const float *__restrict__ nodebox, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= n - 1) return;
     auto box = [&](int c) { return c < 0 ? leafbox + (int64_t)(~c) * 6 : nodebox + (int64_t)c * 6; };
@@ -339,31 +336,28 @@ __global__ void __launch_bounds__(kThreads) k_pack(Node *__restrict__ nodes, Wid
         w.ch[2 * h] = c[h] < 0 ? c[h] : nodes[c[h]].ch.x;
         w.ch[2 * h + 1] = c[h] < 0 ? kNoChild : nodes[c[h]].ch.y;
     }
-    float base[3], step[3];   // (nodebox[0]: the root's; planes that are not finite end at the grid's)
+    const float *own = nodebox + i * 6;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        const float lo = fmaxf(nodebox[k], -1e30f), hi = fminf(nodebox[3 + k], 1e30f);
-        step[k] = fmaxf(fmaxf((hi - lo) * (1.0f / 65520.0f), fmaxf(fabsf(lo), fabsf(hi)) * 0x1p-21f), 1e-35f);
-        base[k] = lo - 4.0f * step[k];
-        if (i == 0) {
-            bounds[8 + k] = base[k];
-            bounds[11 + k] = step[k];
+        // (planes that are not finite end at the grid's ends)
+        float lo = fmaxf(own[k], -kWideFar), hi = fminf(own[3 + k], kWideFar);
+        if (!(lo <= hi)) {
+            lo = -kWideFar;
+            hi = kWideFar;
         }
-    }
+        const float base = lo - (hi - lo) * 4e-5f - fabsf(lo) * 1.2e-7f;
+        const float step = fmaxf((hi - base) * (1.00001f / 254.9f), 1e-35f);
+        w.base[k] = base;
+        w.step[k] = step;
+        w.lo[k] = w.hi[k] = 0;
+        const double per = 1.0 / (double)step;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const float *b = box(w.ch[g] == kNoChild ? c[g / 2] : w.ch[g]);
-        uint32_t q[6];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const float lo = floorf((b[k] - base[k]) / step[k]) - 1.0f;
-            const float hi = ceilf((b[3 + k] - base[k]) / step[k]) + 1.0f;
-            q[k] = (uint32_t)fminf(fmaxf(lo, 0.0f), 65535.0f);
-            q[3 + k] = (uint32_t)fmaxf(fminf(hi, 65535.0f), 0.0f);
+        for (int g = 0; g < 4; ++g) {
+            const float *b = box(w.ch[g] == kNoChild ? c[g / 2] : w.ch[g]);
+            const double ql = floor(((double)b[k] - base) * per - 2e-3), qh = ceil(((double)b[3 + k] - base) * per + 2e-3);
+            w.lo[k] |= (uint32_t)fmin(fmax(ql, 0.0), 255.0) << (8 * g);
+            w.hi[k] |= (uint32_t)fmax(fmin(qh, 255.0), 0.0) << (8 * g);
         }
-        w.box[3 * g] = q[0] | q[1] << 16;
-        w.box[3 * g + 1] = q[2] | q[3] << 16;
-        w.box[3 * g + 2] = q[4] | q[5] << 16;
     }
     wide[i] = w;
 }
@@ -432,8 +426,7 @@ gsrad_status bvh_build(const gsrad_surfels &sf, BvhBuffers &B, hipStream_t st) {
             hipLaunchKernelGGL(k_refit, dim3(nblk(n)), dim3(kThreads), 0, st, B.nodes, B.leaf_parent, B.leafbox,
                                nodebox, height, counter, B.height, n);
         }
-        hipLaunchKernelGGL(k_pack, dim3(nblk(n - 1)), dim3(kThreads), 0, st, B.nodes, B.wide,
-                           B.leafbox, nodebox, B.bounds, n);
+        hipLaunchKernelGGL(k_pack, dim3(nblk(n - 1)), dim3(kThreads), 0, st, B.nodes, B.wide, B.leafbox, nodebox, n);
     }
     return check_hip(hipGetLastError(), "bvh build");
 }

@@ -43,14 +43,17 @@ struct __align__(16) Node {
     int4 ch;
 };
 
-// What the form-factor trace reads instead: a node's four grandchildren (a
-// child that is a leaf stands for itself, its second place empty) in the same
-// 64 bytes, box planes in steps of a grid over the scene (bounds[8..10] base,
-// [11..13] step), rounded outwards.  Box k in words 3 k ... 3 k + 2:
-//   lo.x | lo.y << 16, lo.z | hi.x << 16, hi.y | hi.z << 16
+// What the form-factor trace and row_crossings read instead: a node's four
+// grandchildren (a child that is a leaf stands for itself, its second place
+// empty) in the same 64 bytes.  Box planes are bytes, steps of a grid over the
+// node's own box, rounded outwards: byte k of a word is grandchild k's.  A
+// grid over the whole scene with 16 bits a plane was as fast in even scenes,
+// but one far surfel, or parts of very different size, made its step larger
+// than the surfels.
 struct __align__(16) WideNode {
-    uint32_t box[12];
-    int32_t ch[4];   // as Node's, or kNoChild
+    float base[3], step[3];
+    uint32_t lo[3], hi[3];   // per axis
+    int32_t ch[4];           // as Node's, or kNoChild
 };
 constexpr int kNoChild = 0x7fffffff;
 
@@ -63,7 +66,7 @@ struct BvhDev {
     const float *c;          // [n] opacity constant c_j, original order
     const float *op;         // [n] clamped opacity, original order
     const float *raw_op;     // [n] opacity as given, original order
-    const float *bounds;     // [14]: lo.xyz, hi.xyz, t_eps, diag, WideNode's base.xyz, step.xyz
+    const float *bounds;     // [8]: lo.xyz, hi.xyz, t_eps, diag
     const double *area;      // [n] App. E effective area, original order
     const float *dado;       // [n] d area / d opacity, original order
     float leaf_box_r;        // unused padding for alignment
@@ -250,22 +253,40 @@ __device__ __forceinline__ bool slab(float lox, float loy, float loz, float hix,
     return tmin <= tmax * 1.00001f + 1e-30f;
 }
 
-// The slab test on a WideNode's planes q: with s = step / d and b = (base - o) / d
-// a plane is at fma(q, s, b).
-__device__ __forceinline__ bool wide_slab(float lox, float loy, float loz, float hix, float hiy, float hiz, float sx,
-                                          float sy, float sz, float bx, float by, float bz, float t0, float t1,
-                                          float &tn) {
-    const float ax = __builtin_fmaf(lox, sx, bx), cx = __builtin_fmaf(hix, sx, bx);
-    const float ay = __builtin_fmaf(loy, sy, by), cy = __builtin_fmaf(hiy, sy, by);
-    const float az = __builtin_fmaf(loz, sz, bz), cz = __builtin_fmaf(hiz, sz, bz);
-    const float tmin = fmaxf(fmaxf(fminf(ax, cx), fminf(ay, cy)), fmaxf(fminf(az, cz), t0));
-    const float tmax = fminf(fminf(fmaxf(ax, cx), fmaxf(ay, cy)), fminf(fmaxf(az, cz), t1));
-    tn = tmin;
-    return tmin <= tmax * 1.00001f + 1e-30f;
-}
-
 __device__ __forceinline__ float safe_inv(float d) {
     return fabsf(d) > 1e-30f ? 1.0f / d : copysignf(1e30f, d);
+}
+
+// 1 / d for wide_slab: its products with a WideNode's base and step (at most
+// kWideFar) stay finite.
+constexpr float kWideFar = 1e18f;
+__device__ __forceinline__ float wide_inv(float d) {
+    return fabsf(d) > 1e-18f ? 1.0f / d : copysignf(1e18f, d);
+}
+
+// Which of a WideNode's grandchildren the ray's interval [t0, t1] meets, and
+// where it enters them.  With s = step / d and b = (base - o) / d a plane q is
+// at fma(q, s, b): off by at most 5 roundings of the node's extent (1e-4 steps;
+// k_pack moves the planes out by at least ten times that) and a few of the
+// plane's distance from o (the factor of slab).
+__device__ __forceinline__ void wide_slab(const float4 &q0, const uint4 &q1, const uint4 &q2, const int4 &ch, float ox,
+                                          float oy, float oz, float ix, float iy, float iz, float t0, float t1,
+                                          bool (&hit)[4], float (&tn)[4]) {
+    const float sx = q0.w * ix, sy = __uint_as_float(q1.x) * iy, sz = __uint_as_float(q1.y) * iz;
+    const float bx = (q0.x - ox) * ix, by = (q0.y - oy) * iy, bz = (q0.z - oz) * iz;
+    const uint32_t lo[3] = {q1.z, q1.w, q2.x}, hi[3] = {q2.y, q2.z, q2.w};
+    const int c[4] = {ch.x, ch.y, ch.z, ch.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        auto plane = [&](uint32_t w) { return (float)((w >> (8 * k)) & 0xffu); };
+        const float ax = __builtin_fmaf(plane(lo[0]), sx, bx), cx = __builtin_fmaf(plane(hi[0]), sx, bx);
+        const float ay = __builtin_fmaf(plane(lo[1]), sy, by), cy = __builtin_fmaf(plane(hi[1]), sy, by);
+        const float az = __builtin_fmaf(plane(lo[2]), sz, bz), cz = __builtin_fmaf(plane(hi[2]), sz, bz);
+        const float tmin = fmaxf(fmaxf(fminf(ax, cx), fminf(ay, cy)), fmaxf(fminf(az, cz), t0));
+        const float tmax = fminf(fminf(fmaxf(ax, cx), fmaxf(ay, cy)), fminf(fmaxf(az, cz), t1));
+        tn[k] = tmin;
+        hit[k] = tmin <= tmax * 1.00001f + 1e-30f && (k % 2 == 0 || c[k] != kNoChild);
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))
         uint2 *rec_out = nullptr;
         uint32_t *cnt_out = nullptr;
         float ox = 0.0f, oy = 0.0f, oz = 0.0f, dx = 0.0f, dy = 0.0f, dz = 0.0f;
-        float sx = 0.0f, sy = 0.0f, sz = 0.0f, bx = 0.0f, by = 0.0f, bz = 0.0f;   // grid_slab's step / d, (base - o) / d
+        float ix = 0.0f, iy = 0.0f, iz = 0.0f;
         float T = 1.0f, t0 = 0.0f, t1 = INFINITY;
         uint64_t last = 0;
         double key[kKB];
@@ -236,13 +236,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))
                         dx = __uint_as_float(ent.y);
                         dy = __uint_as_float(ent.z);
                         dz = __uint_as_float(ent.w);
-                        const float ix = safe_inv(dx), iy = safe_inv(dy), iz = safe_inv(dz);
-                        sx = bv.bounds[11] * ix;
-                        sy = bv.bounds[12] * iy;
-                        sz = bv.bounds[13] * iz;
-                        bx = (bv.bounds[8] - ox) * ix;
-                        by = (bv.bounds[9] - oy) * iy;
-                        bz = (bv.bounds[10] - oz) * iz;
+                        ix = wide_inv(dx);
+                        iy = wide_inv(dy);
+                        iz = wide_inv(dz);
                         q = 0;
                         T = 1.0f;
                         last = 0;
@@ -322,19 +318,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))
                 }
                 if (do_node) {
                     const uint4 *nd = reinterpret_cast<const uint4 *>(bv.wide + node);
-                    const uint4 q0 = nd[0], q1 = nd[1], q2 = nd[2], q3 = nd[3];
-                    auto low = [](uint32_t v) { return (float)(v & 0xffffu); };
-                    auto high = [](uint32_t v) { return (float)(v >> 16); };
-                    auto test = [&](uint32_t x, uint32_t y, uint32_t z, float &tn) {
-                        return wide_slab(low(x), high(x), low(y), high(y), low(z), high(z), sx, sy, sz, bx, by, bz, t0,
-                                         t1, tn);
-                    };
-                    const int ch[4] = {(int)q3.x, (int)q3.y, (int)q3.z, (int)q3.w};
+                    const float4 q0 = *reinterpret_cast<const float4 *>(nd);
+                    const uint4 q1 = nd[1], q2 = nd[2];
+                    const int4 q3 = *reinterpret_cast<const int4 *>(nd + 3);
+                    const int ch[4] = {q3.x, q3.y, q3.z, q3.w};
                     float tn[4];
-                    bool h[4] = {test(q0.x, q0.y, q0.z, tn[0]), test(q0.w, q1.x, q1.y, tn[1]),
-                                 test(q1.z, q1.w, q2.x, tn[2]), test(q2.y, q2.z, q2.w, tn[3])};
-                    h[1] = h[1] && ch[1] != kNoChild;
-                    h[3] = h[3] && ch[3] != kNoChild;
+                    bool h[4];
+                    wide_slab(q0, q1, q2, q3, ox, oy, oz, ix, iy, iz, t0, t1, h, tn);
                     // leaves to the queue; the nearest node is next, the
                     // others go on the stack; with none left, pop; an empty
                     // stack ends the walk (the round ends once the queued

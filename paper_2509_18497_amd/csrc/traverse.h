@@ -499,9 +499,7 @@ __device__ __forceinline__ float row_crossings(const BvhDev &bv, const Segment &
                                                int32_t *nodes, int *err, OnHit &&on_hit) {
     int32_t *leaves = nodes + kCrossNodes;
     const int l = threadIdx.x & 15, row = (int)__lane_id() & 48;
-    const float ix = safe_inv(g.dx), iy = safe_inv(g.dy), iz = safe_inv(g.dz);
-    const float sx = bv.bounds[11] * ix, sy = bv.bounds[12] * iy, sz = bv.bounds[13] * iz;
-    const float bx = (bv.bounds[8] - g.ox) * ix, by = (bv.bounds[9] - g.oy) * iy, bz = (bv.bounds[10] - g.oz) * iz;
+    const float ix = wide_inv(g.dx), iy = wide_inv(g.dy), iz = wide_inv(g.dz);
     const float t0 = g.t_lo * 0.99999f, t1 = g.t_hi * 1.00001f;
     long long depth = 0;
     int sp = bv.n > 1 ? 1 : 0, nl = 1 - sp;
@@ -540,22 +538,15 @@ __device__ __forceinline__ float row_crossings(const BvhDev &bv, const Segment &
             bool h[4] = {};
             if (l < m) {
                 const uint4 *q = reinterpret_cast<const uint4 *>(bv.wide + nodes[sp - 1 - l]);
-                const uint4 q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
-                auto low = [](uint32_t x) { return (float)(x & 0xffffu); };
-                auto high = [](uint32_t x) { return (float)(x >> 16); };
-                auto test = [&](uint32_t x, uint32_t y, uint32_t z) {
-                    float tn;
-                    return wide_slab(low(x), high(x), low(y), high(y), low(z), high(z), sx, sy, sz, bx, by, bz, t0, t1,
-                                     tn);
-                };
-                c[0] = (int)q3.x;
-                c[1] = (int)q3.y;
-                c[2] = (int)q3.z;
-                c[3] = (int)q3.w;
-                h[0] = test(q0.x, q0.y, q0.z);
-                h[1] = test(q0.w, q1.x, q1.y) && c[1] != kNoChild;
-                h[2] = test(q1.z, q1.w, q2.x);
-                h[3] = test(q2.y, q2.z, q2.w) && c[3] != kNoChild;
+                const float4 q0 = *reinterpret_cast<const float4 *>(q);
+                const uint4 q1 = q[1], q2 = q[2];
+                const int4 q3 = *reinterpret_cast<const int4 *>(q + 3);
+                c[0] = q3.x;
+                c[1] = q3.y;
+                c[2] = q3.z;
+                c[3] = q3.w;
+                float tn[4];
+                wide_slab(q0, q1, q2, q3, g.ox, g.oy, g.oz, ix, iy, iz, t0, t1, h, tn);
             }
             __builtin_amdgcn_wave_barrier();
             // (counts of the lanes before and of all, through the counts' bits)
