@@ -188,7 +188,7 @@ struct gsrad_ff {
     int rec_cap = 0;
     DevBuf recs, rcnt;
     // capacities the last ray cast needed (starting points of the next)
-    int deep_stack = 0, agg_log2h = 0;
+    int agg_log2h = 0;
     // scratch of the ray-cast path
     DevBuf slab, ell_col, ell_val, row_len, err, scan_temp, redo, pools;
     // opacity backward: per-XCD fixed-point accumulators and scale
@@ -558,7 +558,7 @@ gsrad_status gsrad_form_factors(const gsrad_bvh *bvh, const gsrad_ff_params *p, 
     gsrad_ff *h = created ? new gsrad_ff() : *ff;
     // a reused handle is unusable until this call succeeds (its buffers are
     // overwritten or reallocated on the way)
-    const int prev_rec_cap = h->rec_cap, prev_log2h = h->agg_log2h, prev_deep = h->deep_stack;
+    const int prev_rec_cap = h->rec_cap, prev_log2h = h->agg_log2h;
     invalidate(h);
     auto fail = [&](gsrad_status e) {
         if (created) delete h;
@@ -567,11 +567,10 @@ gsrad_status gsrad_form_factors(const gsrad_bvh *bvh, const gsrad_ff_params *p, 
     hipStream_t st = S(stream);
     const int64_t n = bvh->n;
     const int R = p->rays_per_surfel;
-    // a handle traced before starts from the record slots, stack and
-    // aggregation table its last call needed (the rows do not depend on them)
+    // a handle traced before starts from the record slots and aggregation
+    // table its last call needed (the rows do not depend on them)
     int rcap = created ? kRecCap : std::max(kRecCap, prev_rec_cap);
     const int log2h = created ? kLog2Table : std::max(kLog2Table, prev_log2h);
-    int deep = created ? 0 : prev_deep;
     const int64_t cap_row = p->topk > 0 ? p->topk : (1 << kLog2TableMax);
     gsrad_status e;
     float t_eps = p->t_eps;
@@ -625,7 +624,7 @@ gsrad_status gsrad_form_factors(const gsrad_bvh *bvh, const gsrad_ff_params *p, 
             {
                 ProfScope ps("ff_trace", st);
                 if ((e = launch_ff_trace(bv, R, t_eps, p->t_min, s0, cnt, keep ? 1 : 0, h->recs.as<uint2>(),
-                                         h->rcnt.as<uint32_t>(), rcap, deep, h->pools.p, err, st)) != GSRAD_OK)
+                                         h->rcnt.as<uint32_t>(), rcap, h->pools.p, err, st)) != GSRAD_OK)
                     return fail(e);
             }
             ProfScope ps("ff_aggregate", st);
@@ -646,12 +645,6 @@ gsrad_status gsrad_form_factors(const gsrad_bvh *bvh, const gsrad_ff_params *p, 
                            "ff nnz copy")) != GSRAD_OK)
             return fail(e);
         if ((e = check_hip(hipStreamSynchronize(st), "ff sync")) != GSRAD_OK) return fail(e);
-        // a tree deeper than the shallow traversal stack: trace again with
-        // the deep one
-        if ((flags[0] & kErrStack) && !deep) {
-            deep = 1;
-            continue;
-        }
         // a ray composited more hits than its record slots: the rows are
         // incomplete, so run again with twice the slots
         if ((flags[0] & kErrRecords) && attempt < 4) {
@@ -690,7 +683,6 @@ gsrad_status gsrad_form_factors(const gsrad_bvh *bvh, const gsrad_ff_params *p, 
     h->t_min = p->t_min;
     h->has_records = keep;
     h->rec_cap = rcap;
-    h->deep_stack = deep;
     // most rows needed the largest table: start there next time
     h->agg_log2h = flags[2] > n / 4 ? kLog2TableMax : log2h;
     if (p->flags & GSRAD_FF_COMPACT) {

@@ -61,11 +61,17 @@ constexpr int kFlushNum = 1, kFlushDen = 2;
 // 1/4 +1.8 ms, at 3/8 +0.3, at 5/8 +0.9; a k-buffer of 16 +0.8, of 24 +2.6.
 constexpr int kLeafQ = 20;
 constexpr int kLeafNum = 1, kLeafDen = 2;
-// stack entries a lane of the trace: up to three a level of four grandchildren,
-// mostly one (a bowl of 1 M surfels, 29 levels of the binary tree, stays below
-// 29); a tree that needs more is traced again with the deep stack
-constexpr int kWideShallow = 32, kWideDeep = 96;
-constexpr size_t ff_trace_bytes(int stack) { return (size_t)(stack + kLeafQ) * 256 * sizeof(uint32_t); }
+// Stack of a lane of the trace: up to three entries a level of four
+// grandchildren, so 90 for a tree of 62 levels, but mostly one (an even bowl of
+// 1 M surfels, 29 levels of the binary tree, stays below 29).  kWideStack of
+// them lie in LDS; when these are full the oldest kSpill go to the lane's
+// private memory, up to kAside, and come back when the rest is used up.  Parts of
+// very different size need that: 32k surfels in four bowls of extents 1 to
+// 10^-3, 17.6 ms; traced again with 96 entries in LDS, where a CU holds one
+// workgroup instead of three, 61 ms at first and 39 ms from then on.
+constexpr int kWideStack = 32, kSpill = 16, kAside = 64;
+static_assert(kWideStack - 3 + kAside >= 90, "any tree of 30-bit codes and 32 index bits");
+constexpr size_t kTraceBytes = (size_t)(kWideStack + kLeafQ) * 256 * sizeof(uint32_t);
 
 // Lane index within the wave, recomputed at each use (volatile: not hoisted
 // out of the traversal loop into a register of its own).
@@ -133,7 +139,6 @@ __device__ __forceinline__ uint32_t next_pool(uint32_t *queue, int64_t npools, i
 // takes the next ray at once (the same hits, composited in the same order,
 // as the plain per-ray walk).  Three waves per SIMD (at most 168 VGPRs),
 // held by a launch bound; four (at most 128) were measured no faster.
-template <int STK>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) k_ff_trace(BvhDev bv, int R, float t_eps, float t_min,
                                                   int64_t s_begin, int64_t count, int pool_rays, int64_t npools,
                                                   const uint4 *__restrict__ list, uint32_t *queue,
@@ -171,6 +176,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))
 #pragma unroll
         for (int k = 0; k < kKB; ++k) key[k] = __longlong_as_double((long long)kKeyEmpty);
         int found = 0, sp = 0, node = 0;
+        uint32_t tail[kAside];   // the stack's oldest entries, set aside
+        int aside = 0;
         // queued leaves (LIFO; the order of the leaf tests does not change
         // the round's buffer: it keeps the KB smallest keys whatever the
         // order), and whether the round's walk of the tree is done
@@ -184,6 +191,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))
             t0 = (last ? __uint_as_float((uint32_t)(last >> 32)) : t_eps) * 0.99999f;
             t1 = INFINITY;
             sp = 0;
+            aside = 0;
             node = 0;
             qn = 0;
             walked = false;
@@ -313,7 +321,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))
                 const bool do_leaf = leaf_step && qn > 0, do_node = !leaf_step && can;
                 if (do_leaf) {
                     --qn;
-                    const int s = (int)stack_mem[wave_base + lane_index() + (STK + qn) * 256];
+                    const int s = (int)stack_mem[wave_base + lane_index() + (kWideStack + qn) * 256];
                     visit_leaf<kKB>(bv.rec, s, i, ox, oy, oz, dx, dy, dz, t_eps, last, key, found, t1);
                 }
                 if (do_node) {
@@ -328,25 +336,35 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))
                     // leaves to the queue; the nearest node is next, the
                     // others go on the stack; with none left, pop; an empty
                     // stack ends the walk (the round ends once the queued
-                    // leaves are tested too).  A push past the stack's end
-                    // ends the ray with an error (the launch is repeated with
-                    // the deep stack).  The lane's column: the wave's base
+                    // leaves are tested too).  The lane's column: the wave's base
                     // (uniform) plus the lane index, read again here rather
                     // than held in a register across the loop
                     uint32_t *column = stack_mem + wave_base + lane_index();
-                    const bool ovf = sp > STK - 3;
+                    if (__builtin_expect(sp > kWideStack - 3, 0)) {
+                        if (aside + kSpill <= kAside) {
+#pragma unroll 1
+                            for (int k = 0; k < kSpill; ++k) tail[aside + k] = column[k * 256];
+#pragma unroll 1
+                            for (int k = kSpill; k < sp; ++k) column[(k - kSpill) * 256] = column[k * 256];
+                            aside += kSpill;
+                            sp -= kSpill;
+                        } else {   // (no tree that can be built)
+                            atomicOr(err, kErrStack);
+                            sp = kWideStack - 3;
+                        }
+                    }
                     int next = -1;
                     float near_t = 0.0f;
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         if (!h[k]) continue;
                         if (ch[k] < 0) {
-                            column[(STK + qn) * 256] = (uint32_t)~ch[k];
+                            column[(kWideStack + qn) * 256] = (uint32_t)~ch[k];
                             ++qn;
                             continue;
                         }
                         const bool nearer = next < 0 || tn[k] < near_t;
-                        if (next >= 0 && !ovf) {
+                        if (next >= 0) {
                             column[sp * 256] = (uint32_t)(nearer ? next : ch[k]);
                             ++sp;
                         }
@@ -355,16 +373,17 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))
                     }
                     node = next;
                     if (next < 0) {
+                        if (sp == 0 && aside > 0) {
+                            aside -= kSpill;
+                            sp = kSpill;
+#pragma unroll 1
+                            for (int k = 0; k < kSpill; ++k) column[k * 256] = tail[aside + k];
+                        }
                         if (sp == 0) walked = true;
                         else {
                             --sp;
                             node = (int)column[sp * 256];
                         }
-                    }
-                    if (ovf) {
-                        atomicOr(err, kErrStack);
-                        end_ray();
-                        qn = 0;
                     }
                 }
                 if (trav && walked && qn == 0) trav = false;   // the round's hits are all tested
@@ -1218,7 +1237,7 @@ gsrad_status launch_ray_pools(const BvhDev &bv, int R, uint64_t seed, int64_t s_
 }
 
 gsrad_status launch_ff_trace(const BvhDev &bv, int R, float t_eps, float t_min, int64_t s_begin, int64_t count,
-                             int by_orig, uint2 *recs, uint32_t *rcnt, int rcap, int deep, void *pools, int *err,
+                             int by_orig, uint2 *recs, uint32_t *rcnt, int rcap, void *pools, int *err,
                              hipStream_t st) {
     if (count <= 0 || bv.n == 1) return GSRAD_OK;
     const int pool_rays = R >= kPoolRays ? kPoolRays : (kPoolRays / R) * R;
@@ -1233,17 +1252,8 @@ gsrad_status launch_ff_trace(const BvhDev &bv, int R, float t_eps, float t_min, 
         GSRAD_OK)
         return s;
     const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(npools, 3 * (int64_t)cus));
-    if (deep) {
-        const size_t smem = ff_trace_bytes(kWideDeep);
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_ff_trace<kWideDeep>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        hipLaunchKernelGGL(k_ff_trace<kWideDeep>, dim3((unsigned)grid), dim3(256), smem, st, bv, R, t_eps, t_min,
-                           s_begin, count, pool_rays, npools, list, queue, by_orig, recs, rcnt, rcap, err);
-    } else {
-        hipLaunchKernelGGL(k_ff_trace<kWideShallow>, dim3((unsigned)grid), dim3(256), ff_trace_bytes(kWideShallow), st,
-                           bv, R, t_eps, t_min, s_begin, count, pool_rays, npools, list, queue, by_orig, recs, rcnt,
-                           rcap, err);
-    }
+    hipLaunchKernelGGL(k_ff_trace, dim3((unsigned)grid), dim3(256), kTraceBytes, st, bv, R, t_eps, t_min, s_begin, count,
+                       pool_rays, npools, list, queue, by_orig, recs, rcnt, rcap, err);
     return check_hip(hipGetLastError(), "ff trace launch");
 }
 

@@ -24,7 +24,7 @@ gsrad_status launch_ray_pools(const BvhDev &bv, int R, uint64_t seed, int64_t s_
                               uint32_t *rcnt, void *pools, hipStream_t st);
 // trace of the pools launch_ray_pools made (run it again before a repeat)
 gsrad_status launch_ff_trace(const BvhDev &bv, int R, float t_eps, float t_min, int64_t s_begin, int64_t count,
-                             int by_orig, uint2 *recs, uint32_t *rcnt, int rcap, int deep, void *pools, int *err,
+                             int by_orig, uint2 *recs, uint32_t *rcnt, int rcap, void *pools, int *err,
                              hipStream_t st);
 // Rows overflowing a table of 2^log2h entries (a probe chain of 256) are listed in
 // redo_list (count in redo_cnt[0], tickets in redo_cnt[1]; room for count

@@ -136,8 +136,7 @@ __device__ __forceinline__ float trace_sorted(const BvhDev &bv, float ox, float 
                 }
                 // descend into the nearer hit child and push the other; with
                 // no child left, pop.  A push past the stack's end ends the
-                // walk with an error (the caller traces again with the deep
-                // stack).
+                // walk with an error.
                 const bool both = h0 && h1;
                 const bool n0 = !h1 || (h0 && tn0 <= tn1);
                 ovf = both && sp >= STK;
