@@ -276,7 +276,7 @@ struct gsrad_batch {
     // captured adjoint loop and its arguments
     hipGraph_t agraph = nullptr;
     hipGraphExec_t aexec = nullptr;
-    const void *a_rho = nullptr, *a_gB = nullptr, *a_gE = nullptr, *a_L = nullptr, *a_lam0 = nullptr, *a_ft[3] = {}, *a_h = nullptr;
+    const void *a_rho = nullptr, *a_gE = nullptr, *a_L = nullptr, *a_lam0 = nullptr, *a_ft[3] = {}, *a_h = nullptr;
     int a_nb = -1, a_lpr = 0, a_prec = GSRAD_FP32;
     // lanes per row forced by gsrad_batch_set_lanes (0: tuned)
     int force_fwd = 0, force_adj = 0;
@@ -1765,7 +1765,9 @@ gsrad_status gsrad_batch_create(const gsrad_ff *const *ffs, int32_t n_scenes, co
     std::vector<RowScene> tab;
     b->table.few.clear();
     for (int s = 0; s < n_scenes; ++s) (rows_few(Cs[s]) ? b->table.few : tab).push_back(b->scene(s));
-    const size_t many = tab.size(), tab_bytes = many * sizeof(RowScene);
+    const size_t many = tab.size();
+    for (int s = 0; s < n_scenes; ++s) tab.push_back(b->scene(s));
+    const size_t tab_bytes = tab.size() * sizeof(RowScene);
     std::vector<int64_t> first(3 * many);
     for (int g = 0; g < 3; ++g) {
         int64_t at = 0;
@@ -1781,10 +1783,13 @@ gsrad_status gsrad_batch_create(const gsrad_ff *const *ffs, int32_t n_scenes, co
     b->table.count = (int)many;
     for (int g = 0; g < 3; ++g)
         b->table.first[g] = reinterpret_cast<const int64_t *>(b->scenes.as<char>() + tab_bytes) + g * many;
+    b->table.all = b->table.tab + many;
+    b->table.scenes = n_scenes;
+    b->table.vals = b->vals;
+    if ((e = check_hip(hipMemcpyAsync(b->scenes.p, tab.data(), tab_bytes, hipMemcpyHostToDevice, st),
+                       "scene table copy")) != GSRAD_OK)
+        return fail(e);
     if (many > 0) {
-        if ((e = check_hip(hipMemcpyAsync(b->scenes.p, tab.data(), tab_bytes, hipMemcpyHostToDevice, st),
-                           "scene table copy")) != GSRAD_OK)
-            return fail(e);
         if ((e = check_hip(hipMemcpyAsync(b->scenes.as<char>() + tab_bytes, first.data(), first.size() * 8,
                                           hipMemcpyHostToDevice, st),
                            "scene table copy")) != GSRAD_OK)
@@ -2013,7 +2018,7 @@ gsrad_status gsrad_batch_transport_backward(gsrad_batch *b, const float *rho, co
         GS_TRY(b->Lh.ensure((size_t)vals * 4, "batch BF16 adjoint rows"));
     }
     char *lh = bf ? static_cast<char *>(b->Lh.p) : nullptr;   // two [vals] BF16 slots
-    const bool hit = b->aexec && b->a_rho == rho && b->a_gB == grad_B && b->a_gE == grad_E && b->a_L == L && b->a_lam0 == lam0 &&
+    const bool hit = b->aexec && b->a_rho == rho && b->a_gE == grad_E && b->a_L == L && b->a_lam0 == lam0 &&
                      b->a_nb == nb && b->a_lpr == b->lpr_adj && b->a_ft[0] == FT.row_ptr && b->a_ft[1] == FT.col &&
                      b->a_ft[2] == FT.val && b->a_prec == b->precision && b->a_h == lh;
     if (!hit) {
@@ -2026,7 +2031,6 @@ gsrad_status gsrad_batch_transport_backward(gsrad_batch *b, const float *rho, co
         GS_TRY(check_hip(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal), "begin capture"));
         gsrad_status e = GSRAD_OK;
         float *p = L + (size_t)nb * vals, *p_next = lam0;   // rho lambda^(k+1), rho lambda^(k)
-        for (int s = 0; s < b->S && e == GSRAD_OK; ++s) e = rows_scale(b->scene(s), grad_B, rho, p, b->cap);
         // BF16: the adjoint of the forward above: its first step (the last
         // bounce's transpose) gathers the FP32 lambda^(n), the others
         // lambda^(k+1) rounded to BF16
@@ -2053,7 +2057,6 @@ gsrad_status gsrad_batch_transport_backward(gsrad_batch *b, const float *rho, co
         GS_TRY(check_hip(hipGraphInstantiate(&b->aexec, gr, nullptr, nullptr, 0), "graph instantiate"));
         b->a_rho = rho;
         b->a_gE = grad_E;
-        b->a_gB = grad_B;
         b->a_L = L;
         b->a_lam0 = lam0;
         b->a_nb = nb;
@@ -2066,6 +2069,9 @@ gsrad_status gsrad_batch_transport_backward(gsrad_batch *b, const float *rho, co
     }
     {
         ProfScope ps("batch_adjoint", st);
+        // (not in the graph: a caller's grad_B may move, and the graph would be
+        // captured again for each)
+        GS_TRY(rows_scale_batch(b->table, grad_B, rho, L + (size_t)nb * vals, st));
         GS_TRY(check_hip(hipGraphLaunch(b->aexec, st), "graph launch"));
     }
     if (grad_F || grad_rho) {

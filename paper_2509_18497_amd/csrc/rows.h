@@ -21,6 +21,9 @@ struct RowScene {
 // coefficients, tab[count], and for 16, 32 and 64 lanes per row the first
 // workgroup of each (first[.][count], blocks[.] in all); the others in few.
 struct RowTable {
+    const RowScene *all = nullptr;   // on the device: every scene, in order
+    int scenes = 0;
+    int64_t vals = 0;
     const RowScene *tab = nullptr;
     int count = 0;
     const int64_t *first[3] = {nullptr, nullptr, nullptr};
@@ -44,8 +47,9 @@ gsrad_status rows_bounce_batch(const Csr &F, const RowTable &t, int lanes, const
                                const float *rho, float *Bout, hipStream_t st);
 gsrad_status rows_adjoint_batch(const Csr &FT, const RowTable &t, int lanes, const float *p, const float *rho,
                                 float *lam, float *p_out, float *gE, hipStream_t st);
-// out = rho * in on rows [row0, row0 + n) of C columns
+// out = rho * in on rows [row0, row0 + n) of C columns, or on a batch's rows
 gsrad_status rows_scale(const RowScene &s, const float *in, const float *rho, float *out, hipStream_t st);
+gsrad_status rows_scale_batch(const RowTable &t, const float *in, const float *rho, float *out, hipStream_t st);
 // grad_F[e] and grad_rho of one scene's rows from the forward tape B^(k) and
 // the adjoint tape lambda^(k+1), slot k at k * stride
 gsrad_status rows_sddmm(const Csr &F, const RowScene &s, int nb, int64_t stride, const float *Btape,

@@ -344,6 +344,24 @@ __global__ void __launch_bounds__(256) k_scale_rho(RowScene s, int64_t block0, c
         F3{rho[row * 3] * x.x, rho[row * 3 + 1] * x.y, rho[row * 3 + 2] * x.z};
 }
 
+// The same on all scenes of a batch (tab[count], in order): a lane per
+// coefficient of the whole array
+__global__ void __launch_bounds__(256) k_scale_batch(const RowScene *__restrict__ tab, int count, int64_t lanes,
+                                                     int64_t block0, const float *__restrict__ in,
+                                                     const float *__restrict__ rho, float *__restrict__ out) {
+    const int64_t t = (block0 + blockIdx.x) * 256 + threadIdx.x;
+    if (t >= lanes) return;
+    int lo = 0, hi = count - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (tab[mid].vbase <= 3 * t) lo = mid;
+        else hi = mid - 1;
+    }
+    const int64_t row = tab[lo].row0 + (3 * t - tab[lo].vbase) / tab[lo].C;
+    const F3 x = *reinterpret_cast<const F3 *>(in + 3 * t);
+    *reinterpret_cast<F3 *>(out + 3 * t) = F3{rho[row * 3] * x.x, rho[row * 3 + 1] * x.y, rho[row * 3 + 2] * x.z};
+}
+
 int row_lanes(int C) { return C == 3 ? 1 : C <= 12 ? 4 : 16; }
 
 // Bounces per launch of the sampled products.  One launch of all takes the
@@ -451,6 +469,14 @@ gsrad_status rows_scale(const RowScene &s, const float *in, const float *rho, fl
     if (lanes == 0) return GSRAD_OK;
     each_launch((lanes + 255) / 256, 256, [&](int64_t first, unsigned blocks) {
         hipLaunchKernelGGL(k_scale_rho, dim3(blocks), dim3(256), 0, st, s, first, in, rho, out);
+    });
+    return check_hip(hipGetLastError(), "rho scaling launch");
+}
+
+gsrad_status rows_scale_batch(const RowTable &t, const float *in, const float *rho, float *out, hipStream_t st) {
+    const int64_t lanes = t.vals / 3;
+    each_launch((lanes + 255) / 256, 256, [&](int64_t first, unsigned blocks) {
+        hipLaunchKernelGGL(k_scale_batch, dim3(blocks), dim3(256), 0, st, t.all, t.scenes, lanes, first, in, rho, out);
     });
     return check_hip(hipGetLastError(), "rho scaling launch");
 }
