@@ -256,6 +256,7 @@ struct gsrad_batch {
     std::vector<int64_t> scene_rows;   // row offsets (host copy)
     std::vector<int32_t> scene_cols;   // C_s (host copy)
     std::vector<int64_t> scene_vals;   // value offsets (host copy)
+    std::vector<int64_t> scene_nnz;    // stored entries (host copy)
     DevBuf scenes;                     // RowScene table and first workgroups
     RowTable table;
     // forward iterates B^(0..nb-1) and adjoint iterates lambda^(1..nb)
@@ -292,7 +293,7 @@ struct gsrad_batch {
         return d;
     }
     RowScene scene(int s) const {
-        return {scene_rows[s], scene_rows[s + 1] - scene_rows[s], scene_vals[s], scene_cols[s]};
+        return {scene_rows[s], scene_rows[s + 1] - scene_rows[s], scene_vals[s], scene_cols[s], scene_nnz[s]};
     }
     void drop_graph() {
         if (exec) (void)hipGraphExecDestroy(exec);
@@ -983,7 +984,7 @@ gsrad_status gsrad_transport_solve(const gsrad_ff *ff, const float *rho, const f
             return fail(e);
     } else {
         float *slots = nullptr;
-        const RowScene scene{0, n, 0, C};
+        const RowScene scene{0, n, 0, C, ff->nnz};
         if (tp) {
             if ((e = tp->B.ensure(row_bytes * n_bounces, "forward tape")) != GSRAD_OK) return fail(e);
             slots = tp->B.as<float>();
@@ -1092,7 +1093,7 @@ gsrad_status gsrad_transport_solve_noalloc(const gsrad_ff *ff, const float *rho,
     const float *src = E;
     for (int k = 0; k < n_bounces; ++k) {
         float *dst = k == n_bounces - 1 ? B_out : slots + (size_t)(k & 1) * n * C;
-        GS_TRY(rows_bounce(F, RowScene{0, n, 0, C}, src, E, rho, dst, st));
+        GS_TRY(rows_bounce(F, RowScene{0, n, 0, C, ff->nnz}, src, E, rho, dst, st));
         src = dst;
     }
     return GSRAD_OK;
@@ -1113,7 +1114,8 @@ gsrad_status gsrad_transport_backward(const gsrad_ff *ff, const gsrad_tape *tape
     const int64_t n = ff->n;
     const int C = tape->C, nb = tape->nb;
     const size_t row_bytes = (size_t)n * C * sizeof(float);
-    GS_TRY(check_hip(hipMemcpyAsync(grad_E, grad_B, row_bytes, hipMemcpyDeviceToDevice, st), "grad_E init"));
+    if (nb == 0 || tape->precision == GSRAD_BF16)
+        GS_TRY(check_hip(hipMemcpyAsync(grad_E, grad_B, row_bytes, hipMemcpyDeviceToDevice, st), "grad_E init"));
     if (nb == 0) {
         if (grad_rho) GS_TRY(check_hip(hipMemsetAsync(grad_rho, 0, (size_t)n * 12, st), "grad_rho zero"));
         if (grad_F && ff->nnz > 0)
@@ -1132,12 +1134,10 @@ gsrad_status gsrad_transport_backward(const gsrad_ff *ff, const gsrad_tape *tape
     GS_TRY(tp->lam0.ensure(row_bytes, "adjoint scaled rows"));
     GS_TRY(tp->pp.ensure(row_bytes, "adjoint scaled rows"));
     float *L = tp->L.as<float>();
-    GS_TRY(check_hip(hipMemcpyAsync(L + (size_t)(nb - 1) * n * C, grad_B, row_bytes, hipMemcpyDeviceToDevice, st),
-                     "adjoint seed"));
     const Csr FT = f->csr_t();
-    const RowScene scene{0, n, 0, C};
+    const RowScene scene{0, n, 0, C, ff->nnz};
     float *p = tp->pp.as<float>(), *p_next = tp->lam0.as<float>();   // rho lambda^(k+1), rho lambda^(k)
-    GS_TRY(rows_scale(scene, grad_B, rho, p, st));
+    GS_TRY(rows_seed(scene, grad_B, rho, L + (size_t)(nb - 1) * n * C, grad_E, p, st));
     for (int k = nb - 1; k >= 0; --k) {
         ProfScope ps("adjoint", st);
         GS_TRY(rows_adjoint(FT, scene, p, rho, k >= 1 ? L + (size_t)(k - 1) * n * C : nullptr, k >= 1 ? p_next : nullptr,
@@ -1695,6 +1695,8 @@ gsrad_status gsrad_batch_create(const gsrad_ff *const *ffs, int32_t n_scenes, co
     b->scene_rows.assign(roff.begin(), roff.end());
     b->scene_cols = Cs;
     b->scene_vals = voff;
+    b->scene_nnz.resize(n_scenes);
+    for (int s = 0; s < n_scenes; ++s) b->scene_nnz[s] = ffs[s]->nnz;
     if (!b->F) b->F = new gsrad_ff();
     gsrad_ff *F = b->F;
     const void *old_ptrs[3] = {F->row_ptr.p, F->col.p, F->val.p};
@@ -1766,6 +1768,12 @@ gsrad_status gsrad_batch_create(const gsrad_ff *const *ffs, int32_t n_scenes, co
     b->table.few.clear();
     for (int s = 0; s < n_scenes; ++s) (rows_few(Cs[s]) ? b->table.few : tab).push_back(b->scene(s));
     const size_t many = tab.size();
+    double work = 0.0, whole = 0.0;
+    for (const RowScene &s : tab) {
+        work += (double)s.nnz * s.C;
+        if (rows_whole(s)) whole += (double)s.nnz * s.C;
+    }
+    b->table.whole = 2.0 * whole > work;
     for (int s = 0; s < n_scenes; ++s) tab.push_back(b->scene(s));
     const size_t tab_bytes = tab.size() * sizeof(RowScene);
     std::vector<int64_t> first(3 * many);
@@ -1843,6 +1851,8 @@ gsrad_status autotune_lanes_timed(gsrad_batch *b, const Csr &F, bool adjoint, co
     float best_ms = 0.0f;
     gsrad_status e = GSRAD_OK;
     for (int lpr : {64, 32, 16}) {
+        // (FP32: 16 lanes gather whole rows, which large scenes are slower with)
+        if (lpr == 16 && b->precision == GSRAD_FP32 && !b->table.whole) continue;
         for (int rep = 0; rep < 2 && e == GSRAD_OK; ++rep) {   // the first run warms the caches
             if ((e = check_hip(hipEventRecord(e0, st), "tune record")) != GSRAD_OK) break;
             e = product(lpr);
@@ -1980,8 +1990,8 @@ gsrad_status gsrad_batch_transport_backward(gsrad_batch *b, const float *rho, co
     hipStream_t st = S(stream);
     const int64_t vals = b->vals, rows = b->rows;
     const int nb = b->nb;
-    GS_TRY(check_hip(hipMemcpyAsync(grad_E, grad_B, (size_t)vals * 4, hipMemcpyDeviceToDevice, st), "grad_E init"));
     if (nb == 0) {
+        GS_TRY(check_hip(hipMemcpyAsync(grad_E, grad_B, (size_t)vals * 4, hipMemcpyDeviceToDevice, st), "grad_E init"));
         if (grad_rho) GS_TRY(check_hip(hipMemsetAsync(grad_rho, 0, (size_t)rows * 12, st), "grad_rho zero"));
         if (grad_F && b->F->nnz > 0)
             GS_TRY(check_hip(hipMemsetAsync(grad_F, 0, (size_t)b->F->nnz * 4, st), "grad_F zero"));
@@ -1994,8 +2004,6 @@ gsrad_status gsrad_batch_transport_backward(gsrad_batch *b, const float *rho, co
     GS_TRY(b->Lt.ensure((size_t)(nb + 1) * vals * 4, "batch adjoint tape"));   // + one scratch slot
     GS_TRY(b->lam0.ensure((size_t)vals * 4, "batch adjoint scratch"));
     float *L = b->Lt.as<float>();
-    GS_TRY(check_hip(hipMemcpyAsync(L + (size_t)(nb - 1) * vals, grad_B, (size_t)vals * 4, hipMemcpyDeviceToDevice, st),
-                     "adjoint seed"));
     const Csr FT = b->F->csr_t();
     if (b->force_adj) b->lpr_adj = b->force_adj;
     if (b->lpr_adj == 0) {
@@ -2071,7 +2079,7 @@ gsrad_status gsrad_batch_transport_backward(gsrad_batch *b, const float *rho, co
         ProfScope ps("batch_adjoint", st);
         // (not in the graph: a caller's grad_B may move, and the graph would be
         // captured again for each)
-        GS_TRY(rows_scale_batch(b->table, grad_B, rho, L + (size_t)nb * vals, st));
+        GS_TRY(rows_seed_batch(b->table, grad_B, rho, L + (size_t)(nb - 1) * vals, grad_E, L + (size_t)nb * vals, st));
         GS_TRY(check_hip(hipGraphLaunch(b->aexec, st), "graph launch"));
     }
     if (grad_F || grad_rho) {

@@ -9,12 +9,13 @@
 
 namespace gsrad {
 
-// One scene of a launch: its rows of F, the first column index of its block
-// and where its [n][C] block of values starts.
+// One scene of a launch: its rows of F, the first column index of its block,
+// where its [n][C] block of values starts, and its stored entries.
 struct RowScene {
     int64_t row0 = 0, n = 0;
     int64_t vbase = 0;
     int32_t C = 0;
+    int64_t nnz = 0;
 };
 
 // The scenes of a batch: on the device those with more than four
@@ -29,10 +30,13 @@ struct RowTable {
     const int64_t *first[3] = {nullptr, nullptr, nullptr};
     int64_t blocks[3] = {0, 0, 0};
     std::vector<RowScene> few;
+    bool whole = false;   // scenes of rows_whole hold most of the work
 };
 // whether a scene of C columns goes to few, and the workgroups it takes
 // with `lanes` lanes per row
 bool rows_few(int C);
+// whether less than 64 lanes per row may be the faster ones for the scene
+bool rows_whole(const RowScene &s);
 int64_t rows_blocks(int64_t n, int C, int lanes);
 
 // Bout = E + rho * (F Bin)
@@ -47,9 +51,12 @@ gsrad_status rows_bounce_batch(const Csr &F, const RowTable &t, int lanes, const
                                const float *rho, float *Bout, hipStream_t st);
 gsrad_status rows_adjoint_batch(const Csr &FT, const RowTable &t, int lanes, const float *p, const float *rho,
                                 float *lam, float *p_out, float *gE, hipStream_t st);
-// out = rho * in on rows [row0, row0 + n) of C columns, or on a batch's rows
-gsrad_status rows_scale(const RowScene &s, const float *in, const float *rho, float *out, hipStream_t st);
-gsrad_status rows_scale_batch(const RowTable &t, const float *in, const float *rho, float *out, hipStream_t st);
+// The adjoint's start for a whole F or a batch: lam = gE = grad_B (grad_B may be
+// gE) and p = rho * grad_B
+gsrad_status rows_seed(const RowScene &s, const float *grad_B, const float *rho, float *lam, float *gE, float *p,
+                       hipStream_t st);
+gsrad_status rows_seed_batch(const RowTable &t, const float *grad_B, const float *rho, float *lam, float *gE, float *p,
+                             hipStream_t st);
 // grad_F[e] and grad_rho of one scene's rows from the forward tape B^(k) and
 // the adjoint tape lambda^(k+1), slot k at k * stride
 gsrad_status rows_sddmm(const Csr &F, const RowScene &s, int nb, int64_t stride, const float *Btape,

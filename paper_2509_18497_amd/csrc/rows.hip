@@ -7,7 +7,9 @@
 // G = 1 for M = 1, 4 for M <= 4, else 16, more than 16 coefficients in chunks
 // of equal width.  A wave owns an output row and reads its entries 64 at a
 // time, one a lane; each of its 64 / G groups takes G of them, broadcast to
-// its lanes by DPP, and the groups' sums are added at the end.
+// its lanes by DPP, and the groups' sums are added at the end.  Shorter rows, and
+// rows of chunks that a wave had better gather side by side, take 16 or 32 lanes
+// (row_lanes_of); the sums are the same.
 //
 // What bounds them is where the gathered rows come from and how many gathers
 // are in flight.  Measured on rows of 192 bytes: one instruction gathering
@@ -56,6 +58,12 @@ __host__ __device__ inline int row_width(int M, int g) {
     return (M + c - 1) / c;
 }
 
+// The coefficient that the lane of coefficient m reads: m, or past its chunk
+// (from m0 on) or row the last one of these, whose line the chunk touches
+// anyway.  (The row's first one was a line more for every entry of the later
+// chunks: 20k surfels, 90 coefficients in six chunks of 15, a bounce 0.99 ms.)
+__device__ __forceinline__ int near(int m0, int m, int M, int g) { return min(m, min(m0 + row_width(M, g), M) - 1); }
+
 // Lane N's value in every lane of its row of 16 lanes, or of its quad
 template <int CTRL>
 __device__ __forceinline__ int dpp(int v) {
@@ -99,22 +107,28 @@ struct Entries {
     }
 };
 
-// acc += w_e * in[col_e] over the group's first m <= G entries
-template <int G, bool ALL>
+// acc += w_e * in[col_e] over the group's first m <= N entries
+template <int G, int U0, int N, bool ALL>
 __device__ __forceinline__ void take(const Entries &now, int m, const float *__restrict__ in, int C, float (&acc)[3]) {
-    F3 x[G];
-    unroll<G>([&](auto u) {
-        const int j = now.column<u(), G>();
+    F3 x[N];
+    unroll<N>([&](auto u) {
+        const int j = now.column<U0 + u(), G>();
         x[u()] = *reinterpret_cast<const F3 *>(in + (int64_t)j * C);   // past m: the row's last entry
     });
-    unroll<G>([&](auto u) {
-        const float w = now.weight<u(), G>();
-        if (ALL || u() < m) {
+    unroll<N>([&](auto u) {
+        const float w = now.weight<U0 + u(), G>();
+        if (ALL || U0 + u() < m) {
             acc[0] = __builtin_fmaf(w, x[u()].x, acc[0]);
             acc[1] = __builtin_fmaf(w, x[u()].y, acc[1]);
             acc[2] = __builtin_fmaf(w, x[u()].z, acc[2]);
         }
     });
+}
+
+// Ends one of several sums' part of a loop: left to itself the compiler issues
+// all parts' loads first, in 230 registers
+__device__ __forceinline__ void hold(float (&sum)[3]) {
+    asm volatile("" : "+v"(sum[0]), "+v"(sum[1]), "+v"(sum[2]) : : "memory");
 }
 
 // Sum of v over the groups of a row's LPR lanes, in every lane
@@ -155,9 +169,23 @@ __device__ __forceinline__ bool find_row(const RowArgs &a, RowScene &s, int &m0,
         s = a.one;
     }
     constexpr int R = kThreads / LPR;
-    const int64_t per = (s.n + R - 1) / R;
-    const int chunk = (int)(b / per);
-    const int64_t idx = xcd_block(b - (int64_t)chunk * per, per) * R + threadIdx.x / LPR;
+    const int chunks = row_chunks(s.C / 3, G);
+    // 16 lanes: a row's chunks side by side, together they gather whole rows;
+    // more: one chunk of all rows after the other
+    const int64_t items = s.n * chunks, per = (s.n + R - 1) / R;
+    int chunk = 0;
+    int64_t idx;
+    if (LPR == 16) {
+        idx = xcd_block(b, (items + R - 1) / R) * R + threadIdx.x / LPR;
+        if (chunks > 1) {
+            const int64_t item = idx;
+            idx = items < (int64_t)1 << 32 ? (int64_t)((uint32_t)item / (uint32_t)chunks) : item / chunks;
+            chunk = (int)(item - idx * chunks);
+        }
+    } else {
+        if (chunks > 1) chunk = items < (int64_t)1 << 32 ? (int)((uint32_t)b / (uint32_t)per) : (int)(b / per);
+        idx = xcd_block(b - (int64_t)chunk * per, per) * R + threadIdx.x / LPR;
+    }
     m0 = chunk * row_width(s.C / 3, G);
     if (idx >= s.n) return false;
     row = a.order ? (int64_t)a.order[s.row0 + idx] : s.row0 + idx;
@@ -185,7 +213,7 @@ __global__ void __launch_bounds__(kThreads) k_rows(RowArgs a, const float *__res
 #pragma unroll
     for (int q = 0; q < A; ++q) acc[q][0] = acc[q][1] = acc[q][2] = 0.0f;
     if (b < e) {
-        const float *src = in + s.vbase - s.row0 * s.C + 3 * (on ? m : 0);
+        const float *src = in + s.vbase - s.row0 * s.C + 3 * near(m0, m, M, G);
         Entries next[A];
         auto first_of = [&](int64_t k, int q) { return k + (q * (LPR / G) + sub) * G; };
 #pragma unroll
@@ -196,13 +224,33 @@ __global__ void __launch_bounds__(kThreads) k_rows(RowArgs a, const float *__res
             for (int q = 0; q < A; ++q) {
                 const Entries now = next[q];
                 if (k + 64 < e) next[q].read(a.col, a.val, first_of(k + 64, q) + l, e);
-                take<G, true>(now, G, src, s.C, acc[q]);
+                if constexpr (G == 16 && A == 4) {
+                    take<G, 0, 8, true>(now, G, src, s.C, acc[q]);
+                    hold(acc[q]);
+                    take<G, 8, 8, true>(now, G, src, s.C, acc[q]);
+                } else {
+                    take<G, 0, G, true>(now, G, src, s.C, acc[q]);
+                }
+                if (A > 1) hold(acc[q]);
             }
         }
 #pragma unroll
         for (int q = 0; q < A; ++q) {
             const int n = (int)max<int64_t>(0, min<int64_t>(G, e - first_of(k, q)));
-            if (n > 0) take<G, false>(next[q], n, src, s.C, acc[q]);
+            if constexpr (G == 16) {
+                if constexpr (A == 4) {
+                    if (n > 0) take<G, 0, 8, false>(next[q], n, src, s.C, acc[q]);
+                    hold(acc[q]);
+                    if (n > 8) take<G, 8, 8, false>(next[q], n, src, s.C, acc[q]);
+                } else if (n > 8) {
+                    take<G, 0, 16, false>(next[q], n, src, s.C, acc[q]);
+                } else if (n > 0) {
+                    take<G, 0, 8, false>(next[q], n, src, s.C, acc[q]);
+                }
+            } else if (n > 0) {
+                take<G, 0, G, false>(next[q], n, src, s.C, acc[q]);
+            }
+            if (A > 1) hold(acc[q]);
         }
     }
     // the groups' sums in one order whatever LPR: pairs at distance one
@@ -210,14 +258,12 @@ __global__ void __launch_bounds__(kThreads) k_rows(RowArgs a, const float *__res
     float t[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        if constexpr (A == 1) t[c] = over_groups<G, 64>(acc[0][c]);
-        else if constexpr (A == 2) {
-            // lanes hold groups (0, 1) and (2, 3)
-            const float x = over_groups<G, LPR>(acc[0][c]), y = over_groups<G, LPR>(acc[1][c]);
-            t[c] = x + y;
-        } else {
-            t[c] = (acc[0][c] + acc[1][c]) + (acc[2][c] + acc[3][c]);
-        }
+        float x[A];
+#pragma unroll
+        for (int q = 0; q < A; ++q) x[q] = over_groups<G, LPR>(acc[q][c]);
+        if constexpr (A == 1) t[c] = x[0];
+        else if constexpr (A == 2) t[c] = x[0] + x[1];
+        else t[c] = (x[0] + x[1]) + (x[2] + x[3]);
     }
     if (!on || sub != 0) return;
     const int64_t at = s.vbase + (row - s.row0) * s.C + 3 * m;
@@ -251,104 +297,121 @@ __device__ __forceinline__ float group_sum(float v) {
     return v;
 }
 
-// For each stored entry e = (row, j), over this launch's chunk of columns
-// and its NQ bounces:
+// For each stored entry e = (row, j), over NQ bounces and one chunk of columns
+// or, with CP > 1, all of them, CP at a time side by side:
 //   s_c = sum_k sum_{columns of colour c} lambda^(k+1)[row] B^(k)[j]
 //   grad_F[e] (+)= sum_c rho[row, c] s_c;  grad_rho[row, c] (+)= sum_e F[e] s_c
-// A wave per row, the row's lambda in registers; a group gathers two of its
+// LPR lanes per row, the row's lambda in registers; a group gathers two of its
 // entries' NQ rows at a time.  Both results are linear in the lanes' shares of
 // s_c, so only the one value of dL/dF is summed over a group's lanes for each
-// entry; dL/drho's three are summed over the wave once per row.
-template <int G, int NQ>
-__global__ void __launch_bounds__(kThreads) k_sddmm3(RowArgs a, int m0, int64_t stride,
+// entry; dL/drho's three are summed over the row's lanes once per chunk.
+template <int G, int LPR, int CP, int NQ>
+__global__ void __launch_bounds__(kThreads) k_sddmm3(RowArgs a, int chunk, int64_t stride,
                                                      const float *__restrict__ Bt, const float *__restrict__ Lt,
                                                      float *__restrict__ grad_F, float *__restrict__ grad_rho,
                                                      bool fresh) {
     const RowScene s = a.one;
-    constexpr int R = kThreads / 64;
-    const int64_t idx = xcd_block(blockIdx.x, (s.n + R - 1) / R) * R + threadIdx.x / 64;
+    constexpr int R = kThreads / LPR;
+    const int64_t idx = xcd_block(blockIdx.x, (s.n + R - 1) / R) * R + threadIdx.x / LPR;
     if (idx >= s.n) return;
     const int64_t row = a.order ? (int64_t)a.order[s.row0 + idx] : s.row0 + idx;
-    const int lane = (int)__lane_id();
-    const int M = s.C / 3, l = lane % G, m = m0 + l;
-    const bool on = l < row_width(M, G) && m < M;
+    const int M = s.C / 3, width = row_width(M, G), l = threadIdx.x % G, lane = threadIdx.x % LPR;
     const int64_t b = a.row_ptr[row], e = a.row_ptr[row + 1];
-    float gr[3] = {0.0f, 0.0f, 0.0f};
-    if (b < e) {
-        const float r[3] = {a.rho[row * 3 + 0], a.rho[row * 3 + 1], a.rho[row * 3 + 2]};
-        float lam[NQ][3];
-        const int64_t at = s.vbase + (row - s.row0) * s.C + 3 * (on ? m : 0);
+    static_assert(CP == 1 || (G == 16 && LPR == 16 * CP), "a row of 16 lanes a chunk");
+    constexpr int kRead = CP == 1 ? LPR : G;   // entries of a reading
+    const int at_e = CP == 1 ? lane : l;       // this lane's
+    auto one = [&](int m0, bool first) {
+        const int m = m0 + l;
+        const bool on = l < width && m < M;
+        float gr[3] = {0.0f, 0.0f, 0.0f};
+        if (b < e) {
+            const float r[3] = {a.rho[row * 3 + 0], a.rho[row * 3 + 1], a.rho[row * 3 + 2]};
+            float lam[NQ][3];
+            const int64_t at = s.vbase + (row - s.row0) * s.C + 3 * near(m0, m, M, G);
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const F3 x = *reinterpret_cast<const F3 *>(Lt + q * stride + at);
-            lam[q][0] = x.x;
-            lam[q][1] = x.y;
-            lam[q][2] = x.z;
+            for (int q = 0; q < NQ; ++q) {
+                const F3 x = *reinterpret_cast<const F3 *>(Lt + q * stride + at);
+                lam[q][0] = x.x;
+                lam[q][1] = x.y;
+                lam[q][2] = x.z;
+            }
+            const float *base = Bt + s.vbase - s.row0 * s.C + 3 * near(m0, m, M, G);
+            Entries next;
+            next.read(a.col, a.val, b + at_e, e);
+            for (int64_t k = b; k < e; k += kRead) {
+                const Entries now = next;
+                if (k + kRead < e) next.read(a.col, a.val, k + kRead + at_e, e);
+                const int n = (int)max<int64_t>(0, min<int64_t>(G, e - (k + at_e - l)));
+                float keep = 0.0f;   // dL/dF of the entry this lane read
+                constexpr int P = G == 1 ? 1 : 2;
+                unroll<G / P>([&](auto h) {
+                    constexpr int u0 = h() * P;
+                    if (u0 < n) {
+                        F3 x[P][NQ];
+                        unroll<P>([&](auto u) {
+                            const float *src = base + (int64_t)now.column<u0 + u(), G>() * s.C;
+#pragma unroll
+                            for (int q = 0; q < NQ; ++q) x[u()][q] = *reinterpret_cast<const F3 *>(src + q * stride);
+                        });
+                        unroll<P>([&](auto u) {
+                            float t[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+                            for (int q = 0; q < NQ; ++q) {
+                                t[0] = __builtin_fmaf(lam[q][0], x[u()][q].x, t[0]);
+                                t[1] = __builtin_fmaf(lam[q][1], x[u()][q].y, t[1]);
+                                t[2] = __builtin_fmaf(lam[q][2], x[u()][q].z, t[2]);
+                            }
+                            float g = r[0] * t[0] + r[1] * t[1] + r[2] * t[2];
+                            if (G > 1) g = group_sum<G>(on ? g : 0.0f);
+                            const float f = now.weight<u0 + u(), G>();
+                            if (l == u0 + u()) keep = g;
+                            if (u0 + u() < n) {
+#pragma unroll
+                                for (int c = 0; c < 3; ++c) gr[c] = __builtin_fmaf(f, t[c], gr[c]);
+                            }
+                        });
+                    }
+                });
+                if constexpr (CP > 1) keep = over_groups<16, LPR>(keep);
+                if (grad_F && lane == at_e && k + at_e < e)
+                    grad_F[k + at_e] = first ? keep : grad_F[k + at_e] + keep;
+            }
         }
-        const float *base = Bt + s.vbase - s.row0 * s.C + 3 * (on ? m : 0);
-        Entries next;
-        next.read(a.col, a.val, b + lane, e);
-        for (int64_t k = b; k < e; k += 64) {
-            const Entries now = next;
-            if (k + 64 < e) next.read(a.col, a.val, k + 64 + lane, e);
-            const int n = (int)max<int64_t>(0, min<int64_t>(G, e - (k + lane - l)));
-            float keep = 0.0f;   // dL/dF of the entry this lane read
-            constexpr int P = G == 1 ? 1 : 2;
-            unroll<G / P>([&](auto h) {
-                constexpr int u0 = h() * P;
-                if (u0 < n) {
-                    F3 x[P][NQ];
-                    unroll<P>([&](auto u) {
-                        const float *src = base + (int64_t)now.column<u0 + u(), G>() * s.C;
+        if (!grad_rho) return;
 #pragma unroll
-                        for (int q = 0; q < NQ; ++q) x[u()][q] = *reinterpret_cast<const F3 *>(src + q * stride);
-                    });
-                    unroll<P>([&](auto u) {
-                        float t[3] = {0.0f, 0.0f, 0.0f};
-#pragma unroll
-                        for (int q = 0; q < NQ; ++q) {
-                            t[0] = __builtin_fmaf(lam[q][0], x[u()][q].x, t[0]);
-                            t[1] = __builtin_fmaf(lam[q][1], x[u()][q].y, t[1]);
-                            t[2] = __builtin_fmaf(lam[q][2], x[u()][q].z, t[2]);
-                        }
-                        float g = r[0] * t[0] + r[1] * t[1] + r[2] * t[2];
-                        if (G > 1) g = group_sum<G>(on ? g : 0.0f);
-                        const float f = now.weight<u0 + u(), G>();
-                        if (l == u0 + u()) keep = g;
-                        if (u0 + u() < n) {
-#pragma unroll
-                            for (int c = 0; c < 3; ++c) gr[c] = __builtin_fmaf(f, t[c], gr[c]);
-                        }
-                    });
-                }
-            });
-            if (grad_F && k + lane < e) grad_F[k + lane] = fresh ? keep : grad_F[k + lane] + keep;
+        for (int c = 0; c < 3; ++c) {
+            const float t = over_groups<1, LPR>(on ? gr[c] : 0.0f);
+            if (lane == 0) grad_rho[row * 3 + c] = first ? t : grad_rho[row * 3 + c] + t;
         }
-    }
-    if (!grad_rho) return;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const float t = over_groups<1, 64>(on ? gr[c] : 0.0f);
-        if (lane == 0) grad_rho[row * 3 + c] = fresh ? t : grad_rho[row * 3 + c] + t;
+    };
+    if constexpr (CP == 1) {
+        one(chunk * width, fresh);
+    } else {
+        for (int c = 0; c < row_chunks(M, G); c += CP) one((c + lane / 16) * width, fresh && c == 0);
     }
 }
 
-__global__ void __launch_bounds__(256) k_scale_rho(RowScene s, int64_t block0, const float *__restrict__ in,
-                                                   const float *__restrict__ rho, float *__restrict__ out) {
+// The adjoint's start, a lane per coefficient: lam = gE = in (in may be gE),
+// p = rho in
+__device__ __forceinline__ void seed(int64_t row, int64_t at, const float *in, const float *__restrict__ rho,
+                                     float *__restrict__ lam, float *gE, float *__restrict__ p) {
+    const F3 x = *reinterpret_cast<const F3 *>(in + at);
+    *reinterpret_cast<F3 *>(lam + at) = x;
+    *reinterpret_cast<F3 *>(gE + at) = x;
+    *reinterpret_cast<F3 *>(p + at) = F3{rho[row * 3] * x.x, rho[row * 3 + 1] * x.y, rho[row * 3 + 2] * x.z};
+}
+
+__global__ void __launch_bounds__(256) k_seed(int64_t lanes, int M, int64_t block0, const float *in,
+                                              const float *__restrict__ rho, float *__restrict__ lam, float *gE,
+                                              float *__restrict__ p) {
     const int64_t t = (block0 + blockIdx.x) * 256 + threadIdx.x;
-    const int M = s.C / 3;
-    if (t >= s.n * M) return;
-    const int64_t row = s.row0 + t / M;
-    const F3 x = *reinterpret_cast<const F3 *>(in + s.vbase + 3 * t);
-    *reinterpret_cast<F3 *>(out + s.vbase + 3 * t) =
-        F3{rho[row * 3] * x.x, rho[row * 3 + 1] * x.y, rho[row * 3 + 2] * x.z};
+    if (t < lanes) seed(t / M, 3 * t, in, rho, lam, gE, p);
 }
 
-// The same on all scenes of a batch (tab[count], in order): a lane per
-// coefficient of the whole array
-__global__ void __launch_bounds__(256) k_scale_batch(const RowScene *__restrict__ tab, int count, int64_t lanes,
-                                                     int64_t block0, const float *__restrict__ in,
-                                                     const float *__restrict__ rho, float *__restrict__ out) {
+// on all scenes of a batch (tab[count], in order)
+__global__ void __launch_bounds__(256) k_seed_batch(const RowScene *__restrict__ tab, int count, int64_t lanes,
+                                                    int64_t block0, const float *in, const float *__restrict__ rho,
+                                                    float *__restrict__ lam, float *gE, float *__restrict__ p) {
     const int64_t t = (block0 + blockIdx.x) * 256 + threadIdx.x;
     if (t >= lanes) return;
     int lo = 0, hi = count - 1;
@@ -357,9 +420,7 @@ __global__ void __launch_bounds__(256) k_scale_batch(const RowScene *__restrict_
         if (tab[mid].vbase <= 3 * t) lo = mid;
         else hi = mid - 1;
     }
-    const int64_t row = tab[lo].row0 + (3 * t - tab[lo].vbase) / tab[lo].C;
-    const F3 x = *reinterpret_cast<const F3 *>(in + 3 * t);
-    *reinterpret_cast<F3 *>(out + 3 * t) = F3{rho[row * 3] * x.x, rho[row * 3 + 1] * x.y, rho[row * 3 + 2] * x.z};
+    seed(tab[lo].row0 + (3 * t - tab[lo].vbase) / tab[lo].C, 3 * t, in, rho, lam, gE, p);
 }
 
 int row_lanes(int C) { return C == 3 ? 1 : C <= 12 ? 4 : 16; }
@@ -385,6 +446,34 @@ RowArgs row_args(const Csr &F, const float *rho) {
     return a;
 }
 
+// Lanes per row of a scene's products.  64 where the mean row has more than
+// kShortRow entries; a wave with a shorter row leaves lanes without an entry, so
+// 16 (20k rows of 32 entries, 27 coefficients: bounce 20 -> 15 us), or 32 where
+// 16 would fill less than two waves a SIMD.  The adjoint's rows, F's columns,
+// vary more in length: 16 up to kShortColumn.
+// Rows of several chunks: with 16 lanes a wave gathers four chunks of an entry
+// side by side, with 64 all workgroups one chunk after the other.  The latter
+// pays where the rows' one chunk fits an XCD's L2 and the whole rows do not (20k
+// rows of 512 entries, 270 coefficients: 2.1 against 3.1 ms a bounce).  The
+// former up to kWholeBytes and kWholeChunks (8k rows, 90 coefficients: 224 against
+// 257 us; 540 coefficients: 2.6 against 1.4 ms), for two chunks further (100k
+// rows of 17 coefficients, whose halves share their lines: 1.1 against 1.4 ms),
+// and again where one chunk is past kChunkBytes (100k rows of 128 entries, 90
+// coefficients: 1.8 against 2.1 ms; of 512 both 5.8).
+constexpr int64_t kShortRow = 40, kShortColumn = 12, kManyItems = 8192;
+constexpr int64_t kWholeBytes = (int64_t)18 << 20, kWholeBytesTwo = (int64_t)64 << 20, kChunkBytes = (int64_t)16 << 20;
+constexpr int kWholeChunks = 12;
+int row_lanes_of(const RowScene &s, bool adjoint) {
+    const int64_t chunks = row_chunks(s.C / 3, row_lanes(s.C)), len = s.nnz / std::max<int64_t>(s.n, 1);
+    const bool many = s.n * chunks >= kManyItems;
+    if (adjoint && !many) return 64;
+    if (chunks == 1) return len > (adjoint ? kShortColumn : kShortRow) ? 64 : many ? 16 : 32;
+    if (len <= kShortRow) return many && chunks > kWholeChunks && len > 24 ? 32 : 16;
+    const bool whole = many && chunks <= kWholeChunks && s.n * s.C * 4 <= (chunks == 2 ? kWholeBytesTwo : kWholeBytes);
+    if (whole && (!adjoint || len <= 100)) return 16;
+    return s.n * row_width(s.C / 3, row_lanes(s.C)) * 12 > kChunkBytes && len <= 256 ? 16 : 64;
+}
+
 template <bool ADJ>
 gsrad_status run_scene(const Csr &F, const RowScene &s, const float *in, const float *E, const float *rho, float *out,
                        float *p_out, float *gE, hipStream_t st) {
@@ -392,15 +481,22 @@ gsrad_status run_scene(const Csr &F, const RowScene &s, const float *in, const f
     const int g = row_lanes(s.C);
     RowArgs a = row_args(F, rho);
     a.one = s;
+    const int lanes = row_lanes_of(s, ADJ);
     auto run = [&](auto kernel) {
-        each_launch(rows_blocks(s.n, s.C, 64), kThreads, [&](int64_t first, unsigned blocks) {
+        each_launch(rows_blocks(s.n, s.C, lanes), kThreads, [&](int64_t first, unsigned blocks) {
             a.block0 = first;
             hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), 0, st, a, in, E, out, p_out, gE);
         });
     };
-    if (g == 1) run(k_rows<1, 64, ADJ>);
-    else if (g == 4) run(k_rows<4, 64, ADJ>);
-    else run(k_rows<16, 64, ADJ>);
+    auto with = [&](auto width) {
+        constexpr int G = decltype(width)::value;
+        if (lanes == 16) run(k_rows<G, 16, ADJ>);
+        else if (lanes == 32) run(k_rows<G, 32, ADJ>);
+        else run(k_rows<G, 64, ADJ>);
+    };
+    if (g == 1) with(std::integral_constant<int, 1>{});
+    else if (g == 4) with(std::integral_constant<int, 4>{});
+    else with(std::integral_constant<int, 16>{});
     return check_hip(hipGetLastError(), ADJ ? "adjoint launch" : "bounce launch");
 }
 
@@ -439,9 +535,11 @@ gsrad_status run_batch(const Csr &F, const RowTable &t, int lanes, const float *
 
 bool rows_few(int C) { return row_lanes(C) < 16; }
 
+bool rows_whole(const RowScene &s) { return row_lanes_of(s, false) < 64 || row_lanes_of(s, true) < 64; }
+
 int64_t rows_blocks(int64_t n, int C, int lanes) {
-    const int64_t r = kThreads / lanes;
-    return (n + r - 1) / r * row_chunks(C / 3, row_lanes(C));
+    const int64_t r = kThreads / lanes, chunks = row_chunks(C / 3, row_lanes(C));
+    return lanes == 16 ? (n * chunks + r - 1) / r : (n + r - 1) / r * chunks;
 }
 
 gsrad_status rows_bounce(const Csr &F, const RowScene &s, const float *Bin, const float *E, const float *rho,
@@ -464,55 +562,77 @@ gsrad_status rows_adjoint_batch(const Csr &FT, const RowTable &t, int lanes, con
     return run_batch<true>(FT, t, lanes, p, nullptr, rho, lam, p_out, gE, st);
 }
 
-gsrad_status rows_scale(const RowScene &s, const float *in, const float *rho, float *out, hipStream_t st) {
+gsrad_status rows_seed(const RowScene &s, const float *grad_B, const float *rho, float *lam, float *gE, float *p,
+                       hipStream_t st) {
     const int64_t lanes = s.n * (s.C / 3);
-    if (lanes == 0) return GSRAD_OK;
     each_launch((lanes + 255) / 256, 256, [&](int64_t first, unsigned blocks) {
-        hipLaunchKernelGGL(k_scale_rho, dim3(blocks), dim3(256), 0, st, s, first, in, rho, out);
+        hipLaunchKernelGGL(k_seed, dim3(blocks), dim3(256), 0, st, lanes, s.C / 3, first, grad_B, rho, lam, gE, p);
     });
-    return check_hip(hipGetLastError(), "rho scaling launch");
+    return check_hip(hipGetLastError(), "adjoint seed launch");
 }
 
-gsrad_status rows_scale_batch(const RowTable &t, const float *in, const float *rho, float *out, hipStream_t st) {
+gsrad_status rows_seed_batch(const RowTable &t, const float *grad_B, const float *rho, float *lam, float *gE, float *p,
+                             hipStream_t st) {
     const int64_t lanes = t.vals / 3;
     each_launch((lanes + 255) / 256, 256, [&](int64_t first, unsigned blocks) {
-        hipLaunchKernelGGL(k_scale_batch, dim3(blocks), dim3(256), 0, st, t.all, t.scenes, lanes, first, in, rho, out);
+        hipLaunchKernelGGL(k_seed_batch, dim3(blocks), dim3(256), 0, st, t.all, t.scenes, lanes, first, grad_B, rho, lam,
+                           gE, p);
     });
-    return check_hip(hipGetLastError(), "rho scaling launch");
+    return check_hip(hipGetLastError(), "adjoint seed launch");
+}
+
+// How the sampled products take a scene's rows.  Several chunks: side by side in
+// one launch where the mean row is short (20k rows of 8 entries, 90
+// coefficients, three bounces: 72 us, one launch per chunk 227; of 64 entries
+// 471 and 449, but 8k rows 130 and 163) or there are two of at most twelve (50k rows of 512, 20
+// coefficients: 1.8 and 2.3 ms; 20k of 32: 1.8 and 1.5; 2k of 20: 107 and 67 us).  One chunk: 16 lanes per short row (20k rows of 8
+// entries, 27 coefficients, six bounces: 27 us, with 64 lanes 48).
+int sddmm_chunks(const RowScene &s) {
+    const int chunks = row_chunks(s.C / 3, row_lanes(s.C));
+    if (chunks == 1) return 1;
+    const bool short_rows = s.nnz <= (s.n > kManyItems ? kShortRow : 100) * s.n;
+    return short_rows || (chunks == 2 && s.n >= kManyItems && s.C <= 72) ? (chunks == 2 ? 2 : 4) : 1;
+}
+int sddmm_lanes(const RowScene &s) {
+    const bool one = row_chunks(s.C / 3, row_lanes(s.C)) == 1;
+    return one && s.n >= kManyItems && s.nnz <= kShortRow * s.n ? 16 : 64;
 }
 
 gsrad_status rows_sddmm(const Csr &F, const RowScene &s, int nb, int64_t stride, const float *Btape,
                         const float *Ltape, const float *rho, float *grad_F, float *grad_rho, hipStream_t st) {
     if (s.n == 0 || nb == 0) return GSRAD_OK;
-    const int g = row_lanes(s.C), M = s.C / 3, width = row_width(M, g);
+    const int g = row_lanes(s.C), M = s.C / 3, width = row_width(M, g), chunks = row_chunks(M, g);
     RowArgs a = row_args(F, rho);
     a.one = s;
-    const dim3 grid((unsigned)((s.n + kThreads / 64 - 1) / (kThreads / 64)));
-    const int per = sddmm_bounces(s.n, width);
+    const int cp = sddmm_chunks(s), lanes = cp > 1 ? 16 * cp : sddmm_lanes(s);
+    const int r = kThreads / lanes;
+    const dim3 grid((unsigned)((s.n + r - 1) / r));
+    const int per = cp > 1 ? 8 : sddmm_bounces(s.n, width);
     bool fresh = true;
-    for (int m0 = 0; m0 < M; m0 += width) {
+    for (int chunk = 0; chunk < (cp > 1 ? 1 : chunks); ++chunk) {
         for (int q0 = 0; q0 < nb; q0 += per) {
             const float *B = Btape + q0 * stride, *L = Ltape + q0 * stride;
             auto run = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, a, m0, stride, B, L, grad_F, grad_rho, fresh);
+                hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, a, chunk, stride, B, L, grad_F, grad_rho, fresh);
             };
-#define GS_NQ(N)                                 \
-    case N:                                      \
-        if (g == 1) run(k_sddmm3<1, N>);         \
-        else if (g == 4) run(k_sddmm3<4, N>);    \
-        else run(k_sddmm3<16, N>);               \
-        break
+            auto with = [&](auto bounces) {
+                constexpr int N = decltype(bounces)::value;
+                if (cp == 2) run(k_sddmm3<16, 32, 2, N>);
+                else if (cp == 4) run(k_sddmm3<16, 64, 4, N>);
+                else if (g == 1) run(lanes == 16 ? k_sddmm3<1, 16, 1, N> : k_sddmm3<1, 64, 1, N>);
+                else if (g == 4) run(lanes == 16 ? k_sddmm3<4, 16, 1, N> : k_sddmm3<4, 64, 1, N>);
+                else run(lanes == 16 ? k_sddmm3<16, 16, 1, N> : k_sddmm3<16, 64, 1, N>);
+            };
             switch (std::min(per, nb - q0)) {
-                GS_NQ(1);
-                GS_NQ(2);
-                GS_NQ(3);
-                GS_NQ(4);
-                GS_NQ(5);
-                GS_NQ(6);
-                GS_NQ(7);
-                GS_NQ(8);
+                case 1: with(std::integral_constant<int, 1>{}); break;
+                case 2: with(std::integral_constant<int, 2>{}); break;
+                case 3: with(std::integral_constant<int, 3>{}); break;
+                case 4: with(std::integral_constant<int, 4>{}); break;
+                case 5: with(std::integral_constant<int, 5>{}); break;
+                case 6: with(std::integral_constant<int, 6>{}); break;
+                case 7: with(std::integral_constant<int, 7>{}); break;
+                case 8: with(std::integral_constant<int, 8>{}); break;
             }
-#undef GS_NQ
             fresh = false;
         }
     }
