@@ -1765,44 +1765,16 @@ gsrad_status gsrad_batch_create(const gsrad_ff *const *ffs, int32_t n_scenes, co
         }
     // the scenes as the FP32 row products take them
     std::vector<RowScene> tab;
-    b->table.few.clear();
-    for (int s = 0; s < n_scenes; ++s) (rows_few(Cs[s]) ? b->table.few : tab).push_back(b->scene(s));
-    const size_t many = tab.size();
-    double work = 0.0, whole = 0.0;
-    for (const RowScene &s : tab) {
-        work += (double)s.nnz * s.C;
-        if (rows_whole(s)) whole += (double)s.nnz * s.C;
-    }
-    b->table.whole = 2.0 * whole > work;
+    std::vector<char> image;
     for (int s = 0; s < n_scenes; ++s) tab.push_back(b->scene(s));
-    const size_t tab_bytes = tab.size() * sizeof(RowScene);
-    std::vector<int64_t> first(3 * many);
-    for (int g = 0; g < 3; ++g) {
-        int64_t at = 0;
-        for (size_t s = 0; s < many; ++s) {
-            first[g * many + s] = at;
-            at += rows_blocks(tab[s].n, tab[s].C, 16 << g);
-        }
-        b->table.blocks[g] = at;
-    }
-    if ((e = b->scenes.ensure(std::max<size_t>(tab_bytes + first.size() * 8, 8), "scene table")) != GSRAD_OK)
-        return fail(e);
-    b->table.tab = b->scenes.as<RowScene>();
-    b->table.count = (int)many;
-    for (int g = 0; g < 3; ++g)
-        b->table.first[g] = reinterpret_cast<const int64_t *>(b->scenes.as<char>() + tab_bytes) + g * many;
-    b->table.all = b->table.tab + many;
-    b->table.scenes = n_scenes;
-    b->table.vals = b->vals;
-    if ((e = check_hip(hipMemcpyAsync(b->scenes.p, tab.data(), tab_bytes, hipMemcpyHostToDevice, st),
+    rows_table(tab, &b->table, &image);
+    const void *const old_scenes = b->scenes.p;
+    if ((e = b->scenes.ensure(rows_table_bytes(tab.size()), "scene table")) != GSRAD_OK) return fail(e);
+    if (old_scenes != b->scenes.p) b->drop_graph();
+    b->table.base = b->scenes.as<char>();
+    if ((e = check_hip(hipMemcpyAsync(b->scenes.p, image.data(), image.size(), hipMemcpyHostToDevice, st),
                        "scene table copy")) != GSRAD_OK)
         return fail(e);
-    if (many > 0) {
-        if ((e = check_hip(hipMemcpyAsync(b->scenes.as<char>() + tab_bytes, first.data(), first.size() * 8,
-                                          hipMemcpyHostToDevice, st),
-                           "scene table copy")) != GSRAD_OK)
-            return fail(e);
-    }
     // the host vectors above are sources of asynchronous copies
     if ((e = check_hip(hipStreamSynchronize(st), "batch create sync")) != GSRAD_OK) return fail(e);
     b->nb = -1;
@@ -2084,9 +2056,7 @@ gsrad_status gsrad_batch_transport_backward(gsrad_batch *b, const float *rho, co
     }
     if (grad_F || grad_rho) {
         ProfScope ps("batch_sddmm", st);
-        for (int s = 0; s < b->S; ++s) {
-            GS_TRY(rows_sddmm(b->F->csr(), b->scene(s), nb, vals, b->Bt.as<float>(), L, rho, grad_F, grad_rho, st));
-        }
+        GS_TRY(rows_sddmm_batch(b->F->csr(), b->table, nb, b->Bt.as<float>(), L, rho, grad_F, grad_rho, st));
     }
     return GSRAD_OK;
 }

@@ -18,26 +18,28 @@ struct RowScene {
     int64_t nnz = 0;
 };
 
-// The scenes of a batch: on the device those with more than four
-// coefficients, tab[count], and for 16, 32 and 64 lanes per row the first
-// workgroup of each (first[.][count], blocks[.] in all); the others in few.
+// The scenes of a batch, grouped by the kernel that takes them, and where the
+// groups' tables lie in one block of device memory.
 struct RowTable {
-    const RowScene *all = nullptr;   // on the device: every scene, in order
+    // scenes of one launch: RowScene[count] and their first workgroups,
+    // int64_t[count], at byte offsets of the block
+    struct Part {
+        int g = 0, lanes = 0, cp = 1, per = 0, chunks = 1;
+        int count = 0;
+        size_t tab = 0, first = 0;
+        int64_t blocks = 0;
+    };
+    const char *base = nullptr;      // the block; every scene, in order, at its start
     int scenes = 0;
     int64_t vals = 0;
-    const RowScene *tab = nullptr;
-    int count = 0;
-    const int64_t *first[3] = {nullptr, nullptr, nullptr};
-    int64_t blocks[3] = {0, 0, 0};
-    std::vector<RowScene> few;
-    bool whole = false;   // scenes of rows_whole hold most of the work
+    bool whole = false;              // scenes that 16 lanes per row may suit hold most of the work
+    std::vector<Part> rows[3];       // row products with 16, 32 and 64 lanes per row
+    std::vector<Part> sampled;       // sampled products of the smaller scenes
+    std::vector<RowScene> alone;     // the others, one by one
 };
-// whether a scene of C columns goes to few, and the workgroups it takes
-// with `lanes` lanes per row
-bool rows_few(int C);
-// whether less than 64 lanes per row may be the faster ones for the scene
-bool rows_whole(const RowScene &s);
-int64_t rows_blocks(int64_t n, int C, int lanes);
+// t of the scenes, and the block's contents, at most rows_table_bytes
+void rows_table(const std::vector<RowScene> &scenes, RowTable *t, std::vector<char> *image);
+size_t rows_table_bytes(size_t scenes);
 
 // Bout = E + rho * (F Bin)
 gsrad_status rows_bounce(const Csr &F, const RowScene &s, const float *Bin, const float *E, const float *rho,
@@ -57,9 +59,11 @@ gsrad_status rows_seed(const RowScene &s, const float *grad_B, const float *rho,
                        hipStream_t st);
 gsrad_status rows_seed_batch(const RowTable &t, const float *grad_B, const float *rho, float *lam, float *gE, float *p,
                              hipStream_t st);
-// grad_F[e] and grad_rho of one scene's rows from the forward tape B^(k) and
-// the adjoint tape lambda^(k+1), slot k at k * stride
+// grad_F[e] and grad_rho of one scene's rows, or a batch's, from the forward
+// tape B^(k) and the adjoint tape lambda^(k+1), slot k at k * stride
 gsrad_status rows_sddmm(const Csr &F, const RowScene &s, int nb, int64_t stride, const float *Btape,
                         const float *Ltape, const float *rho, float *grad_F, float *grad_rho, hipStream_t st);
+gsrad_status rows_sddmm_batch(const Csr &F, const RowTable &t, int nb, const float *Btape, const float *Ltape,
+                              const float *rho, float *grad_F, float *grad_rho, hipStream_t st);
 
 }  // namespace gsrad

@@ -152,22 +152,27 @@ struct RowArgs {
     const float *rho;
 };
 
+// The scene of this workgroup, and the workgroup's number in it
+__device__ __forceinline__ int64_t find_scene(const RowArgs &a, RowScene &s) {
+    const int64_t b = a.block0 + blockIdx.x;
+    if (!a.tab) {
+        s = a.one;
+        return b;
+    }
+    int lo = 0, hi = a.count - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (a.first[mid] <= b) lo = mid;
+        else hi = mid - 1;
+    }
+    s = a.tab[lo];
+    return b - a.first[lo];
+}
+
 // The scene and the (chunk, row) of this lane; false past the scene's rows
 template <int G, int LPR>
 __device__ __forceinline__ bool find_row(const RowArgs &a, RowScene &s, int &m0, int64_t &row) {
-    int64_t b = a.block0 + blockIdx.x;
-    if (a.tab) {
-        int lo = 0, hi = a.count - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (a.first[mid] <= b) lo = mid;
-            else hi = mid - 1;
-        }
-        s = a.tab[lo];
-        b -= a.first[lo];
-    } else {
-        s = a.one;
-    }
+    const int64_t b = find_scene(a, s);
     constexpr int R = kThreads / LPR;
     const int chunks = row_chunks(s.C / 3, G);
     // 16 lanes: a row's chunks side by side, together they gather whole rows;
@@ -310,9 +315,11 @@ __global__ void __launch_bounds__(kThreads) k_sddmm3(RowArgs a, int chunk, int64
                                                      const float *__restrict__ Bt, const float *__restrict__ Lt,
                                                      float *__restrict__ grad_F, float *__restrict__ grad_rho,
                                                      bool fresh) {
-    const RowScene s = a.one;
+    RowScene s;
     constexpr int R = kThreads / LPR;
-    const int64_t idx = xcd_block(blockIdx.x, (s.n + R - 1) / R) * R + threadIdx.x / LPR;
+    const int64_t block = find_scene(a, s);
+    if (CP == 1 && chunk * row_width(s.C / 3, G) >= s.C / 3) return;
+    const int64_t idx = xcd_block(block, (s.n + R - 1) / R) * R + threadIdx.x / LPR;
     if (idx >= s.n) return;
     const int64_t row = a.order ? (int64_t)a.order[s.row0 + idx] : s.row0 + idx;
     const int M = s.C / 3, width = row_width(M, G), l = threadIdx.x % G, lane = threadIdx.x % LPR;
@@ -425,6 +432,11 @@ __global__ void __launch_bounds__(256) k_seed_batch(const RowScene *__restrict__
 
 int row_lanes(int C) { return C == 3 ? 1 : C <= 12 ? 4 : 16; }
 
+int64_t rows_blocks(int64_t n, int C, int lanes) {
+    const int64_t r = kThreads / lanes, chunks = row_chunks(C / 3, row_lanes(C));
+    return lanes == 16 ? (n * chunks + r - 1) / r : (n + r - 1) / r * chunks;
+}
+
 // Bounces per launch of the sampled products.  One launch of all takes the
 // fewest instructions, but the chunk of all rows and bounces that it gathers
 // from has to stay in the XCDs' L2: with two against eight per launch 100k
@@ -475,17 +487,12 @@ int row_lanes_of(const RowScene &s, bool adjoint) {
 }
 
 template <bool ADJ>
-gsrad_status run_scene(const Csr &F, const RowScene &s, const float *in, const float *E, const float *rho, float *out,
-                       float *p_out, float *gE, hipStream_t st) {
-    if (s.n == 0) return GSRAD_OK;
-    const int g = row_lanes(s.C);
-    RowArgs a = row_args(F, rho);
-    a.one = s;
-    const int lanes = row_lanes_of(s, ADJ);
+gsrad_status run_rows(RowArgs a, int g, int lanes, int64_t blocks, const float *in, const float *E, float *out,
+                      float *p_out, float *gE, hipStream_t st) {
     auto run = [&](auto kernel) {
-        each_launch(rows_blocks(s.n, s.C, lanes), kThreads, [&](int64_t first, unsigned blocks) {
+        each_launch(blocks, kThreads, [&](int64_t first, unsigned groups) {
             a.block0 = first;
-            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), 0, st, a, in, E, out, p_out, gE);
+            hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), 0, st, a, in, E, out, p_out, gE);
         });
     };
     auto with = [&](auto width) {
@@ -500,47 +507,36 @@ gsrad_status run_scene(const Csr &F, const RowScene &s, const float *in, const f
     return check_hip(hipGetLastError(), ADJ ? "adjoint launch" : "bounce launch");
 }
 
-// The scenes of a batch in one launch; scenes of few columns (G < 16) in
-// launches of their own.
+template <bool ADJ>
+gsrad_status run_scene(const Csr &F, const RowScene &s, const float *in, const float *E, const float *rho, float *out,
+                       float *p_out, float *gE, hipStream_t st) {
+    if (s.n == 0) return GSRAD_OK;
+    RowArgs a = row_args(F, rho);
+    a.one = s;
+    const int lanes = row_lanes_of(s, ADJ);
+    return run_rows<ADJ>(a, row_lanes(s.C), lanes, rows_blocks(s.n, s.C, lanes), in, E, out, p_out, gE, st);
+}
+
+// The scenes of a batch: a launch for each G among them.
 template <bool ADJ>
 gsrad_status run_batch(const Csr &F, const RowTable &t, int lanes, const float *in, const float *E, const float *rho,
                        float *out, float *p_out, float *gE, hipStream_t st) {
-    const int which = lanes == 16 ? 0 : lanes == 32 ? 1 : 2;
     if (lanes != 16 && lanes != 32 && lanes != 64) {
         set_error("ragged product: lanes per row must be 16, 32 or 64");
         return GSRAD_EINVAL;
     }
-    for (const RowScene &s : t.few) {
-        const gsrad_status e = run_scene<ADJ>(F, s, in, E, rho, out, p_out, gE, st);
+    for (const RowTable::Part &p : t.rows[lanes == 16 ? 0 : lanes == 32 ? 1 : 2]) {
+        RowArgs a = row_args(F, rho);
+        a.tab = reinterpret_cast<const RowScene *>(t.base + p.tab);
+        a.first = reinterpret_cast<const int64_t *>(t.base + p.first);
+        a.count = p.count;
+        const gsrad_status e = run_rows<ADJ>(a, p.g, lanes, p.blocks, in, E, out, p_out, gE, st);
         if (e != GSRAD_OK) return e;
     }
-    if (t.count == 0) return GSRAD_OK;
-    RowArgs a = row_args(F, rho);
-    a.tab = t.tab;
-    a.first = t.first[which];
-    a.count = t.count;
-    auto run = [&](auto kernel) {
-        each_launch(t.blocks[which], kThreads, [&](int64_t first, unsigned blocks) {
-            a.block0 = first;
-            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), 0, st, a, in, E, out, p_out, gE);
-        });
-    };
-    if (which == 0) run(k_rows<16, 16, ADJ>);
-    else if (which == 1) run(k_rows<16, 32, ADJ>);
-    else run(k_rows<16, 64, ADJ>);
-    return check_hip(hipGetLastError(), "ragged product launch");
+    return GSRAD_OK;
 }
 
 }  // namespace
-
-bool rows_few(int C) { return row_lanes(C) < 16; }
-
-bool rows_whole(const RowScene &s) { return row_lanes_of(s, false) < 64 || row_lanes_of(s, true) < 64; }
-
-int64_t rows_blocks(int64_t n, int C, int lanes) {
-    const int64_t r = kThreads / lanes, chunks = row_chunks(C / 3, row_lanes(C));
-    return lanes == 16 ? (n * chunks + r - 1) / r : (n + r - 1) / r * chunks;
-}
 
 gsrad_status rows_bounce(const Csr &F, const RowScene &s, const float *Bin, const float *E, const float *rho,
                          float *Bout, hipStream_t st) {
@@ -575,55 +571,57 @@ gsrad_status rows_seed_batch(const RowTable &t, const float *grad_B, const float
                              hipStream_t st) {
     const int64_t lanes = t.vals / 3;
     each_launch((lanes + 255) / 256, 256, [&](int64_t first, unsigned blocks) {
-        hipLaunchKernelGGL(k_seed_batch, dim3(blocks), dim3(256), 0, st, t.all, t.scenes, lanes, first, grad_B, rho, lam,
-                           gE, p);
+        hipLaunchKernelGGL(k_seed_batch, dim3(blocks), dim3(256), 0, st, reinterpret_cast<const RowScene *>(t.base),
+                           t.scenes, lanes, first, grad_B, rho, lam, gE, p);
     });
     return check_hip(hipGetLastError(), "adjoint seed launch");
 }
 
+namespace {
+
 // How the sampled products take a scene's rows.  Several chunks: side by side in
 // one launch where the mean row is short (20k rows of 8 entries, 90
 // coefficients, three bounces: 72 us, one launch per chunk 227; of 64 entries
-// 471 and 449, but 8k rows 130 and 163) or there are two of at most twelve (50k rows of 512, 20
-// coefficients: 1.8 and 2.3 ms; 20k of 32: 1.8 and 1.5; 2k of 20: 107 and 67 us).  One chunk: 16 lanes per short row (20k rows of 8
-// entries, 27 coefficients, six bounces: 27 us, with 64 lanes 48).
-int sddmm_chunks(const RowScene &s) {
-    const int chunks = row_chunks(s.C / 3, row_lanes(s.C));
-    if (chunks == 1) return 1;
-    const bool short_rows = s.nnz <= (s.n > kManyItems ? kShortRow : 100) * s.n;
-    return short_rows || (chunks == 2 && s.n >= kManyItems && s.C <= 72) ? (chunks == 2 ? 2 : 4) : 1;
-}
-int sddmm_lanes(const RowScene &s) {
-    const bool one = row_chunks(s.C / 3, row_lanes(s.C)) == 1;
-    return one && s.n >= kManyItems && s.nnz <= kShortRow * s.n ? 16 : 64;
+// 471 and 449, but 8k rows 130 and 163) or there are two of at most twelve (50k
+// rows of 512, 20 coefficients: 1.8 and 2.3 ms; 20k of 32: 1.8 and 1.5; 2k of
+// 20: 107 and 67 us).  One chunk: 16 lanes per short row (20k rows of 8 entries,
+// 27 coefficients, six bounces: 27 us, with 64 lanes 48).
+RowTable::Part sampled_part(const RowScene &s) {
+    RowTable::Part p;
+    p.g = row_lanes(s.C);
+    const int chunks = row_chunks(s.C / 3, p.g);
+    const bool short_rows = s.nnz <= (s.n > kManyItems || chunks == 1 ? kShortRow : 100) * s.n;
+    if (chunks > 1 && (short_rows || (chunks == 2 && s.n >= kManyItems && s.C <= 72))) p.cp = chunks == 2 ? 2 : 4;
+    p.lanes = p.cp > 1 ? 16 * p.cp : chunks == 1 && s.n >= kManyItems && short_rows ? 16 : 64;
+    p.chunks = p.cp > 1 ? 1 : chunks;
+    p.per = p.cp > 1 ? 8 : sddmm_bounces(s.n, row_width(s.C / 3, p.g));
+    p.blocks = (s.n + kThreads / p.lanes - 1) / (kThreads / p.lanes);
+    return p;
 }
 
-gsrad_status rows_sddmm(const Csr &F, const RowScene &s, int nb, int64_t stride, const float *Btape,
-                        const float *Ltape, const float *rho, float *grad_F, float *grad_rho, hipStream_t st) {
-    if (s.n == 0 || nb == 0) return GSRAD_OK;
-    const int g = row_lanes(s.C), M = s.C / 3, width = row_width(M, g), chunks = row_chunks(M, g);
-    RowArgs a = row_args(F, rho);
-    a.one = s;
-    const int cp = sddmm_chunks(s), lanes = cp > 1 ? 16 * cp : sddmm_lanes(s);
-    const int r = kThreads / lanes;
-    const dim3 grid((unsigned)((s.n + r - 1) / r));
-    const int per = cp > 1 ? 8 : sddmm_bounces(s.n, width);
-    bool fresh = true;
-    for (int chunk = 0; chunk < (cp > 1 ? 1 : chunks); ++chunk) {
-        for (int q0 = 0; q0 < nb; q0 += per) {
+gsrad_status run_sampled(RowArgs a, const RowTable::Part &p, int nb, int64_t stride, const float *Btape,
+                         const float *Ltape, float *grad_F, float *grad_rho, hipStream_t st) {
+    for (int chunk = 0; chunk < p.chunks; ++chunk) {
+        for (int q0 = 0; q0 < nb; q0 += p.per) {
             const float *B = Btape + q0 * stride, *L = Ltape + q0 * stride;
+            // (a scene's first chunk and bounces write, the others add)
+            const bool write = chunk == 0 && q0 == 0;
             auto run = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, st, a, chunk, stride, B, L, grad_F, grad_rho, fresh);
+                each_launch(p.blocks, kThreads, [&](int64_t first, unsigned groups) {
+                    a.block0 = first;
+                    hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), 0, st, a, chunk, stride, B, L, grad_F,
+                                       grad_rho, write);
+                });
             };
             auto with = [&](auto bounces) {
                 constexpr int N = decltype(bounces)::value;
-                if (cp == 2) run(k_sddmm3<16, 32, 2, N>);
-                else if (cp == 4) run(k_sddmm3<16, 64, 4, N>);
-                else if (g == 1) run(lanes == 16 ? k_sddmm3<1, 16, 1, N> : k_sddmm3<1, 64, 1, N>);
-                else if (g == 4) run(lanes == 16 ? k_sddmm3<4, 16, 1, N> : k_sddmm3<4, 64, 1, N>);
-                else run(lanes == 16 ? k_sddmm3<16, 16, 1, N> : k_sddmm3<16, 64, 1, N>);
+                if (p.cp == 2) run(k_sddmm3<16, 32, 2, N>);
+                else if (p.cp == 4) run(k_sddmm3<16, 64, 4, N>);
+                else if (p.g == 1) run(p.lanes == 16 ? k_sddmm3<1, 16, 1, N> : k_sddmm3<1, 64, 1, N>);
+                else if (p.g == 4) run(p.lanes == 16 ? k_sddmm3<4, 16, 1, N> : k_sddmm3<4, 64, 1, N>);
+                else run(p.lanes == 16 ? k_sddmm3<16, 16, 1, N> : k_sddmm3<16, 64, 1, N>);
             };
-            switch (std::min(per, nb - q0)) {
+            switch (std::min(p.per, nb - q0)) {
                 case 1: with(std::integral_constant<int, 1>{}); break;
                 case 2: with(std::integral_constant<int, 2>{}); break;
                 case 3: with(std::integral_constant<int, 3>{}); break;
@@ -633,10 +631,117 @@ gsrad_status rows_sddmm(const Csr &F, const RowScene &s, int nb, int64_t stride,
                 case 7: with(std::integral_constant<int, 7>{}); break;
                 case 8: with(std::integral_constant<int, 8>{}); break;
             }
-            fresh = false;
         }
     }
     return check_hip(hipGetLastError(), "sddmm launch");
+}
+
+}  // namespace
+
+gsrad_status rows_sddmm(const Csr &F, const RowScene &s, int nb, int64_t stride, const float *Btape,
+                        const float *Ltape, const float *rho, float *grad_F, float *grad_rho, hipStream_t st) {
+    if (s.n == 0 || nb == 0) return GSRAD_OK;
+    RowArgs a = row_args(F, rho);
+    a.one = s;
+    return run_sampled(a, sampled_part(s), nb, stride, Btape, Ltape, grad_F, grad_rho, st);
+}
+
+gsrad_status rows_sddmm_batch(const Csr &F, const RowTable &t, int nb, const float *Btape, const float *Ltape,
+                              const float *rho, float *grad_F, float *grad_rho, hipStream_t st) {
+    if (nb == 0) return GSRAD_OK;
+    for (const RowTable::Part &p : t.sampled) {
+        RowArgs a = row_args(F, rho);
+        a.tab = reinterpret_cast<const RowScene *>(t.base + p.tab);
+        a.first = reinterpret_cast<const int64_t *>(t.base + p.first);
+        a.count = p.count;
+        const gsrad_status e = run_sampled(a, p, nb, t.vals, Btape, Ltape, grad_F, grad_rho, st);
+        if (e != GSRAD_OK) return e;
+    }
+    for (const RowScene &s : t.alone) {
+        const gsrad_status e = rows_sddmm(F, s, nb, t.vals, Btape, Ltape, rho, grad_F, grad_rho, st);
+        if (e != GSRAD_OK) return e;
+    }
+    return GSRAD_OK;
+}
+
+// Scenes whose sampled products share launches: up to kJoined rows times chunks.
+// A launch of a small one ends before it has filled the chip (64 scenes of 512
+// rows, 8 lights, K = 9, six bounces: 6.7 ms with launches of their own, 2.4
+// joined; 1,000 of 64 rows 8.1 and 0.2).  Large ones have the same chunk of
+// columns in L2 longer by themselves (16 scenes of 4,096 rows, 30 lights: 21.3
+// and 22.2 ms).
+constexpr int64_t kJoined = 32768;
+static bool joined(const RowScene &s) { return s.n * row_chunks(s.C / 3, row_lanes(s.C)) <= kJoined; }
+
+size_t rows_table_bytes(size_t scenes) { return scenes * 3 * sizeof(RowScene) + scenes * 4 * sizeof(int64_t); }
+
+void rows_table(const std::vector<RowScene> &scenes, RowTable *t, std::vector<char> *image) {
+    *t = RowTable{};
+    image->clear();
+    auto put = [&](const void *p, size_t bytes) {
+        const size_t at = image->size();
+        image->insert(image->end(), static_cast<const char *>(p), static_cast<const char *>(p) + bytes);
+        return at;
+    };
+    put(scenes.data(), scenes.size() * sizeof(RowScene));
+    t->scenes = (int)scenes.size();
+    double work = 0.0, whole = 0.0;
+    for (const RowScene &s : scenes) {
+        const double w = (double)s.nnz * s.C;
+        t->vals += s.n * s.C;
+        work += w;
+        if (row_lanes_of(s, false) < 64 || row_lanes_of(s, true) < 64) whole += w;
+    }
+    t->whole = 2.0 * whole > work;
+    for (int g : {1, 4, 16}) {
+        std::vector<RowScene> of;
+        for (const RowScene &s : scenes)
+            if (row_lanes(s.C) == g) of.push_back(s);
+        if (of.empty()) continue;
+        const size_t tab = put(of.data(), of.size() * sizeof(RowScene));
+        for (int k = 0; k < 3; ++k) {
+            RowTable::Part p;
+            p.g = g;
+            p.lanes = 16 << k;
+            std::vector<int64_t> first;
+            for (const RowScene &s : of) {
+                first.push_back(p.blocks);
+                p.blocks += rows_blocks(s.n, s.C, p.lanes);
+            }
+            p.count = (int)of.size();
+            p.tab = tab;
+            p.first = put(first.data(), first.size() * sizeof(int64_t));
+            t->rows[k].push_back(p);
+        }
+    }
+    // joined: scenes of one kernel and as many bounces a launch
+    std::vector<bool> taken(scenes.size(), false);
+    for (size_t i = 0; i < scenes.size(); ++i) {
+        if (taken[i]) continue;
+        if (!joined(scenes[i])) {
+            t->alone.push_back(scenes[i]);
+            continue;
+        }
+        RowTable::Part p = sampled_part(scenes[i]);
+        std::vector<RowScene> of;
+        std::vector<int64_t> first;
+        int64_t blocks = 0;
+        for (size_t k = i; k < scenes.size(); ++k) {
+            if (taken[k] || !joined(scenes[k])) continue;
+            const RowTable::Part q = sampled_part(scenes[k]);
+            if (q.g != p.g || q.lanes != p.lanes || q.cp != p.cp || q.per != p.per) continue;
+            taken[k] = true;
+            first.push_back(blocks);
+            blocks += q.blocks;
+            of.push_back(scenes[k]);
+            p.chunks = std::max(p.chunks, q.chunks);
+        }
+        p.blocks = blocks;
+        p.count = (int)of.size();
+        p.tab = put(of.data(), of.size() * sizeof(RowScene));
+        p.first = put(first.data(), first.size() * sizeof(int64_t));
+        t->sampled.push_back(p);
+    }
 }
 
 }  // namespace gsrad

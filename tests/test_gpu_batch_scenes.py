@@ -51,3 +51,23 @@ def test_adjoint_follows_a_grad_B_that_moves(g):
         held.append(gB)   # each at an address of its own
         out = g.batch_transport_backward(batch, rows, gB, out=gE)
         _compare(g, ffs, rho, E, batch, nb, gB, B, out)
+
+
+@pytest.mark.parametrize("K,nb", [(1, 3), (4, 9), (9, 2)])
+def test_many_small_scenes(g, K, nb):
+    """Scenes of one to 13 chunks, of rows that 16 and 64 lanes take, of one
+    surfel and of none but empty rows, and one too large to share launches."""
+    sizes = [1, 2, 63, 64, 65, 130, 257, 300, 511, 40, 33000, 90, 200, 129]
+    lengths = [0, 1, 5, 30, 60, 12, 40, 100, 20, 0, 10, 70, 150, 9]
+    lights = [1, 3, 1, 2, 4, 5, 17, 1, 6, 1, 1, 23, 9, 50]
+    ffs, rho, E, batch = _batch(g, sizes, lengths, lights, K)
+    flat, rows = batch.pack(E), torch.cat(rho)
+    gB = dev(scenes.seeded_array(tuple(flat.shape), 30, -1.0, 1.0))
+    B = g.batch_transport_solve(batch, rows, flat, nb)
+    _compare(g, ffs, rho, E, batch, nb, gB, B, g.batch_transport_backward(batch, rows, gB))
+    # the same layout refilled with rows of other lengths: captured loops, other groups
+    other = [g.ff_from_csr(*(dev(a) for a in scenes.seeded_csr(n, k, seed=50 + s)))
+             for s, (n, k) in enumerate(zip(sizes, lengths[::-1]))]
+    batch = g.batch_create(other, lights, K, batch=batch)
+    B = g.batch_transport_solve(batch, rows, flat, nb)
+    _compare(g, other, rho, E, batch, nb, gB, B, g.batch_transport_backward(batch, rows, gB))
