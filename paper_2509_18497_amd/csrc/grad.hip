@@ -1218,7 +1218,7 @@ constexpr int kScaleMargin = 12;
 
 size_t geometry_list_bytes(int64_t n, int R) {
     const int threads = R >= 256 ? 256 : ((R + 63) / 64) * 64;
-    return lists_pay(n, R, kGeometryShift) ? (size_t)ListLayout(n, R, threads, kGeometryShift, kGeometryEntry).bytes : 0;
+    return lists_pay(n, R, kGeometryShift, kListBlocks, 0.0) ? (size_t)ListLayout(n, R, threads, kGeometryShift, kGeometryEntry).bytes : 0;
 }
 
 size_t center_group_bytes() { return (size_t)kRowParts * kRowPart * sizeof(uint2); }

@@ -32,8 +32,10 @@ struct HitLists {
     __host__ __device__ int blocks() const { return 1 << bits; }
 };
 
-// Rule: listed where the rays reach kListRays and the surfels make at most
-// kListBlocks blocks of 2^shift.  1,024 receivers of 128 rays (131k rays):
+// Rule: listed where the rays reach kListRays, the surfels make at most `most`
+// blocks of 2^shift, and a stretch has `share` times as many rays as there are
+// blocks: with fewer its parts are a few contributions each, and the parts'
+// table costs more than the atomics.  1,024 receivers of 128 rays (131k rays):
 // opacity 402 us and geometry 744 us listed, 508 and 2,122 us added directly;
 // 512 of 64 rays, the opacity's 37 us of direct adds leave nothing to gain.
 constexpr int64_t kListRays = (int64_t)1 << 16;
@@ -45,8 +47,9 @@ constexpr int64_t kListRays = (int64_t)1 << 16;
 constexpr int64_t kListBytes = (int64_t)1 << 31;
 constexpr int64_t kListStretches = 1 << 16;
 
-inline bool lists_pay(int64_t n, int R, int shift) {
-    return n * R >= kListRays && ((n - 1) >> shift) < kListBlocks;
+inline bool lists_pay(int64_t n, int R, int shift, int64_t most, double share) {
+    const int64_t blocks = ((n - 1) >> shift) + 1;
+    return n * R >= kListRays && blocks <= most && std::min(R, 256) >= share * (double)blocks;
 }
 
 // Host layout of the workspace: used, parts, entries

@@ -1114,6 +1114,12 @@ __global__ void __launch_bounds__(256) k_opacity_rec(BvhDev bv, int R, const uin
 // CU (2,048 / 4,096 / 8,192 on a 100k-surfel bowl in chunks of 1 GiB: 11.1 +
 // 2.7, 10.0 + 2.7, 9.0 + 4.3 ms).
 constexpr int kOpacityShift = 12;
+// Blocks up to which, and rays of a stretch per block from which on, the lists
+// pay: 100k surfels (25 blocks), 16 / 32 / 64 rays each: added directly 2.7, 4.5,
+// 8.0 ms, listed 3.1, 4.2, 6.1 to 6.8; 250k (62 blocks), 128 rays 24.5 and 26.6;
+// 400k (98 blocks), 32 and 128 rays 14.3 and 37.1, listed 20.0 and 46.4.
+constexpr double kOpacityShare = 1.25;
+constexpr int64_t kOpacityBlocks = 48;
 constexpr int kListSumThreads = 256;
 constexpr int kListSumWgs = 1024;   // workgroups aimed at
 
@@ -1405,7 +1411,7 @@ gsrad_status launch_opacity_rec(const BvhDev &bv, int R, const uint2 *recs, cons
 
 size_t opacity_list_bytes(int64_t n, int R) {
     const int threads = R >= 256 ? 256 : ((R + 63) / 64) * 64;
-    return lists_pay(n, R, kOpacityShift) ? (size_t)ListLayout(n, R, threads, kOpacityShift, sizeof(uint2)).bytes : 0;
+    return R >= 16 && lists_pay(n, R, kOpacityShift, kOpacityBlocks, kOpacityShare) ? (size_t)ListLayout(n, R, threads, kOpacityShift, sizeof(uint2)).bytes : 0;
 }
 
 gsrad_status launch_opacity_finish(const BvhDev &bv, const void *acc, const float *grad_rho, const float *albedo,

@@ -251,8 +251,8 @@ __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
 }
 
 // A row of dL/dF in LDS: its columns (ascending), their values, and the first
-// position of each of kRowBuckets ranges of columns, from which find() searches
-// on.  An open-addressing table needs twice the row, rounded up to a power of
+// position of each of up to kRowBuckets ranges of columns (about two an entry),
+// from which find() searches on.  An open-addressing table needs twice the row, rounded up to a power of
 // two: the rows of a 16k-surfel room (2,544 entries, the longest 4,369) left a
 // CU one workgroup of four waves, now four workgroups (opacity gradient 14.5 ms
 // and 10.0 ms, each with direct adds).
@@ -276,12 +276,14 @@ struct RowIndex {
     __device__ __forceinline__ void load(const int32_t *cols, const float *vals, int entries, float scale, int tid,
                                          int threads) {
         len = entries;
+        int buckets = kRowBuckets;
+        for (; buckets > 64 && buckets > 2 * len; buckets >>= 1) ++shift;
         for (int k = tid; k < len; k += threads) {
             col[k] = (uint32_t)cols[k];
             val[k] = vals[k] * scale;
         }
         __syncthreads();
-        for (int q = tid; q <= kRowBuckets; q += threads) start[q] = (uint16_t)lower(0, len, (uint32_t)q << shift);
+        for (int q = tid; q <= buckets; q += threads) start[q] = (uint16_t)lower(0, len, (uint32_t)q << shift);
         __syncthreads();
     }
     __device__ __forceinline__ int lower(int lo, int hi, uint32_t j) const {
