@@ -656,7 +656,7 @@ __global__ void __launch_bounds__(256) k_fields_finish(BvhDev bv, const unsigned
 // zeroes a counter
 __global__ void k_seg_reset(uint32_t *used) { used[threadIdx.x] = 0; }
 
-template <int PASS>
+template <int PASS, bool LISTED>
 __global__ void __launch_bounds__(256) k_geometry_rec(BvhDev bv, int R, uint64_t seed, const uint2 *__restrict__ recs,
                                                       const uint32_t *__restrict__ rcnt, int rcap, int64_t s0, int64_t nblocks,
                                                       const int64_t *__restrict__ row_ptr,
@@ -680,8 +680,10 @@ __global__ void __launch_bounds__(256) k_geometry_rec(BvhDev bv, int R, uint64_t
     for (int batch = 0; batch < batches; ++batch) {
         const int r = batch * (int)blockDim.x + tid;
         ListStretch list(lists, next, (int64_t)blockIdx.x * batches + batch);
-        list.clear(tid, blockDim.x);
-        __syncthreads();
+        if (LISTED) {
+            list.clear(tid, blockDim.x);
+            __syncthreads();
+        }
         uint32_t m = r < R ? rcnt[(int64_t)i * R + r] : 0u;
         if (m > (uint32_t)rcap) m = 0;
         const uint2 *in = recs + (int64_t)i * rcap * R + r;
@@ -689,7 +691,7 @@ __global__ void __launch_bounds__(256) k_geometry_rec(BvhDev bv, int R, uint64_t
         float T = 1.0f;
         for (uint32_t q = 0; q < m; ++q) {
             const uint2 h = in[(int64_t)q * R];
-            list.count(h.x);
+            if (LISTED) list.count(h.x);
             const float gs = __uint_as_float(h.y);
             const float x = bv.c[h.x] * fabsf(gs);
             if (gs > 0.0f) {
@@ -698,7 +700,7 @@ __global__ void __launch_bounds__(256) k_geometry_rec(BvhDev bv, int R, uint64_t
             }
             T = __fmul_rn(T, exp_fx(-x));
         }
-        list.open(tid, blockDim.x);
+        if (LISTED) list.open(tid, blockDim.x);
         if (W.hi == 0.0f) m = 0;
         float dx, dy, dz, sx, sy, sz;
         ray_direction(ri.c.x, ri.c.y, ri.c.z, ri.d.x, ri.d.y, ri.d.z, ri.b.x, ri.b.y, ri.b.z, (uint64_t)r,
@@ -740,7 +742,7 @@ __global__ void __launch_bounds__(256) k_geometry_rec(BvhDev bv, int R, uint64_t
             const float beta = (ghx * dx + ghy * dy + ghz * dz) / (float)den;
             const float gqx = beta * rk.b.x - ghx, gqy = beta * rk.b.y - ghy, gqz = beta * rk.b.z - ghz;
             cross_terms(rk, du, dw, beta, hx, hy, hz, x10);
-            if (PASS == 1 && list.on) {
+            if (LISTED && list.on) {
                 float4 *e = reinterpret_cast<float4 *>(lists.entry) + 3 * (int64_t)list.place(k);
                 e[0] = make_float4(x10[0], x10[1], x10[2], x10[3]);
                 e[1] = make_float4(x10[4], x10[5], x10[6], x10[7]);
@@ -764,7 +766,7 @@ __global__ void __launch_bounds__(256) k_geometry_rec(BvhDev bv, int R, uint64_t
             accI.add<PASS>(sink, 6 + c, 6 + c, sy * gd[c]);
             accI.add<PASS>(sink, 9 + c, 9 + c, sz * gd[c]);
         }
-        list.close(tid, blockDim.x);
+        if (LISTED) list.close(tid, blockDim.x);
     }
     {
         const int fI[12] = {0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11};
@@ -1317,8 +1319,9 @@ gsrad_status launch_geometry_rec(const BvhDev &bv, int R, uint64_t seed, const u
     }
     static bool attr_set = false;
     if (!attr_set) {
-        for (const void *fn : {reinterpret_cast<const void *>(&k_geometry_rec<0>),
-                               reinterpret_cast<const void *>(&k_geometry_rec<1>)})
+        for (const void *fn : {reinterpret_cast<const void *>(&k_geometry_rec<0, false>),
+                               reinterpret_cast<const void *>(&k_geometry_rec<1, false>),
+                               reinterpret_cast<const void *>(&k_geometry_rec<1, true>)})
             (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
         attr_set = true;
     }
@@ -1331,7 +1334,7 @@ gsrad_status launch_geometry_rec(const BvhDev &bv, int R, uint64_t seed, const u
     auto run = [&](int pass, int stride) {
         if (pass == 0) {
             const int64_t nb = (bv.n + stride - 1) / stride;
-            hipLaunchKernelGGL(k_geometry_rec<0>, dim3((unsigned)nb), dim3(threads), smem, st, bv, R, seed, recs, rcnt,
+            hipLaunchKernelGGL((k_geometry_rec<0, false>), dim3((unsigned)nb), dim3(threads), smem, st, bv, R, seed, recs, rcnt,
                                rcap, (int64_t)0, nb, row_ptr, col, gF, max_row, maxbits, fx, a, stride, none);
             return;
         }
@@ -1339,7 +1342,8 @@ gsrad_status launch_geometry_rec(const BvhDev &bv, int R, uint64_t seed, const u
         for (int64_t s0 = 0; s0 < bv.n; s0 += chunk) {
             const int64_t m = std::min(chunk, bv.n - s0);
             if (ws) hipLaunchKernelGGL(k_seg_reset, dim3(1), dim3(2), 0, st, reinterpret_cast<uint32_t *>(lists.used));
-            hipLaunchKernelGGL(k_geometry_rec<1>, dim3((unsigned)m), dim3(threads),
+            const auto kernel = ws ? k_geometry_rec<1, true> : k_geometry_rec<1, false>;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)m), dim3(threads),
                                smem + (ws ? (size_t)lists.blocks() * 4 : 0), st, bv, R, seed, recs, rcnt, rcap, s0, m,
                                row_ptr, col, gF, max_row, maxbits, fx, a, 1, lists);
             if (ws) {

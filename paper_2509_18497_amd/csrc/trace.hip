@@ -999,6 +999,7 @@ __global__ void __launch_bounds__(256) k_opacity_bwd(BvhDev bv, int R, uint64_t 
 // of a 16k-surfel room 4.6 ms (14.5 ms, also for the larger row table).
 // Compositing backward from the recorded hits: the same FP32 alpha and T
 // sequence as the forward trace, G from row i of dL/dF in LDS.
+template <bool LISTED>
 __global__ void __launch_bounds__(256) k_opacity_rec(BvhDev bv, int R, const uint2 *__restrict__ recs,
                                                      const uint32_t *__restrict__ rcnt, int rcap, int64_t s0, int64_t nblocks,
                                                      const int64_t *__restrict__ row_ptr,
@@ -1043,8 +1044,12 @@ __global__ void __launch_bounds__(256) k_opacity_rec(BvhDev bv, int R, const uin
     for (int batch = 0; batch < batches; ++batch) {
         const int t = batch * (int)blockDim.x + tid;
         ListStretch out(lists, next, (int64_t)blockIdx.x * batches + batch);
-        out.clear(tid, blockDim.x);
-        __syncthreads();
+        if (LISTED) {
+            out.clear(tid, blockDim.x);
+            __syncthreads();
+        } else if (t >= R) {
+            break;
+        }
         const int r = by_len ? (int)ray_of[tid] : t;
         uint32_t m = t < R ? rcnt[(int64_t)i * R + r] : 0u;
         if (m > (uint32_t)rcap) m = 0;
@@ -1066,7 +1071,7 @@ __global__ void __launch_bounds__(256) k_opacity_rec(BvhDev bv, int R, const uin
                 h1 = h2;
                 if (q + 2 < m) h2 = in[(int64_t)(q + 2) * R];
                 if (q + 1 < m) c1 = bv.c[h1.x];
-                out.count(h.x);
+                if (LISTED) out.count(h.x);
                 const float gs = __uint_as_float(h.y);
                 const float x = cq * fabsf(gs);
                 if (gs > 0.0f) {
@@ -1076,8 +1081,9 @@ __global__ void __launch_bounds__(256) k_opacity_rec(BvhDev bv, int R, const uin
                 T = __fmul_rn(T, exp_fx(-x));
             }
         }
-        out.open(tid, blockDim.x);
+        if (LISTED) out.open(tid, blockDim.x);
         if (W.hi == 0.0f) m = 0;   // every G_q alpha_q T_q is 0: no contribution
+        if (!LISTED && m == 0) continue;
         DF P{0.0f, 0.0f};
         T = 1.0f;
         uint2 h1 = m > 0 ? in[0] : make_uint2(0u, 0u);
@@ -1099,12 +1105,12 @@ __global__ void __launch_bounds__(256) k_opacity_rec(BvhDev bv, int R, const uin
             const float G = gs > 0.0f ? row.find(h.x) : 0.0f;
             float v;
             if (opacity_term(G, -expm1f(-x), f, T, g, cq, oq, W, P, v)) {
-                if (out.on) reinterpret_cast<uint2 *>(lists.entry)[out.place(h.x)] = make_uint2(h.x, __float_as_uint(v));
+                if (LISTED && out.on) reinterpret_cast<uint2 *>(lists.entry)[out.place(h.x)] = make_uint2(h.x, __float_as_uint(v));
                 else fx_add(my + h.x, v, scale);
             }
             T = __fmul_rn(T, f);
         }
-        out.close(tid, blockDim.x);
+        if (LISTED) out.close(tid, blockDim.x);
     }
 }
 
@@ -1379,8 +1385,9 @@ gsrad_status launch_opacity_rec(const BvhDev &bv, int R, const uint2 *recs, cons
     const size_t smem = row_index_bytes(max_row);
     static bool attr_set = false;
     if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_opacity_rec), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            160 * 1024 - 4096);
+        for (const void *fn : {reinterpret_cast<const void *>(&k_opacity_rec<false>),
+                               reinterpret_cast<const void *>(&k_opacity_rec<true>)})
+            (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
         attr_set = true;
     }
     if (max_row > kRowIndexMax) {
@@ -1397,7 +1404,7 @@ gsrad_status launch_opacity_rec(const BvhDev &bv, int R, const uint2 *recs, cons
     for (int64_t s0 = 0; s0 < bv.n; s0 += chunk) {
         const int64_t m = std::min(chunk, bv.n - s0);
         if (ws) hipLaunchKernelGGL(k_list_reset, dim3(1), dim3(1), 0, st, lists.used);
-        hipLaunchKernelGGL(k_opacity_rec, dim3((unsigned)m), dim3(threads), smem + (ws ? (size_t)lists.blocks() * 4 : 0), st, bv, R,
+        hipLaunchKernelGGL(ws ? k_opacity_rec<true> : k_opacity_rec<false>, dim3((unsigned)m), dim3(threads), smem + (ws ? (size_t)lists.blocks() * 4 : 0), st, bv, R,
                            recs, rcnt, rcap, s0, m, row_ptr, col, gF, max_row, fx, a, lists);
         if (ws) {
             const int64_t rows = (m * batches + 15) / 16;
