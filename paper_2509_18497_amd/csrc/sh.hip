@@ -386,6 +386,53 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock, K == 9 ? 2 : 3) k_sddmm_s
     }
 }
 
+// The same with every lane reading its own sender's row: no step waits for the
+// one before, which counts where the rows come from L2 and a step is short.
+template <int K>
+__global__ void __launch_bounds__(256) k_sddmm_sh_own(const Frame *__restrict__ frames, const int64_t *__restrict__ row_ptr,
+                                                      const int32_t *__restrict__ col, int64_t n, int Lt, int nb,
+                                                      const float *__restrict__ Btape, const float *__restrict__ Ltape,
+                                                      const float *__restrict__ R, float *__restrict__ grad_F,
+                                                      int64_t nblocks, const int32_t *__restrict__ order) {
+    constexpr int W = 3 * K;
+    const int64_t idx = xcd_block(blockIdx.x, nblocks) * 4 + threadIdx.x / 64;
+    if (idx >= n) return;
+    const int64_t row = order ? (int64_t)order[idx] : idx;
+    const Frame ri = frames[row];
+    const int64_t b = row_ptr[row], e = row_ptr[row + 1];
+    const float *Ri = R + row * W;
+    const size_t plane = (size_t)n * Lt * W;
+    for (int64_t kk = b + __lane_id(); kk < e; kk += 64) {
+        const int32_t j = col[kk];
+        float di[3] = {}, ej[3] = {};
+        if constexpr (K > 1) pair_dirs(ri, frames[j], di, ej);
+        float Yd[K], Ye[K];
+        sh_eval<K>(di[0], di[1], di[2], Yd);
+        sh_eval<K>(ej[0], ej[1], ej[2], Ye);
+        float g = 0.0f;
+        for (int k = 0; k < nb; ++k) {
+            for (int l = 0; l < Lt; ++l) {
+                const float *lam = Ltape + k * plane + (row * Lt + l) * W;
+                const float *bj = Btape + k * plane + ((int64_t)j * Lt + l) * W;
+                float p0 = 0.0f, p1 = 0.0f, p2 = 0.0f, s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
+#pragma unroll
+                for (int q = 0; q < K; ++q) {
+                    p0 = __builtin_fmaf(Yd[q], Ri[3 * q + 0] * lam[3 * q + 0], p0);
+                    p1 = __builtin_fmaf(Yd[q], Ri[3 * q + 1] * lam[3 * q + 1], p1);
+                    p2 = __builtin_fmaf(Yd[q], Ri[3 * q + 2] * lam[3 * q + 2], p2);
+                    s0 = __builtin_fmaf(Ye[q], bj[3 * q + 0], s0);
+                    s1 = __builtin_fmaf(Ye[q], bj[3 * q + 1], s1);
+                    s2 = __builtin_fmaf(Ye[q], bj[3 * q + 2], s2);
+                }
+                g = __builtin_fmaf(p0, s0, g);
+                g = __builtin_fmaf(p1, s1, g);
+                g = __builtin_fmaf(p2, s2, g);
+            }
+        }
+        grad_F[kk] = g;
+    }
+}
+
 // grad_R[i][q] = sum_k sum_l lambda^(k+1)_i[l][q] Q^(k)_i[l][q]
 __global__ void __launch_bounds__(256) k_grad_R(const float *__restrict__ Ltape, const float *__restrict__ Qtape,
                                                 int64_t n, int Lt, int W, int nb, float *__restrict__ grad_R) {
@@ -494,11 +541,31 @@ int sddmm_bounces_sh(int64_t n, int Lt, int K) {
     return (int)std::max<int64_t>(1, kSddmmBytesSh / (n * Lt * K * 12));
 }
 
+// (a sender is then gathered too few times for L2 to matter)
+bool short_rows(const Csr &F) { return F.nnz <= 40 * F.n; }
+
+// Rows read by their own lanes instead of through LDS: K = 4 and 9 for short rows
+// and few of them (512 rows, eight lights, K = 9, four bounces: 153 us, staged
+// 203; 6,000 rows of 256 entries, one light: 102 and 71), K = 1, whose 12 bytes a
+// row gain nothing from LDS, until the senders' rows leave L2 (6,000 rows of a
+// room, one light: 74 us, staged 108; 50k rows, eight lights: 4.1 and 3.6 ms).
+bool sddmm_own(const Csr &F, int K) {
+    if (K == 16) return false;
+    if (K == 1) return short_rows(F) || F.n <= 30000;
+    return F.n <= 1024 || (short_rows(F) && (K == 9 || F.n <= 2048));
+}
+
 template <int K>
 void launch_sddmm_k(const Frame *frames, const Csr &F, int Lt, int nb, const float *Bt, const float *Lt_, const float *R,
                     float *grad_F, hipStream_t st) {
+    if (sddmm_own(F, K)) {
+        const unsigned own = (unsigned)((F.n + 3) / 4);
+        hipLaunchKernelGGL(k_sddmm_sh_own<K>, dim3(own), dim3(256), 0, st, frames, F.row_ptr, F.col, F.n, Lt, nb, Bt, Lt_,
+                           R, grad_F, (int64_t)own, F.order);
+        return;
+    }
     const unsigned g = row_blocks_sh(F.n);
-    const int per = sddmm_bounces_sh(F.n, Lt, K);
+    const int per = short_rows(F) ? nb : sddmm_bounces_sh(F.n, Lt, K);
     for (int k = 0; k < nb; k += per)
         hipLaunchKernelGGL(k_sddmm_sh<K>, dim3(g), dim3(64 * kWavesPerBlock), 0, st, frames, F.row_ptr, F.col, F.n, Lt, k,
                            std::min(nb, k + per), Bt, Lt_, R, grad_F, (int64_t)g, F.order);
