@@ -474,7 +474,7 @@ gsrad_status gsrad_build_bvh(const gsrad_surfels *s, gsrad_bvh **bvh, void *stre
     ENS(rec, n * sizeof(SurfRec), "surfel records");
     ENS(nodes, std::max<int64_t>(n - 1, 1) * sizeof(Node), "bvh nodes");
     ENS(wide, std::max<int64_t>(n - 1, 1) * sizeof(WideNode), "bvh wide nodes");
-    ENS(frames, sh_frame_bytes(n), "surfel frames");
+    ENS(frames, n * sizeof(Frame), "surfel frames");
     ENS(leafbox, n * 6 * sizeof(float), "leaf boxes");
     ENS(leaf_parent, n * 4, "leaf parents");
     ENS(inv, n * 4, "inverse order");
@@ -500,6 +500,7 @@ gsrad_status gsrad_build_bvh(const gsrad_surfels *s, gsrad_bvh **bvh, void *stre
     B.opraw = h->opraw.as<float>();
     B.area = h->area.as<double>();
     B.dado = h->dado.as<float>();
+    B.frames = h->frames.as<Frame>();
     B.bounds = h->bounds.as<float>();
     B.height = h->height.as<int>();
     B.temp = h->temp.p;
@@ -1232,10 +1233,6 @@ gsrad_status gsrad_transport_solve_sh(const gsrad_ff *ff, const gsrad_bvh *bvh, 
             gsrad_ff *m = const_cast<gsrad_ff *>(ff);
             if ((e = m->slab.ensure(std::max(m->slab.bytes, row_bytes * 2), "ping-pong")) != GSRAD_OK) return fail(e);
         }
-        // (the same values by every call on this BVH, in memory its build took:
-        // threads and streams may share the BVH)
-        const DevBuf &frames = bvh->frames;
-        if ((e = launch_sh_frames(bvh->dev(), frames.p, st)) != GSRAD_OK) return fail(e);
         const float *src = E;
         for (int k = 0; k < n_bounces; ++k) {
             float *dst;
@@ -1243,7 +1240,7 @@ gsrad_status gsrad_transport_solve_sh(const gsrad_ff *ff, const gsrad_bvh *bvh, 
             else if (tp) dst = slots + (size_t)(k + 1) * n * C;
             else dst = const_cast<gsrad_ff *>(ff)->slab.as<float>() + (size_t)(k & 1) * n * C;
             ProfScope ps("bounce_sh", st);
-            if ((e = launch_transfer_sh(frames.p, F, n_lights, K, src, E, R, qs ? qs + (size_t)k * n * C : nullptr, dst, 0,
+            if ((e = launch_transfer_sh(bvh->B.frames, F, n_lights, K, src, E, R, qs ? qs + (size_t)k * n * C : nullptr, dst, 0,
                                         st)) != GSRAD_OK)
                 return fail(e);
             src = dst;
@@ -1307,11 +1304,11 @@ gsrad_status gsrad_transport_backward_sh(const gsrad_ff *ff, const gsrad_bvh *bv
         float *lam_out = k >= 1 ? L + (size_t)(k - 1) * n * C : tp->lam0.as<float>();
         ProfScope ps("adjoint_sh", st);
         GS_TRY(launch_scale_rows(lam_in, R, n, Lt, K, u, st));
-        GS_TRY(launch_transfer_sh(bvh->frames.p, FT, Lt, K, u, nullptr, nullptr, lam_out, grad_E, 1, st));
+        GS_TRY(launch_transfer_sh(bvh->B.frames, FT, Lt, K, u, nullptr, nullptr, lam_out, grad_E, 1, st));
     }
     ProfScope ps("sddmm_sh", st);
     if (grad_R) GS_TRY(launch_grad_R(L, tp->Q.as<float>(), n, Lt, K, nb, grad_R, st));
-    if (grad_F) GS_TRY(launch_sddmm_sh(bvh->frames.p, ff->csr(), Lt, K, nb, tp->B.as<float>(), L, R, grad_F, st));
+    if (grad_F) GS_TRY(launch_sddmm_sh(bvh->B.frames, ff->csr(), Lt, K, nb, tp->B.as<float>(), L, R, grad_F, st));
     return GSRAD_OK;
 }
 

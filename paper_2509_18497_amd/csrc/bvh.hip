@@ -111,7 +111,7 @@ __global__ void __launch_bounds__(kThreads) k_records(gsrad_surfels sf, const ui
                                                       float *__restrict__ leafbox, int32_t *__restrict__ inv,
                                                       float *__restrict__ cst, float *__restrict__ opc,
                                                       float *__restrict__ opraw, double *__restrict__ area,
-                                                      float *__restrict__ dado) {
+                                                      float *__restrict__ dado, Frame *__restrict__ frames) {
     const int64_t s = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (s >= sf.n) return;
     const int64_t j = order[s];
@@ -130,6 +130,7 @@ __global__ void __launch_bounds__(kThreads) k_records(gsrad_surfels sf, const ui
     r.c = make_float4(tux, tuy, tuz, c);
     r.d = make_float4(tvx, tvy, tvz, __uint_as_float((uint32_t)j));
     rec[s] = r;
+    frames[j] = Frame{{px, py, pz}, {nx, ny, nz}, {tux, tuy, tuz}, {tvx, tvy, tvz}};
     inv[j] = (int32_t)s;
     cst[j] = c;
     opc[j] = o;
@@ -414,7 +415,7 @@ gsrad_status bvh_build(const gsrad_surfels &sf, BvhBuffers &B, hipStream_t st) {
     s = radix_sort_pairs(k_in, v_in, k_out, v_out, n, 30, rtemp, rbytes, st);
     if (s != GSRAD_OK) return s;
     hipLaunchKernelGGL(k_records, dim3(nblk(n)), dim3(kThreads), 0, st, sf, v_out, B.bounds, B.rec, B.leafbox, B.inv,
-                       B.cst, B.opc, B.opraw, B.area, B.dado);
+                       B.cst, B.opc, B.opraw, B.area, B.dado, B.frames);
     if (n >= 2) {
         hipLaunchKernelGGL(k_karras, dim3(nblk(n - 1)), dim3(kThreads), 0, st, k_out, n, B.nodes, B.leaf_parent);
         if (n <= kSmallTree) {

@@ -19,6 +19,7 @@ struct BvhBuffers {
     float *opraw = nullptr;         // [n] opacity as given
     double *area = nullptr;         // [n] App. E effective area
     float *dado = nullptr;          // [n] d area / d opacity (0 where the clamp is active)
+    Frame *frames = nullptr;        // [n] what the directional transfer reads, by original index
     float *bounds = nullptr;        // [8]
     int *height = nullptr;          // [1] tree height
     void *temp = nullptr;

@@ -57,6 +57,13 @@ struct __align__(16) WideNode {
 };
 constexpr int kNoChild = 0x7fffffff;
 
+// What the directional transfer reads of a surfel, by original index (48
+// bytes): in the order of F's columns, so that no load waits for the surfel's
+// place in the tree.  The build writes them.
+struct Frame {
+    float p[3], n[3], u[3], v[3];
+};
+
 struct BvhDev {
     int64_t n;
     const SurfRec *rec;      // [n] in sorted (Morton) order

@@ -43,21 +43,6 @@ __device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t g) {
     return x * per + (x < rem ? x : rem) + q;
 }
 
-// What the transfer reads of a surfel, by original index (48 bytes): centre,
-// normal, t_u, t_v.  In the order of F's columns, so that no load waits for
-// the surfel's place in the tree.
-struct Frame {
-    float p[3], n[3], u[3], v[3];
-};
-
-__global__ void __launch_bounds__(256) k_frames(BvhDev bv, Frame *__restrict__ out) {
-    const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (s >= bv.n) return;
-    const SurfRec r = bv.rec[s];
-    out[__float_as_uint(r.d.w)] = Frame{{r.a.x, r.a.y, r.a.z}, {r.b.x, r.b.y, r.b.z}, {r.c.x, r.c.y, r.c.z},
-                                        {r.d.x, r.d.y, r.d.z}};
-}
-
 // Unit direction from the centre of `ri` to the centre of `rj` in ri's
 // frame (di) and its opposite in rj's frame (ej).  Coincident centres take
 // the receiver's normal as the direction.
@@ -573,18 +558,9 @@ void launch_sddmm_k(const Frame *frames, const Csr &F, int Lt, int nb, const flo
 
 }  // namespace
 
-size_t sh_frame_bytes(int64_t n) { return (size_t)n * sizeof(Frame); }
-
-gsrad_status launch_sh_frames(const BvhDev &bv, void *frames, hipStream_t st) {
-    hipLaunchKernelGGL(k_frames, dim3((unsigned)((bv.n + 255) / 256)), dim3(256), 0, st, bv,
-                       static_cast<Frame *>(frames));
-    return check_hip(hipGetLastError(), "SH frames launch");
-}
-
-gsrad_status launch_transfer_sh(const void *frames, const Csr &F, int Lt, int K, const float *X, const float *E,
+gsrad_status launch_transfer_sh(const Frame *fr, const Csr &F, int Lt, int K, const float *X, const float *E,
                                 const float *R, float *out_a, float *out_b, int mode, hipStream_t st) {
     if (F.n == 0) return GSRAD_OK;
-    const Frame *fr = static_cast<const Frame *>(frames);
     switch (K) {
         case 1: launch_transfer_k<1>(fr, F, Lt, X, E, R, out_a, out_b, mode, st); break;
         case 4: launch_transfer_k<4>(fr, F, Lt, X, E, R, out_a, out_b, mode, st); break;
@@ -602,10 +578,9 @@ gsrad_status launch_scale_rows(const float *lam, const float *R, int64_t n, int 
     return check_hip(hipGetLastError(), "SH scale launch");
 }
 
-gsrad_status launch_sddmm_sh(const void *frames, const Csr &F, int Lt, int K, int nb, const float *Btape,
+gsrad_status launch_sddmm_sh(const Frame *fr, const Csr &F, int Lt, int K, int nb, const float *Btape,
                              const float *Ltape, const float *R, float *grad_F, hipStream_t st) {
     if (F.n == 0 || F.nnz == 0) return GSRAD_OK;
-    const Frame *fr = static_cast<const Frame *>(frames);
     switch (K) {
         case 1: launch_sddmm_k<1>(fr, F, Lt, nb, Btape, Ltape, R, grad_F, st); break;
         case 4: launch_sddmm_k<4>(fr, F, Lt, nb, Btape, Ltape, R, grad_F, st); break;

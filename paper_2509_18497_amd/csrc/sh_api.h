@@ -9,14 +9,11 @@ namespace gsrad {
 
 // mode 0: out_a = T X (optional), out_b = E + R (.) (T X)
 // mode 1 (F = F^T): out_a = T^T X, out_b += out_a
-// the surfels' frames by original index, read by the launches below
-size_t sh_frame_bytes(int64_t n);
-gsrad_status launch_sh_frames(const BvhDev &bv, void *frames, hipStream_t st);
-gsrad_status launch_transfer_sh(const void *frames, const Csr &F, int Lt, int K, const float *X, const float *E,
+gsrad_status launch_transfer_sh(const Frame *frames, const Csr &F, int Lt, int K, const float *X, const float *E,
                                 const float *R, float *out_a, float *out_b, int mode, hipStream_t st);
 // u = R (.) lam (rows of Lt lights)
 gsrad_status launch_scale_rows(const float *lam, const float *R, int64_t n, int Lt, int K, float *u, hipStream_t st);
-gsrad_status launch_sddmm_sh(const void *frames, const Csr &F, int Lt, int K, int nb, const float *Btape,
+gsrad_status launch_sddmm_sh(const Frame *frames, const Csr &F, int Lt, int K, int nb, const float *Btape,
                              const float *Ltape, const float *R, float *grad_F, hipStream_t st);
 gsrad_status launch_grad_R(const float *Ltape, const float *Qtape, int64_t n, int Lt, int K, int nb, float *grad_R,
                            hipStream_t st);
