@@ -244,8 +244,10 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_scatter(const uint32_t *
 // keys keep their order and the result is the radix sort's.  That takes a
 // histogram, a scan and a scatter per digit, launches that a few workgroups
 // run one after the other: 512 keys of 30 bits some 95 us, here 13 us; a tree
-// of 4,096 surfels is built in 140 us with this sort and 188 us with that.
-constexpr int kSmallSort = 4096;
+// of 4,096 surfels is built in 140 us with this sort and 188 us with that.  Keys
+// of a single digit are faster by radix from some hundred pairs on (3,000
+// pairs of the Monte-Carlo groups: eight sorts and the rest 0.49 ms, so 0.67).
+constexpr int kSmallSort = 4096, kSmallSortOnePass = 512;
 
 __global__ void __launch_bounds__(1024) k_sort_small(const uint32_t *__restrict__ keys,
                                                      const uint32_t *__restrict__ vals, uint32_t *kout,
@@ -302,7 +304,7 @@ gsrad_status radix_sort_pairs(const uint32_t *keys_in, const uint32_t *vals_in, 
     // keys: two of 9 bits instead of three of 8), the digits of equal width
     const int passes = bits <= 0 ? 1 : (bits + kMaxDigitBits - 1) / kMaxDigitBits;
     const int dbits = bits <= 0 ? 1 : (bits + passes - 1) / passes;
-    if (n <= kSmallSort && keys_in != keys_out && vals_in != vals_out) {
+    if (n <= (passes > 1 ? kSmallSort : kSmallSortOnePass) && keys_in != keys_out && vals_in != vals_out) {
         int P = 2;
         while (P < n) P <<= 1;
         const int used = passes * dbits;
