@@ -40,13 +40,13 @@ FLOP_COMP = 30     # compositing one hit (two exponentials, weights)
 # FETCH_SIZE, x1.0000 for WRITE_SIZE), valid only for the kernel sources
 # they were taken on (sha256 over the listed files, in order).
 TRAFFIC = {
-    "ff_trace": {"fetch": 117103.97e6, "write": 11135.33e6,
+    "ff_trace": {"fetch": 117624.58e6, "write": 11137.05e6,
                  "files": ["trace.hip", "traverse.h", "gsrad_internal.h", "trace_api.h"],
-                 "sha256": "9a64b837a92eefb5da112eecb09d82b98958d0c271371fcee07633f415c0da54",
+                 "sha256": "030f0e762a1503c2c74f366a0296d45f52feb113cf9845cc0a3b97628ae16cb5",
                  "summary": "profiles/fruit_bowl_100k_hbm_counters.txt"},
-    "dense_grad_F": {"fetch": 236949.39e6, "write": 4294.97e6,
+    "dense_grad_F": {"fetch": 207550.39e6, "write": 4294.97e6,
                      "files": ["dense.hip", "dense_api.h", "gsrad_internal.h"],
-                     "sha256": "93a246c63f1835d7eec00229cce3ebf5ac38b0f1d6043b6daa9f2b79004ad563",
+                     "sha256": "15cc5d39e749dfc4073dd3d561594a469a93a214b85fc5bf8306f56fc0d658a2",
                      "summary": "profiles/multi_light_32k_hbm_counters.txt"},
 }
 

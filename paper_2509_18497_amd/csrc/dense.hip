@@ -21,12 +21,12 @@
 // nominal, 2.5 PFLOP/s): one wave of 128 x 128 per SIMD, bounce 7.49 ms (808
 // TFLOP/s issued) and dL/dF 129 ms (1.08 PFLOP/s); two waves per SIMD, which
 // fill each other's gaps, 5.73 ms (1.06 PFLOP/s; 8 % of it is the last,
-// half-empty round of workgroups) and 113 ms (1.23 PFLOP/s), the matrix cores
-// busy 65 % of the cycles at 1.8 GHz (a library product of the bounce's shape
-// runs at 1.27 PFLOP/s here).  Measured and not kept: one wave per SIMD with
-// the fragment reads and loads placed between its MFMAs, dL/dF 112 ms but
-// bounces 6.5 ms; K tiles of 32 in four or five stages, 123-125 ms and 7.0 ms
-// (half-line requests).
+// half-empty round of workgroups) and 108 ms (1.29 PFLOP/s), the matrix cores
+// busy 43 and 56 % of the cycles at 2.4 and 2.2 GHz (one wave 32 and 45 %; a
+// library product of the bounce's shape runs at 1.27 PFLOP/s here).  Measured
+// and not kept: one wave per SIMD with the fragment reads and loads placed
+// between its MFMAs, dL/dF 112 ms but bounces 6.5 ms; K tiles of 32 in four or
+// five stages, 123-125 ms and 7.0 ms (half-line requests).
 //
 // A K range may be split into up to three segments with their own A and B
 // (the correction sweep sums F_hi X_hi + F_hi X_lo + F_lo X_hi in one pass).

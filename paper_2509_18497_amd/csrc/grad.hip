@@ -10,8 +10,9 @@
 //                   scales and opacities.
 // k_light_*         the direct light's gradient: lights, albedo, receivers
 //                   and shadow-segment occluders.
-// All sums are 64-bit fixed point with per-field scales (bit-identical
-// between runs), one copy per XCD.
+// The sums over surfels, scales and lights are 64-bit fixed point with a scale
+// per field, one copy per XCD; the albedo's, a surfel's own, is FP32 in the
+// order of the lights.  Both are bit-identical between runs.
 #include <algorithm>
 #include <cstring>
 #include <functional>

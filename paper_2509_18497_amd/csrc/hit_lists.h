@@ -3,13 +3,14 @@
 //
 // A sum per surfel in global memory takes an atomic per contribution; a 100k
 // surfel scene's opacity gradient has 356 M of them (34 G/s: 11 of its 17 ms),
-// the geometry gradient ten times as many a hit (28 of 34 ms for 30k surfels).  Here a workgroup that makes
-// contributions writes them to its own stretch of a list, ordered by block of
-// surfels, and a second kernel gives every block to workgroups that read its
-// parts of all stretches and add in a table in LDS, one place per surfel.
-// Integer sums: the order does not matter.  A block is every 2^bits-th surfel,
-// not a range: neighbours are hit alike, and ranges had up to ten times the
-// mean (the second kernel on a 100k-surfel bowl 2.85 ms, now 0.39 ms a chunk).
+// the geometry gradient ten times as many a hit (28 of 34 ms for 30k surfels).
+// Here a workgroup that makes contributions writes them to its own stretch of a
+// list, ordered by block of surfels, and a second kernel gives every block to
+// workgroups that read its parts of all stretches and add in a table in LDS, one
+// place per surfel.  Integer sums: the order does not matter.  A block is every
+// 2^bits-th surfel, not a range: neighbours are hit alike, and ranges had up to
+// ten times the mean (the second kernel on a 100k-surfel bowl 2.85 ms, now
+// 0.39 ms a chunk).
 #pragma once
 
 #include <algorithm>

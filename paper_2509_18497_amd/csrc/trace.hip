@@ -881,9 +881,9 @@ __device__ __forceinline__ float row_lookup(const uint32_t *lc, const float *lg,
 // its own copy of the accumulators with atomics kept in its L2 (scope of
 // the workgroup: every workgroup that touches copy x runs on XCD x), and
 // k_opacity_finish adds the copies.
-// One hit of the second walk: the sender's contribution to dL/do.
-// The same with the sender's c_j and raw opacity already loaded, returned
-// instead of added; false: none.
+//
+// One hit of the second walk: v, the sender's contribution to dL/do, from its
+// c_j and raw opacity; false: none.
 __device__ __forceinline__ bool opacity_term(float G, float alpha, float f, float T, float g, float cj, float oraw,
                                              DF W, DF &P, float &v) {
     if (G != 0.0f) P = df_add(P, df_prod3(G, alpha, T));
@@ -895,6 +895,7 @@ __device__ __forceinline__ bool opacity_term(float G, float alpha, float f, floa
     return true;
 }
 
+// The same with both read here, and the contribution added.
 __device__ __forceinline__ void opacity_hit(const BvhDev &bv, uint32_t j, float G, float alpha, float f, float T,
                                             float g, DF W, DF &P, unsigned long long *acc, float scale) {
     if (G != 0.0f) P = df_add(P, df_prod3(G, alpha, T));
