@@ -783,6 +783,13 @@ constexpr int kGeometryShift = 9;
 constexpr int kGeometryEntry = 48;   // bytes
 constexpr int kGeometryThreads = 512;
 constexpr int kGeometryWgs = 1536;   // workgroups aimed at
+// Blocks up to which the lists pay whatever the rays, and with 1 / 64 of a ray
+// per block: 400k surfels (782 blocks), 16 / 128 rays each: a room 60 and 143 ms,
+// added directly 79 and 449, a bowl 61 and 130, directly 73 and 344; 1 M, 16 / 32
+// rays 196 and 228, directly 186 and 310; 260k, 4 / 16 rays 25 and 36, directly
+// 23 and 53; 70k with 1, 2 and 4 rays 4.5, 5.3 and 6.1, directly 4.8, 5.6 and 6.4.
+constexpr int64_t kGeometryAlways = 256, kGeometryBlocks = 2048;
+constexpr double kGeometryShare = 1.0 / 64;
 
 __global__ void __launch_bounds__(kGeometryThreads) k_geometry_sum(HitLists lists, int64_t stretches, int64_t n,
                                                                    uint32_t *maxbits, const int *fx,
@@ -1221,7 +1228,9 @@ constexpr int kScaleMargin = 12;
 
 size_t geometry_list_bytes(int64_t n, int R) {
     const int threads = R >= 256 ? 256 : ((R + 63) / 64) * 64;
-    return lists_pay(n, R, kGeometryShift, kListBlocks, 0.0) ? (size_t)ListLayout(n, R, threads, kGeometryShift, kGeometryEntry).bytes : 0;
+    const bool pay = lists_pay(n, R, kGeometryShift, kGeometryAlways, 0.0) ||
+                     lists_pay(n, R, kGeometryShift, kGeometryBlocks, kGeometryShare);
+    return pay ? (size_t)ListLayout(n, R, threads, kGeometryShift, kGeometryEntry).bytes : 0;
 }
 
 size_t center_group_bytes() { return (size_t)kRowParts * kRowPart * sizeof(uint2); }

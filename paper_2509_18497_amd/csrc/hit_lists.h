@@ -20,9 +20,6 @@
 
 namespace gsrad {
 
-// Blocks of surfels a list tells apart, at most
-constexpr int kListBlocks = 512;
-
 // Device view of a list for one chunk of stretches
 struct HitLists {
     unsigned long long *used;   // places given out (zeroed before each chunk)

@@ -80,3 +80,23 @@ def test_center_gradients(g):
     finally:
         del full
         torch.cuda.empty_cache()
+
+
+def test_geometry_gradients_of_many_blocks(g):
+    """2.2 GB of lists (1,024 blocks of surfels) where 190 MB may be taken: all
+    contributions are added directly, and listed once there is room."""
+    n = 262145
+    bvh = g.build_bvh(dev_surfels(scenes.make_config("fruit_bowl", n=n).surfels))
+    ff = g.form_factors(bvh, 16, 3, t_min=1e-4, topk=64)
+    gF = dev(scenes.seeded_array((ff.info()[1],), 8, -1.0, 1.0))
+    full = _leave(1500 * MB)
+    try:
+        direct = g.geometry_backward(bvh, ff, gF)
+    finally:
+        del full
+        torch.cuda.empty_cache()
+    free = torch.cuda.mem_get_info()[0]
+    listed = g.geometry_backward(bvh, ff, gF)
+    torch.cuda.synchronize()
+    assert free - torch.cuda.mem_get_info()[0] > 2000 * MB
+    assert all(torch.equal(direct[f], listed[f]) for f in direct)
