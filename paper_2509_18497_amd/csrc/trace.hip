@@ -127,10 +127,10 @@ __device__ __forceinline__ uint32_t next_pool(uint32_t *queue, int64_t npools, i
 //
 // Bound by the latency of dependent node and leaf loads (12 waves a CU) and, at
 // half of the lanes on average, by the tests' vector instructions.  A node
-// step tests four grandchildren (WideNode), so a ray waits for half as many nodes: 12.8 M
-// rays of a 100k-surfel bowl 43.9 ms, one child pair of 64 bytes a step
-// 54.9 ms, of 32 bytes 53.9 ms (the lines fetched from L2 fell by a third, so
-// these do not bound it).
+// step tests four grandchildren (WideNode), so a ray waits for half as many
+// nodes: 12.8 M rays of a 100k-surfel bowl 43.9 ms, one child pair of 64 bytes a
+// step 54.9 ms, of 32 bytes 53.9 ms (the lines fetched from L2 fell by a third,
+// so these do not bound it).
 //
 // Each lane walks its ray one node per iteration, queueing the leaves it
 // reaches; the wave tests queued leaves once half of its lanes hold one; a
@@ -769,29 +769,58 @@ __global__ void __launch_bounds__(256) k_ell_to_csr(const int32_t *__restrict__ 
 // ---------------------------------------------------------------------------
 // direct light
 // ---------------------------------------------------------------------------
+// Workgroups of rays of W = 16 or 1 lanes, and the words of their stacks in LDS
+constexpr int direct_threads(int W) { return W == 16 ? kRowThreads : kCenterThreads; }
+constexpr int direct_words(int W, int head) { return W == 16 ? kRowThreads / 16 * kRowStack : head * kCenterThreads / 2; }
+
 // Transmittance of receiver i's shadow segment to the light at o + d, by a row
-// of 16 lanes.
+// of 16 lanes or by a lane (HEAD entries of its stack in LDS); the same bits.
+template <int W, int HEAD>
 __device__ __forceinline__ float shadow(const BvhDev &bv, const SurfRec &rr, float dx, float dy, float dz, float len,
                                         uint64_t *stack, int *err) {
     const uint32_t i = __float_as_uint(rr.d.w);
     const Segment g{rr.a.x, rr.a.y, rr.a.z, dx, dy, dz, __fdiv_rn(bv.bounds[6], len), 1.0f};
-    return row_segment(bv, g, i, i, stack, err);
+    if (W == 16) return row_segment(bv, g, i, i, stack + threadIdx.x / 16 * kRowStack, err);
+    float T = 1.0f;
+    trace_segment<HEAD>(bv, g.ox, g.oy, g.oz, dx, dy, dz, i, i, g.t_lo, g.t_hi,
+                        reinterpret_cast<uint32_t *>(stack) + threadIdx.x, direct_threads(W), err,
+                        [&](const SurfRec &r, int) {
+                            const float gamma = kernel_gamma(hit_r2_exact(r, g.ox, g.oy, g.oz, dx, dy, dz));
+                            T = __fmul_rn(T, transmit(r.c.w, gamma));
+                        });
+    return T;
 }
 
-// A row of 16 lanes per (receiver, light); a workgroup's receivers follow each
-// other in Morton order and have one light, so their walks are alike.  16k
-// surfels x 100 lights: 4.1 ms with a lane each, 3.3 ms so; 100k surfels and one
-// light, a wave and a half per SIMD with a lane each: 0.69 ms, 0.18 ms
-// so.  (The product in a fixed order: the light drives the Monte-Carlo draws,
-// which one bit changes; a sum in any order, row_crossings, takes 2.2 ms and
-// 0.13 ms.)
-__global__ void __launch_bounds__(kRowThreads) k_direct(BvhDev bv, const float *__restrict__ albedo,
-                                                        const float *__restrict__ lpos, const float *__restrict__ lI,
-                                                        int64_t block0, int l0, int Lt, int K, float *__restrict__ E, int *err) {
-    __shared__ uint64_t stack[kRowThreads / 16][kRowStack];
-    const int64_t slot = (block0 + blockIdx.x) * (kRowThreads / 16) + threadIdx.x / 16;
-    if (slot >= bv.n) return;
-    const int l = l0 + (int)blockIdx.y;
+// The ray of this thread: receivers follow each other in Morton order; W = 16:
+// a workgroup's have one light, so their walks are alike; W = 1: a receiver's
+// lights follow each other.
+template <int W>
+__device__ __forceinline__ bool direct_ray(int64_t n, int64_t block0, int Lt, int64_t &slot, int &l) {
+    if (W == 16) {
+        slot = (block0 + blockIdx.x) * (kRowThreads / 16) + threadIdx.x / 16;
+        l = (int)blockIdx.y;
+    } else {
+        const int64_t ray = (block0 + blockIdx.x) * direct_threads(W) + threadIdx.x;
+        slot = ray / Lt;
+        l = (int)(ray - slot * Lt);
+    }
+    return slot < n;
+}
+
+// W lanes per (receiver, light), W by direct_rays.  A row of 16: 16k surfels x 100
+// lights 4.1 ms with a lane each, 3.3 ms so; 100k surfels and one light, a wave
+// and a half per SIMD with a lane each: 0.69 ms, 0.18 ms so.  (The product in a
+// fixed order: the light drives the Monte-Carlo draws, which one bit changes; a
+// sum in any order, row_crossings, takes 2.2 ms and 0.13 ms.)
+template <int W, int HEAD = kWalkHead>
+__global__ void __launch_bounds__(direct_threads(W)) k_direct(BvhDev bv, const float *__restrict__ albedo,
+                                                              const float *__restrict__ lpos,
+                                                              const float *__restrict__ lI, int64_t block0, int Lt,
+                                                              int K, float *__restrict__ E, int *err) {
+    __shared__ uint64_t stack[direct_words(W, HEAD)];
+    int64_t slot;
+    int l;
+    if (!direct_ray<W>(bv.n, block0, Lt, slot, l)) return;
     const SurfRec rr = bv.rec[slot];
     const int64_t i = (int64_t)__float_as_uint(rr.d.w);
     float *e = E + ((i * Lt + l) * K) * 3;
@@ -804,21 +833,21 @@ __global__ void __launch_bounds__(kRowThreads) k_direct(BvhDev bv, const float *
     float base = 0.0f;
     if (ndot > 0.0f && dd > 0.0f)
         base = bv.op[i] * 1.1283791670955126f * lI[l] * (ndot / len) / dd *
-               shadow(bv, rr, dx, dy, dz, len, stack[threadIdx.x / 16], err);
-    for (int c = threadIdx.x & 15; c < 3 * K; c += 16) e[c] = c < 3 ? base * albedo[3 * i + c] : 0.0f;
+               shadow<W, HEAD>(bv, rr, dx, dy, dz, len, stack, err);
+    for (int c = threadIdx.x % W; c < 3 * K; c += W) e[c] = c < 3 ? base * albedo[3 * i + c] : 0.0f;
 }
 
 // Direct light with the BRDF: E_i,l = (R_i / pi) (.) Y(w^(i)) I_l max(0, n_i . w) / r^2 T_il
 // with w the unit direction to the light expressed in i's tangent frame.
-template <int K>
-__global__ void __launch_bounds__(kRowThreads) k_direct_sh(BvhDev bv, const float *__restrict__ R,
-                                                           const float *__restrict__ lpos,
-                                                           const float *__restrict__ lI, int64_t block0, int l0, int Lt,
-                                                           float *__restrict__ E, int *err) {
-    __shared__ uint64_t stack[kRowThreads / 16][kRowStack];
-    const int64_t slot = (block0 + blockIdx.x) * (kRowThreads / 16) + threadIdx.x / 16;
-    if (slot >= bv.n) return;
-    const int l = l0 + (int)blockIdx.y;
+template <int K, int W, int HEAD = kWalkHead>
+__global__ void __launch_bounds__(direct_threads(W)) k_direct_sh(BvhDev bv, const float *__restrict__ R,
+                                                                 const float *__restrict__ lpos,
+                                                                 const float *__restrict__ lI, int64_t block0, int Lt,
+                                                                 float *__restrict__ E, int *err) {
+    __shared__ uint64_t stack[direct_words(W, HEAD)];
+    int64_t slot;
+    int l;
+    if (!direct_ray<W>(bv.n, block0, Lt, slot, l)) return;
     const SurfRec rr = bv.rec[slot];
     const int64_t i = (int64_t)__float_as_uint(rr.d.w);
     float *e = E + ((i * Lt + l) * K) * 3;
@@ -831,7 +860,7 @@ __global__ void __launch_bounds__(kRowThreads) k_direct_sh(BvhDev bv, const floa
     float base = 0.0f;
     float Y[K];
     if (ndot > 0.0f && dd > 0.0f) {
-        const float T = shadow(bv, rr, dx, dy, dz, len, stack[threadIdx.x / 16], err);
+        const float T = shadow<W, HEAD>(bv, rr, dx, dy, dz, len, stack, err);
         base = lI[l] * (ndot / len) / dd * T * 0.318309886183791f;
         const float il = 1.0f / len;
         sh_eval<K>((dx * rr.c.x + dy * rr.c.y + dz * rr.c.z) * il, (dx * rr.d.x + dy * rr.d.y + dz * rr.d.z) * il,
@@ -841,10 +870,20 @@ __global__ void __launch_bounds__(kRowThreads) k_direct_sh(BvhDev bv, const floa
         for (int a = 0; a < K; ++a) Y[a] = 0.0f;
     }
     const float *Ri = R + i * K * 3;
+    auto put = [&](int a, float y) {
+        for (int c = 0; c < 3; ++c) e[3 * a + c] = Ri[3 * a + c] * y * base;
+    };
+    if (W == 1) {
 #pragma unroll
-    for (int a = 0; a < K; ++a)
-        for (int c = 0; c < 3; ++c)
-            if (((3 * a + c) & 15) == (int)(threadIdx.x & 15)) e[3 * a + c] = Ri[3 * a + c] * Y[a] * base;
+        for (int a = 0; a < K; ++a) put(a, Y[a]);
+    } else {
+        // lane a of the row: coefficient a
+        const int lane = threadIdx.x % W;
+        float y = Y[0];
+#pragma unroll
+        for (int a = 1; a < K; ++a) y = lane == a ? Y[a] : y;
+        if (lane < K) put(lane, y);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1312,16 +1351,39 @@ gsrad_status launch_ell_to_csr(const int32_t *ell_col, const float *ell_val, int
     return check_hip(hipGetLastError(), "ell to csr launch");
 }
 
-// launches over (receivers, lights), at most kLightGrid lights each (grid limit)
-constexpr int kLightGrid = 32768;
+
+// A lane to a ray where a receiver has many lights: its rays, side by side in a
+// wave, walk alike, and fill the chip without the 16 lanes.  The lane's stack
+// lies in LDS while that holds no waves back, some 2,200 of 64 rays.  us, 16
+// lanes / a lane, bowl and room: 16 surfels x 4,000 lights 31 / 14 and 31 / 12;
+// 64 x 1,000 54 / 53 and 52 / 44, x 700 40 / 50 and 38 / 44; 512 x 500 446 / 350
+// and 530 / 740; 4,000 x 300 1,624 / 1,201 and 2,398 / 3,551; 16k x 100 2,302 /
+// 1,742 and 3,120 / 5,064.  The lines lie where a lane each is the faster in
+// bowls; rooms, whose walks are long and part early, lose a third there.
+constexpr int kLaneLights = 850, kLaneLightsFull = 256;
+constexpr int64_t kLaneFull = 250000, kLaneFew = 140000;
+
+template <typename Kernel, typename... Args>
+static void direct_rays(Kernel rows, Kernel lanes, Kernel few_lanes, const BvhDev &bv, int Lt, hipStream_t st,
+                        const float *surfel, const float *lpos, const float *lI, Args... args) {
+    const int64_t rays = bv.n * Lt;
+    if (Lt >= kLaneLights || (Lt >= kLaneLightsFull && rays >= kLaneFull)) {
+        each_launch((rays + direct_threads(1) - 1) / direct_threads(1), direct_threads(1),
+                    [&](int64_t first, unsigned blocks) {
+                        hipLaunchKernelGGL(rays < kLaneFew ? few_lanes : lanes, dim3(blocks), dim3(direct_threads(1)),
+                                           0, st, bv, surfel, lpos, lI, first, Lt, args...);
+                    });
+        return;
+    }
+    each_launch((bv.n + kRowThreads / 16 - 1) / (kRowThreads / 16), kRowThreads, [&](int64_t first, unsigned blocks) {
+        hipLaunchKernelGGL(rows, dim3(blocks, (unsigned)Lt), dim3(kRowThreads), 0, st, bv, surfel, lpos, lI, first, Lt,
+                           args...);
+    });
+}
 
 gsrad_status launch_direct(const BvhDev &bv, const float *albedo, const float *lpos, const float *lI, int Lt, int K,
                            float *E, int *err, hipStream_t st) {
-    for (int l0 = 0; l0 < Lt; l0 += kLightGrid)
-        each_launch((bv.n + kRowThreads / 16 - 1) / (kRowThreads / 16), kRowThreads, [&](int64_t first, unsigned blocks) {
-            hipLaunchKernelGGL(k_direct, dim3(blocks, (unsigned)std::min(kLightGrid, Lt - l0)), dim3(kRowThreads), 0, st,
-                               bv, albedo, lpos, lI, first, l0, Lt, K, E, err);
-        });
+    direct_rays(k_direct<16>, k_direct<1>, k_direct<1, kStackDeep>, bv, Lt, st, albedo, lpos, lI, K, E, err);
     return check_hip(hipGetLastError(), "direct light launch");
 }
 
@@ -1344,19 +1406,14 @@ static const int *fx_exp_ptr(const BvhDev &bv, const void *acc) {
 
 gsrad_status launch_direct_sh(const BvhDev &bv, const float *R, const float *lpos, const float *lI, int Lt, int K,
                               float *E, int *err, hipStream_t st) {
-    auto run = [&](auto kernel) {
-        for (int l0 = 0; l0 < Lt; l0 += kLightGrid)
-            each_launch((bv.n + kRowThreads / 16 - 1) / (kRowThreads / 16), kRowThreads,
-                        [&](int64_t first, unsigned blocks) {
-                            hipLaunchKernelGGL(kernel, dim3(blocks, (unsigned)std::min(kLightGrid, Lt - l0)),
-                                               dim3(kRowThreads), 0, st, bv, R, lpos, lI, first, l0, Lt, E, err);
-                        });
+    auto run = [&](auto rows, auto lanes, auto few_lanes) {
+        direct_rays(rows, lanes, few_lanes, bv, Lt, st, R, lpos, lI, E, err);
     };
     switch (K) {
-        case 1: run(k_direct_sh<1>); break;
-        case 4: run(k_direct_sh<4>); break;
-        case 9: run(k_direct_sh<9>); break;
-        case 16: run(k_direct_sh<16>); break;
+        case 1: run(k_direct_sh<1, 16>, k_direct_sh<1, 1>, k_direct_sh<1, 1, kStackDeep>); break;
+        case 4: run(k_direct_sh<4, 16>, k_direct_sh<4, 1>, k_direct_sh<4, 1, kStackDeep>); break;
+        case 9: run(k_direct_sh<9, 16>, k_direct_sh<9, 1>, k_direct_sh<9, 1, kStackDeep>); break;
+        case 16: run(k_direct_sh<16, 16>, k_direct_sh<16, 1>, k_direct_sh<16, 1, kStackDeep>); break;
         default: set_error("direct light: K must be 1, 4, 9 or 16"); return GSRAD_EINVAL;
     }
     return check_hip(hipGetLastError(), "SH direct light launch");

@@ -29,18 +29,26 @@ constexpr uint32_t kEmpty = 0xffffffffu;
 // (10 M segments of a 20k-surfel bowl: F 29.6 ms, with a head of 20 24.2 ms).
 constexpr int kWalkHead = 20;
 
+template <int HEAD>
 struct WalkStack {
     uint32_t *lds;
     int stride;
-    uint32_t tail[kStackDeep - kWalkHead];
+    uint32_t tail[kStackDeep - HEAD];
     __device__ __forceinline__ WalkStack(uint32_t *column, int stride_) : lds(column), stride(stride_) {}
     __device__ __forceinline__ void put(int k, uint32_t v) {
-        if (k < kWalkHead) lds[k * stride] = v;
-        else tail[k - kWalkHead] = v;
+        if (k < HEAD) lds[k * stride] = v;
+        else tail[k - HEAD] = v;
     }
-    __device__ __forceinline__ uint32_t get(int k) const {
-        return k < kWalkHead ? lds[k * stride] : tail[k - kWalkHead];
-    }
+    __device__ __forceinline__ uint32_t get(int k) const { return k < HEAD ? lds[k * stride] : tail[k - HEAD]; }
+};
+// all of it in LDS
+template <>
+struct WalkStack<kStackDeep> {
+    uint32_t *lds;
+    int stride;
+    __device__ __forceinline__ WalkStack(uint32_t *column, int stride_) : lds(column), stride(stride_) {}
+    __device__ __forceinline__ void put(int k, uint32_t v) { lds[k * stride] = v; }
+    __device__ __forceinline__ uint32_t get(int k) const { return lds[k * stride]; }
 };
 
 // Workgroups are dispatched round-robin over the 8 XCDs; give each XCD a
@@ -252,10 +260,10 @@ __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
 
 // A row of dL/dF in LDS: its columns (ascending), their values, and the first
 // position of each of up to kRowBuckets ranges of columns (about two an entry),
-// from which find() searches on.  An open-addressing table needs twice the row, rounded up to a power of
-// two: the rows of a 16k-surfel room (2,544 entries, the longest 4,369) left a
-// CU one workgroup of four waves, now four workgroups (opacity gradient 14.5 ms
-// and 10.0 ms, each with direct adds).
+// from which find() searches on.  An open-addressing table needs twice the row,
+// rounded up to a power of two: the rows of a 16k-surfel room (2,544 entries, the
+// longest 4,369) left a CU one workgroup of four waves, now four workgroups
+// (opacity gradient 14.5 ms and 10.0 ms, each with direct adds).
 constexpr int kRowBuckets = 512;
 // bytes of LDS for rows of up to max_row entries
 constexpr size_t row_index_bytes(int64_t max_row) { return (size_t)max_row * 8 + (kRowBuckets + 2) * 2; }
@@ -305,7 +313,7 @@ struct RowIndex {
 // Every surfel other than skip_a and skip_b whose support the segment
 // o + t d, t in (t_lo, t_hi), crosses (D_hit, both faces occlude);
 // on_hit(record, sorted position) per crossing, in traversal order.
-template <typename OnHit>
+template <int HEAD = kWalkHead, typename OnHit>
 __device__ __forceinline__ void trace_segment(const BvhDev &bv, float ox, float oy, float oz, float dx, float dy,
                                               float dz, uint32_t skip_a, uint32_t skip_b, float t_lo, float t_hi,
                                               uint32_t *column, int stride, int *err, OnHit &&on_hit) {
@@ -325,7 +333,7 @@ __device__ __forceinline__ void trace_segment(const BvhDev &bv, float ox, float 
         leaf(0);
         return;
     }
-    WalkStack stack(column, stride);
+    WalkStack<HEAD> stack(column, stride);
     int sp = 0, node = 0;
     bool ovf = false;
     for (;;) {
@@ -484,10 +492,10 @@ __device__ __forceinline__ float row_segment(const BvhDev &bv, const Segment &g,
 // The crossings of a segment by a row of 16 lanes, in no order: on_hit(sorted
 // position) in the lane that finds one; returns the transmittance, e to the
 // minus sum of c gamma.  The sum is in steps of 2^-40, so that it does not
-// depend on the order (which the other rows of the wave have a part in).  Nodes are WideNodes; a round opens up to 16 nodes or
-// tests up to 16 leaves, and the rows of a wave do the same kind, so that a
-// wave does not step through both.  Bound by the vector instructions of the
-// tests: 10 M segments of a 20k-surfel bowl (200 binary nodes and 96 leaves
+// depend on the order (which the other rows of the wave have a part in).  Nodes
+// are WideNodes; a round opens up to 16 nodes or tests up to 16 leaves, and the
+// rows of a wave do the same kind, so that a wave does not step through both.
+// Bound by the vector instructions of the tests: 10 M segments of a 20k-surfel bowl (200 binary nodes and 96 leaves
 // each) 24.2 ms with a lane each, 19.4 ms with a row each taking nodes and
 // leaves as they come, 17.5 ms with WideNodes, 14.6 ms with rounds of one kind.
 // The stack never fills in a tree no higher than trace_segment takes: near its
