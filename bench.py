@@ -40,9 +40,9 @@ FLOP_COMP = 30     # compositing one hit (two exponentials, weights)
 # FETCH_SIZE, x1.0000 for WRITE_SIZE), valid only for the kernel sources
 # they were taken on (sha256 over the listed files, in order).
 TRAFFIC = {
-    "ff_trace": {"fetch": 117624.58e6, "write": 11137.05e6,
+    "ff_trace": {"fetch": 117454.41e6, "write": 11133.76e6,
                  "files": ["trace.hip", "traverse.h", "gsrad_internal.h", "trace_api.h"],
-                 "sha256": "030f0e762a1503c2c74f366a0296d45f52feb113cf9845cc0a3b97628ae16cb5",
+                 "sha256": "51d129569bbd03be2db3a935fdb54875a2984b0da07582522ec66367f82f0f55",
                  "summary": "profiles/fruit_bowl_100k_hbm_counters.txt"},
     "dense_grad_F": {"fetch": 207550.39e6, "write": 4294.97e6,
                      "files": ["dense.hip", "dense_api.h", "gsrad_internal.h"],

@@ -877,7 +877,8 @@ __global__ void __launch_bounds__(direct_threads(W)) k_direct_sh(BvhDev bv, cons
 #pragma unroll
         for (int a = 0; a < K; ++a) put(a, Y[a]);
     } else {
-        // lane a of the row: coefficient a
+        // lane a of the row: coefficient a (a room of 512 surfels, 100 lights,
+        // K = 16: 134 us; each lane masking all of them 148)
         const int lane = threadIdx.x % W;
         float y = Y[0];
 #pragma unroll
